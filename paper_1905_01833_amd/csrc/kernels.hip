@@ -1239,8 +1239,10 @@ __global__ __launch_bounds__(NT, (scan_min_waves<K, LOOP>())) void k_scan_tiles(
   __shared__ uint64_t s_pend[NT][3];  // sums of the location a thread's first element belongs to, when it is emitted there
 
   // nothing to do on an error, or when fewer radix passes ran than some
-  // trace needs (the host then runs the missing passes and scans again)
-  if (b.ctrl->error_flags) return;
+  // trace needs (the host then runs the missing passes and scans again).  A
+  // staging overflow is raised by this kernel itself: the tiles that start
+  // after it still scan, as the host sizes the rescan from every tile's count
+  if (b.ctrl->error_flags & ~(uint32_t)ERR_STAGE_OVERFLOW) return;
   if (ctrl_passes(b.ctrl->pass_bits) > passes_done) return;
   const TileWalk tw = tile_walk(b.n_tiles, gridDim.x, blockIdx.x);
   for (uint32_t tile = tw.first; tile < tw.end; tile = LOOP ? tile + tw.step : tw.end) {
