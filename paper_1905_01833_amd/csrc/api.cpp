@@ -42,13 +42,16 @@ namespace {
 
 constexpr int N_STAGE = ST_COUNT;
 const char* const kStageNames[N_STAGE] = {"init",      "stats",      "layout",     "keygen",  "upsweep",
-                                          "sort_pass", "scan_tiles", "scan_cross", "scan_out", "sort_small"};
+                                          "sort_pass", "scan_tiles", "scan_cross", "scan_out", "sort_small",
+                                          "filter_part", "filter_test", "filter_out"};
 constexpr int MAX_EV = 96;
 
 struct DevBuf {
   void* p = nullptr;
   size_t cap = 0;
 };
+
+enum Kind { KIND_PLAIN = 0, KIND_FIT, KIND_WARP, KIND_PLAIN_LEFT, KIND_WARP_LEFT, N_KIND };
 
 }  // namespace
 
@@ -57,16 +60,18 @@ struct sim_ctx {
   uint32_t n_cu = 256;           // compute units of the device
   hipStream_t stream = nullptr;  // used by sim_check_traces
   uint32_t flags = 0;
-  uint32_t pass_guess = 0;  // radix passes the previous call needed
-  bool wide_guess = false;  // the previous call had a trace needing two-word keys
-  uint32_t fit_pass_guess = 0;  // the same for the fitness count, whose keys are shorter
-  bool fit_wide_guess = false;
-  uint32_t warp_pass_guess = 0;  // ... and for the warp-aware check, whose keys are longer
-  bool warp_wide_guess = false;
-  // per kind as above: the key bits the previous call sorted (0: none yet),
-  // and the digit width its passes (the pass guess) were counted in
-  uint32_t bits_guess = 0, fit_bits_guess = 0, warp_bits_guess = 0;
-  uint32_t db_guess = RADIX_BITS, fit_db_guess = RADIX_BITS, warp_db_guess = RADIX_BITS;
+  // What the previous call of a kind needed: a plain check, the fitness count
+  // (shorter keys), the warp-aware check (longer ones), and either check over
+  // the records its conflict filter left.
+  struct Guess {
+    uint32_t passes = 0;          // radix passes
+    uint32_t bits = 0;            // key bits they sorted (0: no call yet)
+    uint32_t db = RADIX_BITS;     // digit width the passes are counted in
+    bool wide = false;            // some trace needed two-word keys
+  } guess[N_KIND];
+  // Calls of a kind that still go without the conflict filter, after one that
+  // it did not help (see filter_records).
+  uint32_t filter_pause[N_KIND] = {};
   uint64_t alloc_gen = 0;   // bumped whenever a device buffer is reallocated
   uint64_t meta_gen = 0;    // bumped whenever a call's tables are uploaded
   uint64_t host_gen = 0;    // bumped whenever the host copy's trace and group tables are rebuilt
@@ -432,6 +437,22 @@ hipError_t size_buffers(sim_ctx* c, uint64_t total, uint32_t n_traces, uint32_t 
   return ensure(c->out, out_need, false, &c->alloc_gen);
 }
 
+// Grow the fixed regions of a call over the records a conflict filter left,
+// one by one: they are a quarter of the call's at most, so the key buffers,
+// which hold those records, are large enough already and stay.
+hipError_t grow_regions(sim_ctx* c, uint64_t total, uint32_t n_traces, uint32_t n_tiles, uint64_t n_hgroups,
+                        uint32_t key_bytes, uint32_t radix) {
+  size_t need[N_REGION];
+  region_bytes(need, total, n_traces, n_tiles, n_hgroups, key_bytes, radix);
+  for (int r : {R_KEYS0, R_KEYS1})
+    if (region_buf(c, r)->cap < need[r]) return hipErrorInvalidValue;
+  for (int r = 0; r < N_REGION; r++) {
+    const hipError_t e = grow(c, *region_buf(c, r), need[r]);
+    if (e != hipSuccess) return e;
+  }
+  return grow(c, c->out, c->out.cap ? c->out.cap : std::min<uint64_t>(total, 65536) * sizeof(RaceOut));
+}
+
 // Where a call's result goes: a result the library allocates (the ordinary
 // entry points), or buffers the caller owns (the no-allocation entry point).
 struct Sink {
@@ -443,12 +464,53 @@ struct Sink {
   sim_barrier_result** barriers = nullptr;  // also the redundant-barrier check
   sim_fitness* fitness = nullptr;           // instead of the race check: the EP fitness rows (host, n_traces)
   const uint32_t* side = nullptr;           // the warp-aware check: one side word per record (device)
+  // the call over the records a conflict filter left (in the key buffers,
+  // which must not be reallocated): the whole call's offsets, for the
+  // summaries, and staging for every tile (nullptr: none)
+  const uint64_t* whole_offsets = nullptr;
+  RaceOut* stage_half = nullptr;
 };
+
+// Calls that run the conflict filter first: from 2^23 records on, and from
+// 2^21 on when no trace holds more than an eighth of them, since the kept
+// records of a short trace are sorted in LDS, in one launch, while those of a
+// long one go through all the radix launches (measured, filter against none:
+// one trace of 2^22 records 320 us against 290, of 2^23 390 against 440, of
+// 2^24 547 against 707, of 2^26 2014 against 2967; 64 traces of 2^20 records
+// in all 226 against 225, of 2^21 201 against 260).
+constexpr uint64_t FILTER_MIN_RECORDS = 1u << 21, FILTER_ALWAYS_RECORDS = 1u << 23;
+bool filter_pays(const uint64_t* offsets, uint32_t n_traces, uint64_t total) {
+  if (total < FILTER_MIN_RECORDS) return false;
+  if (total >= FILTER_ALWAYS_RECORDS) return true;
+  for (uint32_t i = 0; i < n_traces; i++)
+    if (offsets[i + 1] - offsets[i] > total / 8) return false;
+  return true;
+}
+// After a call whose filter kept more records than it has room for (a
+// quarter of them), this many calls of the kind go without it.
+constexpr uint32_t FILTER_PAUSE = 15;
+constexpr int RUN_FULL = 1;  // run_filtered: take the full path
 
 void barrier_result_free(sim_barrier_result* r) {
   if (!r) return;
   free(r->barriers);
   free(r);
+}
+
+int run_filtered(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_recs, const uint64_t* offsets,
+                 uint32_t n_traces, const uint32_t* tpb, hipStream_t s, const Sink& sink, uint64_t total,
+                 uint32_t n_tiles);
+
+// The pinned host block of a call's tables, grown to `bytes`.
+hipError_t grow_host(sim_ctx* c, size_t bytes) {
+  if (c->h_meta_cap >= bytes) return hipSuccess;
+  if (c->h_meta) (void)hipHostFree(c->h_meta);
+  c->h_meta = nullptr;
+  c->h_meta_cap = 0;
+  c->host_gen++;
+  const hipError_t e = hipHostMalloc(&c->h_meta, bytes + bytes / 8, hipHostMallocDefault);
+  if (e == hipSuccess) c->h_meta_cap = bytes + bytes / 8;
+  return e;
 }
 
 // One call.  Trace i's records start at trace_recs[i] when trace_recs is
@@ -475,17 +537,25 @@ int run(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_
     if (n_tiles > NOALLOC_MAX_TILES)
       return fail(c, SIM_EINVAL, "a no-allocation call holds at most %u tiles of 4096 records", NOALLOC_MAX_TILES);
   }
-  for (auto& t : c->times) t = sim_stage_time{0.0, 0, 0};
+  const bool left = sink.whole_offsets != nullptr;  // the records a conflict filter left
+  if (!left)
+    for (auto& t : c->times) t = sim_stage_time{0.0, 0, 0};
   const bool fit = sink.fitness != nullptr;
   if (fit && noalloc) return fail(c, SIM_EINVAL, "the fitness count has no no-allocation form");
   const bool warp = sink.side != nullptr;
   if (warp && (noalloc || trace_recs || fit || sink.barriers))
     return fail(c, SIM_EINVAL, "the warp-aware check runs on its own, on adjacent device records");
-  // radix passes and key width the previous call of this kind needed
-  uint32_t& pass_guess = fit ? c->fit_pass_guess : (warp ? c->warp_pass_guess : c->pass_guess);
-  bool& wide_guess = fit ? c->fit_wide_guess : (warp ? c->warp_wide_guess : c->wide_guess);
-  uint32_t& bits_guess = fit ? c->fit_bits_guess : (warp ? c->warp_bits_guess : c->bits_guess);
-  uint32_t& db_guess = fit ? c->fit_db_guess : (warp ? c->warp_db_guess : c->db_guess);
+  const Kind kind = fit ? KIND_FIT : (warp ? (left ? KIND_WARP_LEFT : KIND_WARP) : (left ? KIND_PLAIN_LEFT : KIND_PLAIN));
+  auto& gs = c->guess[kind];
+  if (!left && !noalloc && !fit && !sink.barriers && filter_pays(offsets, n_traces, total)) {
+    if (c->filter_pause[kind]) {
+      c->filter_pause[kind]--;
+    } else {
+      const int rf = run_filtered(c, d_records, trace_recs, offsets, n_traces, tpb, s, sink, total, n_tiles);
+      if (rf != RUN_FULL) return rf;
+      c->filter_pause[kind] = FILTER_PAUSE;
+    }
+  }
 
   // result delivery: summaries from the entry list, entries downloaded from
   // `dev_out` (n_races of them)
@@ -513,7 +583,8 @@ int run(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_
       sim_result_free(r);
       return hip_fail(c, e, "result download");
     }
-    for (uint32_t i = 0; i < n_traces; i++) sums[i].n_records = offsets[i + 1] - offsets[i];
+    const uint64_t* whole = left ? sink.whole_offsets : offsets;
+    for (uint32_t i = 0; i < n_traces; i++) sums[i].n_records = whole[i + 1] - whole[i];
     for (uint64_t k = 0; k < n_races; k++) {
       const sim_race& x = races[k];
       if (x.trace >= n_traces) {
@@ -558,12 +629,12 @@ int run(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_
   // where the previous call's widest key sorts in fewer passes with them
   // (no-allocation calls: 8, the scratch's tables are sized for it)
   uint32_t db = tune.digit_bits ? tune.digit_bits : RADIX_BITS;
-  if (!tune.digit_bits && bits_guess &&
-      radix_passes(bits_guess, RADIX_WIDE_BITS) < radix_passes(bits_guess, RADIX_BITS))
+  if (!tune.digit_bits && gs.bits &&
+      radix_passes(gs.bits, RADIX_WIDE_BITS) < radix_passes(gs.bits, RADIX_BITS))
     db = RADIX_WIDE_BITS;
   if (noalloc) db = RADIX_BITS;
   // traces sorted whole in LDS: one tile, or up to four with one-word keys
-  const bool wide = wide_guess;
+  const bool wide = gs.wide;
   const uint32_t small_max_tiles = wide ? 1u : 4u;
   auto& P = c->plan;
   const bool plan_hit = P.valid && P.host_gen == c->host_gen && P.bias == tune.group_shift_bias &&
@@ -578,16 +649,10 @@ int run(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_
       n_hgroups64 += (nt + (1ull << gs) - 1) >> gs;
     }
   const size_t h_bytes = host_bytes(n_traces, n_tiles, n_hgroups64);
-  if (c->h_meta_cap < h_bytes) {
-    if (noalloc) return fail(c, SIM_EINVAL, "the call's tables exceed the context's pinned tables");
-    if (c->h_meta) (void)hipHostFree(c->h_meta);
-    c->h_meta = nullptr;
-    c->h_meta_cap = 0;
-    c->host_gen++;  // (a plan hit never gets here: its tables fitted before)
-    e = hipHostMalloc(&c->h_meta, h_bytes + h_bytes / 8, hipHostMallocDefault);
-    if (e != hipSuccess) return hip_fail(c, e, "pinned allocation");
-    c->h_meta_cap = h_bytes + h_bytes / 8;
-  }
+  if (c->h_meta_cap < h_bytes && noalloc)
+    return fail(c, SIM_EINVAL, "the call's tables exceed the context's pinned tables");
+  // (a plan hit never grows it: its tables fitted before)
+  if ((e = grow_host(c, h_bytes)) != hipSuccess) return hip_fail(c, e, "pinned allocation");
   TraceDesc* hd = (TraceDesc*)c->h_meta;
   TileRef* ht = (TileRef*)(hd + n_traces);
   GroupRef* hg = (GroupRef*)(ht + n_tiles);
@@ -680,8 +745,9 @@ int run(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_
     out_p = (RaceOut*)rest;
     out_cap = rest_bytes / sizeof(RaceOut);
   } else {
-    if ((e = size_buffers(c, total, n_traces, n_tiles, n_hgroups, key_bytes, 1u << db)) != hipSuccess)
-      return hip_fail(c, e, "device allocation");
+    e = left ? grow_regions(c, total, n_traces, n_tiles, n_hgroups, key_bytes, 1u << db)
+             : size_buffers(c, total, n_traces, n_tiles, n_hgroups, key_bytes, 1u << db);
+    if (e != hipSuccess) return hip_fail(c, e, "device allocation");
     for (int r = 0; r < N_REGION; r++) reg[r] = region_buf(c, r)->p;
     out_p = (RaceOut*)c->out.p;
     out_cap = c->out.cap / sizeof(RaceOut);
@@ -715,6 +781,7 @@ int run(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_
   b.group_sum = (uint32_t*)reg[R_GSUM];
   b.stage = nullptr;
   b.stage_ref = nullptr;
+  b.stage_half = sink.stage_half;
   b.ctrl = (Ctrl*)reg[R_CTRL];
   b.out = out_p;
   b.out_cap = out_cap;
@@ -798,7 +865,7 @@ int run(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_
 
   // (a call of one-tile traces has all its passes done before the scan)
   // (a guess counted in another width is recounted from the key bits)
-  const uint32_t prev_guess = db == db_guess || !bits_guess ? pass_guess : radix_passes(bits_guess, db);
+  const uint32_t prev_guess = db == gs.db || !gs.bits ? gs.passes : radix_passes(gs.bits, db);
   const uint32_t guess = all_small ? MAX_PASSES : (prev_guess < MAX_PASSES ? prev_guess : MAX_PASSES);
   int first_scan_ev = 0;  // events of the first round before its scan
   auto first_round = [&]() -> hipError_t {
@@ -823,7 +890,7 @@ int run(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_
   // whose record addresses are not part of the shape, nor for calls that
   // may not allocate: instantiating a graph does.)
   const bool use_graph =
-      (c->flags & SIM_CFG_GRAPHS) && !prof && s != nullptr && guess > 0 && !trace_recs && !noalloc && !fit && !warp;
+      (c->flags & SIM_CFG_GRAPHS) && !prof && s != nullptr && guess > 0 && !trace_recs && !noalloc && !fit && !warp && !left;
   auto& G = c->graph;
   const bool replay = use_graph && G.exec && G.records == d_records && G.stream == s && G.total == total &&
                       G.n_traces == n_traces && G.n_tiles == n_tiles && G.gen == c->alloc_gen && G.guess == guess &&
@@ -888,7 +955,7 @@ int run(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_
   if (ctl.error_flags & ERR_NEEDS_WIDE) {
     // a trace needs two-word keys: run the whole call again in that mode
     // (the next call starts in it while its traces keep needing it)
-    wide_guess = true;
+    gs.wide = true;
     return run(c, d_records, trace_recs, offsets, n_traces, tpb, s, sink, noalloc);
   }
   const uint32_t needed = ctrl_passes(ctl.pass_bits);
@@ -901,11 +968,11 @@ int run(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_
     ctl = *c->h_ctrl;
   }
   if (!all_small) {  // an LDS-sorted call tells nothing about global passes
-    pass_guess = needed;
-    db_guess = db;
-    bits_guess = ctl.pass_bits & 0xFFFFu;
+    gs.passes = needed;
+    gs.db = db;
+    gs.bits = ctl.pass_bits & 0xFFFFu;
   }
-  wide_guess = ctl.wide_traces > 0;
+  gs.wide = ctl.wide_traces > 0;
   if (fit) {
     if (ctl.error_flags) return fail(c, SIM_EDEVICE, "internal kernel check failed (flags 0x%x)", ctl.error_flags);
     if ((e = hipMemcpyAsync(sink.fitness, fit_out, (size_t)n_traces * sizeof(FitOut), hipMemcpyDeviceToHost, s)) ||
@@ -1057,6 +1124,121 @@ int run(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_
   }
   *sink.barriers = br;
   return SIM_OK;
+}
+
+// A call with the conflict filter (filter.h) first: the records that may race
+// are gathered on the device, and run() checks those alone.  A racing pair's
+// records are all among them, so the entries are the whole call's.  Returns
+// RUN_FULL when the filter keeps more records than there is room for; the
+// caller then takes the full path.
+//
+// Everything lives in the buffers a full call of this size has anyway: keys0
+// holds the filter keys (4 bytes per record), the bucket rows and the
+// survivor bitmap, the upper half of keys1 the surviving records, the tables
+// are in the regions of the full call's tables.
+int run_filtered(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_recs, const uint64_t* offsets,
+                 uint32_t n_traces, const uint32_t* tpb, hipStream_t s, const Sink& sink, uint64_t total,
+                 uint32_t n_tiles) {
+  const bool warp = sink.side != nullptr;
+  // tables: traces up, survivor offsets down
+  const size_t tr_bytes = ((size_t)n_traces * sizeof(FTrace) + 15) / 16 * 16;
+  hipError_t e = grow_host(c, tr_bytes + ((size_t)n_traces + 1) * sizeof(uint32_t));
+  if (e != hipSuccess) return hip_fail(c, e, "pinned allocation");
+  c->host_gen++;  // the tables of the previous call are overwritten
+  FTrace* ht = (FTrace*)c->h_meta;
+  uint32_t* h_off = (uint32_t*)((char*)c->h_meta + tr_bytes);
+  uint64_t rows = 0;
+  uint32_t tiles = 0, buckets = 0, large = 0, max_lgb = 0;
+  for (uint32_t i = 0; i < n_traces; i++) {
+    const uint64_t n = offsets[i + 1] - offsets[i];
+    const uint32_t nt = (uint32_t)((n + FT - 1) / FT), lgb = filter_lgb(n);
+    ht[i] = FTrace{trace_recs ? (const void*)trace_recs[i] : (const void*)(d_records + offsets[i]), n, rows,
+                   (uint32_t)offsets[i], tpb[i], tiles, nt, buckets, lgb, filter_sbits(n, lgb),
+                   (uint32_t)(offsets[i] >> 5) + i};
+    rows += (uint64_t)nt * ((1u << lgb) + 1);
+    tiles += nt;
+    buckets += nt ? 1u << lgb : 0u;
+    max_lgb = std::max(max_lgb, lgb);
+    if ((n >> lgb) > FILTER_BUCKET) large = 1;
+  }
+  if (!large)  // (the kernel of ordinary buckets has room for one bit less)
+    for (uint32_t i = 0; i < n_traces; i++) ht[i].sbits = std::min(ht[i].sbits, FILTER_SLOT_BITS - 1);
+  auto up = [](uint64_t x) { return (x + 255) / 256 * 256; };
+  const uint64_t rows_at = up(4 * total), surv_at = up(rows_at + 4 * rows), surv_words = (total >> 5) + n_traces + 1;
+  const uint64_t hot_at = up(surv_at + 4 * surv_words);
+  const uint64_t out_at = up(4 * total);
+  const uint64_t half = 8 * total;  // bytes of a key buffer
+  // room per trace for hot buckets: 127, or fewer among many short traces
+  // (whose buckets are few)
+  const uint32_t hot_stride = total / n_traces >= 32768 ? 256u : (total / n_traces >= 1024 ? 16u : 2u);
+  if (hot_at + 4ull * hot_stride * n_traces > half || out_at + 16 > half || tiles + (uint64_t)buckets > 2ull * n_tiles) return RUN_FULL;
+  // Under a device limit the regions of the call over the survivors are sized
+  // here too (9-bit digits, a histogram group per tile at most), as that call
+  // must not release anything; otherwise they grow when they have to.
+  if ((e = c->dev_limit ? size_buffers(c, total, n_traces, n_tiles, n_tiles, 8, RADIX_MAX)
+                        : size_buffers(c, total, n_traces, n_tiles, 0, 8, RADIX)) != hipSuccess)
+    return hip_fail(c, e, "device allocation");
+  char* k0 = (char*)c->keys0.p;
+  char* k1 = (char*)c->keys1.p;
+  uint32_t* words = (uint32_t*)c->stats_part.p;  // 48 bytes per 4096-record tile
+  FilterBuffers f;
+  f.tr = (const FTrace*)c->meta.p;
+  f.n_traces = n_traces;
+  f.n_tiles = tiles;
+  f.n_buckets = buckets;
+  f.tile_trace = words;
+  f.tile_cnt = words + tiles;
+  f.bucket_trace = words + 2 * (uint64_t)tiles;
+  f.hot = f.bucket_trace + buckets;
+  f.n_hot = f.hot + buckets;
+  f.trace_hot = (uint32_t*)(k0 + hot_at);
+  f.hot_stride = hot_stride;
+  f.hot_maps = (uint32_t*)k1;  // the lower half of keys1
+  f.max_hot = (uint32_t)(out_at / ((1u << FILTER_SLOT_BITS) / 8));
+  f.max_lgb = max_lgb;
+  f.large = large;
+  f.trace_off = (uint32_t*)c->layout.p;
+  f.keys = (uint32_t*)k0;
+  f.rows = (uint32_t*)(k0 + rows_at);
+  f.survive = (uint32_t*)(k0 + surv_at);
+  f.side = sink.side;
+  // room for the survivors and, in the warp-aware check, their side words
+  f.out_cap = (uint32_t)((half - out_at) / (warp ? 20 : 16));
+  f.out = k1 + out_at;
+  f.out_side = (uint32_t*)(k1 + out_at + 16ull * f.out_cap);
+  f.ctrl = (Ctrl*)c->ctrl.p;
+  const bool prof = (c->flags & SIM_CFG_PROFILE) != 0;
+  auto mark = [&](int k) { return prof ? hipEventRecord(c->ev[k], s) : hipSuccess; };
+  if ((e = hipMemcpyAsync(c->meta.p, ht, tr_bytes, hipMemcpyHostToDevice, s)))
+    return hip_fail(c, e, "table upload");
+  c->meta_gen++;
+  if ((e = mark(0)) || (e = launch_filter_part(f, s)) || (e = mark(1)) || (e = launch_filter_test(f, s)) ||
+      (e = mark(2)) || (e = launch_filter_out(f, s)) || (e = mark(3)) ||
+      (e = hipMemcpyAsync(h_off, f.trace_off, ((size_t)n_traces + 1) * sizeof(uint32_t), hipMemcpyDeviceToHost, s)) ||
+      (e = hipMemcpyAsync(c->h_ctrl, f.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s)) ||
+      (e = hipStreamSynchronize(s)))
+    return hip_fail(c, e, "conflict filter");
+  if (prof)
+    for (int k = 0; k < 3; k++) {
+      float ms = 0;
+      (void)hipEventElapsedTime(&ms, c->ev[k], c->ev[k + 1]);
+      c->times[ST_FILTER_PART + k].ms += ms;
+      c->times[ST_FILTER_PART + k].launches += 1;
+    }
+  if (c->h_ctrl->error_flags & LAYOUT_ERR_RECORD)
+    return fail(c, SIM_ERECORD, "invalid record at index %llu (action > 2 or space > 1)",
+                (unsigned long long)c->h_ctrl->first_bad);
+  const uint64_t kept = h_off[n_traces];
+  if (kept > f.out_cap) return RUN_FULL;
+  std::vector<uint64_t> left(h_off, h_off + n_traces + 1);  // (the host block is overwritten by the next call's tables)
+  Sink sub = sink;
+  sub.whole_offsets = offsets;
+  sub.side = warp && kept ? f.out_side : nullptr;
+  // staging beside the survivors' keys (16 bytes each at most): an entry of
+  // 64 bytes for two records
+  const uint64_t stage_at = up(16 * kept);
+  if (stage_at + 32 * kept <= half) sub.stage_half = (RaceOut*)(k0 + stage_at);
+  return run(c, (const sim_record*)f.out, nullptr, left.data(), n_traces, tpb, s, sub, false);
 }
 
 void divergence_result_free(sim_divergence_result* r) {

@@ -39,124 +39,14 @@
 #include "barrier.h"
 #include "launch.h"
 #include "segstate.h"
+#include "wave.h"
 
 namespace sc {
 
-constexpr int NWAVE = NT / 64;
 static_assert(NT == (int)RADIX, "one thread per digit in the radix kernels");
 static_assert(GROUP == NT, "one thread per tile in the output kernels");
 constexpr uint64_t SEGF = 1ull << 63;   // head flag of packed segmented values
 constexpr uint32_t CLS_NONE = 3;        // padding element past the end of a trace
-
-// ------------------------------------------------------------- utilities
-
-// record fields from its two 64-bit halves (little-endian sim_record)
-struct Rec {
-  uint64_t unit;
-  uint32_t tid, epoch, action, space;
-};
-__device__ __forceinline__ Rec unpack_rec(ulonglong2 v) {
-  Rec r;
-  r.unit = v.x;
-  r.tid = (uint32_t)v.y;
-  r.epoch = (uint32_t)(v.y >> 32) & 0xFFFFu;
-  r.action = (uint32_t)(v.y >> 48) & 0xFFu;
-  r.space = (uint32_t)(v.y >> 56);
-  return r;
-}
-
-
-// Cross-lane moves of the wave's data-parallel primitives (DPP): the value
-// of another lane, or 0 where that lane is outside the pattern or the row
-// is masked off.  Row = 16 lanes.
-enum : int {
-  DPP_ROW_SHR1 = 0x111, DPP_ROW_SHR2 = 0x112, DPP_ROW_SHR4 = 0x114, DPP_ROW_SHR8 = 0x118,
-  DPP_WAVE_SHR1 = 0x138,   // lane i gets lane i - 1
-  DPP_ROW_BCAST15 = 0x142, // last lane of each row to the next row
-  DPP_ROW_BCAST31 = 0x143  // lane 31 to rows 2 and 3
-};
-// (`old` instead of 0 where the source lane is outside the pattern.)
-template <int CTRL, int ROWS = 0xf>
-__device__ __forceinline__ uint32_t dpp(uint32_t v, uint32_t old = 0u) {
-  return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, ROWS, 0xf, false);
-}
-template <int CTRL, int ROWS = 0xf>
-__device__ __forceinline__ uint64_t dpp(uint64_t v, uint64_t old = 0ull) {
-  return ((uint64_t)dpp<CTRL, ROWS>((uint32_t)(v >> 32), (uint32_t)(old >> 32)) << 32) |
-         dpp<CTRL, ROWS>((uint32_t)v, (uint32_t)old);
-}
-
-__device__ __forceinline__ uint32_t readlane(uint32_t v, int lane) {
-  return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
-}
-__device__ __forceinline__ uint64_t readlane(uint64_t v, int lane) {
-  return ((uint64_t)readlane((uint32_t)(v >> 32), lane) << 32) | readlane((uint32_t)v, lane);
-}
-__device__ __forceinline__ uint64_t readfirstlane(uint64_t v) {
-  return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32) |
-         (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-}
-
-// Reduction over the 64 lanes with an associative, commutative operator
-// whose identity is `id`: the scan pattern below ends with the total in
-// lane 63, which every lane then reads.
-template <typename T, typename Op>
-__device__ __forceinline__ T wave_reduce(T v, T id, Op op) {
-  v = op(dpp<DPP_ROW_SHR1>(v, id), v);
-  v = op(dpp<DPP_ROW_SHR2>(v, id), v);
-  v = op(dpp<DPP_ROW_SHR4>(v, id), v);
-  v = op(dpp<DPP_ROW_SHR8>(v, id), v);
-  v = op(dpp<DPP_ROW_BCAST15, 0xa>(v, id), v);
-  v = op(dpp<DPP_ROW_BCAST31, 0xc>(v, id), v);
-  return readlane(v, 63);
-}
-template <typename T>
-__device__ __forceinline__ T wave_min(T v) {
-  return wave_reduce(v, (T)~(T)0, [](T a, T b) { return a < b ? a : b; });
-}
-template <typename T>
-__device__ __forceinline__ T wave_max(T v) {
-  return wave_reduce(v, (T)0, [](T a, T b) { return a > b ? a : b; });
-}
-
-// Inclusive scan over the 64 lanes of a wave with an associative operator
-// whose identity is 0: within rows (shifts 1, 2, 4, 8), then across rows
-// (row 0's total into row 1 and row 2's into row 3, then lane 31's into
-// rows 2 and 3).
-template <typename T, typename Op>
-__device__ __forceinline__ T wave_incl_scan(T v, Op op) {
-  v = op(dpp<DPP_ROW_SHR1>(v), v);
-  v = op(dpp<DPP_ROW_SHR2>(v), v);
-  v = op(dpp<DPP_ROW_SHR4>(v), v);
-  v = op(dpp<DPP_ROW_SHR8>(v), v);
-  v = op(dpp<DPP_ROW_BCAST15, 0xa>(v), v);
-  v = op(dpp<DPP_ROW_BCAST31, 0xc>(v), v);
-  return v;
-}
-
-// Exclusive sum over a workgroup of NW waves; *total receives the sum of all
-// values.  Every thread of the workgroup must call it (it holds barriers).
-template <int NW>
-__device__ uint32_t block_excl_sum_n(uint32_t v, uint32_t* lds /* NW */, uint32_t* total) {
-  const uint32_t lane = __lane_id(), wave = threadIdx.x >> 6;
-  const uint32_t inc = wave_incl_scan(v, [](uint32_t a, uint32_t b) { return a + b; });
-  if (lane == 63) lds[wave] = inc;
-  __syncthreads();
-  uint32_t pre = 0, tot = 0;
-#pragma unroll
-  for (int w = 0; w < NW; w++) {
-    const uint32_t x = lds[w];
-    if (w < (int)wave) pre += x;
-    tot += x;
-  }
-  __syncthreads();
-  *total = tot;
-  return pre + inc - v;
-}
-
-__device__ __forceinline__ uint32_t block_excl_sum(uint32_t v, uint32_t* lds /* NWAVE */, uint32_t* total) {
-  return block_excl_sum_n<NWAVE>(v, lds, total);
-}
 
 // Segmented exclusive scan over the workgroup of three packed words that
 // share one head flag (SEGF in bit 63 of the first: the thread holds a
@@ -321,19 +211,6 @@ __device__ __forceinline__ void wave_hist_add(uint32_t* h, uint32_t dg, bool val
 }
 
 // -------------------------------------------------------------- k_stats
-// A tile's records, read through the pointer its table entry holds.  To the
-// compiler that pointer is generic, so it would load through flat
-// instructions, and a flat load also holds up every wait for an LDS
-// operation.  Records are always in memory the GPU addresses as global, so
-// they are read as global memory.
-typedef uint64_t rec_words __attribute__((ext_vector_type(2)));
-typedef const __attribute__((address_space(1))) rec_words* GRecords;
-__device__ __forceinline__ GRecords global_records(const void* p) { return (GRecords)p; }
-__device__ __forceinline__ ulonglong2 load_record(GRecords p, uint32_t j) {
-  const rec_words v = p[j];
-  return ulonglong2{v.x, v.y};
-}
-
 // Per-tile partial statistics; k_layout reduces them per trace.
 
 // HIST: also the tile histogram of radix digit 0 for calls whose digit 0 is
@@ -1209,6 +1086,10 @@ __device__ __forceinline__ void write_entry(RaceOut* dst, uint32_t trace, const 
 // dedicated buffer (sized by the host from that scan's counts).
 __device__ __forceinline__ RaceOut* stage_of(const Buffers& b, uint32_t tile, const TraceDesc& T,
                                              const TraceLayout& L, uint64_t start, uint32_t n_in, uint32_t* cap) {
+  if (b.stage_half) {  // a complete location holds two records of the tile, so this never overflows
+    *cap = n_in / 2;
+    return b.stage_half + (T.off + start) / 2;
+  }
   if (b.stage_ref) {
     const uint64_t ref = b.stage_ref[tile];
     if (ref & STAGE_CAP_MASK) {
@@ -1815,8 +1696,14 @@ __global__ __launch_bounds__(NT) void k_scan_out(Buffers b, uint32_t passes_done
   const uint32_t ex = block_excl_sum(inc + cf, sc, &tot);
   // the last workgroup publishes the call's total
   if (blockIdx.x + 1 == gridDim.x && threadIdx.x == 0) b.ctrl->total_entries = group_base + tot;
-  if (!valid || inc + cf == 0) return;
-  uint64_t pos = group_base + ex;
+  // The group's entries, copied in quarters of 16 bytes by all threads: a
+  // tile may hold none or two thousand, so a thread finds its entry's tile in
+  // the prefix (a thread per tile copied 20 entries of 64 bytes one by one
+  // where most locations race: 21 us on 500 tiles).
+  __shared__ uint32_t s_first[NT + 1];
+  __shared__ const RaceOut* s_stage[NT];
+  s_first[threadIdx.x] = ex;
+  if (threadIdx.x == 0) s_first[NT] = tot;
   if (inc) {
     const TileRef tr = b.tiles[t];
     const TraceDesc T = b.desc[tr.trace];
@@ -1824,11 +1711,22 @@ __global__ __launch_bounds__(NT) void k_scan_out(Buffers b, uint32_t passes_done
     const uint64_t start = (uint64_t)tr.local * TILE;
     const uint32_t n_in = (uint32_t)min<uint64_t>((uint64_t)TILE, T.n - start);
     uint32_t cap;
-    const RaceOut* st = stage_of(b, t, T, L, start, n_in, &cap);
-    for (uint32_t e = 0; e < inc && e < cap; e++, pos++)
-      if (pos < b.out_cap) b.out[pos] = st[e];
+    s_stage[threadIdx.x] = stage_of(b, t, T, L, start, n_in, &cap);  // (a tile beyond its cap raised an error above)
   }
-  if (cf && pos < b.out_cap) b.out[pos] = b.cross[t];
+  __shared__ uint32_t s_inc[NT];
+  s_inc[threadIdx.x] = inc;
+  __syncthreads();
+  for (uint32_t q = threadIdx.x; q < 4 * tot; q += NT) {
+    const uint32_t e = q >> 2;
+    if (group_base + e >= b.out_cap) break;
+    uint32_t lo = 0;  // the last tile whose first entry is at or before e
+#pragma unroll
+    for (uint32_t step = NT / 2; step; step >>= 1)
+      if (s_first[lo + step] <= e) lo += step;
+    const uint32_t k = e - s_first[lo];
+    const RaceOut* src = k < s_inc[lo] ? s_stage[lo] + k : b.cross + ((uint64_t)blockIdx.x * GROUP + lo);
+    ((ulonglong2*)(b.out + group_base + e))[q & 3u] = ((const ulonglong2*)src)[q & 3u];
+  }
 }
 
 __global__ void k_reset_errors(Ctrl* ctrl, uint32_t mask) {

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "filter.h"
 #include "keys.h"
 #include "tilewalk.h"
 
@@ -96,6 +97,7 @@ struct Buffers {            // device pointers of one call
   uint32_t* cross_flag;     // [tile]
   uint32_t* group_sum;      // [group]
   RaceOut* stage;           // dedicated staging of the tiles stage_ref names (see STAGE_CAP_BITS)
+  RaceOut* stage_half;      // or staging for every tile, an entry per two records (record r's at r / 2)
   const uint64_t* stage_ref;// [tile], or nullptr: every tile stages in its slice of the idle key buffer
   Ctrl* ctrl;
   RaceOut* out;
@@ -124,6 +126,31 @@ struct Buffers {            // device pointers of one call
   uint32_t digit_bits;      // digit width of the radix passes after pass 0: RADIX_BITS or RADIX_WIDE_BITS
 };
 
+struct FilterBuffers {      // device pointers of a call's conflict filter (filter.h, filter.hip)
+  const FTrace* tr;
+  uint32_t n_traces, n_tiles, n_buckets;
+  uint32_t* tile_trace;     // [tile] its trace
+  uint32_t* bucket_trace;   // [bucket] its trace
+  uint32_t* keys;           // [record] a tile's keys by bucket: slot << FT_BITS | place in the tile
+  uint32_t* rows;           // [tile][buckets + 1] first write | first read << 16 of each bucket in the tile
+  uint32_t* hot;            // [bucket] flags of hot words (filter.hip), and the place of the bucket's bitmap
+  uint32_t* n_hot;          // buckets with a stored bitmap
+  uint32_t* trace_hot;      // [trace][hot_stride] its hot buckets
+  uint32_t hot_stride;      // words of a trace's list
+  uint32_t* hot_maps;       // their bitmaps
+  uint32_t max_hot;         // room for this many
+  uint32_t max_lgb;         // the largest FTrace::lgb of the call
+  uint32_t large;           // 1: some trace's buckets hold more than FILTER_BUCKET records on average
+  uint32_t* survive;        // bitmap of the records that may race (FTrace::surv0)
+  uint32_t* tile_cnt;       // [tile] survivors, then the survivors before the tile
+  uint32_t* trace_off;      // [trace + 1] survivors before the trace
+  const uint32_t* side;     // warp-aware check: one side word per record, else nullptr
+  void* out;                // the surviving records (and their side words)
+  uint32_t* out_side;
+  uint32_t out_cap;         // records `out` holds
+  Ctrl* ctrl;
+};
+
 // Barrier instances (per trace and boundary) of the redundant-barrier check:
 // `copies` copies of every counter pair, spread over cache lines, summed by
 // the host.  Trace i's boundaries start at bar_base[i].
@@ -134,7 +161,7 @@ struct BarrierCount {
 
 // Kernel stages, in launch order.
 enum Stage { ST_INIT = 0, ST_STATS, ST_LAYOUT, ST_KEYGEN, ST_UPSWEEP, ST_SORT, ST_SCAN, ST_CROSS, ST_OUT,
-             ST_SORT_SMALL, ST_COUNT };
+             ST_SORT_SMALL, ST_FILTER_PART, ST_FILTER_TEST, ST_FILTER_OUT, ST_COUNT };
 
 hipError_t launch_init(const Buffers& b, hipStream_t s);
 hipError_t launch_stats(const Buffers& b, hipStream_t s);
@@ -147,6 +174,11 @@ hipError_t launch_scan_tiles(const Buffers& b, uint32_t passes_done, hipStream_t
 hipError_t launch_scan_cross(const Buffers& b, uint32_t passes_done, hipStream_t s);
 hipError_t launch_scan_out(const Buffers& b, uint32_t passes_done, hipStream_t s);
 hipError_t launch_reset_errors(const Buffers& b, uint32_t mask, hipStream_t s);
+// The conflict filter, in this order: keys by bucket and record checks; the
+// survivor bitmap; the surviving records and each trace's number of them.
+hipError_t launch_filter_part(const FilterBuffers& f, hipStream_t s);
+hipError_t launch_filter_test(const FilterBuffers& f, hipStream_t s);
+hipError_t launch_filter_out(const FilterBuffers& f, hipStream_t s);
 // Redundant-barrier check over the sorted keys of a finished call: clears
 // `table` (n_counts entries) and counts every trace's barrier instances.
 hipError_t launch_barriers(const Buffers& b, const uint64_t* bar_base, BarrierCount* table, uint64_t n_counts,

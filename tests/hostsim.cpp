@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "../paper_1905_01833_amd/csrc/barrier.h"
+#include "../paper_1905_01833_amd/csrc/filter.h"
 #include "../paper_1905_01833_amd/csrc/segstate.h"
 #include "../paper_1905_01833_amd/csrc/tilewalk.h"
 
@@ -376,4 +377,71 @@ extern "C" int hs_digit_plan(uint64_t seed, int trials) {
   for (uint32_t db : {RADIX_BITS, RADIX_WIDE_BITS})
     bad += plan_sort_impl<uint64_t>(seed + db, trials, db) + plan_sort_impl<u128>(seed + 2 * db, trials, db);
   return bad;
+}
+
+// The conflict filter (filter.h) as its kernels decide: keep[i] is set for
+// every record that survives.  x_slots: slots of the exact table; rounds: how
+// often it is tried (0: the bitmaps alone, as for a list that overflows).
+extern "C" void hs_filter(const rec* recs, const uint64_t* off, uint32_t n_traces, const uint32_t* tpb, uint32_t x_slots,
+                          int rounds, uint8_t* keep) {
+  for (uint32_t t = 0; t < n_traces; t++) {
+    const uint64_t n = off[t + 1] - off[t];
+    const rec* r = recs + off[t];
+    uint8_t* kp = keep + off[t];
+    const uint32_t lgb = filter_lgb(n), sb = std::min(filter_sbits(n, lgb), FILTER_SLOT_BITS - 1), smask = (1u << sb) - 1;
+    std::vector<std::vector<uint32_t>> bucket((size_t)1 << lgb);
+    std::vector<uint32_t> slot(n);
+    for (uint64_t i = 0; i < n; i++) {
+      const uint32_t h = filter_group(r[i].unit, r[i].tid / tpb[t], r[i].epoch, r[i].space);
+      bucket[filter_bucket(h, lgb)].push_back((uint32_t)i);
+      slot[i] = h & ((1u << FILTER_SLOT_BITS) - 1) & smask;
+      kp[i] = 0;
+    }
+    for (auto& b : bucket) {
+      std::vector<uint8_t> A((size_t)smask + 1), D((size_t)smask / 2 + 1);
+      for (uint32_t i : b)
+        if (r[i].action) {
+          if (A[slot[i]]) D[slot[i] >> 1] = 1;
+          A[slot[i]] = 1;
+        }
+      for (uint32_t i : b)
+        if (!r[i].action && A[slot[i]]) D[slot[i] >> 1] = kp[i] = 1;
+      for (uint32_t i : b)
+        if (r[i].action && D[slot[i] >> 1]) kp[i] = 1;
+      for (int round = 0; round < rounds; round++) {
+        std::vector<uint32_t> mn(x_slots, ~0u), mx(x_slots, 0u), act(x_slots, 0u);
+        auto slots = [&](uint32_t i, uint32_t* se, uint32_t* sl) {
+          const uint32_t blk = r[i].tid / tpb[t];
+          *se = filter_exact_hash(r[i].unit, blk, r[i].epoch, 2u + r[i].space, (uint32_t)round) & (x_slots - 1);
+          *sl = r[i].space ? *se : filter_exact_hash(r[i].unit, 0, 0, 1, (uint32_t)round) & (x_slots - 1);
+        };
+        auto put = [&](uint32_t s, uint32_t id, uint32_t a) {
+          mn[s] = std::min(mn[s], id);
+          mx[s] = std::max(mx[s], id);
+          act[s] |= a;
+        };
+        for (uint32_t i : b)
+          if (kp[i]) {
+            uint32_t se, sl;
+            slots(i, &se, &sl);
+            put(se, r[i].tid, 1u << r[i].action);
+            if (!r[i].space) put(sl, r[i].tid / tpb[t], 1u << r[i].action);
+          }
+        for (uint32_t i : b)
+          if (kp[i]) {
+            uint32_t se, sl;
+            slots(i, &se, &sl);
+            auto races = [&](uint32_t s) { return mn[s] != mx[s] && ((act[s] & 2u) || (act[s] & 5u) == 5u); };
+            kp[i] = races(se) || races(sl);
+          }
+      }
+    }
+  }
+}
+
+// Records of the fullest of 2^lgb filter buckets (threads of one block).
+extern "C" uint64_t hs_filter_most(const rec* recs, uint64_t n, uint32_t lgb) {
+  std::vector<uint64_t> c((size_t)1 << lgb);
+  for (uint64_t i = 0; i < n; i++) c[filter_bucket(filter_group(recs[i].unit, 0, recs[i].epoch, recs[i].space), lgb)]++;
+  return *std::max_element(c.begin(), c.end());
 }
