@@ -1737,20 +1737,29 @@ __global__ void k_reset_errors(Ctrl* ctrl, uint32_t mask) {
 //
 // Redundant-barrier check (Alg. 5, second loop) over the sorted keys of a
 // finished call: one thread per element; an element that heads a barrier
-// instance (barrier.h) reads the two epoch runs around it straight from the
-// key buffer (they are short except on the hottest locations) and counts
-// the instance, racing or not, under its trace and boundary.
+// instance (barrier.h) walks the two epoch runs around it and counts the
+// instance, racing or not, under its trace and boundary.
+//
+// Bound by latency: a walk of the runs by single loads from memory took 1.06
+// ms for 2^22 records (runs of up to 180 records on hot words), and one over
+// keys staged in LDS, long runs by the whole wave, 118 us.  The records of a
+// run are in thread order, so its smallest and largest thread per action are
+// its first and last record of that action: with the tile's run starts and
+// actions as bitmaps in LDS they are found by bit scans, in the one word of
+// 64 elements that holds most runs.  Only a run that leaves the tile is read
+// from memory, by the whole wave.
 //
 // Counts are summed per tile in LDS (boundaries below 256; later ones go to
 // global memory directly) and added to one of `copies` copies of the
 // trace's counters, chosen by tile, so that the atomics of many workgroups
 // spread over several cache lines.
-
 template <typename K, bool LOOP>
 __global__ __launch_bounds__(NT) void k_barriers(Buffers b, const uint64_t* __restrict__ bar_base,
                                                  BarrierCount* table, uint32_t copies) {
   constexpr uint32_t NBIN = 256;
   __shared__ uint32_t s_inst[NBIN], s_race[NBIN];
+  __shared__ K s_key[TILE + 1];  // the key before the tile, then the tile's
+  __shared__ uint64_t s_run[TILE / 64], s_act[3][TILE / 64];  // run starts, and the elements of each action
   if (b.ctrl->error_flags) return;
   const TileWalk tw = tile_walk(b.n_tiles, gridDim.x, blockIdx.x);
   for (uint32_t tile = tw.first; tile < tw.end; tile = LOOP ? tile + tw.step : tw.end) {
@@ -1762,18 +1771,137 @@ __global__ __launch_bounds__(NT) void k_barriers(Buffers b, const uint64_t* __re
     const TileRef tr = b.tiles[tile];
     const TraceDesc T = b.desc[tr.trace];
     const TraceLayout L = b.layout[tr.trace];
-    const K* keys = (const K*)b.keys[L.npasses & 1u] + T.off;  // the trace's sorted keys
     const uint64_t start = (uint64_t)tr.local * TILE;
     const uint32_t n_in = tr.n_flags & ~TILE_SHORT;
+    const K* keys = (const K*)b.keys[L.npasses & 1u] + T.off + start;  // the tile's sorted keys
     BarrierCount* counts = table + bar_base[tr.trace] * copies;
+    const uint32_t lane = tx & 63u;
+    {
+      K k[ITEMS];
+#pragma unroll
+      for (int r = 0; r < ITEMS; r++) {
+        const uint32_t j = tx + r * NT;
+        k[r] = j < n_in ? keys[j] : (K)0;
+      }
+#pragma unroll
+      for (int r = 0; r < ITEMS; r++) s_key[1 + tx + r * NT] = k[r];
+      if (tx == 0) s_key[0] = start ? keys[-1] : (K)0;
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < ITEMS; r++) {
+        const uint32_t j = tx + r * NT, c = action_class(k[r]);
+        const bool in = j < n_in;
+        const uint64_t run = __ballot(!in || start + j == 0 || (s_key[j] >> L.shift_e) != (k[r] >> L.shift_e));
+        const uint64_t a0 = __ballot(in && c == 0), a1 = __ballot(in && c == 1), a2 = __ballot(in && c == 2);
+        if (lane == 0) {
+          s_run[j >> 6] = run;  // (the elements past the tile's end start runs: the last run ends there)
+          s_act[0][j >> 6] = a0;
+          s_act[1][j >> 6] = a1;
+          s_act[2][j >> 6] = a2;
+        }
+      }
+    }
     __syncthreads();
+    // first set bit of m in [i, end), or end; last one in [lo, i), or ~0
+    auto next_bit = [&](const uint64_t* m, uint32_t i, uint32_t end) -> uint32_t {
+      uint32_t w = i >> 6;
+      uint64_t x = i < end ? m[w] & (~0ull << (i & 63u)) : 0ull;
+      while (!x) {
+        if (++w << 6 >= end) return end;
+        x = m[w];
+      }
+      return min((w << 6) + (uint32_t)__builtin_ctzll(x), end);
+    };
+    auto prev_bit = [&](const uint64_t* m, uint32_t lo, uint32_t i) -> uint32_t {
+      if (i <= lo) return ~0u;
+      uint32_t w = (i - 1) >> 6;
+      uint64_t x = m[w] & (~0ull >> (63u - ((i - 1) & 63u)));
+      while (!x) {
+        if (w << 6 <= lo) return ~0u;
+        x = m[--w];
+      }
+      const uint32_t k = (w << 6) + 63u - (uint32_t)__builtin_clzll(x);
+      return k >= lo ? k : ~0u;
+    };
+    // the records of a run's part [lo, hi) inside the tile
+    auto summary = [&](uint32_t lo, uint32_t hi, BarrierSide& side) {
+      side.clear();
+      if (lo >= hi) return;
+      if (lo >> 6 == (hi - 1) >> 6) {
+        const uint64_t in = (~0ull << (lo & 63u)) & (~0ull >> (63u - ((hi - 1) & 63u)));
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+          const uint64_t x = s_act[c][lo >> 6] & in;
+          if (!x) continue;
+          const uint32_t w = (lo >> 6) << 6;
+          side.mn[c] = key_ltid_t<K>(L, s_key[1 + w + (uint32_t)__builtin_ctzll(x)]);
+          side.mx[c] = key_ltid_t<K>(L, s_key[1 + w + 63u - (uint32_t)__builtin_clzll(x)]);
+        }
+      } else {
+#pragma unroll 1
+        for (int c = 0; c < 3; c++) {
+          const uint32_t f = next_bit(s_act[c], lo, hi);
+          if (f == hi) continue;
+          const uint32_t mn = key_ltid_t<K>(L, s_key[1 + f]), mx = key_ltid_t<K>(L, s_key[1 + prev_bit(s_act[c], lo, hi)]);
+          for (int q = 0; q < 3; q++)
+            if (q == c) {
+              side.mn[q] = mn;
+              side.mx[q] = mx;
+            }
+        }
+      }
+    };
+    // the part of a run outside the tile, from element `from` on in steps of
+    // +1 or -1: 64 elements at a time, for one lane's instance after another
+    const int64_t i_min = -(int64_t)start, i_end = (int64_t)(T.n - start);
+    auto outside = [&](bool mine, int64_t from, int step, const K& run, BarrierSide& side) {
+      uint64_t todo = __ballot(mine);
+      while (todo) {
+        const int who = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        const K id = readlane_key(run, who);
+        BarrierSide part;
+        part.clear();
+        for (int64_t i = from + (int64_t)step * lane;; i += (int64_t)step * 64) {
+          bool in = i >= i_min && i < i_end;
+          if (in) {
+            const K y = keys[i];
+            in = (y >> L.shift_e) == id;
+            if (in) part.add(L, y);
+          }
+          if (__ballot(in) != ~0ull) break;  // (the run's elements are the first lanes)
+        }
+        part.reduce([](uint32_t a, bool mn) { return mn ? wave_min(a) : wave_max(a); });
+        if ((int)lane == who) side.merge(part);
+      }
+    };
 #pragma unroll 1
     for (int r = 0; r < ITEMS; r++) {
       const uint32_t j = tx + r * NT;
-      if (j >= n_in) break;
-      uint32_t e0;
-      bool racing;
-      if (!barrier_instance<K>(L, keys, T.n, start + j, &e0, &racing)) continue;
+      BarrierSide before, after;
+      before.clear();
+      after.clear();
+      uint32_t e0 = 0;
+      bool head = false, back = false, fwd = false;  // an instance; its runs leave the tile
+      K rw = 0, rx = 0;
+      if (j < n_in && start + j != 0) {
+        const K x = s_key[j + 1], w = s_key[j];
+        rw = w >> L.shift_e;
+        rx = x >> L.shift_e;
+        head = barrier_head<K>(L, w, x);
+        if (head) {
+          e0 = key_epoch_t<K>(L, w);
+          const uint32_t p = prev_bit(s_run, 0, j), s0 = p == ~0u ? 0u : p, e = next_bit(s_run, j + 1, n_in);
+          summary(s0, j, before);
+          summary(j, e, after);
+          back = p == ~0u && start != 0;  // (with j = 0 all of the run is before the tile)
+          fwd = e == n_in;
+        }
+      }
+      outside(back, -1, -1, rw, before);
+      outside(fwd, n_in, 1, rx, after);
+      if (!head) continue;
+      const bool racing = barrier_races(before, after);
       if (e0 < NBIN) {
         atomicAdd(&s_inst[e0], 1u);
         if (racing) atomicAdd(&s_race[e0], 1u);

@@ -51,6 +51,10 @@ __device__ __forceinline__ uint32_t readlane(uint32_t v, int lane) {
 __device__ __forceinline__ uint64_t readlane(uint64_t v, int lane) {
   return ((uint64_t)readlane((uint32_t)(v >> 32), lane) << 32) | readlane((uint32_t)v, lane);
 }
+__device__ __forceinline__ uint64_t readlane_key(uint64_t v, int lane) { return readlane(v, lane); }
+__device__ __forceinline__ u128 readlane_key(u128 v, int lane) {
+  return ((u128)readlane((uint64_t)(v >> 64), lane) << 64) | readlane((uint64_t)v, lane);
+}
 __device__ __forceinline__ uint64_t readfirstlane(uint64_t v) {
   return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32) |
          (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
