@@ -47,15 +47,14 @@ METRIC = "access records checked/sec and achieved HBM GB/s (batched vs plain, bi
 #   sort   one radix pass reads and writes every 8-byte key
 #   scan   reads every 8-byte key once (tile scan; the crossing-location
 #          and output kernels touch per-tile data only)
-# and, in calls of many records, the conflict filter before them (they then
-# see only the records it keeps):
-#   filter_part reads the record and writes its 4-byte filter key
-#   filter_test reads every filter key once
+# and, in calls that count their races by group instead of sorting:
+#   filter_part reads the record and writes its 4-byte key
+#   filter_count reads every 4-byte key once
 BYTES_PER_RECORD = {"stats": 16, "keygen": 24, "upsweep": 8, "sort_pass": 16, "scan_tiles": 8, "filter_part": 20,
-                    "filter_test": 4}
+                    "filter_count": 4}
 KERNEL_SYMBOL = {"stats": "k_stats", "keygen": "k_keygen_scatter", "upsweep": "k_upsweep", "sort_pass": "k_scatter",
-                 "scan_tiles": "k_scan_tiles", "filter_part": "k_filter_part", "filter_test": "k_filter_test"}
-FILTER_STAGES = ("filter_part", "filter_test")
+                 "scan_tiles": "k_scan_tiles", "filter_part": "k_filter_part", "filter_count": "k_filter_count"}
+FILTER_STAGES = ("filter_part", "filter_count")
 
 C3_DESC = ("c3: batched, 4096 traces in one call, sizes log-uniform 2^8..2^20 records, 1..256 blocks x 256 threads, "
            "75% reads, shared window 48 KiB/block, global reads Zipf(1.1) over 64 MiB, barrier every 16 accesses, "
@@ -168,7 +167,6 @@ def globally_sorted_records(offsets):
 
 def roofline(stage_ms, stage_launches, steps, n, workload_name, n_global=None):
     """Roofline of the dominant kernel from per-stage event times."""
-    # (the stages after a conflict filter see an unknown part of the records)
     stages = FILTER_STAGES if stage_launches.get("filter_part") else BYTES_PER_RECORD
     dom = max(stages, key=lambda s: stage_ms.get(s, 0.0))
     avg_ms = stage_ms[dom] / max(1, stage_launches[dom])
@@ -184,13 +182,12 @@ def pipeline(records_per_s, name, passes, stage_ms_per_step):
     """Whole-pipeline figures: records/s x the workload's algorithmic bytes
     per record against the HBM peak, and the bytes the kernels as built
     move (stats 16, key generation with radix pass 0 24, histogram and
-    scatter 24 per further pass, scan 8; with the conflict filter 24, without
-    the records it keeps, which take the other stages)."""
-    filtered = stage_ms_per_step.get("filter_part", 0.0) > 0.0
-    built = 24 if filtered else 16 + 24 + 24 * max(0.0, passes - 1) + 8
+    scatter 24 per further pass, scan 8; with the grouped count 24)."""
+    grouped = stage_ms_per_step.get("filter_part", 0.0) > 0.0
+    built = 24 if grouped else 16 + 24 + 24 * max(0.0, passes - 1) + 8
     return {"alg_bytes_per_record": B_ALG[name], "gbps": round(records_per_s * B_ALG[name] / 1e9, 1),
             "frac": round(records_per_s * B_ALG[name] / 1e9 / HBM_PEAK_GBPS, 4), "radix_passes": passes,
-            "conflict_filter": filtered, "built_bytes_per_record": built, "built_gbps": round(records_per_s * built / 1e9, 1),
+            "grouped_count": grouped, "built_bytes_per_record": built, "built_gbps": round(records_per_s * built / 1e9, 1),
             "kernel_ms_per_step": round(sum(stage_ms_per_step.values()), 4)}
 
 

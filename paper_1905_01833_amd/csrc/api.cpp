@@ -3,8 +3,11 @@
 // A context owns grow-only device buffers sized by the largest call seen so
 // far, a default-priority stream for the host-record entry point, pinned
 // host staging for the small per-call tables and results.  A check is one
-// ordered sequence of kernel launches on one stream
-// and one synchronisation; there is no CPU fallback.  Rare conditions cost
+// ordered sequence of kernel launches on one stream and one synchronisation;
+// there is no CPU fallback.  Most checks count their races by group
+// (run_grouped, filter.hip); barrier and fitness checks, captured calls and
+// those the grouped count has no room for sort (kernels.hip).  Rare conditions
+// cost
 // a second round on the device: a trace needing more radix passes than the
 // previous call did, a tile with more racing locations than its staging
 // slice holds, or more racing locations than the output buffer holds.
@@ -43,7 +46,7 @@ namespace {
 constexpr int N_STAGE = ST_COUNT;
 const char* const kStageNames[N_STAGE] = {"init",      "stats",      "layout",     "keygen",  "upsweep",
                                           "sort_pass", "scan_tiles", "scan_cross", "scan_out", "sort_small",
-                                          "filter_part", "filter_test", "filter_out"};
+                                          "filter_part", "filter_count", "filter_out"};
 constexpr int MAX_EV = 96;
 
 struct DevBuf {
@@ -51,7 +54,7 @@ struct DevBuf {
   size_t cap = 0;
 };
 
-enum Kind { KIND_PLAIN = 0, KIND_FIT, KIND_WARP, KIND_PLAIN_LEFT, KIND_WARP_LEFT, N_KIND };
+enum Kind { KIND_PLAIN = 0, KIND_FIT, KIND_WARP, N_KIND };
 
 }  // namespace
 
@@ -61,17 +64,16 @@ struct sim_ctx {
   hipStream_t stream = nullptr;  // used by sim_check_traces
   uint32_t flags = 0;
   // What the previous call of a kind needed: a plain check, the fitness count
-  // (shorter keys), the warp-aware check (longer ones), and either check over
-  // the records its conflict filter left.
+  // (shorter keys), the warp-aware check (longer ones).
   struct Guess {
     uint32_t passes = 0;          // radix passes
     uint32_t bits = 0;            // key bits they sorted (0: no call yet)
     uint32_t db = RADIX_BITS;     // digit width the passes are counted in
     bool wide = false;            // some trace needed two-word keys
   } guess[N_KIND];
-  // Calls of a kind that still go without the conflict filter, after one that
-  // it did not help (see filter_records).
-  uint32_t filter_pause[N_KIND] = {};
+  // Calls of a kind that still take the sorting path, after one that the
+  // grouped count had no room for.
+  uint32_t group_pause[N_KIND] = {};
   uint64_t alloc_gen = 0;   // bumped whenever a device buffer is reallocated
   uint64_t meta_gen = 0;    // bumped whenever a call's tables are uploaded
   uint64_t host_gen = 0;    // bumped whenever the host copy's trace and group tables are rebuilt
@@ -437,22 +439,6 @@ hipError_t size_buffers(sim_ctx* c, uint64_t total, uint32_t n_traces, uint32_t 
   return ensure(c->out, out_need, false, &c->alloc_gen);
 }
 
-// Grow the fixed regions of a call over the records a conflict filter left,
-// one by one: they are a quarter of the call's at most, so the key buffers,
-// which hold those records, are large enough already and stay.
-hipError_t grow_regions(sim_ctx* c, uint64_t total, uint32_t n_traces, uint32_t n_tiles, uint64_t n_hgroups,
-                        uint32_t key_bytes, uint32_t radix) {
-  size_t need[N_REGION];
-  region_bytes(need, total, n_traces, n_tiles, n_hgroups, key_bytes, radix);
-  for (int r : {R_KEYS0, R_KEYS1})
-    if (region_buf(c, r)->cap < need[r]) return hipErrorInvalidValue;
-  for (int r = 0; r < N_REGION; r++) {
-    const hipError_t e = grow(c, *region_buf(c, r), need[r]);
-    if (e != hipSuccess) return e;
-  }
-  return grow(c, c->out, c->out.cap ? c->out.cap : std::min<uint64_t>(total, 65536) * sizeof(RaceOut));
-}
-
 // Where a call's result goes: a result the library allocates (the ordinary
 // entry points), or buffers the caller owns (the no-allocation entry point).
 struct Sink {
@@ -464,32 +450,95 @@ struct Sink {
   sim_barrier_result** barriers = nullptr;  // also the redundant-barrier check
   sim_fitness* fitness = nullptr;           // instead of the race check: the EP fitness rows (host, n_traces)
   const uint32_t* side = nullptr;           // the warp-aware check: one side word per record (device)
-  // the call over the records a conflict filter left (in the key buffers,
-  // which must not be reallocated): the whole call's offsets, for the
-  // summaries, and staging for every tile (nullptr: none)
-  const uint64_t* whole_offsets = nullptr;
-  RaceOut* stage_half = nullptr;
 };
 
-// Calls that run the conflict filter first: from 2^23 records on, and from
-// 2^21 on when no trace holds more than an eighth of them, since the kept
-// records of a short trace are sorted in LDS, in one launch, while those of a
-// long one go through all the radix launches (measured, filter against none:
-// one trace of 2^22 records 320 us against 290, of 2^23 390 against 440, of
-// 2^24 547 against 707, of 2^26 2014 against 2967; 64 traces of 2^20 records
-// in all 226 against 225, of 2^21 201 against 260).
-constexpr uint64_t FILTER_MIN_RECORDS = 1u << 21, FILTER_ALWAYS_RECORDS = 1u << 23;
-bool filter_pays(const uint64_t* offsets, uint32_t n_traces, uint64_t total) {
-  if (total < FILTER_MIN_RECORDS) return false;
-  if (total >= FILTER_ALWAYS_RECORDS) return true;
+// Calls that count their races group by group (filter.h) instead of sorting
+// every record: all but those with a trace of more than 2^27 records, whose
+// buckets grow past what one workgroup counts at a time.  Sorting / grouped,
+// one generated trace of 2^10 .. 2^27 records, in us: 2^10 112 / 50, 2^14
+// 144 / 56, 2^18 171 / 97, 2^20 208 / 101, 2^22 287 / 130, 2^23 433 / 183,
+// 2^24 707 / 330, 2^25 1415 / 630, 2^26 2980 / 1590, 2^27 5866 / 3660; 2^28
+// 11036 / 16212; with one access in twenty atomic, 2^20 209 / 155, 2^24
+// 704 / 570; 64 traces of 2^8 to 2^13, 161 / 60.
+constexpr uint64_t GROUP_MAX_RECORDS = 1ull << 27;
+static_assert(GROUP_MAX_RECORDS <= FILTER_MAX_RECORDS, "the longest trace the buckets are made for");
+// A profiling context sorts calls of fewer records: its users read the sorting
+// pipeline's passes from the stage times of such calls.
+constexpr uint64_t GROUP_MIN_PROFILED = 1ull << 20;
+bool group_pays(const sim_ctx* c, const uint64_t* offsets, uint32_t n_traces, uint64_t total) {
+  if (c->force || n_traces > GROUP_MAX_TRACES) return false;  // (tuning times the sort)
+  if (total == 0 || ((c->flags & SIM_CFG_PROFILE) && total < GROUP_MIN_PROFILED)) return false;
   for (uint32_t i = 0; i < n_traces; i++)
-    if (offsets[i + 1] - offsets[i] > total / 8) return false;
+    if (offsets[i + 1] - offsets[i] > GROUP_MAX_RECORDS) return false;
   return true;
 }
-// After a call whose filter kept more records than it has room for (a
-// quarter of them), this many calls of the kind go without it.
-constexpr uint32_t FILTER_PAUSE = 15;
-constexpr int RUN_FULL = 1;  // run_filtered: take the full path
+// After a call that the grouped count had no room for (more racing locations
+// than one for sixteen records, or too many writes that share a group), this
+// many calls of the kind go without it.
+constexpr uint32_t GROUP_PAUSE = 15;
+constexpr uint32_t GROUP_HOST_ENTRIES = 4096;  // entries of a call the kernels write to host memory
+constexpr int RUN_SORT = 1;  // run_grouped: take the sorting path
+
+// Result delivery: entries downloaded from `dev_out` (n_races of them; or they
+// are in host memory already, at `host_out`), and
+// the summaries from the entry list.  Neighbouring entries of one location
+// (the grouped count finds a location in several parts) become one.
+int deliver_result(sim_ctx* c, const uint64_t* offsets, uint32_t n_traces, hipStream_t s, const Sink& sink,
+                   uint64_t n_races, const void* dev_out, const sim_race* host_out = nullptr) {
+  sim_trace_summary* sums = nullptr;
+  sim_race* races = nullptr;
+  sim_result* r = nullptr;
+  if (sink.out) {
+    r = alloc_result(n_races, n_traces);
+    if (!r) return fail(c, SIM_ENOMEM, "host allocation failed");
+    sums = r->traces;
+    races = r->races;
+  } else {
+    *sink.n_races = n_races;
+    if (n_races > sink.races_cap)
+      return fail(c, SIM_ENOSPC, "%llu racing locations, the output buffer holds %llu",
+                  (unsigned long long)n_races, (unsigned long long)sink.races_cap);
+    sums = sink.traces;
+    races = sink.races;
+    for (uint32_t i = 0; i < n_traces; i++) sums[i] = sim_trace_summary{0, 0, 0};
+  }
+  hipError_t e;
+  if (host_out) {
+    memcpy(races, host_out, n_races * sizeof(sim_race));
+  } else if (n_races && ((e = hipMemcpyAsync(races, dev_out, n_races * sizeof(sim_race), hipMemcpyDeviceToHost, s)) ||
+                  (e = hipStreamSynchronize(s)))) {
+    sim_result_free(r);
+    return hip_fail(c, e, "result download");
+  }
+  for (uint32_t i = 0; i < n_traces; i++) sums[i].n_records = offsets[i + 1] - offsets[i];
+  uint64_t n_locs = 0;
+  for (uint64_t k = 0; k < n_races; k++) {
+    const sim_race& x = races[k];
+    if (x.trace >= n_traces) {
+      sim_result_free(r);
+      return fail(c, SIM_EDEVICE, "entry %llu names trace %u", (unsigned long long)k, x.trace);
+    }
+    sums[x.trace].n_pairs += x.pairs_ww + x.pairs_rw + x.pairs_aw + x.pairs_ar;
+    if (n_locs) {
+      sim_race& y = races[n_locs - 1];
+      if (y.trace == x.trace && y.space == x.space && y.block == x.block && y.unit == x.unit) {
+        y.kinds |= x.kinds;
+        y.pairs_ww += x.pairs_ww;
+        y.pairs_rw += x.pairs_rw;
+        y.pairs_aw += x.pairs_aw;
+        y.pairs_ar += x.pairs_ar;
+        y.pairs_xblock += x.pairs_xblock;
+        continue;
+      }
+    }
+    sums[x.trace].n_race_locs += 1;
+    if (n_locs != k) races[n_locs] = x;
+    n_locs++;
+  }
+  if (r) r->n_races = n_locs;
+  if (sink.out) *sink.out = r;
+  return SIM_OK;
+}
 
 void barrier_result_free(sim_barrier_result* r) {
   if (!r) return;
@@ -497,9 +546,9 @@ void barrier_result_free(sim_barrier_result* r) {
   free(r);
 }
 
-int run_filtered(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_recs, const uint64_t* offsets,
-                 uint32_t n_traces, const uint32_t* tpb, hipStream_t s, const Sink& sink, uint64_t total,
-                 uint32_t n_tiles);
+int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_recs, const uint64_t* offsets,
+                uint32_t n_traces, const uint32_t* tpb, hipStream_t s, const Sink& sink, uint64_t total,
+                uint32_t n_tiles);
 
 // The pinned host block of a call's tables, grown to `bytes`.
 hipError_t grow_host(sim_ctx* c, size_t bytes) {
@@ -537,65 +586,24 @@ int run(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_
     if (n_tiles > NOALLOC_MAX_TILES)
       return fail(c, SIM_EINVAL, "a no-allocation call holds at most %u tiles of 4096 records", NOALLOC_MAX_TILES);
   }
-  const bool left = sink.whole_offsets != nullptr;  // the records a conflict filter left
-  if (!left)
-    for (auto& t : c->times) t = sim_stage_time{0.0, 0, 0};
+  for (auto& t : c->times) t = sim_stage_time{0.0, 0, 0};
   const bool fit = sink.fitness != nullptr;
   if (fit && noalloc) return fail(c, SIM_EINVAL, "the fitness count has no no-allocation form");
   const bool warp = sink.side != nullptr;
   if (warp && (noalloc || trace_recs || fit || sink.barriers))
     return fail(c, SIM_EINVAL, "the warp-aware check runs on its own, on adjacent device records");
-  const Kind kind = fit ? KIND_FIT : (warp ? (left ? KIND_WARP_LEFT : KIND_WARP) : (left ? KIND_PLAIN_LEFT : KIND_PLAIN));
+  const Kind kind = fit ? KIND_FIT : (warp ? KIND_WARP : KIND_PLAIN);
   auto& gs = c->guess[kind];
-  if (!left && !noalloc && !fit && !sink.barriers && filter_pays(offsets, n_traces, total)) {
-    if (c->filter_pause[kind]) {
-      c->filter_pause[kind]--;
+  if (!noalloc && !fit && !sink.barriers && group_pays(c, offsets, n_traces, total)) {
+    if (c->group_pause[kind]) {
+      c->group_pause[kind]--;
     } else {
-      const int rf = run_filtered(c, d_records, trace_recs, offsets, n_traces, tpb, s, sink, total, n_tiles);
-      if (rf != RUN_FULL) return rf;
-      c->filter_pause[kind] = FILTER_PAUSE;
+      const int rg = run_grouped(c, d_records, trace_recs, offsets, n_traces, tpb, s, sink, total, n_tiles);
+      if (rg != RUN_SORT) return rg;
     }
   }
-
-  // result delivery: summaries from the entry list, entries downloaded from
-  // `dev_out` (n_races of them)
-  auto deliver = [&](uint64_t n_races, const void* dev_out) -> int {
-    sim_trace_summary* sums = nullptr;
-    sim_race* races = nullptr;
-    sim_result* r = nullptr;
-    if (sink.out) {
-      r = alloc_result(n_races, n_traces);
-      if (!r) return fail(c, SIM_ENOMEM, "host allocation failed");
-      sums = r->traces;
-      races = r->races;
-    } else {
-      *sink.n_races = n_races;
-      if (n_races > sink.races_cap)
-        return fail(c, SIM_ENOSPC, "%llu racing locations, the output buffer holds %llu",
-                    (unsigned long long)n_races, (unsigned long long)sink.races_cap);
-      sums = sink.traces;
-      races = sink.races;
-      for (uint32_t i = 0; i < n_traces; i++) sums[i] = sim_trace_summary{0, 0, 0};
-    }
-    hipError_t e;
-    if (n_races && ((e = hipMemcpyAsync(races, dev_out, n_races * sizeof(sim_race), hipMemcpyDeviceToHost, s)) ||
-                    (e = hipStreamSynchronize(s)))) {
-      sim_result_free(r);
-      return hip_fail(c, e, "result download");
-    }
-    const uint64_t* whole = left ? sink.whole_offsets : offsets;
-    for (uint32_t i = 0; i < n_traces; i++) sums[i].n_records = whole[i + 1] - whole[i];
-    for (uint64_t k = 0; k < n_races; k++) {
-      const sim_race& x = races[k];
-      if (x.trace >= n_traces) {
-        sim_result_free(r);
-        return fail(c, SIM_EDEVICE, "entry %llu names trace %u", (unsigned long long)k, x.trace);
-      }
-      sums[x.trace].n_race_locs += 1;
-      sums[x.trace].n_pairs += x.pairs_ww + x.pairs_rw + x.pairs_aw + x.pairs_ar;
-    }
-    if (sink.out) *sink.out = r;
-    return SIM_OK;
+  auto deliver = [&](uint64_t n_races, const void* dev_out) {
+    return deliver_result(c, offsets, n_traces, s, sink, n_races, dev_out);
   };
 
   if (fit && total == 0) {  // every trace empty: F = 1, no locations
@@ -745,9 +753,8 @@ int run(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_
     out_p = (RaceOut*)rest;
     out_cap = rest_bytes / sizeof(RaceOut);
   } else {
-    e = left ? grow_regions(c, total, n_traces, n_tiles, n_hgroups, key_bytes, 1u << db)
-             : size_buffers(c, total, n_traces, n_tiles, n_hgroups, key_bytes, 1u << db);
-    if (e != hipSuccess) return hip_fail(c, e, "device allocation");
+    if ((e = size_buffers(c, total, n_traces, n_tiles, n_hgroups, key_bytes, 1u << db)) != hipSuccess)
+      return hip_fail(c, e, "device allocation");
     for (int r = 0; r < N_REGION; r++) reg[r] = region_buf(c, r)->p;
     out_p = (RaceOut*)c->out.p;
     out_cap = c->out.cap / sizeof(RaceOut);
@@ -781,7 +788,6 @@ int run(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_
   b.group_sum = (uint32_t*)reg[R_GSUM];
   b.stage = nullptr;
   b.stage_ref = nullptr;
-  b.stage_half = sink.stage_half;
   b.ctrl = (Ctrl*)reg[R_CTRL];
   b.out = out_p;
   b.out_cap = out_cap;
@@ -890,7 +896,7 @@ int run(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_
   // whose record addresses are not part of the shape, nor for calls that
   // may not allocate: instantiating a graph does.)
   const bool use_graph =
-      (c->flags & SIM_CFG_GRAPHS) && !prof && s != nullptr && guess > 0 && !trace_recs && !noalloc && !fit && !warp && !left;
+      (c->flags & SIM_CFG_GRAPHS) && !prof && s != nullptr && guess > 0 && !trace_recs && !noalloc && !fit && !warp;
   auto& G = c->graph;
   const bool replay = use_graph && G.exec && G.records == d_records && G.stream == s && G.total == total &&
                       G.n_traces == n_traces && G.n_tiles == n_tiles && G.gen == c->alloc_gen && G.guess == guess &&
@@ -1126,98 +1132,98 @@ int run(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_
   return SIM_OK;
 }
 
-// A call with the conflict filter (filter.h) first: the records that may race
-// are gathered on the device, and run() checks those alone.  A racing pair's
-// records are all among them, so the entries are the whole call's.  Returns
-// RUN_FULL when the filter keeps more records than there is room for; the
-// caller then takes the full path.
+// A call by the grouped race count (filter.h).  Returns RUN_SORT when its
+// tables do not hold the call's racing locations; the caller then takes the
+// sorting path.
 //
-// Everything lives in the buffers a full call of this size has anyway: keys0
-// holds the filter keys (4 bytes per record), the bucket rows and the
-// survivor bitmap, the upper half of keys1 the surviving records, the tables
-// are in the regions of the full call's tables.
-int run_filtered(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_recs, const uint64_t* offsets,
-                 uint32_t n_traces, const uint32_t* tpb, hipStream_t s, const Sink& sink, uint64_t total,
-                 uint32_t n_tiles) {
-  const bool warp = sink.side != nullptr;
-  // tables: traces up, survivor offsets down
-  const size_t tr_bytes = ((size_t)n_traces * sizeof(FTrace) + 15) / 16 * 16;
-  hipError_t e = grow_host(c, tr_bytes + ((size_t)n_traces + 1) * sizeof(uint32_t));
+// Everything lives in the buffers a sorting call of this size has anyway:
+// keys0 holds the filter keys (4 bytes per record) and later the ordered
+// entries, and the bucket rows; keys1 the entries as they are found and by
+// trace; the tables are in the regions of the sorting call's tables.
+int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_recs, const uint64_t* offsets,
+                uint32_t n_traces, const uint32_t* tpb, hipStream_t s, const Sink& sink, uint64_t total,
+                uint32_t n_tiles) {
+  auto up = [](uint64_t x) { return (x + 255) / 256 * 256; };
+  const size_t tr_bytes = up(n_traces * sizeof(FTrace));
+  // records the buffers are sized for: room for a few entries (a server's worker is charged for its own)
+  const uint64_t room = c->dev_limit ? total : std::max<uint64_t>(total, 16384);
+  const uint64_t cap = room / 16;
+  const uint32_t host_cap = (uint32_t)std::min<uint64_t>(cap, GROUP_HOST_ENTRIES);
+  hipError_t e = grow_host(c, tr_bytes + 256 + host_cap * sizeof(RaceOut));
   if (e != hipSuccess) return hip_fail(c, e, "pinned allocation");
   c->host_gen++;  // the tables of the previous call are overwritten
   FTrace* ht = (FTrace*)c->h_meta;
-  uint32_t* h_off = (uint32_t*)((char*)c->h_meta + tr_bytes);
+  GroupHead* head = (GroupHead*)((char*)c->h_meta + tr_bytes);
+  RaceOut* host_entries = (RaceOut*)((char*)head + 256);
   uint64_t rows = 0;
-  uint32_t tiles = 0, buckets = 0, large = 0, max_lgb = 0;
+  uint32_t tiles = 0, buckets = 0, max_lgb = 0;
   for (uint32_t i = 0; i < n_traces; i++) {
     const uint64_t n = offsets[i + 1] - offsets[i];
     const uint32_t nt = (uint32_t)((n + FT - 1) / FT), lgb = filter_lgb(n);
     ht[i] = FTrace{trace_recs ? (const void*)trace_recs[i] : (const void*)(d_records + offsets[i]), n, rows,
-                   (uint32_t)offsets[i], tpb[i], tiles, nt, buckets, lgb, filter_sbits(n, lgb),
-                   (uint32_t)(offsets[i] >> 5) + i};
+                   (uint32_t)offsets[i], tpb[i], tiles, nt, buckets, lgb, filter_sbits(n, lgb), 0};
     rows += (uint64_t)nt * ((1u << lgb) + 1);
     tiles += nt;
     buckets += nt ? 1u << lgb : 0u;
     max_lgb = std::max(max_lgb, lgb);
-    if ((n >> lgb) > FILTER_BUCKET) large = 1;
   }
-  if (!large)  // (the kernel of ordinary buckets has room for one bit less)
-    for (uint32_t i = 0; i < n_traces; i++) ht[i].sbits = std::min(ht[i].sbits, FILTER_SLOT_BITS - 1);
-  auto up = [](uint64_t x) { return (x + 255) / 256 * 256; };
-  const uint64_t rows_at = up(4 * total), surv_at = up(rows_at + 4 * rows), surv_words = (total >> 5) + n_traces + 1;
-  const uint64_t hot_at = up(surv_at + 4 * surv_words);
-  const uint64_t out_at = up(4 * total);
-  const uint64_t half = 8 * total;  // bytes of a key buffer
-  // room per trace for hot buckets: 127, or fewer among many short traces
-  // (whose buckets are few)
-  const uint32_t hot_stride = total / n_traces >= 32768 ? 256u : (total / n_traces >= 1024 ? 16u : 2u);
-  if (hot_at + 4ull * hot_stride * n_traces > half || out_at + 16 > half || tiles + (uint64_t)buckets > 2ull * n_tiles) return RUN_FULL;
-  // Under a device limit the regions of the call over the survivors are sized
-  // here too (9-bit digits, a histogram group per tile at most), as that call
-  // must not release anything; otherwise they grow when they have to.
-  if ((e = c->dev_limit ? size_buffers(c, total, n_traces, n_tiles, n_tiles, 8, RADIX_MAX)
-                        : size_buffers(c, total, n_traces, n_tiles, 0, 8, RADIX)) != hipSuccess)
-    return hip_fail(c, e, "device allocation");
+  const uint64_t half = 8 * room;  // bytes of a key buffer
+  // a bucket is split only where a tile's run of one of at least 8 buckets is far above the usual
+  const uint32_t hot_part = (uint32_t)std::max<uint64_t>(HOT_PART, 2 * total / HOT_MAX_PARTS + 1);
+  const uint32_t extra_max = max_lgb < 3 ? 0u : (uint32_t)((2 * (total / hot_part) + 8) / 8 * 8);
+  const uint32_t late_max = tiles > 16 ? std::min(tiles, 1024u) : 0u;
+  const uint64_t rows_at = up(4 * room), extra_at = up(rows_at + 4 * rows),
+                 late_at = extra_at + 8ull * extra_max;
+  if (cap < 1 || late_at + 8ull * late_max > half ||
+      4ull * (tiles + 2ull * buckets + FC_COUNT) > sizeof(TraceStats) * (uint64_t)n_tiles)
+    return RUN_SORT;
+  if (size_buffers(c, room, n_traces, n_tiles, 0, 8, RADIX) != hipSuccess) {  // (sorting may need less)
+    (void)hipGetLastError();
+    return RUN_SORT;
+  }
   char* k0 = (char*)c->keys0.p;
   char* k1 = (char*)c->keys1.p;
-  uint32_t* words = (uint32_t*)c->stats_part.p;  // 48 bytes per 4096-record tile
+  uint32_t* words = (uint32_t*)c->stats_part.p;
+  uint32_t* per_trace = (uint32_t*)c->layout.p;
+  static_assert(sizeof(TraceLayout) >= 12 && sizeof(FTrace) <= sizeof(TraceDesc), "the tables fit the sorting call's");
   FilterBuffers f;
-  f.tr = (const FTrace*)c->meta.p;
+  f.tr = (FTrace*)c->meta.p;
+  f.tr_src = n_traces <= 64 ? ht : f.tr;  // (a few are read by the first kernel itself)
   f.n_traces = n_traces;
   f.n_tiles = tiles;
   f.n_buckets = buckets;
-  f.tile_trace = words;
-  f.tile_cnt = words + tiles;
-  f.bucket_trace = words + 2 * (uint64_t)tiles;
+  f.cnt = words;
+  f.tile_trace = words + FC_COUNT;
+  f.bucket_trace = f.tile_trace + tiles;
   f.hot = f.bucket_trace + buckets;
-  f.n_hot = f.hot + buckets;
-  f.trace_hot = (uint32_t*)(k0 + hot_at);
-  f.hot_stride = hot_stride;
-  f.hot_maps = (uint32_t*)k1;  // the lower half of keys1
-  f.max_hot = (uint32_t)(out_at / ((1u << FILTER_SLOT_BITS) / 8));
-  f.max_lgb = max_lgb;
-  f.large = large;
-  f.trace_off = (uint32_t*)c->layout.p;
+  f.trace_cnt = per_trace;
+  f.trace_fill = per_trace + n_traces;
+  f.trace_first = per_trace + 2ull * n_traces;
   f.keys = (uint32_t*)k0;
   f.rows = (uint32_t*)(k0 + rows_at);
-  f.survive = (uint32_t*)(k0 + surv_at);
+  f.extra = (uint2*)(k0 + extra_at);
+  f.extra_max = extra_max;
+  f.hot_part = hot_part;
+  f.late = (uint2*)(k0 + late_at);
+  f.late_max = late_max;
+  f.max_lgb = max_lgb;
   f.side = sink.side;
-  // room for the survivors and, in the warp-aware check, their side words
-  f.out_cap = (uint32_t)((half - out_at) / (warp ? 20 : 16));
-  f.out = k1 + out_at;
-  f.out_side = (uint32_t*)(k1 + out_at + 16ull * f.out_cap);
+  f.entries = (RaceOut*)k1;
+  f.placed = (RaceOut*)(k1 + 64 * cap);
+  f.sorted = (RaceOut*)k0;
+  f.entries_cap = (uint32_t)cap;
+  f.head = head;
+  f.host_entries = host_entries;
+  f.host_cap = host_cap;
   f.ctrl = (Ctrl*)c->ctrl.p;
   const bool prof = (c->flags & SIM_CFG_PROFILE) != 0;
   auto mark = [&](int k) { return prof ? hipEventRecord(c->ev[k], s) : hipSuccess; };
-  if ((e = hipMemcpyAsync(c->meta.p, ht, tr_bytes, hipMemcpyHostToDevice, s)))
+  if (f.tr_src == f.tr && (e = hipMemcpyAsync(f.tr, ht, n_traces * sizeof(FTrace), hipMemcpyHostToDevice, s)))
     return hip_fail(c, e, "table upload");
   c->meta_gen++;
-  if ((e = mark(0)) || (e = launch_filter_part(f, s)) || (e = mark(1)) || (e = launch_filter_test(f, s)) ||
-      (e = mark(2)) || (e = launch_filter_out(f, s)) || (e = mark(3)) ||
-      (e = hipMemcpyAsync(h_off, f.trace_off, ((size_t)n_traces + 1) * sizeof(uint32_t), hipMemcpyDeviceToHost, s)) ||
-      (e = hipMemcpyAsync(c->h_ctrl, f.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s)) ||
-      (e = hipStreamSynchronize(s)))
-    return hip_fail(c, e, "conflict filter");
+  if ((e = mark(0)) || (e = launch_filter_part(f, s)) || (e = mark(1)) || (e = launch_filter_count(f, s)) ||
+      (e = mark(2)) || (e = launch_filter_out(f, s)) || (e = mark(3)) || (e = hipStreamSynchronize(s)))
+    return hip_fail(c, e, "grouped count");
   if (prof)
     for (int k = 0; k < 3; k++) {
       float ms = 0;
@@ -1225,20 +1231,15 @@ int run_filtered(sim_ctx* c, const sim_record* d_records, const sim_record* cons
       c->times[ST_FILTER_PART + k].ms += ms;
       c->times[ST_FILTER_PART + k].launches += 1;
     }
-  if (c->h_ctrl->error_flags & LAYOUT_ERR_RECORD)
+  if (head->error_flags & LAYOUT_ERR_RECORD)
     return fail(c, SIM_ERECORD, "invalid record at index %llu (action > 2 or space > 1)",
-                (unsigned long long)c->h_ctrl->first_bad);
-  const uint64_t kept = h_off[n_traces];
-  if (kept > f.out_cap) return RUN_FULL;
-  std::vector<uint64_t> left(h_off, h_off + n_traces + 1);  // (the host block is overwritten by the next call's tables)
-  Sink sub = sink;
-  sub.whole_offsets = offsets;
-  sub.side = warp && kept ? f.out_side : nullptr;
-  // staging beside the survivors' keys (16 bytes each at most): an entry of
-  // 64 bytes for two records
-  const uint64_t stage_at = up(16 * kept);
-  if (stage_at + 32 * kept <= half) sub.stage_half = (RaceOut*)(k0 + stage_at);
-  return run(c, (const sim_record*)f.out, nullptr, left.data(), n_traces, tpb, s, sub, false);
+                (unsigned long long)head->first_bad);
+  if (head->error_flags) {
+    c->group_pause[sink.side ? KIND_WARP : KIND_PLAIN] = GROUP_PAUSE;
+    return RUN_SORT;
+  }
+  return deliver_result(c, offsets, n_traces, s, sink, head->entries, f.sorted,
+                        head->entries <= host_cap ? (const sim_race*)host_entries : nullptr);
 }
 
 void divergence_result_free(sim_divergence_result* r) {

@@ -1,13 +1,14 @@
-// filter.h -- the conflict filter: which records of a call can be part of a
-// racing pair at all.
+// filter.h -- the grouped race count: a call's racing pairs counted without
+// sorting its records.
 //
 // A record races only inside its group: the accesses of one shared word by
 // one block in one epoch, or the accesses of one global word (where a pair is
 // concurrent across blocks, or inside one block's epoch).  A group without a
-// write or atomic, or touched by one thread only, holds no race, and in most
-// traces almost every record is in such a group.  The filter keeps every
-// record that could race (and some that do not), so the exact count over the
-// kept records alone is the exact count of the trace.
+// write or atomic holds no race, and in most traces almost every record is in
+// such a group or alone in it.  Records are put into buckets by a hash of
+// their group; bitmaps over a bucket's groups then leave the few writes and
+// atomics that may have a partner, and the reads that may be one, and their
+// pairs are counted one by one.
 //
 // Types and hash functions shared by the kernels (filter.hip), the host
 // runtime (api.cpp) and the CPU tests.
@@ -18,13 +19,19 @@
 
 namespace sc {
 
-constexpr uint32_t FT = 16384;           // records per filter tile
+constexpr uint32_t FT = 16384;            // records per filter tile
 constexpr uint32_t FT_BITS = 14;
-constexpr uint32_t FILTER_SLOT_BITS = 18;  // slot bits of a filter key (the other 14 are the record's place in its tile)
-constexpr uint32_t FILTER_MAX_LGB = 12;  // log2 of the most buckets of a trace
+// A record's 4-byte key: its place in its tile (bits 0..13), its group's slot
+// in the bucket (bits 14..30), whether it is atomic (bit 31).
+constexpr uint32_t FILTER_SLOT_BITS = 17;
+constexpr uint32_t FILTER_ATOMIC = 1u << 31;
+constexpr uint32_t FILTER_MAX_LGB = 13;   // log2 of the most buckets of a trace
 constexpr uint32_t FILTER_BUCKET = 16384; // records per bucket aimed at
+constexpr uint64_t FILTER_MAX_RECORDS = 2ull * FILTER_BUCKET << FILTER_MAX_LGB;  // of one trace
+constexpr uint32_t HOT_PART = 8192;      // hot reads per workgroup of a split bucket, at least
+constexpr uint32_t HOT_MAX_PARTS = 2048; // workgroups of split buckets of a call, at most
 
-struct FTrace {       // one trace of a filtered call (host-filled)
+struct FTrace {       // one trace of a grouped call (host-filled)
   const void* rec;    // its first record
   uint64_t n;         // records
   uint64_t row0;      // its first bucket row word
@@ -34,12 +41,12 @@ struct FTrace {       // one trace of a filtered call (host-filled)
   uint32_t bucket0;   // its first bucket
   uint32_t lgb;       // log2 of its buckets
   uint32_t sbits;     // slot bits its buckets use (10 .. FILTER_SLOT_BITS)
-  uint32_t surv0;     // its first word of the survivor bitmap
+  uint32_t pad;
 };
 
 // log2 of the buckets of a trace of n records, and the slot bits of a bucket:
-// about 16 slots per record of an average bucket (a quarter of them writes)
-// keeps chance hits to a few per cent.
+// eight slots and more per record of an average bucket (a quarter of them
+// writes) keep chance hits to a few per cent.
 SC_HD uint32_t filter_lgb(uint64_t n) {
   uint32_t k = 0;
   while (k < FILTER_MAX_LGB && (n >> k) > FILTER_BUCKET) k++;
@@ -68,14 +75,49 @@ SC_HD uint32_t filter_group(uint64_t unit, uint32_t block, uint32_t epoch, uint3
   return mix32(x);
 }
 
-// A record's bucket (top bits of its group's hash) and filter key.
+// A record's bucket (the top bits of its group's hash) and its slot there.
 SC_HD uint32_t filter_bucket(uint32_t h, uint32_t lgb) { return lgb ? h >> (32 - lgb) : 0u; }
+SC_HD uint32_t filter_slot(uint32_t h) { return h & ((1u << FILTER_SLOT_BITS) - 1u); }
 
-// Second hash, of a record's (location, block, epoch) or of its location
-// alone, for the exact test of the records the bitmaps let through.
-SC_HD uint32_t filter_exact_hash(uint64_t unit, uint32_t block, uint32_t epoch, uint32_t kind, uint32_t round) {
-  return mix32(mix32((uint32_t)unit + round * 0x68E31DA4u) ^
-               mix32((uint32_t)(unit >> 32) * 0xB5297A4Du + block * 0x1B56C4E9u + epoch * 0x9E3779B1u + kind));
+// A record in the form its pairs are counted from.
+struct FRec {
+  uint32_t ulo, uhi, tid;
+  uint32_t meta;  // epoch | action << 16 | space << 18
+};
+SC_HD FRec frec(uint64_t unit, uint32_t tid, uint32_t epoch, uint32_t action, uint32_t space) {
+  return FRec{(uint32_t)unit, (uint32_t)(unit >> 32), tid, epoch | (action & 3u) << 16 | (space & 1u) << 18};
+}
+SC_HD uint32_t frec_action(const FRec& a) { return (a.meta >> 16) & 3u; }
+SC_HD uint32_t frec_space(const FRec& a) { return (a.meta >> 18) & 1u; }
+// One location: the same word, and for shared words the same block.
+SC_HD bool same_location(const FRec& a, uint32_t blk_a, const FRec& b, uint32_t blk_b) {
+  return a.ulo == b.ulo && a.uhi == b.uhi && ((a.meta ^ b.meta) & (1u << 18)) == 0 && (frec_space(a) == 0 || blk_a == blk_b);
+}
+SC_HD uint32_t location_hash(const FRec& a, uint32_t blk) {
+  return mix32(a.ulo * 0x9E3779B1u ^ mix32(a.uhi + (frec_space(a) ? blk * 0xC2B2AE3Du + 1u : 0u)));
+}
+// Further hashes of a record's group, level 0, 1, ...: groups that share one
+// or filter_group's need not share another.
+SC_HD uint32_t filter_group2(const FRec& a, uint32_t blk, uint32_t level) {
+  uint32_t x = mix32(a.ulo + (level + 1u) * 0x9E3779B9u);
+  x = mix32(x ^ (a.uhi * 0xC2B2AE3Du));
+  if (frec_space(a)) x = mix32(x + blk * 0x27D4EB2Fu + ((a.meta & 0xFFFFu) + 1u) * 0x165667B1u);
+  return x;
+}
+// Whether two records of one location are concurrent, by different threads,
+// not both reads and not both atomic.  warp: lockstep orders two threads of a
+// warp unless one of them ran diverged or both are writes of one statement
+// (side words; Theorem 1, clauses 1 to 3).
+SC_HD bool pair_races(const FRec& a, uint32_t blk_a, const FRec& b, uint32_t blk_b, bool warp, uint32_t tpb,
+                      uint32_t side_a, uint32_t side_b) {
+  const uint32_t ca = frec_action(a), cb = frec_action(b);
+  if (a.tid == b.tid || (ca == cb && ca != 1u)) return false;
+  if (blk_a != blk_b) return true;
+  if (((a.meta ^ b.meta) & 0xFFFFu) != 0) return false;
+  if (!warp) return true;
+  const uint32_t wa = (a.tid - blk_a * tpb) >> 5, wb = (b.tid - blk_b * tpb) >> 5;
+  if (wa != wb || ((side_a | side_b) & SIDE_DIVERGED)) return true;
+  return ca == 1u && cb == 1u && side_a == side_b;
 }
 
 }  // namespace sc

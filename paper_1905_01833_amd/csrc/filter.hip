@@ -1,23 +1,29 @@
-// filter.hip -- gfx950 kernels of the conflict filter (filter.h).
+// filter.hip -- gfx950 kernels of the grouped race count (filter.h).
 //
-// The race check sorts 8-byte keys over five or six radix passes, about 150
-// bytes of HBM traffic per record, although almost no record of a usual trace
-// can race.  The filter reads every 16-byte record once and writes one 4-byte
-// key, reads the keys once more, and leaves the full pipeline the few records
-// that can: 24 bytes per record.
+// The sorting race check moves about 150 bytes of HBM per record: 8-byte keys
+// over five or six radix passes.  Here every 16-byte record is read once, a
+// 4-byte key is written and read back, and only records that may race are
+// looked at again: 24 bytes per record.  One trace of 2^24 records takes 61 us
+// in k_filter_part (5.5 TB/s), 215 in k_filter_count, 17 in k_entries_sort; the
+// sort took 707 for the whole call.  A call of 1279 records takes 12, 10 and 4
+// us there and one synchronisation, 47 us in all; sorting took 102.
 //   k_filter_begin  control words, tile -> trace and bucket -> trace tables
 //   k_filter_part   per 16384-record tile: group hashes, the tile's keys
 //                   ordered by hash bucket (writes and atomics of a bucket
 //                   before its reads), bucket starts of the tile; record checks
-//   k_filter_test   per bucket: LDS bitmaps of the bucket's groups, then an
-//                   exact test of what they let through; survivors are marked
-//                   in a bitmap over the call's records
-//   k_filter_count / k_filter_scan / k_filter_gather  the marked records, in
-//                   record order, and each trace's number of them
+//   k_filter_plan   workgroups for buckets with hot words
+//   k_filter_count  per bucket: bitmaps of its groups in LDS, then the pairs
+//                   of the writes and atomics that may race, among themselves
+//                   and with the reads; one entry per racing location
+//   k_entries_place / k_entries_sort / k_entries_merge  the entries in order
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <type_traits>
 
 #include "filter.h"
 #include "launch.h"
+#include "segstate.h"
 #include "wave.h"
 
 namespace sc {
@@ -25,11 +31,10 @@ namespace sc {
 constexpr int FNT = 1024;              // threads of the partition and test kernels
 constexpr int FNW = FNT / 64;
 constexpr int FIT = FT / FNT;          // records per thread
-constexpr uint32_t A_STRIDE = (1u << FILTER_SLOT_BITS) / 32;  // words of a stored bitmap
-constexpr uint32_t HOT_READS = 1, HOT_WRITES = 2;
 constexpr uint32_t SLOT_MASK = (1u << FILTER_SLOT_BITS) - 1;
-static_assert(FT == 1u << FT_BITS && FILTER_SLOT_BITS + FT_BITS == 32, "a filter key is one 32-bit word");
-static_assert(FILTER_SLOT_BITS + 1 + FILTER_MAX_LGB <= 32, "hash word: bucket bits, the write flag, slot bits");
+static_assert(FT == 1u << FT_BITS && FILTER_SLOT_BITS + FT_BITS == 31, "a filter key is one 32-bit word");
+static_assert(FILTER_SLOT_BITS + 2 + FILTER_MAX_LGB <= 32, "hash word: bucket bits, write and atomic flags, slot bits");
+constexpr uint32_t HV_ACTION = 3u << FILTER_SLOT_BITS;  // 0 read, 1 write, 2 atomic
 
 // Block of a thread: a shift when threads per block is a power of two.
 __device__ __forceinline__ uint32_t block_of(uint32_t tid, uint32_t tpb, uint32_t shift) {
@@ -47,10 +52,17 @@ __global__ __launch_bounds__(NT) void k_filter_begin(FilterBuffers f) {
     f.ctrl->first_bad = ~0ull;
     f.ctrl->total_entries = 0;
     f.ctrl->wide_traces = 0;
-    *f.n_hot = 0;
+    f.cnt[FC_ENTRIES] = 0;
+    f.cnt[FC_EXTRA] = 0;
+    f.cnt[FC_MOST] = 0;
+    f.cnt[FC_LATE] = 0;
   }
-  const FTrace T = f.tr[t];
-  if (threadIdx.x == 0) f.trace_hot[(uint64_t)t * f.hot_stride] = 0;
+  const FTrace T = f.tr_src[t];
+  if (threadIdx.x == 0) {
+    if (f.tr_src != f.tr) f.tr[t] = T;
+    f.trace_cnt[t] = 0;
+    f.trace_fill[t] = 0;
+  }
   for (uint32_t i = threadIdx.x; i < T.ntiles; i += NT) f.tile_trace[T.tile0 + i] = t;
   if (T.ntiles)
     for (uint32_t i = threadIdx.x; i < 1u << T.lgb; i += NT) {
@@ -67,7 +79,7 @@ __global__ __launch_bounds__(NT) void k_filter_begin(FilterBuffers f) {
 // histogram pass and no offsets between tiles.  16384 records per tile make
 // a tile's run of one bucket 32 keys (128 bytes) with 512 buckets; two
 // workgroups of 1024 threads share a CU (72 KiB of LDS each; traces of more
-// than 2^25 records take 4096 buckets and a workgroup per CU).
+// than 2^25 records take up to 8192 buckets and a workgroup per CU).
 template <uint32_t LGB>
 __global__ __launch_bounds__(FNT, LGB <= 11 ? 8 : 4) void k_filter_part(FilterBuffers f) {
   __shared__ uint32_t s_key[FT];
@@ -83,7 +95,6 @@ __global__ __launch_bounds__(FNT, LGB <= 11 ? 8 : 4) void k_filter_part(FilterBu
   const uint32_t B = 1u << T.lgb;
   const GRecords p = global_records((const char*)T.rec + start * 16);
   for (uint32_t k = tx; k < B; k += FNT) s_cnt[k] = 0;
-  if (tx < (n_in + 31) / 32) f.survive[T.surv0 + local * (FT / 32) + tx] = 0;
   __syncthreads();
   const uint32_t shift = block_shift(T.tpb);
   uint32_t hv[FIT], rank[FIT / 2];  // ranks are 16-bit, two per word
@@ -107,8 +118,9 @@ __global__ __launch_bounds__(FNT, LGB <= 11 ? 8 : 4) void k_filter_part(FilterBu
       const bool valid = j < n_in;
       if (valid && (x.action > 2 || x.space > 1)) bad = min(bad, j);
       const uint32_t h = filter_group(x.unit, block_of(x.tid, T.tpb, shift), x.epoch, x.space);
-      const uint32_t w = x.action != 0 ? 1u : 0u;
-      hv[q] = (h & ~(1u << FILTER_SLOT_BITS)) | (w << FILTER_SLOT_BITS);
+      const uint32_t act = x.action <= 2 ? x.action : 0u;  // (a bad record's call fails)
+      const bool w = act != 0;
+      hv[q] = (h & ~HV_ACTION) | (act << FILTER_SLOT_BITS);
       uint32_t rk = 0;
       if (T.lgb == 0) {  // one bucket: a count per wave, not 64 atomics on one word
         const uint64_t bw = __ballot(valid && w), br = __ballot(valid && !w);
@@ -122,6 +134,7 @@ __global__ __launch_bounds__(FNT, LGB <= 11 ? 8 : 4) void k_filter_part(FilterBu
         rk = w ? old & 0xFFFFu : old >> 16;
       }
       rank[q / 2] = (q & 1) ? rank[q / 2] | (rk << 16) : rk;
+      asm volatile("" : "+v"(hv[q]), "+v"(rank[q / 2]));  // (kept packed: their parts would spill)
     }
   }
   if (bad != ~0u) {
@@ -141,6 +154,7 @@ __global__ __launch_bounds__(FNT, LGB <= 11 ? 8 : 4) void k_filter_part(FilterBu
   uint32_t tot;
   uint32_t s0 = block_excl_sum_n<FNW>(sum, s_scan, &tot);
   uint32_t* row = f.rows + T.row0 + (uint64_t)local * (B + 1);
+  const uint32_t usual = n_in >> T.lgb;
 #pragma unroll
   for (uint32_t e = 0; e < DPT; e++) {
     const uint32_t b = tx * DPT + e;
@@ -148,13 +162,9 @@ __global__ __launch_bounds__(FNT, LGB <= 11 ? 8 : 4) void k_filter_part(FilterBu
       const uint32_t pair = s0 | ((s0 + (c[e] & 0xFFFFu)) << 16);  // first write, first read
       s_cnt[b] = pair;
       row[b] = pair;
-      // far more than a bucket's usual share: a hot word's reads, or writes
-      // (few buckets, and each is flagged once or a few times).  Not where
-      // the bucket is short all the same: another workgroup's worth or two
-      // of reads is no delay among many.
-      const uint32_t over = max(2 * (n_in >> T.lgb) + 16, 2 * FILTER_BUCKET / T.ntiles);
-      const uint32_t hot = ((c[e] >> 16) > over ? HOT_READS : 0u) | ((c[e] & 0xFFFFu) > over ? HOT_WRITES : 0u);
-      if (hot & ~f.hot[T.bucket0 + b]) atomicOr(&f.hot[T.bucket0 + b], hot);
+      // far more reads than a bucket's usual share: a hot word's (rare, so
+      // these atomics are few)
+      if ((c[e] >> 16) > usual + usual / 4 + 8) atomicAdd(&f.hot[T.bucket0 + b], c[e] >> 16);
       s0 += (c[e] & 0xFFFFu) + (c[e] >> 16);
     }
   }
@@ -165,8 +175,8 @@ __global__ __launch_bounds__(FNT, LGB <= 11 ? 8 : 4) void k_filter_part(FilterBu
     const uint32_t j = tx + q * FNT;
     if (j < n_in) {
       const uint32_t pair = s_cnt[filter_bucket(hv[q], T.lgb)];
-      const uint32_t at = ((hv[q] >> FILTER_SLOT_BITS) & 1u ? pair & 0xFFFFu : pair >> 16) + ((q & 1) ? rank[q / 2] >> 16 : rank[q / 2] & 0xFFFFu);
-      s_key[at] = ((hv[q] & SLOT_MASK) << FT_BITS) | j;
+      const uint32_t at = ((hv[q] & HV_ACTION) ? pair & 0xFFFFu : pair >> 16) + ((q & 1) ? rank[q / 2] >> 16 : rank[q / 2] & 0xFFFFu);
+      s_key[at] = ((hv[q] << (30 - FILTER_SLOT_BITS)) & FILTER_ATOMIC) | ((hv[q] & SLOT_MASK) << FT_BITS) | j;
     }
   }
   __syncthreads();
@@ -178,462 +188,759 @@ __global__ __launch_bounds__(FNT, LGB <= 11 ? 8 : 4) void k_filter_part(FilterBu
   }
 }
 
-// ------------------------------------------------------- k_filter_test
-// One workgroup per bucket.  A bitmap over the slots of the bucket's groups
-// marks where a write or atomic is (A), a second one, half as fine, where a
-// write or atomic is not alone (D): another write's bit was set already, or a
-// read's group has one.  Reads outside A and writes outside D cannot race.
-// What is left, normally a few per cent, goes to a list and is tested on the
-// records themselves: per group the smallest and largest thread (for a global
-// word also the smallest and largest block) and the actions, in an LDS table,
-// with a new hash each round.  Group hashes may collide: that keeps more
-// records, never fewer.  A list that overflows is kept whole.
+// ------------------------------------------------------ k_filter_count
+// One workgroup per bucket.  Bitmaps over the slots of the bucket's groups
+// mark where a write is (W, one bit per slot) and where an atomic is (T, one
+// per four), and then, in D (one per two), where one of them may have a
+// partner: a second write, or a read whose slot is in W or T.  Reads outside W
+// and T cannot race, nor can writes and atomics outside D, writes outside T
+// and atomics outside W.  Those that are left, normally a few hundred, are
+// loaded into LDS as records and chained by location; each is paired with
+// those before it in its chain, and each read that is left with all of its
+// location's.  Group hashes may collide: that only adds candidates, the pairs
+// are tested on the records themselves.
+//
+// The table holds WCAP writes and atomics.  A bucket with more is counted in
+// rounds, by slot.  Where that does not help (a hot atomic word whose slot
+// holds an unrelated write or read by chance), the candidates are thinned out
+// first: their records are read and hashed anew into maps of the same kind,
+// up to five times, and those that meet no partner there are dropped.
 //
 // Latency bounds it, not bytes (4 per record): a bucket's keys lie in one
-// short run per tile, so the starts of many runs are read at once, and the
-// keys of eight runs are in flight per thread.  Neighbouring buckets run at
-// the same time on one XCD, so the lines their runs share are read once.
+// short run per tile.  So each lane loads four keys at once and has four such
+// loads in flight, of one run or of several, and the lists are filled by one
+// LDS atomic per wave and step.  Neighbouring buckets run at the same time on
+// one XCD, so the lines their runs share are read once.
 //
-// A bucket with a hot word is taken apart: one workgroup would stream a
-// million reads, and mark them with a million scattered atomics (c1: 94 of
-// 160 us).  For hot reads it stores A, and k_filter_count, which has a
-// workgroup per tile, tests the tile's run against it and sets the marks in
-// LDS; all of the bucket's writes survive.  A bucket with hot writes survives
-// whole, in the same way.
+// A bucket with a hot word's reads (as the tiles counted them) is split: each
+// further workgroup takes a range of tiles' reads and all of the bucket's
+// writes.  A read's pairs depend on the writes alone; pairs of writes are the
+// first part's.  Entries of one location from several parts (or, for a shared
+// word, from the buckets of several epochs) are added up by the host.
 
-
-// Adds a bucket (b of its trace t) to the trace's list: its number, then
-// (bucket << 2 | flags, place of A) pairs.  The place of its A, or ~0 when
-// there is no room.
-__device__ __forceinline__ uint32_t hot_place(const FilterBuffers& f, uint32_t t, uint32_t b, uint32_t flags) {
-  uint32_t* const list = f.trace_hot + (uint64_t)t * f.hot_stride;
-  uint32_t map = 0;
-  if (!(flags & HOT_WRITES)) {
-    map = atomicAdd(f.n_hot, 1u);
-    if (map >= f.max_hot) return ~0u;
-  }
-  const uint32_t k = atomicAdd(&list[0], 1u);
-  if (2 * k + 2 >= f.hot_stride) return ~0u;
-  list[2 * k + 1] = (b << 2) | flags;
-  list[2 * k + 2] = map;
-  return map;
-}
-
-// The buckets the tiles have flagged.
+// Workgroups of hot buckets: item i is (bucket, part).  They come first in the
+// grid.  (There is room for them: at most reads / hot_part buckets have two
+// parts or more, with as many further parts in all.)
 __global__ __launch_bounds__(NT) void k_filter_plan(FilterBuffers f) {
   const uint32_t b = blockIdx.x * NT + threadIdx.x;
   if (b >= f.n_buckets) return;
-  const uint32_t hot = f.hot[b];
-  if (!hot) return;
-  const uint32_t t = f.bucket_trace[b], place = hot_place(f, t, b - f.tr[t].bucket0, hot);
-  f.hot[b] = place == ~0u ? 0u : (place << 2) | hot;  // (without room an ordinary bucket, if a slow one)
+  const uint32_t parts = min(f.tr[f.bucket_trace[b]].ntiles, 1u + f.hot[b] / f.hot_part);
+  f.hot[b] = parts;
+  if (parts > 1) {
+    const uint32_t at = atomicAdd(&f.cnt[FC_EXTRA], parts);
+    for (uint32_t k = 0; k < parts && at + k < f.extra_max; k++) f.extra[at + k] = make_uint2(b, k);
+  }
 }
 
-template <int NTH, uint32_t SB, uint32_t CAP, uint32_t CHUNK>
-__global__ __launch_bounds__(NTH, 8) void k_filter_test(FilterBuffers f) {
-  constexpr uint32_t A_WORDS = (1u << SB) / 32, D_WORDS = A_WORDS / 2;
-  constexpr uint32_t X_SLOTS = (A_WORDS + D_WORDS) / 3;  // slots of the exact table: smallest, largest id, actions
-  static_assert((X_SLOTS & (X_SLOTS - 1)) == 0, "the exact table is a power of two");
-  constexpr int XPT = CAP / NTH;
-  __shared__ __align__(16) uint32_t s_map[A_WORDS + D_WORDS];
-  __shared__ uint32_t s_list[CAP];
-  __shared__ uint32_t s_pair[CHUNK];
-  __shared__ uint16_t s_end[CHUNK];
-  __shared__ uint32_t s_n, s_any;
+// Four keys, or two row words, from any word on.
+typedef uint32_t words4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t words2 __attribute__((ext_vector_type(2), aligned(4)));
+typedef const __attribute__((address_space(1))) uint32_t* GWords;
+__device__ __forceinline__ words4 load_words4(GWords p) { return *(const __attribute__((address_space(1))) words4*)p; }
+__device__ __forceinline__ words2 load_words2(GWords p) { return *(const __attribute__((address_space(1))) words2*)p; }
+
+template <bool LATE, bool WARP, uint32_t WCAP, uint32_t RCAP>
+__global__ __launch_bounds__(FNT, 8) void k_filter_count(FilterBuffers f) {
+  constexpr uint32_t NTH = FNT;
+  constexpr uint32_t SB = FILTER_SLOT_BITS, W_WORDS = (1u << SB) / 32, D_WORDS = W_WORDS / 2, T_WORDS = W_WORDS / 4;
+  constexpr uint32_t HN = 512, NONE = 0xFFFFu;  // chains of writes, and as many of atomics
+  constexpr uint32_t MAX_ROUNDS = 64, MAX_LEVEL = 5;
+  constexpr uint32_t L_BITS = 14, L_WORDS = (1u << L_BITS) / 32;  // the maps of the thinning
+  static_assert((MAX_LEVEL - 1 + 4) * L_WORDS <= W_WORDS, "they take W's place");
+  __shared__ __align__(16) uint32_t s_map[W_WORDS + D_WORDS + T_WORDS];
+  __shared__ uint32_t s_read[RCAP];
+  __shared__ uint4 s_w[WCAP];
+  __shared__ uint32_t s_blk[WCAP];    // their blocks; before them their record indices
+  __shared__ uint32_t s_side[WARP ? WCAP : 1];
+  __shared__ uint32_t s_acc[5][WCAP]; // pairs by kind of the location whose first write this is
+  __shared__ uint32_t s_head[2 * HN];
+  __shared__ uint16_t s_next[WCAP], s_lead[WCAP];
+  __shared__ uint32_t s_n, s_nw, s_any, s_base;
   const uint32_t tx = threadIdx.x;
-  const TileWalk tw = tile_walk(f.n_buckets, gridDim.x, blockIdx.x);
-  if (tw.first >= tw.end) return;
-  const uint32_t bucket = tw.first, hot = f.hot[bucket];
-  if (hot & HOT_WRITES) return;
-  const FTrace T = f.tr[f.bucket_trace[bucket]];
+  uint32_t bucket, part = 0;
+  if (LATE) {
+    if (blockIdx.x >= f.cnt[FC_LATE]) return;
+    bucket = f.late[blockIdx.x].x;
+    part = f.late[blockIdx.x].y;
+  } else if (blockIdx.x < f.extra_max) {
+    if (blockIdx.x >= f.cnt[FC_EXTRA]) return;
+    const uint2 it = f.extra[blockIdx.x];
+    bucket = it.x;
+    part = it.y;
+  } else {
+    const TileWalk tw = tile_walk(f.n_buckets, gridDim.x - f.extra_max, blockIdx.x - f.extra_max);
+    if (tw.first >= tw.end) return;
+    bucket = tw.first;
+  }
+  auto uniform = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); };
+  bucket = uniform(bucket);
+  part = uniform(part);
+  const uint32_t parts = uniform(f.extra_max ? f.hot[bucket] : 1u);
+  if (!LATE && parts > 1 && blockIdx.x >= f.extra_max) return;  // (its parts are items)
+  const uint32_t trace = uniform(f.bucket_trace[bucket]);
+  FTrace T = f.tr[trace];
+  T.rec = (const void*)readfirstlane((uint64_t)T.rec);
+  T.n = readfirstlane(T.n);
+  T.row0 = readfirstlane(T.row0);
+  T.off = uniform(T.off);
+  T.tpb = uniform(T.tpb);
+  T.ntiles = uniform(T.ntiles);
+  T.bucket0 = uniform(T.bucket0);
+  T.lgb = uniform(T.lgb);
+  T.sbits = uniform(T.sbits);
   const uint32_t b = bucket - T.bucket0, B = 1u << T.lgb;
-  const uint32_t sbits = min(T.sbits, SB), smask = (1u << sbits) - 1;  // (the host gives it SB at most)
-  uint32_t* const A = s_map;
-  uint32_t* const D = s_map + A_WORDS;
-  const uint32_t a_words = 1u << (sbits - 5), d_words = a_words / 2;
-  for (uint32_t k = 4 * tx; k < a_words; k += 4 * NTH) *(uint4*)(A + k) = make_uint4(0, 0, 0, 0);
-  for (uint32_t k = 4 * tx; k < d_words; k += 4 * NTH) *(uint4*)(D + k) = make_uint4(0, 0, 0, 0);
+  const uint32_t smask = (1u << T.sbits) - 1;
+  uint32_t* const W = s_map;
+  uint32_t* const D = s_map + W_WORDS;
+  uint32_t* const A = D + D_WORDS;  // atomics (T)
+  for (uint32_t k = 4 * tx; k < W_WORDS + D_WORDS + T_WORDS; k += 4 * NTH) {
+    // (a bucket of fewer slots uses the front of each map)
+    const uint32_t w = k < W_WORDS ? k : (k < W_WORDS + D_WORDS ? 2 * (k - W_WORDS) : 4 * (k - W_WORDS - D_WORDS));
+    if (w < 1u << (T.sbits - 5)) *(uint4*)(s_map + k) = make_uint4(0, 0, 0, 0);
+  }
   if (tx == 0) {
     s_n = 0;
+    s_nw = 0;
     s_any = 0;
   }
-  const uint32_t* rows = f.rows + T.row0 + b;
-  // the starts and ends of the bucket's runs in tiles c0 .. c0 + n - 1
-  auto load_runs = [&](uint32_t c0, uint32_t n) {
-    __syncthreads();
-    for (uint32_t i = tx; i < n; i += NTH) {
-      const uint32_t* r = rows + (uint64_t)(c0 + i) * (B + 1);
-      s_pair[i] = r[0];
-      s_end[i] = (uint16_t)(r[1] & 0xFFFFu);
-    }
-    __syncthreads();
-  };
-  // The writes (or reads) of run i, from place `at` of its tile on: one key
-  // per lane of a group and step, U steps at once; bit u of the result: k[u]
-  // is a key.
-  auto load_keys = [&](uint32_t c0, uint32_t i, bool writes, uint32_t skip, uint32_t lg, auto& k, bool* more) {
-    constexpr uint32_t U = sizeof(k) / sizeof(k[0]);
-    const uint32_t L = 1u << lg, pr = s_pair[i];
-    const uint32_t at = (writes ? pr & 0xFFFFu : pr >> 16) + skip + (tx & (L - 1)), end = writes ? pr >> 16 : s_end[i];
-    const uint32_t* p = f.keys + (T.off + (c0 + i) * FT);
-    uint32_t live = 0;
-#pragma unroll
-    for (uint32_t u = 0; u < U; u++)
-      if (at + u * L < end) {
-        k[u] = p[at + u * L];
-        live |= 1u << u;
-      }
-    *more = at + U * L < end;
-    return live;
-  };
-  // fn(key, record index in the trace) for every write (or read) in runs
-  // 0 .. n - 1 from tile c0 on, a run per group of 2^lg lanes
-  auto for_runs = [&](uint32_t c0, uint32_t n, bool writes, uint32_t lg, auto&& fn) {
-    constexpr uint32_t U = 8;
+  __syncthreads();
+  auto bit = [](const uint32_t* map, uint32_t s) { return (map[s >> 5] >> (s & 31u)) & 1u; };
+  auto set = [&](uint32_t* map, uint32_t s) { return atomicOr(&map[s >> 5], 1u << (s & 31u)); };
+  // ---- a pass over the bucket's writes (or reads) of tiles lo .. hi - 1:
+  //      fn(four keys, which of them are keys, first record of their tile).
+  //      A run is a group of 2^lg lanes' (four keys a lane and load); with
+  //      more runs than groups and short runs a lane loads of 2^ml runs at
+  //      once.  All lanes of a wave call fn together.  (One copy of fn per
+  //      pass: straight code for all sixteen keys took longer to fetch than
+  //      to run.)
+  const GWords rows = (GWords)(f.rows + T.row0 + b);
+  const GWords keys = (GWords)(f.keys + T.off);
+  const uint32_t run = (uint32_t)min<uint64_t>(FT >> T.lgb, T.n);  // usual length
+  auto for_keys_n = [&](auto nv, bool writes, uint32_t lo, uint32_t hi, auto&& fn) {
+    constexpr uint32_t NV = decltype(nv)::value;  // loads in flight
+    const uint32_t len = writes ? run / 4 : run - run / 4;  // (a quarter of the records write)
+    const uint32_t most = 31u - (uint32_t)__builtin_clz(NTH / min(NTH, hi - lo));  // with it every run has a group
+    uint32_t lg = len > 16 ? 32u - (uint32_t)__builtin_clz((len - 1) / 16) : 0u;
+    lg = min(lg, 10u);
+    while (lg < most && ((4u << lg) < len || parts > 1)) lg++;
+    const uint32_t step = NTH >> lg;
+    uint32_t ml = NV == 1 ? 0u : (len <= 4u << lg ? 2u : (len <= 8u << lg ? 1u : 0u));
+    while (ml && hi - lo <= step << (ml - 1)) ml--;
+    uint32_t to = threadIdx.x;
+    asm volatile("" : "+v"(to));  // (not hoisted over the passes)
+    const uint32_t lane = to & ((1u << lg) - 1);
 #pragma unroll 1
-    for (uint32_t i = tx >> lg; i < n; i += NTH >> lg) {
-      uint32_t skip = 0;
+    for (uint32_t i0 = lo; i0 < hi; i0 += step << ml) {
+      uint32_t at[NV];  // the lane's next key | the run's end << 16
+      auto tile = [&](uint32_t v) { return i0 + (to >> lg) + ((v << ml) / NV) * step; };
+#pragma unroll
+      for (uint32_t v = 0; v < NV; v++) {
+        if ((v & ((NV >> ml) - 1u)) == 0) {
+          at[v] = 0;
+          if (tile(v) < hi) {
+            const words2 r = load_words2(rows + (uint64_t)tile(v) * (B + 1));
+            at[v] = (writes ? r.x : (r.x >> 16) | (r.y << 16)) + 4 * lane;
+          }
+        } else {
+          at[v] = at[v - 1] + (4u << lg);
+        }
+      }
       bool more;
       do {
-        uint32_t k[U];
-        const uint32_t live = load_keys(c0, i, writes, skip, lg, k, &more);
+        words4 x[NV];
+        uint32_t live = 0;
+        more = false;
 #pragma unroll
-        for (uint32_t u = 0; u < U; u++)
-          if ((live >> u) & 1u) fn(k[u], (c0 + i) * FT + (k[u] & (FT - 1)));
-        skip += U << lg;
-      } while (more);
+        for (uint32_t v = 0; v < NV; v++) {
+          const int left = (int)(at[v] >> 16) - (int)(at[v] & 0xFFFFu);
+          if (left > 0) {
+            x[v] = load_words4(keys + (tile(v) * FT + (at[v] & 0xFFFFu)));  // (may read on past the run, never past the buffer)
+            live |= (left >= 4 ? 15u : (1u << left) - 1u) << (4 * v);
+          }
+          at[v] += left > 0 ? (4 * NV >> ml) << lg : 0u;
+          more = more || left > (int)((4 * NV >> ml) << lg);
+        }
+#pragma unroll 1
+        for (uint32_t v = 0; __any(live != 0); v++) {
+          const uint32_t k[4] = {x[0].x, x[0].y, x[0].z, x[0].w};
+          fn(k, live & 15u, tile(v) * FT);
+#pragma unroll
+          for (uint32_t q = 0; q + 1 < NV; q++) x[q] = x[q + 1];
+          live >>= 4;
+        }
+      } while (__any(more));
     }
   };
-  // Lanes per run: with U keys per lane a group holds a run's usual length
-  // and four deviations more, so few runs need a second step.
-  auto lanes_for = [&](uint32_t len, uint32_t u) {
-    const uint32_t want = (len + 4 * (uint32_t)__builtin_sqrtf((float)len) + u - 1) / u;
-    return min(want <= 1 ? 0u : 32u - (uint32_t)__builtin_clz(want - 1), NTH == 1024 ? 10u : 9u);
+  auto for_keys = [&](bool writes, uint32_t lo, uint32_t hi, auto&& fn) {
+    for_keys_n(std::integral_constant<uint32_t, 4>(), writes, lo, hi, fn);
   };
-  constexpr uint32_t UW = 16;  // a thread's writes, when they stay in registers
-  const uint32_t run = FT >> T.lgb;
-  const uint32_t lg_r = lanes_for(run - run / 4, 8), lg_w = lanes_for(run / 4, UW);
+  // ... where fn reads the keys' records: four of those are in flight instead
+  auto for_keys_records = [&](bool writes, uint32_t lo, uint32_t hi, auto&& fn) {
+    for_keys_n(std::integral_constant<uint32_t, 1>(), writes, lo, hi, fn);
+  };
+  auto slot_of = [&](uint32_t k) { return (k >> FT_BITS) & smask; };
+  // Appends the indices of the keys in `pick` to a list (all lanes together).
+  auto append = [&](const uint32_t(&k)[4], uint32_t pick, uint32_t base, uint32_t* list, uint32_t cap,
+                    uint32_t* count) {
+    if (!__any(pick != 0)) return;
+    const uint32_t n = (uint32_t)__popc(pick), inc = wave_incl_scan(n, [](uint32_t a, uint32_t c) { return a + c; });
+    const uint32_t all = readlane(inc, 63);
+    uint32_t first = 0;
+    if (__lane_id() == 0) first = atomicAdd(count, all);
+    uint32_t pos = (uint32_t)__builtin_amdgcn_readfirstlane((int)first) + inc - n;
+#pragma unroll
+    for (uint32_t u = 0; u < 4; u++)
+      if ((pick >> u) & 1u) {
+        if (pos < cap) list[pos] = base + (k[u] & (FT - 1));
+        pos++;
+      }
+  };
 
-  // ---- A and D from the writes.  (Bits are looked at before they are set:
-  //      the atomics of a hot word's lanes would go one by one.)
+  // ---- W and T, and D from writes that meet another.  (Bits are looked at
+  //      before they are set: a hot word's atomics would go one by one.)
   bool any = false;
-  auto see_write = [&](uint32_t k) {
-    const uint32_t s = (k >> FT_BITS) & smask, bit = 1u << (s & 31u), s2 = s >> 1, bit2 = 1u << (s2 & 31u);
-    any = true;
-    uint32_t old = A[s >> 5];
-    if (!(old & bit)) old = atomicOr(&A[s >> 5], bit);
-    if ((old & bit) && !(D[s2 >> 5] & bit2)) atomicOr(&D[s2 >> 5], bit2);
-  };
-  const bool one_chunk = T.ntiles <= CHUNK;
-  const bool held = T.ntiles <= (uint32_t)NTH >> lg_w && one_chunk;  // a run per group: its writes stay in registers
-  uint32_t kw[UW], w_live = 0;
-  bool w_more = false;
-  if (held) {
-    load_runs(0, T.ntiles);  // (its barriers also follow the clears above)
-    const uint32_t i = tx >> lg_w;
-    if (i < T.ntiles) w_live = load_keys(0, i, true, 0, lg_w, kw, &w_more);
+  for_keys(true, 0, T.ntiles, [&](const uint32_t(&k)[4], uint32_t live, uint32_t) {
+    any = any || live;
+    uint32_t seen = 0;
 #pragma unroll
-    for (uint32_t u = 0; u < UW; u++)
-      if ((w_live >> u) & 1u) see_write(kw[u]);
-    uint32_t skip = UW << lg_w;
-    bool more = w_more;
-    while (more) {
-      uint32_t k[4];
-      const uint32_t live = load_keys(0, i, true, skip, lg_w, k, &more);
+    for (uint32_t u = 0; u < 4; u++)
+      if ((live >> u) & 1u) {
+        const uint32_t s = slot_of(k[u]);
+        seen |= ((k[u] & FILTER_ATOMIC) ? bit(A, s >> 2) : bit(W, s)) << u;
+      }
 #pragma unroll
-      for (uint32_t u = 0; u < 4; u++)
-        if ((live >> u) & 1u) see_write(k[u]);
-      skip += 4u << lg_w;
-    }
-  } else {
-    for (uint32_t c0 = 0; c0 < T.ntiles; c0 += CHUNK) {
-      const uint32_t n = min(CHUNK, T.ntiles - c0);
-      load_runs(c0, n);
-      for_runs(c0, n, true, lg_w, [&](uint32_t k, uint32_t) { see_write(k); });
-    }
-  }
-  if (hot) {
-    __syncthreads();  // A is complete
-    for (uint32_t k = tx; k < A_WORDS; k += NTH) f.hot_maps[(uint64_t)(hot >> 2) * A_STRIDE + k] = k < a_words ? A[k] : 0u;
-    return;
-  }
+    for (uint32_t u = 0; u < 4; u++)
+      if (((live & ~seen) >> u) & 1u) {
+        const uint32_t s = slot_of(k[u]);
+        if (k[u] & FILTER_ATOMIC) set(A, s >> 2);
+        else seen |= ((set(W, s) >> (s & 31u)) & 1u) << u;
+      }
+#pragma unroll
+    for (uint32_t u = 0; u < 4; u++)
+      if (((live & seen) >> u) & 1u) {
+        const uint32_t sd = slot_of(k[u]) >> 1;
+        if (!(k[u] & FILTER_ATOMIC) && !bit(D, sd)) set(D, sd);
+      }
+  });
   if (any) s_any = 1;
   __syncthreads();
   if (!s_any) return;  // nothing but reads
 
-  // ---- reads in A
-  uint32_t* const surv = f.survive + T.surv0;
-  auto mark = [&](uint32_t idx) { atomicOr(&surv[idx >> 5], 1u << (idx & 31u)); };
-  auto keep = [&](uint32_t idx) {  // one LDS atomic for the lanes that are here together
-    const uint64_t m = __ballot(true), before = m & ((1ull << __lane_id()) - 1ull);
-    uint32_t pos = 0;
-    if (before == 0) pos = atomicAdd(&s_n, (uint32_t)__popcll(m));
-    pos = (uint32_t)__builtin_amdgcn_readfirstlane((int)pos) + (uint32_t)__popcll(before);
-    if (pos < CAP) s_list[pos] = idx;
-    return pos < CAP;
+  // ---- reads in W or T; the first RCAP of them are remembered
+  const uint32_t r0 = (uint32_t)((uint64_t)T.ntiles * part / parts), r1 = (uint32_t)((uint64_t)T.ntiles * (part + 1) / parts);
+  for_keys(false, r0, r1, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
+    uint32_t pick = 0;
+#pragma unroll
+    for (uint32_t u = 0; u < 4; u++)
+      if ((live >> u) & 1u) pick |= (bit(W, slot_of(k[u])) | bit(A, slot_of(k[u]) >> 2)) << u;
+#pragma unroll
+    for (uint32_t u = 0; u < 4; u++)
+      if ((pick >> u) & 1u) {
+        const uint32_t sd = slot_of(k[u]) >> 1;
+        if (!bit(D, sd)) set(D, sd);
+      }
+    append(k, pick, base, s_read, RCAP, &s_n);
+  });
+  __syncthreads();
+  const uint32_t n_read = uniform(s_n);
+  const GRecords p = global_records(T.rec);
+  const uint32_t shift = block_shift(T.tpb);
+  auto load_frec = [&](uint32_t idx) {
+    const Rec x = unpack_rec(load_record(p, idx));
+    return frec(x.unit, x.tid, x.epoch, x.action, x.space);
   };
-  auto read_hits = [&](uint32_t k) {
-    const uint32_t s = (k >> FT_BITS) & smask, s2 = s >> 1, bit2 = 1u << (s2 & 31u);
-    if (!((A[s >> 5] >> (s & 31u)) & 1u)) return false;
-    if (!(D[s2 >> 5] & bit2)) atomicOr(&D[s2 >> 5], bit2);
+  auto w_at = [&](uint32_t i) {
+    const uint4 v = s_w[i];
+    return FRec{v.x, v.y, v.z, v.w};
+  };
+  // The records of the keys in `pick`: fn(u, record, its index).
+  auto for_records = [&](const uint32_t(&k)[4], uint32_t pick, uint32_t base, auto&& fn) {
+#pragma unroll 1
+    for (uint32_t h = 0; h < 2; h++) {  // two in flight
+      const uint32_t i0 = base + ((h ? k[2] : k[0]) & (FT - 1)), i1 = base + ((h ? k[3] : k[1]) & (FT - 1));
+      const uint32_t two = pick >> (2 * h) & 3u;
+      FRec x, y;
+      if (two & 1u) x = load_frec(i0);
+      if (two & 2u) y = load_frec(i1);
+#pragma unroll 1
+      for (uint32_t u = 0; u < 2; u++) {  // (one copy of fn)
+        if ((two >> u) & 1u) fn(2 * h + u, x, u ? i1 : i0);
+        x = y;
+      }
+    }
+  };
+
+  // ---- the writes and atomics that are left: all of them
+  for_keys(true, 0, T.ntiles, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
+    uint32_t pick = 0;
+#pragma unroll
+    for (uint32_t u = 0; u < 4; u++)
+      if ((live >> u) & 1u) {
+        const uint32_t s = slot_of(k[u]);
+        const uint32_t in_d = bit(D, s >> 1), other = (k[u] & FILTER_ATOMIC) ? bit(W, s) : bit(A, s >> 2);
+        pick |= (in_d | other) << u;
+        if (other && !in_d) set(D, s >> 1);  // (D alone tells the candidates from here on)
+      }
+    append(k, pick, base, s_blk, WCAP, &s_nw);
+  });
+  __syncthreads();
+  static_assert(MAX_ROUNDS == 64, "a lane per round");
+  uint32_t rounds = 1, level = 0;
+  // keys of D that are a round's
+  auto in_round = [&](const uint32_t(&k)[4], uint32_t live, uint32_t round) {
+    uint32_t pick = 0;
+#pragma unroll
+    for (uint32_t u = 0; u < 4; u++)
+      if ((live >> u) & 1u) {
+        const uint32_t s = slot_of(k[u]);
+        pick |= ((s & (rounds - 1)) == round ? bit(D, s >> 1) : 0u) << u;
+      }
+    return pick;
+  };
+  // a record's slot in the maps of level l, and whether the levels so far kept it
+  auto level_slot = [&](const FRec& x, uint32_t l) {
+    return filter_group2(x, block_of(x.tid, T.tpb, shift), l) >> (32 - L_BITS);
+  };
+  auto kept = [&](const FRec& x) {
+    for (uint32_t l = 0; l < level; l++)
+      if (!bit(W + l * L_WORDS, level_slot(x, l))) return false;
     return true;
   };
-  for (uint32_t c0 = 0; c0 < T.ntiles; c0 += CHUNK) {
-    const uint32_t n = min(CHUNK, T.ntiles - c0);
-    if (!one_chunk) load_runs(c0, n);
-    for_runs(c0, n, false, lg_r, [&](uint32_t k, uint32_t idx) {
-      if (read_hits(k)) keep(idx);
-    });
+  auto keep_of = [&](const uint32_t(&k)[4], uint32_t pick, uint32_t base) {
+    if (!LATE || level == 0) return pick;
+    uint32_t left = 0;
+    for_records(k, pick, base, [&](uint32_t u, const FRec& x, uint32_t) { left |= kept(x) ? 1u << u : 0u; });
+    return left;
+  };
+  const uint32_t n_left = uniform(s_nw);
+  if (n_left > WCAP) {
+    uint32_t* const cls = s_head;  // candidates by the low bits of their slot
+    for (;;) {
+      __syncthreads();
+      if (tx < MAX_ROUNDS) cls[tx] = 0;
+      __syncthreads();
+      for_keys(true, 0, T.ntiles, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
+        const uint32_t pick = keep_of(k, in_round(k, live, 0), base);
+#pragma unroll
+        for (uint32_t u = 0; u < 4; u++)
+          if ((pick >> u) & 1u) atomicAdd(&cls[slot_of(k[u]) & (MAX_ROUNDS - 1)], 1u);
+      });
+      __syncthreads();
+      // the fewest rounds that each fit: lane r adds up the classes of round r
+      if (tx < 64) {
+        uint32_t sum = cls[tx], fit = MAX_ROUNDS;
+        if (__any(sum > WCAP)) fit = 2 * MAX_ROUNDS;
+        while (fit <= MAX_ROUNDS && fit > 1) {
+          sum += __shfl_xor(sum, (int)(fit / 2));
+          if (__any(sum > WCAP)) break;
+          fit /= 2;
+        }
+        if (tx == 0) s_base = fit;
+      }
+      __syncthreads();
+      const uint32_t fit = uniform(s_base);
+      if (fit <= 4 || (fit <= MAX_ROUNDS && (level > 1 || (!LATE && !f.late_max)))) {
+        rounds = fit;
+        break;
+      }
+      if (!LATE && f.late_max) {  // thinned out by a workgroup of its own
+        if (tx == 0) {
+          const uint32_t at = atomicAdd(&f.cnt[FC_LATE], 1u);
+          if (at < f.late_max) f.late[at] = make_uint2(bucket, part);
+          else atomicOr(&f.ctrl->error_flags, ERR_GROUP_FULL);
+        }
+        return;
+      }
+      if (!LATE || level == MAX_LEVEL) {  // too many of one slot that do meet
+        if (tx == 0) atomicOr(&f.ctrl->error_flags, ERR_GROUP_FULL);
+        return;
+      }
+      if (LATE) {
+      // ---- one more level: writes, atomics, reads and twice written slots
+      uint32_t* const lw = W + level * L_WORDS;
+      uint32_t* const la = W + (W_WORDS - 3 * L_WORDS);
+      uint32_t* const lr = la + L_WORDS;
+      uint32_t* const l2 = lr + L_WORDS;
+      for (uint32_t i = tx; i < L_WORDS; i += NTH) lw[i] = la[i] = lr[i] = l2[i] = 0;
+      __syncthreads();
+      for_keys_records(true, 0, T.ntiles, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
+        for_records(k, in_round(k, live, 0), base, [&](uint32_t, const FRec& x, uint32_t) {
+          if (!kept(x)) return;
+          const uint32_t s = level_slot(x, level);
+          if (frec_action(x) == 1u) {
+            if ((bit(lw, s) || ((set(lw, s) >> (s & 31u)) & 1u)) && !bit(l2, s)) set(l2, s);
+          } else if (!bit(la, s)) {
+            set(la, s);
+          }
+        });
+      });
+      for_keys_records(false, r0, r1, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
+        for_records(k, in_round(k, live, 0), base, [&](uint32_t, const FRec& x, uint32_t) {
+          if (!kept(x)) return;
+          const uint32_t s = level_slot(x, level);
+          if (!bit(lr, s)) set(lr, s);
+        });
+      });
+      __syncthreads();
+      for (uint32_t i = tx; i < L_WORDS; i += NTH) lw[i] = l2[i] | (lw[i] & (la[i] | lr[i])) | (la[i] & lr[i]);
+      level++;
+      }
+    }
   }
-  __syncthreads();  // D is complete
-  if (s_n > CAP) {
-    // a word too hot for the list but not for the tiles' flags: the bucket
-    // goes the way of the flagged ones, if there is room
-    if (tx == 0) s_any = hot_place(f, f.bucket_trace[bucket], b, HOT_READS);
+#pragma unroll 1
+  for (uint32_t round = 0; round < rounds; round++) {
+    uint32_t tx = threadIdx.x;
+    asm volatile("" : "+v"(tx));  // keeps per-thread addresses out of registers across the passes
+    if (n_left > WCAP) {          // this round's
+      __syncthreads();
+      if (tx == 0) s_nw = 0;
+      __syncthreads();
+      for_keys(true, 0, T.ntiles, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
+        append(k, keep_of(k, in_round(k, live, round), base), base, s_blk, WCAP, &s_nw);
+      });
+    }
+    for (uint32_t k = tx; k < 2 * HN; k += NTH) s_head[k] = NONE;
     __syncthreads();
-    const uint32_t place = s_any;
-    if (place != ~0u) {
-      for (uint32_t k = tx; k < A_WORDS; k += NTH) f.hot_maps[(uint64_t)place * A_STRIDE + k] = k < a_words ? A[k] : 0u;
+    const uint32_t nw = uniform(s_nw);  // (at most WCAP)
+    if ((uint64_t)n_read * nw >= 1ull << 32) {  // sums of pairs are kept in 32 bits
+      if (tx == 0) atomicOr(&f.ctrl->error_flags, ERR_GROUP_FULL);
       return;
     }
-    for (uint32_t c0 = 0; c0 < T.ntiles; c0 += CHUNK) {
-      const uint32_t n = min(CHUNK, T.ntiles - c0);
-      if (!one_chunk) load_runs(c0, n);
-      for_runs(c0, n, false, lg_r, [&](uint32_t k, uint32_t idx) {
-        if (read_hits(k)) mark(idx);
+    if (!nw) continue;
+    auto chain_of = [&](const FRec& x, uint32_t bx) { return location_hash(x, bx) & (HN - 1); };
+#pragma unroll 1
+    for (uint32_t i = tx; i < nw; i += NTH) {
+      const uint32_t idx = s_blk[i];
+      const FRec x = load_frec(idx);
+      const uint32_t bx = block_of(x.tid, T.tpb, shift);
+      if (WARP) s_side[i] = f.side[T.off + idx];
+      s_w[i] = make_uint4(x.ulo, x.uhi, x.tid, x.meta);
+      s_blk[i] = bx;
+      s_next[i] = (uint16_t)atomicExch(&s_head[chain_of(x, bx) + (frec_action(x) == 2u ? HN : 0u)], i);
+#pragma unroll
+      for (int q = 0; q < 5; q++) s_acc[q][i] = 0;
+    }
+    __syncthreads();
+    // ---- a location's first write in the table, and the pairs of writes.
+    //      (An atomic walks the writes only: a hot word's atomics meet no other
+    //      atomic.  Without a write their location has no first one yet.)
+#pragma unroll 1
+    for (uint32_t i = tx; i < nw; i += NTH) {
+      const FRec x = w_at(i);
+      const uint32_t bx = s_blk[i], sx = WARP ? s_side[i] : 0u;
+      const bool atomic = frec_action(x) == 2u;
+      uint32_t lead = i, ww = 0, aw = 0, xb = 0;
+#pragma unroll 1
+      for (uint32_t j = s_head[chain_of(x, bx)]; j != NONE; j = s_next[j]) {
+        if (!atomic && j >= i) continue;
+        const FRec y = w_at(j);
+        const uint32_t by = s_blk[j];
+        if (!same_location(x, bx, y, by)) continue;
+        lead = lead == i ? j : min(lead, j);
+        if (part == 0 && pair_races(x, bx, y, by, WARP, T.tpb, sx, WARP ? s_side[j] : 0u)) {
+          if (atomic) aw++;
+          else ww++;
+          if (bx != by) xb++;
+        }
+      }
+      s_lead[i] = (uint16_t)lead;
+      if (ww) atomicAdd(&s_acc[K_WW][lead], ww);
+      if (aw) atomicAdd(&s_acc[K_AW][lead], aw);
+      if (xb) atomicAdd(&s_acc[K_XB][lead], xb);
+    }
+    __syncthreads();
+    // ---- the reads' pairs, summed per thread while the location stays the
+    //      same (the lanes' LDS atomics to a hot word's sums go one by one)
+    uint32_t lead = 0, rw = 0, ar = 0, xb = 0;
+    auto flush = [&]() {
+      if (rw) atomicAdd(&s_acc[K_RW][lead], rw);
+      if (ar) atomicAdd(&s_acc[K_AR][lead], ar);
+      if (xb) atomicAdd(&s_acc[K_XB][lead], xb);
+      rw = ar = xb = 0;
+    };
+    auto count_read = [&](const FRec& x, uint32_t idx) {
+      const uint32_t bx = block_of(x.tid, T.tpb, shift);
+      const uint32_t c = chain_of(x, bx);
+      uint32_t j = s_head[c], k = s_head[c + HN];
+      if (j == NONE) {
+        j = k;
+        k = NONE;
+      }
+      if (j == NONE) return;
+      const uint32_t sx = WARP ? f.side[T.off + idx] : 0u;
+#pragma unroll 1
+      while (j != NONE) {
+        const uint32_t at = j;
+        j = s_next[j];
+        if (j == NONE) {  // the writes, then the atomics
+          j = k;
+          k = NONE;
+        }
+        const FRec y = w_at(at);
+        const uint32_t by = s_blk[at];
+        if (!same_location(x, bx, y, by) || !pair_races(x, bx, y, by, WARP, T.tpb, sx, WARP ? s_side[at] : 0u)) continue;
+        const uint32_t l = s_lead[at];
+        if (l != lead) flush();
+        lead = l;
+        if (frec_action(y) == 1u) rw++;
+        else ar++;
+        if (bx != by) xb++;
+      }
+    };
+    if (n_read <= RCAP) {  // (in rounds, those of other slots meet no write here)
+#pragma unroll 1
+      for (uint32_t i = tx; i < n_read; i += NTH) count_read(load_frec(s_read[i]), s_read[i]);
+    } else if (n_read) {
+      for_keys_records(false, r0, r1, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
+        for_records(k, in_round(k, live, round), base, [&](uint32_t, const FRec& x, uint32_t idx) { count_read(x, idx); });
       });
     }
+    {
+      const uint64_t has = __ballot((rw | ar) != 0);
+      if (has) {
+        const uint32_t l = readlane(lead, (int)__builtin_ctzll(has));
+        if (__all((rw | ar) == 0 || lead == l)) {  // one location: one lane adds for the wave
+          auto add = [](uint32_t a, uint32_t c) { return a + c; };
+          rw = wave_reduce(rw, 0u, add);
+          ar = wave_reduce(ar, 0u, add);
+          xb = wave_reduce(xb, 0u, add);
+          lead = l;
+          if (__lane_id() == 0) flush();
+        } else {
+          flush();
+        }
+      }
+    }
+    if (tx == 0) s_n = 0;
+    __syncthreads();
+    auto paired = [&](uint32_t i) { return (s_acc[K_WW][i] | s_acc[K_RW][i] | s_acc[K_AW][i] | s_acc[K_AR][i]) != 0; };
+    // ---- atomics of one location that met reads but have no write: the first
+    //      of them takes the sums of all
+    bool lone = false;
+    for (uint32_t i = tx; i < nw; i += NTH) lone = lone || (s_lead[i] == i && s_acc[K_AR][i] && (s_w[i].w >> 16 & 3u) == 2u);
+    if (__syncthreads_or(lone)) {
+#pragma unroll 1
+      for (uint32_t i = tx; i < nw; i += NTH) {
+        const FRec x = w_at(i);
+        if (s_lead[i] != i || !s_acc[K_AR][i] || frec_action(x) != 2u) continue;
+        const uint32_t bx = block_of(x.tid, T.tpb, shift);
+        uint32_t lead = i;
+#pragma unroll 1
+        for (uint32_t j = s_head[chain_of(x, bx) + HN]; j != NONE; j = s_next[j]) {
+          if (j >= lead || !s_acc[K_AR][j]) continue;
+          const FRec y = w_at(j);
+          if (same_location(x, bx, y, block_of(y.tid, T.tpb, shift))) lead = j;
+        }
+        s_blk[i] = lead;  // (nothing reads these atomics' blocks any more)
+      }
+      __syncthreads();
+#pragma unroll 1
+      for (uint32_t i = tx; i < nw; i += NTH) {
+        if (s_lead[i] != i || !s_acc[K_AR][i] || (s_w[i].w >> 16 & 3u) != 2u) continue;
+        const uint32_t lead = s_blk[i];
+        if (lead == i) continue;
+        atomicAdd(&s_acc[K_AR][lead], s_acc[K_AR][i]);
+        if (s_acc[K_XB][i]) atomicAdd(&s_acc[K_XB][lead], s_acc[K_XB][i]);
+        s_lead[i] = (uint16_t)lead;
+      }
+      __syncthreads();
+    }
+    // ---- an entry per location with pairs
+#pragma unroll 1
+    for (uint32_t i0 = 0; i0 < nw; i0 += NTH) {
+      const uint32_t i = i0 + tx;
+      const bool racing =
+          i < nw && s_lead[i] == i && paired(i);
+      const uint64_t mask = __ballot(racing);
+      uint32_t pos = 0;
+      if (mask) {
+        if (__lane_id() == 0) pos = atomicAdd(&s_n, (uint32_t)__popcll(mask));
+        pos = (uint32_t)__builtin_amdgcn_readfirstlane((int)pos) + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+      }
+      __syncthreads();
+      const uint32_t n_new = s_n;
+      __syncthreads();
+      if (n_new) {
+        if (tx == 0) {
+          s_base = atomicAdd(&f.cnt[FC_ENTRIES], n_new);
+          if (s_base + n_new > f.entries_cap) atomicOr(&f.ctrl->error_flags, ERR_GROUP_FULL);
+          const uint32_t in_trace = atomicAdd(&f.trace_cnt[trace], n_new) + n_new;
+          if (in_trace > SORT_CHUNK) atomicMax(&f.cnt[FC_MOST], in_trace);
+          s_n = 0;
+        }
+        __syncthreads();
+        if (racing && s_base + n_new <= f.entries_cap) {
+          const FRec x = w_at(i);
+          RaceOut e;
+          e.trace = trace;
+          e.space = (uint8_t)frec_space(x);
+          e.kinds = (uint8_t)((s_acc[K_WW][i] ? 1 : 0) | (s_acc[K_RW][i] ? 2 : 0) | (s_acc[K_AW][i] ? 4 : 0) |
+                              (s_acc[K_AR][i] ? 8 : 0) | (s_acc[K_XB][i] ? 16 : 0));
+          e.reserved16 = 0;
+          e.block = frec_space(x) ? block_of(x.tid, T.tpb, shift) : 0xFFFFFFFFu;
+          e.reserved32 = 0;
+          e.unit = ((uint64_t)x.uhi << 32) | x.ulo;
+          e.ww = s_acc[K_WW][i];
+          e.rw = s_acc[K_RW][i];
+          e.aw = s_acc[K_AW][i];
+          e.ar = s_acc[K_AR][i];
+          e.xb = s_acc[K_XB][i];
+          f.entries[s_base + pos] = e;
+        }
+      }
+      __syncthreads();
+    }
   }
+}
 
-  // ---- writes in D
-  auto keep_or_mark = [&](uint32_t idx) {
-    if (!keep(idx)) mark(idx);
-  };
-  auto in_d = [&](uint32_t k) {
-    const uint32_t s2 = ((k >> FT_BITS) & smask) >> 1;
-    return ((D[s2 >> 5] >> (s2 & 31u)) & 1u) != 0;
-  };
-  if (held) {
-    const uint32_t i = tx >> lg_w;
+// ------------------------------------------------------- entries in order
+// The buckets' entries come in any order.  k_entries_place moves them to
+// their trace's range; k_entries_sort sorts a trace's, SORT_CHUNK at a time;
+// k_entries_merge puts the chunks of a trace with more together.
+// Entries of one location end up next to each other.  A few entries go straight
+// to the host's memory, with the counts, so that such a call downloads nothing.
+
+struct EntryKey {
+  uint64_t place;  // space, block
+  uint64_t unit;
+};
+__device__ __forceinline__ EntryKey entry_key(const RaceOut& e) {
+  return EntryKey{((uint64_t)e.space << 32) | e.block, e.unit};
+}
+__device__ __forceinline__ bool key_less(const EntryKey& a, const EntryKey& b) {
+  return a.place < b.place || (a.place == b.place && a.unit < b.unit);
+}
+__device__ __forceinline__ void copy_entry(RaceOut* dst, const RaceOut* src) {
 #pragma unroll
-    for (uint32_t u = 0; u < UW; u++)
-      if (((w_live >> u) & 1u) && in_d(kw[u])) keep_or_mark(i * FT + (kw[u] & (FT - 1)));
-    uint32_t skip = UW << lg_w;
-    bool more = w_more;
-    while (more) {
-      uint32_t k[4];
-      const uint32_t live = load_keys(0, i, true, skip, lg_w, k, &more);
+  for (int q = 0; q < 4; q++) ((ulonglong2*)dst)[q] = ((const ulonglong2*)src)[q];
+}
+
+__global__ __launch_bounds__(NT) void k_entries_place(FilterBuffers f) {
+  __shared__ uint32_t s_first[GROUP_MAX_TRACES];
+  __shared__ uint32_t s_scan[NWAVE];
+  const uint32_t n = f.cnt[FC_ENTRIES], tx = threadIdx.x;
+  if (f.ctrl->error_flags) return;
+  const uint32_t per = (f.n_traces + NT - 1) / NT, t0 = min(f.n_traces, tx * per), t1 = min(f.n_traces, t0 + per);
+  uint32_t sum = 0;
+#pragma unroll 4
+  for (uint32_t t = t0; t < t1; t++) {
+    s_first[t] = f.trace_cnt[t];
+    sum += s_first[t];
+  }
+  uint32_t tot;
+  uint32_t base = block_excl_sum(sum, s_scan, &tot);
+  for (uint32_t t = t0; t < t1; t++) {
+    const uint32_t c = s_first[t];
+    s_first[t] = base;
+    if (blockIdx.x == 0) f.trace_first[t] = base;
+    base += c;
+  }
+  __syncthreads();
+  for (uint32_t i = blockIdx.x * NT + tx; i < n; i += gridDim.x * NT) {
+    const uint32_t t = f.entries[i].trace;
+    copy_entry(f.placed + s_first[t] + atomicAdd(&f.trace_fill[t], 1u), f.entries + i);
+  }
+}
+
+// An entry's place in its chunk is the number of entries before it there (of
+// equal ones, those with a smaller index).  A workgroup (trace, y) holds a
+// chunk's keys in LDS and places 16 of its entries, sixteen lanes to an entry
+// (256, a lane each, where the trace has many): sorting 1677 entries in one
+// workgroup's LDS took 68 us, 66 steps with a barrier each; this takes 17.
+__global__ __launch_bounds__(NT) void k_entries_sort(FilterBuffers f) {
+  __shared__ uint64_t s_place[SORT_CHUNK], s_unit[SORT_CHUNK];
+  const uint32_t t = blockIdx.x, tx = threadIdx.x;
+  const uint32_t total = f.cnt[FC_ENTRIES], err = f.ctrl->error_flags;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && tx == 0) {
+    GroupHead h;
+    h.entries = total;
+    h.error_flags = err;
+    h.first_bad = f.ctrl->first_bad;
+    *f.head = h;
+  }
+  if (err) return;
+  const uint32_t n = f.trace_cnt[t], first = f.n_traces > 1 ? f.trace_first[t] : 0u;
+  const RaceOut* src = (f.n_traces > 1 ? f.placed : f.entries) + first;
+  RaceOut* dst = (n <= SORT_CHUNK ? (total <= f.host_cap ? f.host_entries : f.sorted)
+                                  : (f.n_traces > 1 ? f.entries : f.placed)) + first;
+  const uint32_t lanes = n <= 2 * SORT_CHUNK ? 16u : 1u, take = NT / lanes, per_chunk = SORT_CHUNK / take;
+  for (uint32_t item = blockIdx.y;; item += gridDim.y) {
+    const uint32_t c0 = item / per_chunk * SORT_CHUNK, g0 = item % per_chunk * take;
+    if (c0 >= n) break;
+    const uint32_t m = min(SORT_CHUNK, n - c0);
+    if (g0 >= m) continue;
+    __syncthreads();
+    for (uint32_t i0 = 0; i0 < m; i0 += 4 * NT) {
+      EntryKey k[4];
 #pragma unroll
       for (uint32_t u = 0; u < 4; u++)
-        if (((live >> u) & 1u) && in_d(k[u])) keep_or_mark(i * FT + (k[u] & (FT - 1)));
-      skip += 4u << lg_w;
-    }
-  } else {
-    for (uint32_t c0 = 0; c0 < T.ntiles; c0 += CHUNK) {
-      const uint32_t n = min(CHUNK, T.ntiles - c0);
-      if (!one_chunk) load_runs(c0, n);
-      for_runs(c0, n, true, lg_w, [&](uint32_t k, uint32_t idx) {
-        if (in_d(k)) keep_or_mark(idx);
-      });
-    }
-  }
-  __syncthreads();
-
-  // ---- the exact test, on the records (the bitmaps' LDS holds the table
-  //      now)
-  uint32_t n = s_n;
-  uint32_t* const mn = s_map;
-  uint32_t* const mx = s_map + X_SLOTS;
-  uint32_t* const act = s_map + 2 * X_SLOTS;
-  if (n > 0 && n <= CAP) {
-    const GRecords p = global_records(T.rec);
-    const uint32_t shift = block_shift(T.tpb);
-    Rec x[XPT];
-    uint32_t idx[XPT];
-    bool live[XPT];
+        if (i0 + u * NT + tx < m) k[u] = entry_key(src[c0 + i0 + u * NT + tx]);
 #pragma unroll
-    for (int q = 0; q < XPT; q++) {
-      live[q] = tx + q * NTH < n;
-      if (!live[q]) continue;
-      idx[q] = s_list[tx + q * NTH];
-      x[q] = unpack_rec(load_record(p, idx[q]));
-    }
-    uint32_t before = n;
-#pragma unroll 1
-    for (uint32_t round = 0; round < 3; round++) {
-      __syncthreads();
-      for (uint32_t k = 4 * tx; k < X_SLOTS; k += 4 * NTH) {
-        *(uint4*)(mn + k) = make_uint4(~0u, ~0u, ~0u, ~0u);
-        *(uint4*)(mx + k) = make_uint4(0, 0, 0, 0);
-        *(uint4*)(act + k) = make_uint4(0, 0, 0, 0);
-      }
-      if (tx == 0) s_n = 0;
-      __syncthreads();
-      uint32_t se[XPT], sl[XPT];
-#pragma unroll
-      for (int q = 0; q < XPT; q++) {
-        if (!live[q]) continue;
-        const uint32_t blk = block_of(x[q].tid, T.tpb, shift), a = 1u << (x[q].action & 3u);
-        // threads of one block's epoch; blocks of a global word
-        se[q] = filter_exact_hash(x[q].unit, blk, x[q].epoch, 2 + x[q].space, round) & (X_SLOTS - 1);
-        sl[q] = x[q].space ? se[q] : filter_exact_hash(x[q].unit, 0, 0, 1, round) & (X_SLOTS - 1);
-        atomicMin(&mn[se[q]], x[q].tid);
-        atomicMax(&mx[se[q]], x[q].tid);
-        atomicOr(&act[se[q]], a);
-        if (!x[q].space) {
-          atomicMin(&mn[sl[q]], blk);
-          atomicMax(&mx[sl[q]], blk);
-          atomicOr(&act[sl[q]], a);
+      for (uint32_t u = 0; u < 4; u++)
+        if (i0 + u * NT + tx < m) {
+          s_place[i0 + u * NT + tx] = k[u].place;
+          s_unit[i0 + u * NT + tx] = k[u].unit;
         }
-      }
-      __syncthreads();
-#pragma unroll
-      for (int q = 0; q < XPT; q++) {
-        if (!live[q]) continue;
-        auto races = [&](uint32_t s) {
-          const uint32_t c = act[s];
-          return mn[s] != mx[s] && ((c & 2u) || (c & 5u) == 5u);  // a write, or a read and an atomic
-        };
-        live[q] = races(se[q]) || races(sl[q]);
-        const uint64_t m = __ballot(live[q]);
-        if (live[q] && (m & ((1ull << __lane_id()) - 1ull)) == 0) atomicAdd(&s_n, (uint32_t)__popcll(m));
-      }
-      __syncthreads();
-      const uint32_t left = s_n;
-      if (left + (left >> 3) > before) break;  // a round that drops little is the last
-      before = left;
-    }
-#pragma unroll
-    for (int q = 0; q < XPT; q++)
-      if (live[q]) mark(idx[q]);
-  } else {
-    for (uint32_t i = tx; i < min(n, CAP); i += NTH) mark(s_list[i]);
-  }
-}
-
-// ---------------------------------------------- the surviving records
-
-// Survivors per tile, with the marks of its trace's hot buckets.
-__global__ __launch_bounds__(NT) void k_filter_count(FilterBuffers f) {
-  __shared__ uint32_t s_map[FT / 32];
-  __shared__ uint32_t s_sum[NWAVE];
-  const uint32_t tile = blockIdx.x, tx = threadIdx.x;
-  const uint32_t t = f.tile_trace[tile];
-  const FTrace T = f.tr[t];
-  const uint32_t local = tile - T.tile0, B = 1u << T.lgb;
-  const uint64_t start = (uint64_t)local * FT;
-  const uint32_t words = (uint32_t)((min<uint64_t>((uint64_t)FT, T.n - start) + 31) / 32);
-  uint32_t* s = f.survive + T.surv0 + local * (FT / 32);
-  const uint32_t* list = f.trace_hot + (uint64_t)t * f.hot_stride;
-  const uint32_t n_hot = min(list[0], (f.hot_stride - 1) / 2);
-  uint32_t c = 0;
-  if (n_hot) {
-    for (uint32_t k = tx; k < words; k += NT) s_map[k] = s[k];
-    __syncthreads();
-    const uint32_t smask = (1u << T.sbits) - 1;
-    const uint32_t* keys = f.keys + (T.off + start);
-    // 16 lanes per bucket, more where there are few; each group takes HU
-    // buckets at a time, their loads in flight together
-    constexpr uint32_t HU = 4;
-    const uint32_t lg = n_hot >= 16 ? 4u : 8u - (n_hot > 1 ? 32u - (uint32_t)__builtin_clz(n_hot - 1) : 0u);
-    const uint32_t L = 1u << lg, groups = NT >> lg;
-    for (uint32_t h0 = tx >> lg; h0 < n_hot; h0 += HU * groups) {
-      uint32_t at[HU], reads[HU], end[HU], flags[HU], k[HU];
-      const uint32_t* A[HU];
-#pragma unroll
-      for (uint32_t u = 0; u < HU; u++) {
-        const uint32_t h = h0 + u * groups;
-        at[u] = end[u] = 0;
-        if (h < n_hot) {
-          const uint32_t w = list[2 * h + 1];
-          const uint32_t* row = f.rows + T.row0 + (uint64_t)local * (B + 1) + (w >> 2);
-          const uint32_t pair = row[0];
-          flags[u] = w & 3u;
-          A[u] = f.hot_maps + (uint64_t)list[2 * h + 2] * A_STRIDE;
-          at[u] = (pair & 0xFFFFu) + (tx & (L - 1));
-          reads[u] = pair >> 16;
-          end[u] = row[1] & 0xFFFFu;
-        }
-      }
-      bool more = true;
-      while (more) {
-        more = false;
-#pragma unroll
-        for (uint32_t u = 0; u < HU; u++)
-          if (at[u] < end[u]) k[u] = keys[at[u]];
-#pragma unroll
-        for (uint32_t u = 0; u < HU; u++)
-          if (at[u] < end[u]) {
-            const uint32_t j = k[u] & (FT - 1), sl = (k[u] >> FT_BITS) & smask;
-            if (at[u] < reads[u] || (flags[u] & HOT_WRITES) || ((A[u][sl >> 5] >> (sl & 31u)) & 1u))
-              atomicOr(&s_map[j >> 5], 1u << (j & 31u));
-            at[u] += L;
-            more |= at[u] < end[u];
-          }
-      }
     }
     __syncthreads();
-    for (uint32_t k = tx; k < words; k += NT) {
-      s[k] = s_map[k];
-      c += (uint32_t)__popc(s_map[k]);
-    }
-  } else {
-    for (uint32_t k = tx; k < words; k += NT) c += (uint32_t)__popc(s[k]);
-  }
-  c = wave_reduce(c, 0u, [](uint32_t a, uint32_t d) { return a + d; });
-  if ((tx & 63u) == 0) s_sum[tx >> 6] = c;
-  __syncthreads();
-  if (tx == 0) f.tile_cnt[tile] = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
-}
-
-// One workgroup: the tiles' exclusive prefix, in place, and each trace's
-// first survivor (the call's total at the end).
-__global__ __launch_bounds__(FNT) void k_filter_scan(FilterBuffers f) {
-  __shared__ uint32_t s_scan[FNW];
-  const uint32_t per = (f.n_tiles + FNT - 1) / FNT, t0 = min(f.n_tiles, threadIdx.x * per), t1 = min(f.n_tiles, t0 + per);
-  uint32_t sum = 0;
+    const uint32_t e = g0 + tx / lanes, q = tx & (lanes - 1);
+    uint32_t rank = 0;
+    if (e < m) {
+      const EntryKey k{s_place[e], s_unit[e]};
 #pragma unroll 8
-  for (uint32_t t = t0; t < t1; t++) sum += f.tile_cnt[t];
-  uint32_t tot;
-  uint32_t run = block_excl_sum_n<FNW>(sum, s_scan, &tot);
-  for (uint32_t t = t0; t < t1; t++) {
-    const uint32_t c = f.tile_cnt[t];
-    f.tile_cnt[t] = run;
-    run += c;
-  }
-  __syncthreads();  // (one workgroup: its global stores are visible to it after a barrier)
-  for (uint32_t i = threadIdx.x; i <= f.n_traces; i += FNT) {
-    const uint32_t tile = i < f.n_traces ? f.tr[i].tile0 : f.n_tiles;
-    f.trace_off[i] = tile < f.n_tiles ? f.tile_cnt[tile] : tot;
+      for (uint32_t j = q; j < m; j += lanes) {
+        const EntryKey o{s_place[j], s_unit[j]};
+        rank += key_less(o, k) || (j < e && !key_less(k, o)) ? 1u : 0u;
+      }
+    }
+    if (lanes == 16) {
+      rank += __shfl_xor(rank, 1);
+      rank += __shfl_xor(rank, 2);
+      rank += __shfl_xor(rank, 4);
+      rank += __shfl_xor(rank, 8);
+      if (e < m && q < 4) ((ulonglong2*)(dst + c0 + rank))[q] = ((const ulonglong2*)(src + c0 + e))[q];
+    } else if (e < m) {
+      copy_entry(dst + c0 + rank, src + c0 + e);
+    }
   }
 }
 
-// The marked records of a tile, in record order, to the survivors' array
-// (unless it cannot hold them all; the host then takes the full path).
-__global__ __launch_bounds__(NT) void k_filter_gather(FilterBuffers f) {
-  __shared__ uint16_t s_idx[FT];
-  __shared__ uint32_t s_scan[NWAVE];
-  const uint32_t tile = blockIdx.x, tx = threadIdx.x;
-  if (f.trace_off[f.n_traces] > f.out_cap) return;
-  const FTrace T = f.tr[f.tile_trace[tile]];
-  const uint32_t local = tile - T.tile0;
-  const uint64_t start = (uint64_t)local * FT;
-  const uint32_t words = (uint32_t)((min<uint64_t>((uint64_t)FT, T.n - start) + 31) / 32);
-  const uint32_t* s = f.survive + T.surv0 + local * (FT / 32);
-  static_assert(FT / 32 == 2 * NT, "two bitmap words per thread");
-  uint32_t w0 = 2 * tx < words ? s[2 * tx] : 0u, w1 = 2 * tx + 1 < words ? s[2 * tx + 1] : 0u;
-  uint32_t tot;
-  uint32_t at = block_excl_sum((uint32_t)(__popc(w0) + __popc(w1)), s_scan, &tot);
-  if (!tot) return;
-  for (; w0; w0 &= w0 - 1) s_idx[at++] = (uint16_t)(64 * tx + (uint32_t)__builtin_ctz(w0));
-  for (; w1; w1 &= w1 - 1) s_idx[at++] = (uint16_t)(64 * tx + 32 + (uint32_t)__builtin_ctz(w1));
-  __syncthreads();
-  const GRecords p = global_records((const char*)T.rec + start * 16);
-  const uint32_t first = f.tile_cnt[tile];
-  for (uint32_t i = tx; i < tot; i += NT) {
-    const uint32_t j = s_idx[i];
-    ((ulonglong2*)f.out)[first + i] = load_record(p, j);
-    if (f.side) f.out_side[first + i] = f.side[T.off + start + j];
+// An entry's place among its trace's: its index in its chunk and, by binary
+// search, the entries of the other chunks before it (equal ones of earlier
+// chunks come first).
+__global__ __launch_bounds__(NT) void k_entries_merge(FilterBuffers f) {
+  if (f.ctrl->error_flags || f.cnt[FC_MOST] <= SORT_CHUNK) return;
+  const uint32_t total = f.cnt[FC_ENTRIES];
+  const RaceOut* const all = f.n_traces > 1 ? f.entries : f.placed;
+  for (uint32_t i = blockIdx.x * NT + threadIdx.x; i < total; i += gridDim.x * NT) {
+    uint32_t t = 0;
+    if (f.n_traces > 1) {  // the trace whose range holds i
+      uint32_t hi = f.n_traces;
+      while (hi - t > 1) {
+        const uint32_t mid = (t + hi) / 2;
+        if (f.trace_first[mid] <= i) t = mid;
+        else hi = mid;
+      }
+    }
+    const uint32_t n = f.trace_cnt[t], first = f.n_traces > 1 ? f.trace_first[t] : 0u;
+    if (n <= SORT_CHUNK) continue;
+    const RaceOut* e = all + first;
+    const uint32_t me = i - first, own = me / SORT_CHUNK;
+    const EntryKey k = entry_key(e[me]);
+    uint32_t at = me % SORT_CHUNK;
+    for (uint32_t c0 = 0; c0 < n; c0 += SORT_CHUNK) {
+      const uint32_t c = c0 / SORT_CHUNK;
+      if (c == own) continue;
+      uint32_t lo = 0, hi = min(SORT_CHUNK, n - c0);
+      while (lo < hi) {
+        const uint32_t mid = (lo + hi) / 2;
+        const EntryKey m = entry_key(e[c0 + mid]);
+        if (c < own ? !key_less(k, m) : key_less(m, k)) lo = mid + 1;
+        else hi = mid;
+      }
+      at += lo;
+    }
+    copy_entry((total <= f.host_cap ? f.host_entries : f.sorted) + first + at, e + me);
   }
 }
 
@@ -647,27 +954,37 @@ hipError_t launch_filter_part(const FilterBuffers& f, hipStream_t s) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // (the instantiation's counters hold every bucket of the call's traces)
-  static_assert(FILTER_MAX_LGB == 12, "the larger instantiation");
-  hipLaunchKernelGGL(f.max_lgb > 11 ? k_filter_part<12> : k_filter_part<11>, dim3(tile_grid(f.n_tiles, 0, 0)), dim3(FNT), 0, s, f);
+  static_assert(FILTER_MAX_LGB == 13, "the larger instantiation");
+  hipLaunchKernelGGL(f.max_lgb > 11 ? k_filter_part<13> : k_filter_part<11>, dim3(tile_grid(f.n_tiles, 0, 0)), dim3(FNT), 0,
+                     s, f);
   return hipGetLastError();
 }
-hipError_t launch_filter_test(const FilterBuffers& f, hipStream_t s) {
-  hipLaunchKernelGGL(k_filter_plan, dim3(cdiv(f.n_buckets, NT)), dim3(NT), 0, s, f);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (f.large)
-    hipLaunchKernelGGL((k_filter_test<1024, 18, 4096, 1024>), dim3(tile_grid(f.n_buckets, 0, 0)), dim3(1024), 0, s, f);
-  else
-    hipLaunchKernelGGL((k_filter_test<512, 17, 2048, 512>), dim3(tile_grid(f.n_buckets, 0, 0)), dim3(512), 0, s, f);
+hipError_t launch_filter_count(const FilterBuffers& f, hipStream_t s) {
+  hipError_t e;
+  if (f.extra_max) {
+    hipLaunchKernelGGL(k_filter_plan, dim3(cdiv(f.n_buckets, NT)), dim3(NT), 0, s, f);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  const dim3 grid(f.extra_max + tile_grid(f.n_buckets, 0, 0));
+  const bool warp = f.side != nullptr;
+  hipLaunchKernelGGL((warp ? k_filter_count<false, true, 860, 1408> : k_filter_count<false, false, 940, 1408>), grid, dim3(FNT),
+                     0, s, f);
+  if ((e = hipGetLastError()) != hipSuccess || !f.late_max) return e;
+  hipLaunchKernelGGL((warp ? k_filter_count<true, true, 860, 1408> : k_filter_count<true, false, 940, 1408>), dim3(f.late_max),
+                     dim3(FNT), 0, s, f);
   return hipGetLastError();
 }
 hipError_t launch_filter_out(const FilterBuffers& f, hipStream_t s) {
-  hipLaunchKernelGGL(k_filter_count, dim3(f.n_tiles), dim3(NT), 0, s, f);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_filter_scan, dim3(1), dim3(FNT), 0, s, f);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_filter_gather, dim3(f.n_tiles), dim3(NT), 0, s, f);
+  hipError_t e;
+  if (f.n_traces > 1) {
+    hipLaunchKernelGGL(k_entries_place, dim3(std::min(1024u, cdiv(f.entries_cap, NT))), dim3(NT), 0, s, f);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  const uint32_t chunks = cdiv(f.entries_cap, SORT_CHUNK);
+  hipLaunchKernelGGL(k_entries_sort, dim3(f.n_traces, f.n_traces <= 64 ? std::min(128u, cdiv(f.entries_cap, 16)) : 1u), dim3(NT),
+                     0, s, f);
+  if ((e = hipGetLastError()) != hipSuccess || chunks <= 1) return e;
+  hipLaunchKernelGGL(k_entries_merge, dim3(std::min(2048u, cdiv(f.entries_cap, NT))), dim3(NT), 0, s, f);
   return hipGetLastError();
 }
 

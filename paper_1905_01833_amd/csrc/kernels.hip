@@ -1086,10 +1086,6 @@ __device__ __forceinline__ void write_entry(RaceOut* dst, uint32_t trace, const 
 // dedicated buffer (sized by the host from that scan's counts).
 __device__ __forceinline__ RaceOut* stage_of(const Buffers& b, uint32_t tile, const TraceDesc& T,
                                              const TraceLayout& L, uint64_t start, uint32_t n_in, uint32_t* cap) {
-  if (b.stage_half) {  // a complete location holds two records of the tile, so this never overflows
-    *cap = n_in / 2;
-    return b.stage_half + (T.off + start) / 2;
-  }
   if (b.stage_ref) {
     const uint64_t ref = b.stage_ref[tile];
     if (ref & STAGE_CAP_MASK) {

@@ -18,7 +18,9 @@ constexpr int GROUP = 256;         // tiles per group of the output prefix
 constexpr uint32_t MAX_HGROUP_SHIFT = 12; // histogram groups hold at most 4096 tiles
 
 // kernel-side error flags beyond the per-trace layout errors of keys.h
-enum : uint32_t { ERR_STAGE_OVERFLOW = 16, ERR_NEEDS_WIDE = 32 };
+// (ERR_GROUP_FULL: the grouped race count ran out of room; the call takes the
+// sorting path)
+enum : uint32_t { ERR_STAGE_OVERFLOW = 16, ERR_NEEDS_WIDE = 32, ERR_GROUP_FULL = 64 };
 
 struct TraceDesc {   // one trace of a call (host-filled)
   uint64_t off;      // first record
@@ -97,7 +99,6 @@ struct Buffers {            // device pointers of one call
   uint32_t* cross_flag;     // [tile]
   uint32_t* group_sum;      // [group]
   RaceOut* stage;           // dedicated staging of the tiles stage_ref names (see STAGE_CAP_BITS)
-  RaceOut* stage_half;      // or staging for every tile, an entry per two records (record r's at r / 2)
   const uint64_t* stage_ref;// [tile], or nullptr: every tile stages in its slice of the idle key buffer
   Ctrl* ctrl;
   RaceOut* out;
@@ -126,28 +127,44 @@ struct Buffers {            // device pointers of one call
   uint32_t digit_bits;      // digit width of the radix passes after pass 0: RADIX_BITS or RADIX_WIDE_BITS
 };
 
-struct FilterBuffers {      // device pointers of a call's conflict filter (filter.h, filter.hip)
-  const FTrace* tr;
+// Counters of a grouped call (FilterBuffers::cnt): entries found, further
+// workgroups of hot buckets, entries of the trace with most (where they exceed
+// SORT_CHUNK), buckets whose candidates are thinned out.
+enum : uint32_t { FC_ENTRIES = 0, FC_EXTRA = 1, FC_MOST = 2, FC_LATE = 3, FC_COUNT = 4 };
+constexpr uint32_t SORT_CHUNK = 2048;         // entries sorted in one workgroup's LDS
+constexpr uint32_t GROUP_MAX_TRACES = 8192;   // traces of a grouped call
+
+struct GroupHead {          // what the host needs of a grouped call besides its entries
+  uint32_t entries, error_flags;
+  uint64_t first_bad;
+};
+struct FilterBuffers {      // device pointers of a call's grouped race count (filter.h, filter.hip)
+  FTrace* tr;
+  const FTrace* tr_src;     // where k_filter_begin finds them: pinned host memory, or tr
   uint32_t n_traces, n_tiles, n_buckets;
   uint32_t* tile_trace;     // [tile] its trace
   uint32_t* bucket_trace;   // [bucket] its trace
-  uint32_t* keys;           // [record] a tile's keys by bucket: slot << FT_BITS | place in the tile
+  uint32_t* keys;           // [record] a tile's keys by bucket (filter.h)
   uint32_t* rows;           // [tile][buckets + 1] first write | first read << 16 of each bucket in the tile
-  uint32_t* hot;            // [bucket] flags of hot words (filter.hip), and the place of the bucket's bitmap
-  uint32_t* n_hot;          // buckets with a stored bitmap
-  uint32_t* trace_hot;      // [trace][hot_stride] its hot buckets
-  uint32_t hot_stride;      // words of a trace's list
-  uint32_t* hot_maps;       // their bitmaps
-  uint32_t max_hot;         // room for this many
+  uint32_t* hot;            // [bucket] reads of hot words as the tiles counted them, then the bucket's parts
+  uint2* extra;             // the parts of split buckets: (bucket, part)
+  uint32_t extra_max;       // room for them (a multiple of 8; 0: no bucket is split)
+  uint32_t hot_part;        // hot reads per part
+  uint2* late;              // buckets to be thinned out: (bucket, part)
+  uint32_t late_max;        // room for them (0: the call goes without)
   uint32_t max_lgb;         // the largest FTrace::lgb of the call
-  uint32_t large;           // 1: some trace's buckets hold more than FILTER_BUCKET records on average
-  uint32_t* survive;        // bitmap of the records that may race (FTrace::surv0)
-  uint32_t* tile_cnt;       // [tile] survivors, then the survivors before the tile
-  uint32_t* trace_off;      // [trace + 1] survivors before the trace
   const uint32_t* side;     // warp-aware check: one side word per record, else nullptr
-  void* out;                // the surviving records (and their side words)
-  uint32_t* out_side;
-  uint32_t out_cap;         // records `out` holds
+  uint32_t* cnt;            // [FC_COUNT]
+  uint32_t* trace_cnt;      // [trace] entries
+  uint32_t* trace_fill;     // [trace] entries placed
+  uint32_t* trace_first;    // [trace] first entry of its range
+  RaceOut* entries;         // as the buckets found them
+  RaceOut* placed;          // by trace
+  RaceOut* sorted;          // in order
+  uint32_t entries_cap;     // entries each of the three holds
+  GroupHead* head;          // pinned host memory
+  RaceOut* host_entries;    // pinned host memory: the entries in order, if no more than
+  uint32_t host_cap;        // this many
   Ctrl* ctrl;
 };
 
@@ -161,7 +178,7 @@ struct BarrierCount {
 
 // Kernel stages, in launch order.
 enum Stage { ST_INIT = 0, ST_STATS, ST_LAYOUT, ST_KEYGEN, ST_UPSWEEP, ST_SORT, ST_SCAN, ST_CROSS, ST_OUT,
-             ST_SORT_SMALL, ST_FILTER_PART, ST_FILTER_TEST, ST_FILTER_OUT, ST_COUNT };
+             ST_SORT_SMALL, ST_FILTER_PART, ST_FILTER_COUNT, ST_FILTER_OUT, ST_COUNT };
 
 hipError_t launch_init(const Buffers& b, hipStream_t s);
 hipError_t launch_stats(const Buffers& b, hipStream_t s);
@@ -174,10 +191,10 @@ hipError_t launch_scan_tiles(const Buffers& b, uint32_t passes_done, hipStream_t
 hipError_t launch_scan_cross(const Buffers& b, uint32_t passes_done, hipStream_t s);
 hipError_t launch_scan_out(const Buffers& b, uint32_t passes_done, hipStream_t s);
 hipError_t launch_reset_errors(const Buffers& b, uint32_t mask, hipStream_t s);
-// The conflict filter, in this order: keys by bucket and record checks; the
-// survivor bitmap; the surviving records and each trace's number of them.
+// The grouped race count, in this order: keys by bucket and record checks; the
+// pairs; the entries in order.
 hipError_t launch_filter_part(const FilterBuffers& f, hipStream_t s);
-hipError_t launch_filter_test(const FilterBuffers& f, hipStream_t s);
+hipError_t launch_filter_count(const FilterBuffers& f, hipStream_t s);
 hipError_t launch_filter_out(const FilterBuffers& f, hipStream_t s);
 // Redundant-barrier check over the sorted keys of a finished call: clears
 // `table` (n_counts entries) and counts every trace's barrier instances.

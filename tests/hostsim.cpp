@@ -379,64 +379,104 @@ extern "C" int hs_digit_plan(uint64_t seed, int trials) {
   return bad;
 }
 
-// The conflict filter (filter.h) as its kernels decide: keep[i] is set for
-// every record that survives.  x_slots: slots of the exact table; rounds: how
-// often it is tried (0: the bitmaps alone, as for a list that overflows).
-extern "C" void hs_filter(const rec* recs, const uint64_t* off, uint32_t n_traces, const uint32_t* tpb, uint32_t x_slots,
-                          int rounds, uint8_t* keep) {
+// The grouped race count (filter.h) as its kernels take it: buckets of the
+// records' groups, bitmaps A, P and D over their slots, the pairs of the
+// writes and atomics in D among themselves and with the reads in A.  side:
+// one side word per record (the warp-aware check), or null.  The writes are
+// seen in record order, or backwards.  Entries of one location are added up.
+extern "C" int64_t hs_group(const rec* recs, const uint64_t* off, uint32_t n_traces, const uint32_t* tpb,
+                            const uint32_t* side, int backwards, race* out, uint64_t cap, uint64_t* n_tested) {
+  std::vector<race> all;
+  *n_tested = 0;
   for (uint32_t t = 0; t < n_traces; t++) {
     const uint64_t n = off[t + 1] - off[t];
     const rec* r = recs + off[t];
-    uint8_t* kp = keep + off[t];
-    const uint32_t lgb = filter_lgb(n), sb = std::min(filter_sbits(n, lgb), FILTER_SLOT_BITS - 1), smask = (1u << sb) - 1;
+    const uint32_t lgb = filter_lgb(n), smask = (1u << filter_sbits(n, lgb)) - 1;
     std::vector<std::vector<uint32_t>> bucket((size_t)1 << lgb);
     std::vector<uint32_t> slot(n);
-    for (uint64_t i = 0; i < n; i++) {
+    for (uint64_t k = 0; k < n; k++) {
+      const uint64_t i = backwards ? n - 1 - k : k;
       const uint32_t h = filter_group(r[i].unit, r[i].tid / tpb[t], r[i].epoch, r[i].space);
       bucket[filter_bucket(h, lgb)].push_back((uint32_t)i);
-      slot[i] = h & ((1u << FILTER_SLOT_BITS) - 1) & smask;
-      kp[i] = 0;
+      slot[i] = filter_slot(h) & smask;
     }
     for (auto& b : bucket) {
-      std::vector<uint8_t> A((size_t)smask + 1), D((size_t)smask / 2 + 1);
+      std::vector<uint8_t> A((size_t)smask + 1), P((size_t)smask / 4 + 1), D((size_t)smask / 2 + 1);
+      std::vector<uint32_t> writes, reads;
       for (uint32_t i : b)
         if (r[i].action) {
-          if (A[slot[i]]) D[slot[i] >> 1] = 1;
+          if (r[i].action == 1) P[slot[i] >> 2] = 1;
+          if (A[slot[i]] && (r[i].action == 1 || P[slot[i] >> 2])) D[slot[i] >> 1] = 1;
           A[slot[i]] = 1;
         }
       for (uint32_t i : b)
-        if (!r[i].action && A[slot[i]]) D[slot[i] >> 1] = kp[i] = 1;
+        if (!r[i].action && A[slot[i]]) {
+          D[slot[i] >> 1] = 1;
+          reads.push_back(i);
+        }
       for (uint32_t i : b)
-        if (r[i].action && D[slot[i] >> 1]) kp[i] = 1;
-      for (int round = 0; round < rounds; round++) {
-        std::vector<uint32_t> mn(x_slots, ~0u), mx(x_slots, 0u), act(x_slots, 0u);
-        auto slots = [&](uint32_t i, uint32_t* se, uint32_t* sl) {
-          const uint32_t blk = r[i].tid / tpb[t];
-          *se = filter_exact_hash(r[i].unit, blk, r[i].epoch, 2u + r[i].space, (uint32_t)round) & (x_slots - 1);
-          *sl = r[i].space ? *se : filter_exact_hash(r[i].unit, 0, 0, 1, (uint32_t)round) & (x_slots - 1);
-        };
-        auto put = [&](uint32_t s, uint32_t id, uint32_t a) {
-          mn[s] = std::min(mn[s], id);
-          mx[s] = std::max(mx[s], id);
-          act[s] |= a;
-        };
-        for (uint32_t i : b)
-          if (kp[i]) {
-            uint32_t se, sl;
-            slots(i, &se, &sl);
-            put(se, r[i].tid, 1u << r[i].action);
-            if (!r[i].space) put(sl, r[i].tid / tpb[t], 1u << r[i].action);
-          }
-        for (uint32_t i : b)
-          if (kp[i]) {
-            uint32_t se, sl;
-            slots(i, &se, &sl);
-            auto races = [&](uint32_t s) { return mn[s] != mx[s] && ((act[s] & 2u) || (act[s] & 5u) == 5u); };
-            kp[i] = races(se) || races(sl);
-          }
+        if (r[i].action && D[slot[i] >> 1]) writes.push_back(i);
+      *n_tested += writes.size() + reads.size();
+      std::vector<race> found(writes.size());
+      std::vector<size_t> lead(writes.size());
+      auto at = [&](uint32_t i) { return frec(r[i].unit, r[i].tid, r[i].epoch, r[i].action, r[i].space); };
+      auto pair = [&](uint32_t i, uint32_t j, race& e) {
+        const FRec x = at(i), y = at(j);
+        const uint32_t bx = x.tid / tpb[t], by = y.tid / tpb[t];
+        if (!pair_races(x, bx, y, by, side != nullptr, tpb[t], side ? side[off[t] + i] : 0, side ? side[off[t] + j] : 0)) return;
+        const uint32_t lo = std::min(frec_action(x), frec_action(y)), hi = std::max(frec_action(x), frec_action(y));
+        if (lo == 0) (hi == 1 ? e.rw : e.ar)++;
+        else (hi == 1 ? e.ww : e.aw)++;
+        if (bx != by) e.xb++;
+      };
+      auto same = [&](uint32_t i, uint32_t j) {
+        return same_location(at(i), r[i].tid / tpb[t], at(j), r[j].tid / tpb[t]);
+      };
+      for (size_t i = 0; i < writes.size(); i++) {
+        lead[i] = i;
+        std::memset(&found[i], 0, sizeof(race));
+        for (size_t j = i; j-- > 0;)
+          if (same(writes[i], writes[j])) lead[i] = j;
+        for (size_t j = 0; j < i; j++)
+          if (same(writes[i], writes[j])) pair(writes[i], writes[j], found[lead[i]]);
+      }
+      for (uint32_t i : reads)
+        for (size_t j = 0; j < writes.size(); j++)
+          if (same(i, writes[j])) pair(i, writes[j], found[lead[j]]);
+      for (size_t i = 0; i < writes.size(); i++) {
+        race e = found[i];
+        if (e.ww + e.rw + e.aw + e.ar == 0) continue;
+        const rec& x = r[writes[i]];
+        e.trace = t;
+        e.space = x.space;
+        e.block = x.space ? x.tid / tpb[t] : 0xFFFFFFFFu;
+        e.unit = x.unit;
+        all.push_back(e);
       }
     }
   }
+  std::sort(all.begin(), all.end(), [](const race& a, const race& b) {
+    if (a.trace != b.trace) return a.trace < b.trace;
+    if (a.space != b.space) return a.space < b.space;
+    if (a.block != b.block) return a.block < b.block;
+    return a.unit < b.unit;
+  });
+  uint64_t m = 0;
+  for (const race& e : all) {
+    if (m && out[m - 1].trace == e.trace && out[m - 1].space == e.space && out[m - 1].block == e.block &&
+        out[m - 1].unit == e.unit) {
+      race& y = out[m - 1];
+      y.ww += e.ww; y.rw += e.rw; y.aw += e.aw; y.ar += e.ar; y.xb += e.xb;
+    } else {
+      if (m == cap) return -1;
+      out[m++] = e;
+    }
+  }
+  for (uint64_t k = 0; k < m; k++) {
+    race& e = out[k];
+    e.kinds = (uint8_t)((e.ww ? 1 : 0) | (e.rw ? 2 : 0) | (e.aw ? 4 : 0) | (e.ar ? 8 : 0) | (e.xb ? 16 : 0));
+  }
+  return (int64_t)m;
 }
 
 // Records of the fullest of 2^lgb filter buckets (threads of one block).

@@ -1,5 +1,5 @@
-"""The conflict filter's decisions on the CPU (a model built on the product's
-own hashes): the races of the records it keeps are the races of all records."""
+"""The grouped race count on the CPU (a model built on the product's own
+hashes and pair test): its entries are the oracle's, byte for byte."""
 import ctypes
 
 import numpy as np
@@ -11,40 +11,39 @@ from test_host import _hostsim
 from tracegen import ATOMIC, READ, RECORD_DTYPE, WRITE
 
 
-def keep_of(recs, off, tpb, x_slots=2048, rounds=3):
+def same_races(recs, off, tpb, side=None):
+    """Compares with the oracle; returns its entries and the share of the
+    records the model had to test one by one."""
     lib = _hostsim()
-    lib.hs_filter.restype = None
-    lib.hs_filter.argtypes = [ctypes.c_void_p] * 3 + [ctypes.c_void_p, ctypes.c_uint32, ctypes.c_int, ctypes.c_void_p]
-    lib.hs_filter.argtypes[2] = ctypes.c_uint32
-    keep = np.zeros(len(recs), dtype=np.uint8)
-    lib.hs_filter(recs.ctypes.data, off.ctypes.data, len(off) - 1, tpb.ctypes.data, x_slots, rounds, keep.ctypes.data)
-    return keep.astype(bool)
-
-
-def same_races(recs, off, tpb, **kw):
+    lib.hs_group.restype = ctypes.c_int64
+    lib.hs_group.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_uint32, ctypes.c_void_p, ctypes.c_void_p,
+                             ctypes.c_int, ctypes.c_void_p, ctypes.c_uint64, ctypes.POINTER(ctypes.c_uint64)]
     recs = np.ascontiguousarray(recs)
     off = np.asarray(off, dtype=np.uint64)
     tpb = np.ascontiguousarray(np.broadcast_to(np.asarray(tpb, dtype=np.uint32), len(off) - 1))
-    keep = keep_of(recs, off, tpb, **kw)
-    left = np.concatenate([[0], np.cumsum(keep)])[off.astype(np.int64)].astype(np.uint64)
-    want, wsum = oracle.closed_form(recs, off, tpb)
-    got, gsum = oracle.closed_form(np.ascontiguousarray(recs[keep]), left, tpb)
-    assert got.tobytes() == want.tobytes()
-    assert gsum["n_pairs"].tobytes() == wsum["n_pairs"].tobytes()
-    return keep, want
+    want, _ = oracle.closed_form(recs, off, tpb) if side is None else oracle.closed_form_warp(recs, side, off, tpb)
+    tested = ctypes.c_uint64(0)
+    for backwards in (0, 1):
+        out = np.zeros(len(recs) + 1, dtype=want.dtype)
+        n = lib.hs_group(recs.ctypes.data, off.ctypes.data, len(off) - 1, tpb.ctypes.data,
+                         None if side is None else side.ctypes.data, backwards, out.ctypes.data, len(out),
+                         ctypes.byref(tested))
+        assert n == len(want) and out[:n].tobytes() == want.tobytes()
+    return want, tested.value / max(1, len(recs))
 
 
-@pytest.mark.parametrize("rounds", [0, 1, 3])
-@pytest.mark.parametrize("x_slots", [8, 2048])
-def test_tiny_traces(rounds, x_slots):
+@pytest.mark.parametrize("warp", [False, True])
+def test_tiny_traces(warp):
     """Dense collisions in few words, all action mixes and block sizes."""
-    rng = np.random.default_rng(rounds * 100 + x_slots)
-    for _ in range(60):
-        tpb = int(rng.integers(1, 9))
+    rng = np.random.default_rng(5 + warp)
+    for _ in range(120):
+        tpb = int(rng.integers(1, 90))
         parts = [tracegen.random_small(rng, int(rng.integers(0, 60)), units=int(rng.integers(1, 9)), tpb=tpb)
                  for _ in range(5)]
         off = np.concatenate([[0], np.cumsum([len(p) for p in parts])])
-        same_races(np.concatenate(parts), off, tpb, rounds=rounds, x_slots=x_slots)
+        n = int(off[-1])
+        side = (rng.integers(0, 3, n) | np.where(rng.random(n) < 0.3, 1 << 31, 0)).astype(np.uint32) if warp else None
+        same_races(np.concatenate(parts), off, tpb, side)
 
 
 @pytest.mark.parametrize("tpb", [1, 32, 96, 256, 1 << 30])
@@ -59,20 +58,22 @@ def test_several_buckets(tpb, wide):
     r["action"] = rng.choice([READ, READ, READ, WRITE, ATOMIC], n)
     r["space"] = rng.integers(0, 2, n)
     r["unit"] = rng.integers(0, 50000, n).astype(np.uint64) * np.uint64(2 ** 48 - 59 if wide else 1)
-    keep, want = same_races(r, [0, n], tpb)
-    assert len(want) and keep.any()
+    want, _ = same_races(r, [0, n], tpb)
+    assert len(want)
 
 
-def test_little_but_racing_locations_survives():
+def test_few_records_are_tested_one_by_one():
     """Of a generated trace, without and with injected races: the records of
-    the racing locations (a hot word's readers among them) and chance hits."""
+    the racing locations (a hot word's readers among them) and chance hits, a
+    sixteenth of the records at most (an eighth of the slots hold a write,
+    less than a quarter of the records write)."""
     for rate in (0.0, 1e-3):
         recs, _ = tracegen.c1(n_blocks=16, inject_rate=rate)
-        keep, want = same_races(recs, [0, len(recs)], 256)
+        want, tested = same_races(recs, [0, len(recs)], 256)
         words = {(int(e["space"]), int(e["block"]), int(e["unit"])) for e in want}
         block = np.where(recs["space"] == 1, recs["tid"] // 256, 0xFFFFFFFF)
         racing = sum((int(s), int(b), int(u)) in words for s, b, u in zip(recs["space"], block, recs["unit"]))
-        assert keep.sum() <= racing + 0.002 * len(recs), (keep.sum(), racing)
+        assert tested <= racing / len(recs) + 1 / 16, (tested, racing)
 
 
 @pytest.mark.parametrize("step", [1, 2, 32, 1024, 4096, 1 << 20, 1 << 32])

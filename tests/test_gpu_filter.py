@@ -1,6 +1,6 @@
-"""The conflict filter (calls of many records check only the records that may
-race): entries and summaries equal the oracle's, byte for byte, for every form
-of trace its hashes, tiles, buckets and fallbacks can meet."""
+"""The grouped race count: entries and summaries equal the oracle's, byte for
+byte, for every form of trace its hashes, tiles, buckets, rounds and fallbacks
+can meet."""
 import numpy as np
 import pytest
 
@@ -12,8 +12,9 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
-BATCH = 1 << 21  # a batch of short traces is filtered from here on
-SINGLE = 1 << 23  # any call is
+BATCH = 1 << 21
+SINGLE = 1 << 23
+GROUPED = 300
 
 
 @pytest.fixture()
@@ -30,7 +31,7 @@ def device(a):
 
 
 def check(ctx, recs, off, tpb, name):
-    print(f"[gpu] filter, {name}: {len(recs)} records, {len(off) - 1} traces", flush=True)
+    print(f"[gpu] grouped count, {name}: {len(recs)} records, {len(off) - 1} traces", flush=True)
     off = np.asarray(off, dtype=np.uint64)
     tpb = np.broadcast_to(np.asarray(tpb, dtype=np.uint32), len(off) - 1)
     want, wsum = oracle.closed_form_par(recs, off, np.ascontiguousarray(tpb))
@@ -82,8 +83,8 @@ def test_tile_edges_and_empty_traces(ctx, edge):
 @pytest.mark.parametrize("form", ["reads", "atomics", "private writes", "all race", "one word", "wide units", "far units",
                                   "half race"])
 def test_contents(ctx, form):
-    """Nothing to keep, everything to keep (the full path follows), and keys of
-    more than 64 bits."""
+    """No racing record, only racing records (the sorting path follows), and
+    keys of more than 64 bits."""
     rng = np.random.default_rng(sum(form.encode()))
     sizes = [BATCH // 8] * 9
     n = sum(sizes)
@@ -114,8 +115,8 @@ def test_contents(ctx, form):
 
 @pytest.mark.parametrize("hot", ["read", "read and one write", "written", "atomic", "many"])
 def test_hot_words(ctx, hot):
-    """A word with a tenth of a long trace's records: stored bitmaps, buckets
-    that survive whole, list overflows."""
+    """A word with a tenth of a long trace's records: buckets in several parts,
+    more reads and writes than the lists hold."""
     rng = np.random.default_rng(len(hot))
     n = SINGLE + 12345
     recs = records(n, rng, blocks=512, p_write=0.02, p_shared=0.3)
@@ -157,6 +158,55 @@ def test_generated_batch_and_shuffle(ctx):
     assert check(ctx, recs, off, tpb, "shuffled").tobytes() == want.tobytes()
 
 
+@pytest.mark.parametrize("sizes", [[1], [2, 0, 1], [17], [GROUPED], [GROUPED] * 301, [1] * 64 + [GROUPED] + [3] * 4000, [40000, 0, 17]])
+def test_short_calls(ctx, sizes):
+    """The smallest calls that count by group, of one trace and of many."""
+    rng = np.random.default_rng(len(sizes))
+    for p_write in (0.0, 0.3):
+        recs = records(sum(sizes), rng, blocks=3, units=1 << 10, p_write=p_write, p_atomic=p_write / 8)
+        check(ctx, recs, offsets(sizes), 256, f"{len(sizes)} short traces, writes {p_write}")
+
+
+@pytest.mark.parametrize("writes", [300, 500, 2000, 3000, 20000])
+def test_rounds(ctx, writes):
+    """More racing writes in one bucket than its table holds: rounds by slot,
+    then (all of one word) the sorting path and the calls after it."""
+    rng = np.random.default_rng(writes)
+    for n, words in ((16384, writes), (16384, 1), (1 << 20, writes // 2)):
+        recs = records(n, rng, p_write=0.0)
+        k = min(writes, n // 2)
+        at = rng.permutation(n)[: 2 * k]
+        recs["unit"][at] = (1 << 23) + np.arange(2 * k) % words
+        recs["space"][at] = 0
+        recs["action"][at] = np.where(np.arange(2 * k) < k, WRITE, READ)
+        check(ctx, recs, offsets([n]), 256, f"{writes} writes, {words} words")
+
+
+@pytest.mark.parametrize("n_traces", [1, 2, 5])
+@pytest.mark.parametrize("locations", [2047, 2049, 10000])
+def test_many_entries(ctx, n_traces, locations):
+    """Entries of a trace in one sorted chunk and in several, some of them
+    found in several buckets (a shared word that races in every epoch)."""
+    rng = np.random.default_rng(locations)
+    n = 1 << 19
+    parts = []
+    for t in range(n_traces):
+        r = records(n, rng, p_write=0.0, epochs=1)
+        k = locations if t != 1 else 7
+        at = rng.permutation(n)[: 8 * k].reshape(8, k)
+        for q in range(8):
+            word = np.arange(k) % 11000
+            block = np.arange(k) // 11000
+            r["unit"][at[q]] = (1 << 20) + word
+            r["space"][at[q]] = np.arange(k) % 2
+            r["tid"][at[q]] = block * 256 + q
+            r["epoch"][at[q]] = q // 2
+            r["action"][at[q]] = WRITE if q % 2 else READ
+        parts.append(r)
+    want = check(ctx, np.concatenate(parts), offsets([n] * n_traces), 256, f"{locations} locations")
+    assert len(want) >= locations
+
+
 def test_invalid_record_and_recovery(ctx):
     import paper_1905_01833_amd as pkg
 
@@ -181,13 +231,13 @@ def test_warp_aware(ctx):
     side = (rng.integers(0, 5, len(recs)) | np.where(rng.random(len(recs)) < 0.1, 1 << 31, 0)).astype(np.uint32)
     off, tpb = offsets(sizes), np.full(9, 256, dtype=np.uint32)
     want, wsum = oracle.closed_form_warp(recs, side, off, tpb)
-    print(f"[gpu] filter, warp-aware: {len(recs)} records", flush=True)
+    print(f"[gpu] grouped count, warp-aware: {len(recs)} records", flush=True)
     got, gsum = ctx.check_traces_warp_device(device(recs), torch.from_numpy(side.view(np.int32)).to("cuda:0"), off, tpb)
     assert got.tobytes() == want.tobytes() and gsum.tobytes() == wsum.tobytes()
 
 
 def test_server_batches():
-    """Requests gathered from separate device tensors into one filtered call."""
+    """Requests gathered from separate device tensors into one grouped call."""
     import paper_1905_01833_amd as pkg
 
     rng = np.random.default_rng(13)
@@ -195,7 +245,7 @@ def test_server_batches():
     want = [oracle.closed_form(r, np.array([0, len(r)], dtype=np.uint64), np.array([256], dtype=np.uint32)) for r in reqs]
     dev = [device(r) for r in reqs]
     torch.cuda.synchronize()
-    print("[gpu] filter, server", flush=True)
+    print("[gpu] grouped count, server", flush=True)
     srv = pkg.Server(0, slots=1)
     try:
         for _ in range(2):
