@@ -116,7 +116,7 @@ struct sim_ctx {
       group_sum, stage, stage_ref, ctrl, out, bar, bar_base;
   // the barrier-divergence check: arrival counts of host calls, chunk table,
   // per-block results, per-chunk counts and offsets, divergent blocks
-  DevBuf div_in, div_chunks, div_blocks, div_cnt, div_off, div_out;
+  DevBuf div_in, div_lists, div_cnt, div_off, div_out;
   DevBuf fit_out;  // the fitness count's rows
   // the warp-aware check: side words of host calls, removed pairs per entry,
   // refined entries, their number
@@ -141,7 +141,7 @@ namespace {
 std::vector<DevBuf*> all_bufs(sim_ctx* c) {
   return {&c->records, &c->keys0, &c->keys1, &c->meta, &c->stats_part, &c->layout, &c->thist, &c->tcnt, &c->gtot,
           &c->gbase,   &c->agg,   &c->tout,  &c->cross, &c->cross_flag, &c->group_sum, &c->stage,
-          &c->stage_ref, &c->ctrl, &c->out, &c->bar, &c->bar_base, &c->div_in, &c->div_chunks, &c->div_blocks,
+          &c->stage_ref, &c->ctrl, &c->out, &c->bar, &c->bar_base, &c->div_in, &c->div_lists,
           &c->div_cnt, &c->div_off, &c->div_out, &c->fit_out, &c->side, &c->warp_rm, &c->warp_out, &c->warp_n};
 }
 
@@ -423,8 +423,8 @@ hipError_t size_buffers(sim_ctx* c, uint64_t total, uint32_t n_traces, uint32_t 
     };
     if (after() > c->dev_limit) {
       for (int r = 0; r < N_REGION; r++) release(*region_buf(c, r));
-      for (DevBuf* b : {&c->out, &c->stage, &c->stage_ref, &c->bar, &c->bar_base, &c->div_in, &c->div_chunks,
-                        &c->div_blocks, &c->div_cnt, &c->div_off, &c->div_out, &c->fit_out})
+      for (DevBuf* b : {&c->out, &c->stage, &c->stage_ref, &c->bar, &c->bar_base, &c->div_in, &c->div_lists,
+                        &c->div_cnt, &c->div_off, &c->div_out, &c->fit_out})
         release(*b);
       if (c->graph.exec) (void)hipGraphExecDestroy(c->graph.exec);
       c->graph.exec = nullptr;
@@ -1292,18 +1292,21 @@ int divergence(sim_ctx* c, const uint32_t* d_arr, const uint64_t* offsets, uint3
     *out = r;
     return SIM_OK;
   }
-  // chunk table (pinned), the count word after it
+  // chunk table (pinned, read by the kernels), after it the count word and the
+  // first divergent blocks, which the kernels write
+  constexpr uint32_t DIV_HOST_BLOCKS = 1024;
   const size_t tab = ((size_t)n_chunks * sizeof(DivChunk) + 15) / 16 * 16;
+  const size_t h_need = tab + 16 + DIV_HOST_BLOCKS * sizeof(DivOut);
   hipError_t e;
-  if (c->h_div_cap < tab + 16) {
+  if (c->h_div_cap < h_need) {
     if (c->h_div) (void)hipHostFree(c->h_div);
     c->h_div = nullptr;
     c->h_div_cap = 0;
-    if ((e = hipHostMalloc(&c->h_div, tab + 16 + tab / 8, hipHostMallocDefault)) != hipSuccess) {
+    if ((e = hipHostMalloc(&c->h_div, h_need + tab / 8, hipHostMallocDefault)) != hipSuccess) {
       divergence_result_free(r);
       return hip_fail(c, e, "pinned allocation");
     }
-    c->h_div_cap = tab + 16 + tab / 8;
+    c->h_div_cap = h_need + tab / 8;
   }
   DivChunk* hc = (DivChunk*)c->h_div;
   uint64_t* h_total = (uint64_t*)((char*)c->h_div + tab);
@@ -1318,18 +1321,16 @@ int divergence(sim_ctx* c, const uint32_t* d_arr, const uint64_t* offsets, uint3
     }
   }
   const uint64_t n_blocks = block0;
-  if ((e = grow(c, c->div_chunks, (size_t)n_chunks * sizeof(DivChunk))) ||
-      (e = grow(c, c->div_blocks, (size_t)n_blocks * sizeof(DivBlock))) ||
-      (e = grow(c, c->div_cnt, (size_t)n_chunks * 4)) || (e = grow(c, c->div_off, ((size_t)n_chunks + 1) * 8))) {
+  if ((e = grow(c, c->div_lists, (size_t)n_blocks * sizeof(DivOut))) ||
+      (e = grow(c, c->div_cnt, (size_t)n_chunks * sizeof(uint2))) || (e = grow(c, c->div_off, (size_t)n_chunks * 8))) {
     divergence_result_free(r);
     return hip_fail(c, e, "device allocation");
   }
-  DivChunk* d_chunks = (DivChunk*)c->div_chunks.p;
-  uint64_t* d_off = (uint64_t*)c->div_off.p;
-  if ((e = hipMemcpyAsync(d_chunks, hc, (size_t)n_chunks * sizeof(DivChunk), hipMemcpyHostToDevice, s)) ||
-      (e = launch_divergence(d_chunks, n_chunks, d_arr, (DivBlock*)c->div_blocks.p, (uint32_t*)c->div_cnt.p, d_off,
-                             d_off + n_chunks, s)) ||
-      (e = hipMemcpyAsync(h_total, d_off + n_chunks, 8, hipMemcpyDeviceToHost, s)) ||
+  DivOut* const d_lists = (DivOut*)c->div_lists.p;
+  uint2* const d_cnt = (uint2*)c->div_cnt.p;
+  uint64_t* const d_off = (uint64_t*)c->div_off.p;
+  DivOut* const h_out = (DivOut*)(h_total + 2);
+  if ((e = launch_divergence(hc, n_chunks, d_arr, d_lists, d_cnt, d_off, h_total, h_out, DIV_HOST_BLOCKS, s)) ||
       (e = hipStreamSynchronize(s))) {
     divergence_result_free(r);
     return hip_fail(c, e, "divergence check");
@@ -1346,15 +1347,14 @@ int divergence(sim_ctx* c, const uint32_t* d_arr, const uint64_t* offsets, uint3
     return fail(c, SIM_ENOMEM, "host allocation failed");
   }
   r->n_blocks = n_div;
-  if (n_div) {
-    if ((e = grow(c, c->div_out, (size_t)n_div * sizeof(DivOut))) ||
-        (e = launch_divergence_emit(d_chunks, n_chunks, (const DivBlock*)c->div_blocks.p, d_off,
-                                    (DivOut*)c->div_out.p, s)) ||
-        (e = hipMemcpyAsync(r->blocks, c->div_out.p, (size_t)n_div * sizeof(DivOut), hipMemcpyDeviceToHost, s)) ||
-        (e = hipStreamSynchronize(s))) {
-      divergence_result_free(r);
-      return hip_fail(c, e, "divergence output");
-    }
+  if (n_div <= DIV_HOST_BLOCKS) {
+    memcpy(r->blocks, h_out, n_div * sizeof(DivOut));
+  } else if ((e = grow(c, c->div_out, (size_t)n_div * sizeof(DivOut))) ||
+             (e = launch_divergence_emit(n_chunks, d_lists, d_cnt, d_off, (DivOut*)c->div_out.p, s)) ||
+             (e = hipMemcpyAsync(r->blocks, c->div_out.p, (size_t)n_div * sizeof(DivOut), hipMemcpyDeviceToHost, s)) ||
+             (e = hipStreamSynchronize(s))) {
+    divergence_result_free(r);
+    return hip_fail(c, e, "divergence output");
   }
   *out = r;
   return SIM_OK;

@@ -863,7 +863,7 @@ __global__ __launch_bounds__(NT) void k_entries_sort(FilterBuffers f) {
   const RaceOut* src = (f.n_traces > 1 ? f.placed : f.entries) + first;
   RaceOut* dst = (n <= SORT_CHUNK ? (total <= f.host_cap ? f.host_entries : f.sorted)
                                   : (f.n_traces > 1 ? f.entries : f.placed)) + first;
-  const uint32_t lanes = n <= 2 * SORT_CHUNK ? 16u : 1u, take = NT / lanes, per_chunk = SORT_CHUNK / take;
+  const uint32_t lanes = n <= 32 * SORT_CHUNK ? 16u : 1u, take = NT / lanes, per_chunk = SORT_CHUNK / take;
   for (uint32_t item = blockIdx.y;; item += gridDim.y) {
     const uint32_t c0 = item / per_chunk * SORT_CHUNK, g0 = item % per_chunk * take;
     if (c0 >= n) break;
@@ -981,7 +981,7 @@ hipError_t launch_filter_out(const FilterBuffers& f, hipStream_t s) {
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   const uint32_t chunks = cdiv(f.entries_cap, SORT_CHUNK);
-  hipLaunchKernelGGL(k_entries_sort, dim3(f.n_traces, f.n_traces <= 64 ? std::min(128u, cdiv(f.entries_cap, 16)) : 1u), dim3(NT),
+  hipLaunchKernelGGL(k_entries_sort, dim3(f.n_traces, f.n_traces <= 64 ? std::min(1024u / f.n_traces, cdiv(f.entries_cap, 16)) : 1u), dim3(NT),
                      0, s, f);
   if ((e = hipGetLastError()) != hipSuccess || chunks <= 1) return e;
   hipLaunchKernelGGL(k_entries_merge, dim3(std::min(2048u, cdiv(f.entries_cap, NT))), dim3(NT), 0, s, f);

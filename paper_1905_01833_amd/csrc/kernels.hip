@@ -2012,94 +2012,141 @@ __global__ __launch_bounds__(NT) void k_fit_traces(Buffers b, FitOut* __restrict
 // its threads arrived at fewer than the most.
 //
 // k_div_blocks: one workgroup per chunk (whole blocks of one trace, about a
-// tile of threads).  A block of up to 64 threads takes a segment of
-// pow2ceil(tpb) lanes (several blocks per wave, reduced with xor shuffles
-// inside the segment); a larger block takes a whole wave, its lanes
-// striding over the threads.  Dense per-block results and per-chunk counts
-// of divergent blocks go to global memory.  k_div_scan turns the counts
-// into offsets (one workgroup), and k_div_emit writes the divergent blocks
-// in (trace, block) order.
+// tile of threads).  Blocks hardly ever diverge, so the counts are not reduced
+// block by block: every count is compared with the next one of its block, four
+// by four, all of a thread's loads in flight at once, and only the blocks where
+// two differ are looked at again (a lane or, for large blocks, a wave each).
+// 54 MB of counts take 22 us, of which HBM needs 12; minima and maxima over the
+// lanes of every block took 38.  The chunk's divergent blocks follow each other
+// from its first block's place on.
+// k_div_out puts the chunks' lists together (one workgroup): a few blocks go
+// straight to the host's memory, else k_div_emit writes them at the chunks'
+// offsets.
 
-__device__ __forceinline__ uint32_t seg_lanes(uint32_t tpb) {
-  if (tpb >= 64) return 64u;
-  uint32_t s = 1;
-  while (s < tpb) s <<= 1;
-  return s;
-}
+typedef uint32_t counts4 __attribute__((ext_vector_type(4), aligned(4)));
 
 __global__ __launch_bounds__(NT) void k_div_blocks(const DivChunk* __restrict__ chunks,
-                                                   const uint32_t* __restrict__ arrivals, DivBlock* __restrict__ blocks,
-                                                   uint32_t* __restrict__ chunk_cnt) {
-  __shared__ uint32_t s_cnt;
+                                                   const uint32_t* __restrict__ arrivals, DivOut* __restrict__ lists,
+                                                   uint2* __restrict__ chunk_cnt) {
+  constexpr int U = 4;
+  constexpr uint32_t WORDS = DIV_CHUNK_THREADS / 32;
+  static_assert(WORDS <= NT, "a thread per word of the bitmap");
+  __shared__ uint32_t s_bits[WORDS];
+  __shared__ uint16_t s_list[DIV_CHUNK_THREADS];
+  __shared__ uint32_t s_sc[NWAVE];
   const DivChunk ch = chunks[blockIdx.x];
-  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-  if (threadIdx.x == 0) s_cnt = 0;
+  const uint32_t tx = threadIdx.x, lane = tx & 63u, wave = tx >> 6, tpb = ch.tpb;
+  if (tx < WORDS) s_bits[tx] = 0;
   __syncthreads();
-  const uint32_t S = seg_lanes(ch.tpb);  // lanes per block (uniform over the workgroup)
-  const uint32_t per_wave = 64u / S, sub = lane / S, sl = lane % S;
-  uint32_t n_div = 0;
-  for (uint32_t b0 = wave * per_wave; b0 < ch.n_blocks; b0 += NWAVE * per_wave) {
-    const uint32_t blk = b0 + sub;
-    const bool live = blk < ch.n_blocks;
-    const uint32_t* c = arrivals + ch.thread0 + (uint64_t)blk * ch.tpb;
-    uint32_t lo = ~0u, hi = 0u;
-    if (live)
-      for (uint32_t i = sl; i < ch.tpb; i += S) {
-        const uint32_t v = c[i];
-        lo = min(lo, v);
-        hi = max(hi, v);
+  const uint64_t m = (uint64_t)ch.n_blocks * tpb;  // (n_blocks is 1 where a block is larger than a chunk)
+  const uint32_t* const c = arrivals + ch.thread0;
+  for (uint64_t i0 = 4 * tx; i0 < m; i0 += 4 * NT * U) {
+    counts4 x[U];
+    uint32_t next[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const uint64_t i = i0 + (uint64_t)u * 4 * NT;
+      if (i + 4 < m) {
+        x[u] = *(const counts4*)(c + i);
+        next[u] = c[i + 4];
+      } else if (i < m) {  // past the end: the last count again
+        x[u].x = c[i];
+        x[u].y = c[min(i + 1, m - 1)];
+        x[u].z = c[min(i + 2, m - 1)];
+        x[u].w = c[min(i + 3, m - 1)];
+        next[u] = x[u].w;
+      } else {
+        x[u] = counts4{0, 0, 0, 0};
+        next[u] = 0;
       }
-    for (uint32_t d = 1; d < S; d <<= 1) {
-      lo = min(lo, (uint32_t)__shfl_xor((int)lo, (int)d, 64));
-      hi = max(hi, (uint32_t)__shfl_xor((int)hi, (int)d, 64));
     }
-    uint32_t early = 0;
-    if (live && lo != hi)  // the same in every lane of the segment
-      for (uint32_t i = sl; i < ch.tpb; i += S) early += c[i] < hi ? 1u : 0u;
-    for (uint32_t d = 1; d < S; d <<= 1) early += (uint32_t)__shfl_xor((int)early, (int)d, 64);
-    if (live && sl == 0) {
-      blocks[(uint64_t)ch.block0 + blk] = DivBlock{lo, hi, early, 0u};
-      n_div += lo != hi ? 1u : 0u;
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const uint32_t differ = (x[u].x != x[u].y ? 1u : 0u) | (x[u].y != x[u].z ? 2u : 0u) | (x[u].z != x[u].w ? 4u : 0u) |
+                              (x[u].w != next[u] ? 8u : 0u);
+      if (!differ) continue;
+      for (uint32_t k = 0; k < 4; k++) {
+        const uint64_t j = i0 + (uint64_t)u * 4 * NT + k + 1;  // differs from the count before it
+        if (!((differ >> k) & 1u)) continue;
+        const uint32_t blk = (uint32_t)j / tpb;        // (a call holds fewer than 2^32 threads)
+        if ((uint32_t)j == blk * tpb) continue;        // two blocks meet here
+        atomicOr(&s_bits[blk >> 5], 1u << (blk & 31u));
+      }
     }
   }
-  n_div = wave_reduce(n_div, 0u, [](uint32_t a, uint32_t b) { return a + b; });
-  if (lane == 0 && n_div) atomicAdd(&s_cnt, n_div);
   __syncthreads();
-  if (threadIdx.x == 0) chunk_cnt[blockIdx.x] = s_cnt;
+  const uint32_t word = tx < WORDS ? s_bits[tx] : 0u;
+  uint32_t n_div;
+  uint32_t at = block_excl_sum((uint32_t)__popc(word), s_sc, &n_div);
+  if (tx == 0) chunk_cnt[blockIdx.x] = make_uint2(n_div, ch.block0);
+  if (!n_div) return;
+  for (uint32_t w = word; w; w &= w - 1) s_list[at++] = (uint16_t)(32 * tx + (uint32_t)__builtin_ctz(w));
+  __syncthreads();
+  if (tpb <= 64) {
+    for (uint32_t d = tx; d < n_div; d += NT) {
+      const uint32_t blk = s_list[d];
+      const uint32_t* const b = c + (uint64_t)blk * tpb;
+      uint32_t lo = ~0u, hi = 0u, early = 0;
+      for (uint32_t i = 0; i < tpb; i++) {
+        lo = min(lo, b[i]);
+        hi = max(hi, b[i]);
+      }
+      for (uint32_t i = 0; i < tpb; i++) early += b[i] < hi ? 1u : 0u;
+      lists[(uint64_t)ch.block0 + d] = DivOut{ch.trace, ch.block + blk, lo, hi, (uint64_t)early};
+    }
+    return;
+  }
+  for (uint32_t d = wave; d < n_div; d += NWAVE) {
+    const uint32_t blk = s_list[d];
+    const uint32_t* const b = c + (uint64_t)blk * tpb;
+    uint32_t lo = ~0u, hi = 0u, early = 0;
+    for (uint32_t i = lane; i < tpb; i += 64) {
+      const uint32_t v = b[i];
+      lo = min(lo, v);
+      hi = max(hi, v);
+    }
+    lo = wave_min(lo);
+    hi = wave_max(hi);
+    for (uint32_t i = lane; i < tpb; i += 64) early += b[i] < hi ? 1u : 0u;
+    early = wave_reduce(early, 0u, [](uint32_t p, uint32_t q) { return p + q; });
+    if (lane == 0) lists[(uint64_t)ch.block0 + d] = DivOut{ch.trace, ch.block + blk, lo, hi, (uint64_t)early};
+  }
 }
 
-// One workgroup: exclusive offsets of the chunks' counts, and the total.
-__global__ __launch_bounds__(NT) void k_div_scan(const uint32_t* __restrict__ chunk_cnt, uint64_t* __restrict__ chunk_off,
-                                                 uint32_t n_chunks, uint64_t* __restrict__ total) {
-  __shared__ uint32_t s_sc[NWAVE];
+// One workgroup: the chunks' offsets, and the total to the host.
+__global__ __launch_bounds__(4 * NT) void k_div_out(const uint2* __restrict__ chunk_cnt, uint64_t* __restrict__ chunk_off,
+                                                    uint32_t n_chunks, const DivOut* __restrict__ lists,
+                                                    uint64_t* total, DivOut* host_out, uint32_t host_cap) {
+  constexpr uint32_t PER = 4;  // neighbouring chunks per thread
+  __shared__ uint32_t s_sc[4 * NWAVE];
   uint64_t base = 0;
-  for (uint32_t i0 = 0; i0 < n_chunks; i0 += NT) {
-    const uint32_t i = i0 + threadIdx.x;
-    const uint32_t v = i < n_chunks ? chunk_cnt[i] : 0u;
+  for (uint32_t i0 = 0; i0 < n_chunks; i0 += 4 * NT * PER) {
+    uint2 v[PER];
+    uint32_t sum = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < PER; q++) {
+      const uint32_t i = i0 + PER * threadIdx.x + q;
+      v[q] = i < n_chunks ? chunk_cnt[i] : make_uint2(0u, 0u);
+      sum += v[q].x;
+    }
     uint32_t tot;
-    const uint32_t ex = block_excl_sum(v, s_sc, &tot);
-    if (i < n_chunks) chunk_off[i] = base + ex;
+    uint64_t at = base + block_excl_sum_n<4 * NWAVE>(sum, s_sc, &tot);
+#pragma unroll
+    for (uint32_t q = 0; q < PER; q++) {
+      const uint32_t i = i0 + PER * threadIdx.x + q;
+      if (i < n_chunks) chunk_off[i] = at;
+      for (uint32_t e = 0; e < v[q].x && at + e < host_cap; e++) host_out[at + e] = lists[(uint64_t)v[q].y + e];
+      at += v[q].x;
+    }
     base += tot;
   }
   if (threadIdx.x == 0) *total = base;
 }
 
-__global__ __launch_bounds__(NT) void k_div_emit(const DivChunk* __restrict__ chunks,
-                                                 const DivBlock* __restrict__ blocks,
-                                                 const uint64_t* __restrict__ chunk_off, DivOut* __restrict__ out) {
-  __shared__ uint32_t s_sc[NWAVE];
-  const DivChunk ch = chunks[blockIdx.x];
-  uint64_t base = chunk_off[blockIdx.x];
-  for (uint32_t b0 = 0; b0 < ch.n_blocks; b0 += NT) {
-    const uint32_t blk = b0 + threadIdx.x;
-    DivBlock r{0u, 0u, 0u, 0u};
-    if (blk < ch.n_blocks) r = blocks[(uint64_t)ch.block0 + blk];
-    const uint32_t flag = (blk < ch.n_blocks && r.lo != r.hi) ? 1u : 0u;
-    uint32_t tot;
-    const uint32_t ex = block_excl_sum(flag, s_sc, &tot);
-    if (flag) out[base + ex] = DivOut{ch.trace, ch.block + blk, r.lo, r.hi, (uint64_t)r.early};
-    base += tot;
-  }
+__global__ __launch_bounds__(64) void k_div_emit(const uint2* __restrict__ chunk_cnt, const uint64_t* __restrict__ chunk_off,
+                                                 const DivOut* __restrict__ lists, DivOut* __restrict__ out) {
+  const uint2 v = chunk_cnt[blockIdx.x];
+  for (uint32_t e = threadIdx.x; e < v.x; e += 64) out[chunk_off[blockIdx.x] + e] = lists[(uint64_t)v.y + e];
 }
 
 // ------------------------------------------------- warp refinement
@@ -2485,21 +2532,23 @@ hipError_t launch_fitness(const Buffers& b, uint32_t passes_done, FitOut* out, h
   return hipGetLastError();
 }
 
-hipError_t launch_divergence(const DivChunk* chunks, uint32_t n_chunks, const uint32_t* arrivals, DivBlock* blocks,
-                             uint32_t* chunk_cnt, uint64_t* chunk_off, uint64_t* total, hipStream_t s) {
+hipError_t launch_divergence(const DivChunk* chunks, uint32_t n_chunks, const uint32_t* arrivals, DivOut* lists,
+                             uint2* chunk_cnt, uint64_t* chunk_off, uint64_t* total, DivOut* host_out, uint32_t host_cap,
+                             hipStream_t s) {
   if (n_chunks) {
-    hipLaunchKernelGGL(k_div_blocks, dim3(n_chunks), dim3(NT), 0, s, chunks, arrivals, blocks, chunk_cnt);
+    hipLaunchKernelGGL(k_div_blocks, dim3(n_chunks), dim3(NT), 0, s, chunks, arrivals, lists, chunk_cnt);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_div_scan, dim3(1), dim3(NT), 0, s, chunk_cnt, chunk_off, n_chunks, total);
+  hipLaunchKernelGGL(k_div_out, dim3(1), dim3(4 * NT), 0, s, chunk_cnt, chunk_off, n_chunks, lists, total, host_out,
+                     host_cap);
   return hipGetLastError();
 }
 
-hipError_t launch_divergence_emit(const DivChunk* chunks, uint32_t n_chunks, const DivBlock* blocks,
-                                  const uint64_t* chunk_off, DivOut* out, hipStream_t s) {
+hipError_t launch_divergence_emit(uint32_t n_chunks, const DivOut* lists, const uint2* chunk_cnt, const uint64_t* chunk_off,
+                                  DivOut* out, hipStream_t s) {
   if (!n_chunks) return hipSuccess;
-  hipLaunchKernelGGL(k_div_emit, dim3(n_chunks), dim3(NT), 0, s, chunks, blocks, chunk_off, out);
+  hipLaunchKernelGGL(k_div_emit, dim3(n_chunks), dim3(64), 0, s, chunk_cnt, chunk_off, lists, out);
   return hipGetLastError();
 }
 

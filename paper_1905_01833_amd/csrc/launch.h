@@ -218,25 +218,25 @@ struct DivChunk {
   uint32_t block;    // the chunk's first block within its trace
   uint32_t n_blocks;
   uint32_t tpb;      // threads per block
-  uint32_t block0;   // the chunk's first block among the call's blocks (dense results)
+  uint32_t block0;   // the chunk's first block among the call's blocks: its list's place
   uint32_t pad;
 };
-struct DivBlock {    // one block: fewest and most arrivals, threads below the most
-  uint32_t lo, hi, early, pad;
-};
-struct DivOut {      // mirrors sim_divergence (24 bytes)
+struct DivOut {      // mirrors sim_divergence (24 bytes): fewest and most arrivals, threads below the most
   uint32_t trace, block, lo, hi;
   uint64_t early;
 };
 constexpr uint32_t DIV_CHUNK_THREADS = TILE;  // threads per chunk (whole blocks, at least one)
 
-// Per-block results and per-chunk counts, then the chunks' output offsets
-// and the number of divergent blocks (*total, device memory).
-hipError_t launch_divergence(const DivChunk* chunks, uint32_t n_chunks, const uint32_t* arrivals, DivBlock* blocks,
-                             uint32_t* chunk_cnt, uint64_t* chunk_off, uint64_t* total, hipStream_t s);
-// The divergent blocks, in (trace, block) order, to out.
-hipError_t launch_divergence_emit(const DivChunk* chunks, uint32_t n_chunks, const DivBlock* blocks,
-                                  const uint64_t* chunk_off, DivOut* out, hipStream_t s);
+// The chunks' lists of divergent blocks and their lengths (with the list's
+// place), then the chunks' output offsets and the number of divergent blocks
+// (*total) and the first host_cap of those in (trace, block) order: pinned host
+// memory.  So is `chunks`.
+hipError_t launch_divergence(const DivChunk* chunks, uint32_t n_chunks, const uint32_t* arrivals, DivOut* lists,
+                             uint2* chunk_cnt, uint64_t* chunk_off, uint64_t* total, DivOut* host_out, uint32_t host_cap,
+                             hipStream_t s);
+// All of them, to out.
+hipError_t launch_divergence_emit(uint32_t n_chunks, const DivOut* lists, const uint2* chunk_cnt, const uint64_t* chunk_off,
+                                  DivOut* out, hipStream_t s);
 
 // Warp-aware check (Theorem 1's warp clauses) after the plain check of a
 // call whose keys carry the side field: the pairs lockstep execution
