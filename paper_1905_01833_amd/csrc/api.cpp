@@ -476,6 +476,12 @@ bool group_pays(const sim_ctx* c, const uint64_t* offsets, uint32_t n_traces, ui
 // than one for sixteen records, or too many writes that share a group), this
 // many calls of the kind go without it.
 constexpr uint32_t GROUP_PAUSE = 15;
+// Calls whose traces all hold no more records are counted without a partition,
+// a workgroup per trace.  Partitioned / direct, in us: one trace of 2^10 48 / 35,
+// 2^12 51 / 38, 2^13 53 / 44, 2^14 58 / 55; 64 traces of 2^8 to 2^11 56 / 42, of
+// 2^10 to 2^13 59 / 50, of 2^12 to 2^15 (the short ones direct) 67 / 100.
+constexpr uint64_t GROUP_DIRECT_RECORDS = 8192;
+static_assert(GROUP_DIRECT_RECORDS <= FT, "a direct trace's keys name its records");
 constexpr uint32_t GROUP_HOST_ENTRIES = 4096;  // entries of a call the kernels write to host memory
 constexpr int RUN_SORT = 1;  // run_grouped: take the sorting path
 
@@ -1156,6 +1162,7 @@ int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const
   GroupHead* head = (GroupHead*)((char*)c->h_meta + tr_bytes);
   RaceOut* host_entries = (RaceOut*)((char*)head + 256);
   uint64_t rows = 0;
+  uint64_t longest = 0;
   uint32_t tiles = 0, buckets = 0, max_lgb = 0;
   for (uint32_t i = 0; i < n_traces; i++) {
     const uint64_t n = offsets[i + 1] - offsets[i];
@@ -1165,6 +1172,7 @@ int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const
     rows += (uint64_t)nt * ((1u << lgb) + 1);
     tiles += nt;
     buckets += nt ? 1u << lgb : 0u;
+    longest = std::max(longest, n);
     max_lgb = std::max(max_lgb, lgb);
   }
   const uint64_t half = 8 * room;  // bytes of a key buffer
@@ -1192,6 +1200,7 @@ int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const
   f.n_traces = n_traces;
   f.n_tiles = tiles;
   f.n_buckets = buckets;
+  f.direct = longest <= GROUP_DIRECT_RECORDS;
   f.cnt = words;
   f.tile_trace = words + FC_COUNT;
   f.bucket_trace = f.tile_trace + tiles;

@@ -239,8 +239,14 @@ typedef const __attribute__((address_space(1))) uint32_t* GWords;
 __device__ __forceinline__ words4 load_words4(GWords p) { return *(const __attribute__((address_space(1))) words4*)p; }
 __device__ __forceinline__ words2 load_words2(GWords p) { return *(const __attribute__((address_space(1))) words2*)p; }
 
-template <bool LATE, bool WARP, uint32_t WCAP, uint32_t RCAP>
+// A call of short traces needs no partition: MODE DIRECT_TRACE is a workgroup
+// per trace, which reads the records itself, keeps their keys in record order
+// and makes the passes over those.  A call of 1279 records took 12 us in
+// k_filter_part and 12 here, and takes 12 so (47 and 36 us in all).
+enum : int { BY_BUCKET = 0, LATE_BUCKET = 1, DIRECT_TRACE = 2 };
+template <int MODE, bool WARP, uint32_t WCAP, uint32_t RCAP>
 __global__ __launch_bounds__(FNT, 8) void k_filter_count(FilterBuffers f) {
+  constexpr bool LATE = MODE == LATE_BUCKET, DIRECT = MODE == DIRECT_TRACE;
   constexpr uint32_t NTH = FNT;
   constexpr uint32_t SB = FILTER_SLOT_BITS, W_WORDS = (1u << SB) / 32, D_WORDS = W_WORDS / 2, T_WORDS = W_WORDS / 4;
   constexpr uint32_t HN = 512, NONE = 0xFFFFu;  // chains of writes, and as many of atomics
@@ -258,7 +264,10 @@ __global__ __launch_bounds__(FNT, 8) void k_filter_count(FilterBuffers f) {
   __shared__ uint32_t s_n, s_nw, s_any, s_base;
   const uint32_t tx = threadIdx.x;
   uint32_t bucket, part = 0;
-  if (LATE) {
+  if (DIRECT) {
+    if (!f.tr[blockIdx.x].n) return;
+    bucket = 0;
+  } else if (LATE) {
     if (blockIdx.x >= f.cnt[FC_LATE]) return;
     bucket = f.late[blockIdx.x].x;
     part = f.late[blockIdx.x].y;
@@ -275,9 +284,9 @@ __global__ __launch_bounds__(FNT, 8) void k_filter_count(FilterBuffers f) {
   auto uniform = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); };
   bucket = uniform(bucket);
   part = uniform(part);
-  const uint32_t parts = uniform(f.extra_max ? f.hot[bucket] : 1u);
-  if (!LATE && parts > 1 && blockIdx.x >= f.extra_max) return;  // (its parts are items)
-  const uint32_t trace = uniform(f.bucket_trace[bucket]);
+  const uint32_t parts = uniform(f.extra_max && !DIRECT ? f.hot[bucket] : 1u);
+  if (MODE == BY_BUCKET && parts > 1 && blockIdx.x >= f.extra_max) return;  // (its parts are items)
+  const uint32_t trace = DIRECT ? blockIdx.x : uniform(f.bucket_trace[bucket]);
   FTrace T = f.tr[trace];
   T.rec = (const void*)readfirstlane((uint64_t)T.rec);
   T.n = readfirstlane(T.n);
@@ -318,6 +327,34 @@ __global__ __launch_bounds__(FNT, 8) void k_filter_count(FilterBuffers f) {
   const uint32_t run = (uint32_t)min<uint64_t>(FT >> T.lgb, T.n);  // usual length
   auto for_keys_n = [&](auto nv, bool writes, uint32_t lo, uint32_t hi, auto&& fn) {
     constexpr uint32_t NV = decltype(nv)::value;  // loads in flight
+    if constexpr (DIRECT) {
+      uint32_t to = threadIdx.x;
+      asm volatile("" : "+v"(to));
+      for (uint32_t i0 = 0; i0 < (uint32_t)T.n; i0 += 4 * NV * NTH) {
+        words4 x[NV];
+#pragma unroll
+        for (uint32_t v = 0; v < NV; v++) {
+          x[v] = words4{0, 0, 0, 0};
+          if (i0 + 4 * (to + v * NTH) < (uint32_t)T.n) x[v] = load_words4(keys + (i0 + 4 * (to + v * NTH)));
+        }
+#pragma unroll 1
+        for (uint32_t v = 0; v < NV; v++) {
+          const uint32_t i = i0 + 4 * (to + v * NTH);
+          if (!__any(i < (uint32_t)T.n)) break;
+          uint32_t k[4] = {x[0].x, x[0].y, x[0].z, x[0].w}, live = 0;
+#pragma unroll
+          for (uint32_t u = 0; u < 4; u++) {
+            const uint32_t act = k[u] & 3u;
+            live |= (i + u < (uint32_t)T.n && (act != 0) == writes ? 1u : 0u) << u;
+            k[u] = (k[u] & ~3u) | (act == 2 ? FILTER_ATOMIC : 0u) | (i + u);
+          }
+          fn(k, live, 0u);
+#pragma unroll
+          for (uint32_t q = 0; q + 1 < NV; q++) x[q] = x[q + 1];
+        }
+      }
+      return;
+    }
     const uint32_t len = writes ? run / 4 : run - run / 4;  // (a quarter of the records write)
     const uint32_t most = 31u - (uint32_t)__builtin_clz(NTH / min(NTH, hi - lo));  // with it every run has a group
     uint32_t lg = len > 16 ? 32u - (uint32_t)__builtin_clz((len - 1) / 16) : 0u;
@@ -399,7 +436,7 @@ __global__ __launch_bounds__(FNT, 8) void k_filter_count(FilterBuffers f) {
   // ---- W and T, and D from writes that meet another.  (Bits are looked at
   //      before they are set: a hot word's atomics would go one by one.)
   bool any = false;
-  for_keys(true, 0, T.ntiles, [&](const uint32_t(&k)[4], uint32_t live, uint32_t) {
+  auto see_writes = [&](const uint32_t(&k)[4], uint32_t live, uint32_t) {
     any = any || live;
     uint32_t seen = 0;
 #pragma unroll
@@ -421,7 +458,46 @@ __global__ __launch_bounds__(FNT, 8) void k_filter_count(FilterBuffers f) {
         const uint32_t sd = slot_of(k[u]) >> 1;
         if (!(k[u] & FILTER_ATOMIC) && !bit(D, sd)) set(D, sd);
       }
-  });
+  };
+  if constexpr (DIRECT) {  // the records: their keys (slot | action), and the writes among them
+    constexpr uint32_t Q = 8;  // records in flight per thread
+    const GRecords p = global_records(T.rec);
+    const uint32_t shift = block_shift(T.tpb), n = (uint32_t)T.n;
+    uint32_t bad = ~0u;
+#pragma unroll 1
+    for (uint32_t i0 = 0; i0 < n; i0 += Q * NTH) {
+      ulonglong2 x[Q];
+#pragma unroll
+      for (uint32_t u = 0; u < Q; u++) {
+        const uint32_t j = i0 + tx + u * NTH;
+        x[u] = j < n ? load_record(p, j) : ulonglong2{0ull, 0ull};
+      }
+#pragma unroll 1
+      for (uint32_t h = 0; h < Q && i0 + h * NTH < n; h += 4) {
+        uint32_t k[4], live = 0;
+#pragma unroll
+        for (uint32_t u = 0; u < 4; u++) {
+          const uint32_t j = i0 + tx + (h + u) * NTH;
+          const Rec r = unpack_rec(x[u]);
+          if (j < n && (r.action > 2 || r.space > 1)) bad = min(bad, j);
+          const uint32_t act = r.action <= 2 ? r.action : 0u;  // (a bad record's call fails)
+          k[u] = filter_slot(filter_group(r.unit, block_of(r.tid, T.tpb, shift), r.epoch, r.space)) << FT_BITS;
+          if (j < n) f.keys[T.off + j] = k[u] | act;
+          live |= (j < n && act ? 1u : 0u) << u;
+          if (act == 2) k[u] |= FILTER_ATOMIC;
+        }
+        see_writes(k, live, 0u);
+#pragma unroll
+        for (uint32_t u = 0; u + 4 < Q; u++) x[u] = x[u + 4];
+      }
+    }
+    if (bad != ~0u) {
+      atomicOr(&f.ctrl->error_flags, LAYOUT_ERR_RECORD);
+      atomicMin((unsigned long long*)&f.ctrl->first_bad, (unsigned long long)(T.off + (uint64_t)bad));
+    }
+  } else {
+    for_keys(true, 0, T.ntiles, see_writes);
+  }
   if (any) s_any = 1;
   __syncthreads();
   if (!s_any) return;  // nothing but reads
@@ -539,11 +615,11 @@ __global__ __launch_bounds__(FNT, 8) void k_filter_count(FilterBuffers f) {
       }
       __syncthreads();
       const uint32_t fit = uniform(s_base);
-      if (fit <= 4 || (fit <= MAX_ROUNDS && (level > 1 || (!LATE && !f.late_max)))) {
+      if (fit <= 4 || (fit <= MAX_ROUNDS && (level > 1 || DIRECT || (!LATE && !f.late_max)))) {
         rounds = fit;
         break;
       }
-      if (!LATE && f.late_max) {  // thinned out by a workgroup of its own
+      if (!LATE && !DIRECT && f.late_max) {  // thinned out by a workgroup of its own
         if (tx == 0) {
           const uint32_t at = atomicAdd(&f.cnt[FC_LATE], 1u);
           if (at < f.late_max) f.late[at] = make_uint2(bucket, part);
@@ -845,7 +921,7 @@ __global__ __launch_bounds__(NT) void k_entries_place(FilterBuffers f) {
 // An entry's place in its chunk is the number of entries before it there (of
 // equal ones, those with a smaller index).  A workgroup (trace, y) holds a
 // chunk's keys in LDS and places 16 of its entries, sixteen lanes to an entry
-// (256, a lane each, where the trace has many): sorting 1677 entries in one
+// (256, a lane each, where one has many, or the call many traces): sorting 1677 entries in one
 // workgroup's LDS took 68 us, 66 steps with a barrier each; this takes 17.
 __global__ __launch_bounds__(NT) void k_entries_sort(FilterBuffers f) {
   __shared__ uint64_t s_place[SORT_CHUNK], s_unit[SORT_CHUNK];
@@ -863,7 +939,7 @@ __global__ __launch_bounds__(NT) void k_entries_sort(FilterBuffers f) {
   const RaceOut* src = (f.n_traces > 1 ? f.placed : f.entries) + first;
   RaceOut* dst = (n <= SORT_CHUNK ? (total <= f.host_cap ? f.host_entries : f.sorted)
                                   : (f.n_traces > 1 ? f.entries : f.placed)) + first;
-  const uint32_t lanes = n <= 32 * SORT_CHUNK ? 16u : 1u, take = NT / lanes, per_chunk = SORT_CHUNK / take;
+  const uint32_t lanes = gridDim.y > 1 && n <= 32 * SORT_CHUNK ? 16u : 1u, take = NT / lanes, per_chunk = SORT_CHUNK / take;
   for (uint32_t item = blockIdx.y;; item += gridDim.y) {
     const uint32_t c0 = item / per_chunk * SORT_CHUNK, g0 = item % per_chunk * take;
     if (c0 >= n) break;
@@ -955,6 +1031,7 @@ hipError_t launch_filter_part(const FilterBuffers& f, hipStream_t s) {
   if (e != hipSuccess) return e;
   // (the instantiation's counters hold every bucket of the call's traces)
   static_assert(FILTER_MAX_LGB == 13, "the larger instantiation");
+  if (f.direct) return hipSuccess;
   hipLaunchKernelGGL(f.max_lgb > 11 ? k_filter_part<13> : k_filter_part<11>, dim3(tile_grid(f.n_tiles, 0, 0)), dim3(FNT), 0,
                      s, f);
   return hipGetLastError();
@@ -967,11 +1044,16 @@ hipError_t launch_filter_count(const FilterBuffers& f, hipStream_t s) {
   }
   const dim3 grid(f.extra_max + tile_grid(f.n_buckets, 0, 0));
   const bool warp = f.side != nullptr;
-  hipLaunchKernelGGL((warp ? k_filter_count<false, true, 860, 1408> : k_filter_count<false, false, 940, 1408>), grid, dim3(FNT),
-                     0, s, f);
-  if ((e = hipGetLastError()) != hipSuccess || !f.late_max) return e;
-  hipLaunchKernelGGL((warp ? k_filter_count<true, true, 860, 1408> : k_filter_count<true, false, 940, 1408>), dim3(f.late_max),
+  if (f.direct) {
+    hipLaunchKernelGGL((warp ? k_filter_count<DIRECT_TRACE, true, 860, 1408> : k_filter_count<DIRECT_TRACE, false, 940, 1408>),
+                       dim3(f.n_traces), dim3(FNT), 0, s, f);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL((warp ? k_filter_count<BY_BUCKET, true, 860, 1408> : k_filter_count<BY_BUCKET, false, 940, 1408>), grid,
                      dim3(FNT), 0, s, f);
+  if ((e = hipGetLastError()) != hipSuccess || !f.late_max) return e;
+  hipLaunchKernelGGL((warp ? k_filter_count<LATE_BUCKET, true, 860, 1408> : k_filter_count<LATE_BUCKET, false, 940, 1408>),
+                     dim3(f.late_max), dim3(FNT), 0, s, f);
   return hipGetLastError();
 }
 hipError_t launch_filter_out(const FilterBuffers& f, hipStream_t s) {

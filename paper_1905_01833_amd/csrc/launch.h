@@ -142,6 +142,7 @@ struct FilterBuffers {      // device pointers of a call's grouped race count (f
   FTrace* tr;
   const FTrace* tr_src;     // where k_filter_begin finds them: pinned host memory, or tr
   uint32_t n_traces, n_tiles, n_buckets;
+  uint32_t direct;          // 1: every trace is counted by one workgroup from its records
   uint32_t* tile_trace;     // [tile] its trace
   uint32_t* bucket_trace;   // [bucket] its trace
   uint32_t* keys;           // [record] a tile's keys by bucket (filter.h)

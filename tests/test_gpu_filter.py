@@ -158,7 +158,7 @@ def test_generated_batch_and_shuffle(ctx):
     assert check(ctx, recs, off, tpb, "shuffled").tobytes() == want.tobytes()
 
 
-@pytest.mark.parametrize("sizes", [[1], [2, 0, 1], [17], [GROUPED], [GROUPED] * 301, [1] * 64 + [GROUPED] + [3] * 4000, [40000, 0, 17]])
+@pytest.mark.parametrize("sizes", [[1], [2, 0, 1], [17], [4095, 4096, 4097], [8191], [8192, 0, 8192], [8193, 5], [8192] * 40, [GROUPED], [GROUPED] * 301, [1] * 64 + [GROUPED] + [3] * 4000, [40000, 0, 17]])
 def test_short_calls(ctx, sizes):
     """The smallest calls that count by group, of one trace and of many."""
     rng = np.random.default_rng(len(sizes))
