@@ -455,11 +455,11 @@ struct Sink {
 // Calls that count their races group by group (filter.h) instead of sorting
 // every record: all but those with a trace of more than 2^27 records, whose
 // buckets grow past what one workgroup counts at a time.  Sorting / grouped,
-// one generated trace of 2^10 .. 2^27 records, in us: 2^10 112 / 50, 2^14
-// 144 / 56, 2^18 171 / 97, 2^20 208 / 101, 2^22 287 / 130, 2^23 433 / 183,
-// 2^24 707 / 330, 2^25 1415 / 630, 2^26 2980 / 1590, 2^27 5866 / 3660; 2^28
+// one generated trace of 2^10 .. 2^27 records, in us: 2^10 112 / 35, 2^14
+// 144 / 55, 2^18 171 / 94, 2^20 208 / 100, 2^22 287 / 124, 2^23 433 / 178,
+// 2^24 707 / 302, 2^25 1415 / 599, 2^26 2980 / 1390, 2^27 5866 / 3520; 2^28
 // 11036 / 16212; with one access in twenty atomic, 2^20 209 / 155, 2^24
-// 704 / 570; 64 traces of 2^8 to 2^13, 161 / 60.
+// 704 / 540; 64 traces of 2^8 to 2^13, 161 / 50.
 constexpr uint64_t GROUP_MAX_RECORDS = 1ull << 27;
 static_assert(GROUP_MAX_RECORDS <= FILTER_MAX_RECORDS, "the longest trace the buckets are made for");
 // A profiling context sorts calls of fewer records: its users read the sorting
@@ -1177,8 +1177,8 @@ int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const
   }
   const uint64_t half = 8 * room;  // bytes of a key buffer
   // a bucket is split only where a tile's run of one of at least 8 buckets is far above the usual
-  const uint32_t hot_part = (uint32_t)std::max<uint64_t>(HOT_PART, 2 * total / HOT_MAX_PARTS + 1);
-  const uint32_t extra_max = max_lgb < 3 ? 0u : (uint32_t)((2 * (total / hot_part) + 8) / 8 * 8);
+  const uint32_t hot_part = (uint32_t)std::max<uint64_t>(HOT_PART, total / HOT_SHARE);
+  const uint32_t extra_max = max_lgb < 3 ? 0u : (uint32_t)((std::min<uint64_t>(total / FILTER_BUCKET, HOT_MAX_ITEMS) + 8) / 8 * 8);
   const uint32_t late_max = tiles > 16 ? std::min(tiles, 1024u) : 0u;
   const uint64_t rows_at = up(4 * room), extra_at = up(rows_at + 4 * rows),
                  late_at = extra_at + 8ull * extra_max;

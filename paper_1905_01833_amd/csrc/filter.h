@@ -28,8 +28,12 @@ constexpr uint32_t FILTER_ATOMIC = 1u << 31;
 constexpr uint32_t FILTER_MAX_LGB = 13;   // log2 of the most buckets of a trace
 constexpr uint32_t FILTER_BUCKET = 16384; // records per bucket aimed at
 constexpr uint64_t FILTER_MAX_RECORDS = 2ull * FILTER_BUCKET << FILTER_MAX_LGB;  // of one trace
-constexpr uint32_t HOT_PART = 8192;      // hot reads per workgroup of a split bucket, at least
-constexpr uint32_t HOT_MAX_PARTS = 2048; // workgroups of split buckets of a call, at most
+constexpr uint32_t HOT_PART = 8192;      // hot reads per workgroup of a split bucket, at least: a part reads
+                                         // all of its bucket's writes again (with 16384 the warp-aware check of
+                                         // 2^22 records took 150 us, with 8192 142, with 5000 138 but 2^23 183
+                                         // against 180)
+constexpr uint32_t HOT_SHARE = 1024;     // ... and of a call's records, one in so many
+constexpr uint32_t HOT_MAX_ITEMS = 2048; // workgroups of hot buckets of a call, at most
 
 struct FTrace {       // one trace of a grouped call (host-filled)
   const void* rec;    // its first record

@@ -4,9 +4,9 @@
 // over five or six radix passes.  Here every 16-byte record is read once, a
 // 4-byte key is written and read back, and only records that may race are
 // looked at again: 24 bytes per record.  One trace of 2^24 records takes 61 us
-// in k_filter_part (5.5 TB/s), 215 in k_filter_count, 17 in k_entries_sort; the
-// sort took 707 for the whole call.  A call of 1279 records takes 12, 10 and 4
-// us there and one synchronisation, 47 us in all; sorting took 102.
+// in k_filter_part (5.5 TB/s), 170 in k_filter_count, 19 in k_entries_sort; the
+// sort took 707 for the whole call.  A call of 1279 records takes 12 us in one
+// count kernel and one synchronisation, 35 us in all; sorting took 102.
 //   k_filter_begin  control words, tile -> trace and bucket -> trace tables
 //   k_filter_part   per 16384-record tile: group hashes, the tile's keys
 //                   ordered by hash bucket (writes and atomics of a bucket
@@ -219,17 +219,23 @@ __global__ __launch_bounds__(FNT, LGB <= 11 ? 8 : 4) void k_filter_part(FilterBu
 // word, from the buckets of several epochs) are added up by the host.
 
 // Workgroups of hot buckets: item i is (bucket, part).  They come first in the
-// grid.  (There is room for them: at most reads / hot_part buckets have two
-// parts or more, with as many further parts in all.)
+// grid, also those of one part: started among the others, a bucket that takes
+// four times as long ends long after them (215 us for a trace of 2^24 records,
+// 170 so).  Where the items run out, a bucket stays whole and
+// in its place.
+constexpr uint32_t NO_BUCKET = 0xFFFFFFFFu, HOT_ITEM = 1u << 31;
 __global__ __launch_bounds__(NT) void k_filter_plan(FilterBuffers f) {
   const uint32_t b = blockIdx.x * NT + threadIdx.x;
   if (b >= f.n_buckets) return;
-  const uint32_t parts = min(f.tr[f.bucket_trace[b]].ntiles, 1u + f.hot[b] / f.hot_part);
-  f.hot[b] = parts;
-  if (parts > 1) {
+  const uint32_t hot = f.hot[b], parts = min(f.tr[f.bucket_trace[b]].ntiles, 1u + hot / f.hot_part);
+  uint32_t word = 1;
+  if (hot > f.hot_part / 4) {
     const uint32_t at = atomicAdd(&f.cnt[FC_EXTRA], parts);
-    for (uint32_t k = 0; k < parts && at + k < f.extra_max; k++) f.extra[at + k] = make_uint2(b, k);
+    const bool room = at < f.extra_max && parts <= f.extra_max - at;
+    for (uint32_t k = 0; k < parts && at + k < f.extra_max; k++) f.extra[at + k] = make_uint2(room ? b : NO_BUCKET, k);
+    if (room) word = parts | HOT_ITEM;
   }
+  f.hot[b] = word;
 }
 
 // Four keys, or two row words, from any word on.
@@ -274,6 +280,7 @@ __global__ __launch_bounds__(FNT, 8) void k_filter_count(FilterBuffers f) {
   } else if (blockIdx.x < f.extra_max) {
     if (blockIdx.x >= f.cnt[FC_EXTRA]) return;
     const uint2 it = f.extra[blockIdx.x];
+    if (it.x == NO_BUCKET) return;
     bucket = it.x;
     part = it.y;
   } else {
@@ -284,8 +291,8 @@ __global__ __launch_bounds__(FNT, 8) void k_filter_count(FilterBuffers f) {
   auto uniform = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); };
   bucket = uniform(bucket);
   part = uniform(part);
-  const uint32_t parts = uniform(f.extra_max && !DIRECT ? f.hot[bucket] : 1u);
-  if (MODE == BY_BUCKET && parts > 1 && blockIdx.x >= f.extra_max) return;  // (its parts are items)
+  const uint32_t item = uniform(f.extra_max && !DIRECT ? f.hot[bucket] : 1u), parts = item & ~HOT_ITEM;
+  if (MODE == BY_BUCKET && (item & HOT_ITEM) && blockIdx.x >= f.extra_max) return;
   const uint32_t trace = DIRECT ? blockIdx.x : uniform(f.bucket_trace[bucket]);
   FTrace T = f.tr[trace];
   T.rec = (const void*)readfirstlane((uint64_t)T.rec);
