@@ -256,7 +256,7 @@ __global__ __launch_bounds__(FNT, 8) void k_filter_count(FilterBuffers f) {
   constexpr uint32_t NTH = FNT;
   constexpr uint32_t SB = FILTER_SLOT_BITS, W_WORDS = (1u << SB) / 32, D_WORDS = W_WORDS / 2, T_WORDS = W_WORDS / 4;
   constexpr uint32_t HN = 512, NONE = 0xFFFFu;  // chains of writes, and as many of atomics
-  constexpr uint32_t MAX_ROUNDS = 64, MAX_LEVEL = 5;
+  constexpr uint32_t MAX_ROUNDS = 64, MAX_LEVEL = 5, MANY_WRITERS = 16;
   constexpr uint32_t L_BITS = 14, L_WORDS = (1u << L_BITS) / 32;  // the maps of the thinning
   static_assert((MAX_LEVEL - 1 + 4) * L_WORDS <= W_WORDS, "they take W's place");
   __shared__ __align__(16) uint32_t s_map[W_WORDS + D_WORDS + T_WORDS];
@@ -267,6 +267,9 @@ __global__ __launch_bounds__(FNT, 8) void k_filter_count(FilterBuffers f) {
   __shared__ uint32_t s_acc[5][WCAP]; // pairs by kind of the location whose first write this is
   __shared__ uint32_t s_head[2 * HN];
   __shared__ uint16_t s_next[WCAP], s_lead[WCAP];
+  __shared__ uint32_t s_bhead[LATE ? HN : 1];   // chains of one location and block
+  __shared__ uint16_t s_bnext[LATE ? WCAP : 1];
+  __shared__ uint32_t s_tot[LATE ? WCAP : 1];   // writes | atomics << 16 of the location whose first write this is
   __shared__ uint32_t s_n, s_nw, s_any, s_base;
   const uint32_t tx = threadIdx.x;
   uint32_t bucket, part = 0;
@@ -683,6 +686,7 @@ __global__ __launch_bounds__(FNT, 8) void k_filter_count(FilterBuffers f) {
       });
     }
     for (uint32_t k = tx; k < 2 * HN; k += NTH) s_head[k] = NONE;
+    if (LATE && tx < HN) s_bhead[tx] = NONE;
     __syncthreads();
     const uint32_t nw = uniform(s_nw);  // (at most WCAP)
     if ((uint64_t)n_read * nw >= 1ull << 32) {  // sums of pairs are kept in 32 bits
@@ -691,6 +695,7 @@ __global__ __launch_bounds__(FNT, 8) void k_filter_count(FilterBuffers f) {
     }
     if (!nw) continue;
     auto chain_of = [&](const FRec& x, uint32_t bx) { return location_hash(x, bx) & (HN - 1); };
+    auto block_chain = [&](const FRec& x, uint32_t bx) { return mix32(location_hash(x, bx) + bx) & (HN - 1); };
 #pragma unroll 1
     for (uint32_t i = tx; i < nw; i += NTH) {
       const uint32_t idx = s_blk[i];
@@ -699,6 +704,10 @@ __global__ __launch_bounds__(FNT, 8) void k_filter_count(FilterBuffers f) {
       if (WARP) s_side[i] = f.side[T.off + idx];
       s_w[i] = make_uint4(x.ulo, x.uhi, x.tid, x.meta);
       s_blk[i] = bx;
+      if constexpr (LATE) {
+        s_tot[i] = 0;
+        s_bnext[i] = (uint16_t)atomicExch(&s_bhead[block_chain(x, bx)], i);
+      }
       s_next[i] = (uint16_t)atomicExch(&s_head[chain_of(x, bx) + (frec_action(x) == 2u ? HN : 0u)], i);
 #pragma unroll
       for (int q = 0; q < 5; q++) s_acc[q][i] = 0;
@@ -712,7 +721,7 @@ __global__ __launch_bounds__(FNT, 8) void k_filter_count(FilterBuffers f) {
       const FRec x = w_at(i);
       const uint32_t bx = s_blk[i], sx = WARP ? s_side[i] : 0u;
       const bool atomic = frec_action(x) == 2u;
-      uint32_t lead = i, ww = 0, aw = 0, xb = 0;
+      uint32_t lead = i, ww = 0, aw = 0, xb = 0, before = 0;
 #pragma unroll 1
       for (uint32_t j = s_head[chain_of(x, bx)]; j != NONE; j = s_next[j]) {
         if (!atomic && j >= i) continue;
@@ -720,6 +729,7 @@ __global__ __launch_bounds__(FNT, 8) void k_filter_count(FilterBuffers f) {
         const uint32_t by = s_blk[j];
         if (!same_location(x, bx, y, by)) continue;
         lead = lead == i ? j : min(lead, j);
+        before++;
         if (part == 0 && pair_races(x, bx, y, by, WARP, T.tpb, sx, WARP ? s_side[j] : 0u)) {
           if (atomic) aw++;
           else ww++;
@@ -727,11 +737,37 @@ __global__ __launch_bounds__(FNT, 8) void k_filter_count(FilterBuffers f) {
         }
       }
       s_lead[i] = (uint16_t)lead;
+      if (MODE == BY_BUCKET && before >= MANY_WRITERS) s_any = 2;
       if (ww) atomicAdd(&s_acc[K_WW][lead], ww);
       if (aw) atomicAdd(&s_acc[K_AW][lead], aw);
       if (xb) atomicAdd(&s_acc[K_XB][lead], xb);
     }
     __syncthreads();
+    // ---- many reads and a word of many writers: counted by a later workgroup,
+    //      per location and block.  (With 70 writers of the hottest word the
+    //      pairs one by one made a trace of 2^24 records take 668 us, 412 so.)
+    if (MODE == BY_BUCKET && f.late_max && rounds == 1 && n_read > RCAP && s_any == 2) {
+      if (tx == 0) {
+        const uint32_t at = atomicAdd(&f.cnt[FC_LATE], 1u);
+        if (at < f.late_max) f.late[at] = make_uint2(bucket, part);
+        s_base = at;
+      }
+      __syncthreads();
+      if (s_base < f.late_max) return;
+    }
+    if constexpr (LATE) {  // from here on the chains of writes hold their locations' first ones
+      if (tx < HN) s_head[tx] = NONE;
+      __syncthreads();
+#pragma unroll 1
+      for (uint32_t i = tx; i < nw; i += NTH) {
+        const FRec x = w_at(i);
+        const bool atomic = frec_action(x) == 2u;
+        const uint32_t lead = s_lead[i];
+        if (!atomic || lead != i) atomicAdd(&s_tot[lead], atomic ? 0x10000u : 1u);
+        if (!atomic && lead == i) s_next[i] = (uint16_t)atomicExch(&s_head[chain_of(x, s_blk[i])], i);
+      }
+      __syncthreads();
+    }
     // ---- the reads' pairs, summed per thread while the location stays the
     //      same (the lanes' LDS atomics to a hot word's sums go one by one)
     uint32_t lead = 0, rw = 0, ar = 0, xb = 0;
@@ -743,31 +779,68 @@ __global__ __launch_bounds__(FNT, 8) void k_filter_count(FilterBuffers f) {
     };
     auto count_read = [&](const FRec& x, uint32_t idx) {
       const uint32_t bx = block_of(x.tid, T.tpb, shift);
-      const uint32_t c = chain_of(x, bx);
-      uint32_t j = s_head[c], k = s_head[c + HN];
-      if (j == NONE) {
-        j = k;
-        k = NONE;
-      }
-      if (j == NONE) return;
-      const uint32_t sx = WARP ? f.side[T.off + idx] : 0u;
+      if constexpr (LATE) {  // all of the location's writes race but some of the read's own block's
+        const uint32_t c = chain_of(x, bx);
+        uint32_t j = s_head[c];
+        while (j != NONE && !same_location(x, bx, w_at(j), s_blk[j])) j = s_next[j];
+        if (j != NONE) {
+          uint32_t left = s_tot[j], own = 0;
 #pragma unroll 1
-      while (j != NONE) {
-        const uint32_t at = j;
-        j = s_next[j];
-        if (j == NONE) {  // the writes, then the atomics
+          for (uint32_t q = s_bhead[block_chain(x, bx)]; q != NONE; q = s_bnext[q]) {
+            const FRec y = w_at(q);
+            if (s_blk[q] != bx || !same_location(x, bx, y, bx)) continue;
+            own++;
+            if (!pair_races(x, bx, y, bx, WARP, T.tpb, WARP ? f.side[T.off + idx] : 0u, WARP ? s_side[q] : 0u))
+              left -= frec_action(y) == 1u ? 1u : 0x10000u;
+          }
+          if (left) {
+            if (j != lead) flush();
+            lead = j;
+            rw += left & 0xFFFFu;
+            ar += left >> 16;
+            xb += (s_tot[j] & 0xFFFFu) + (s_tot[j] >> 16) - own;
+          }
+          return;
+        }
+#pragma unroll 1
+        for (j = s_head[c + HN]; j != NONE; j = s_next[j]) {  // a location with atomics only
+          const FRec y = w_at(j);
+          const uint32_t by = s_blk[j];
+          if (!same_location(x, bx, y, by) ||
+              !pair_races(x, bx, y, by, WARP, T.tpb, WARP ? f.side[T.off + idx] : 0u, WARP ? s_side[j] : 0u))
+            continue;
+          if (j != lead) flush();
+          lead = j;
+          ar++;
+          if (bx != by) xb++;
+        }
+      } else {
+        const uint32_t c = chain_of(x, bx);
+        uint32_t j = s_head[c], k = s_head[c + HN];
+        if (j == NONE) {
           j = k;
           k = NONE;
         }
-        const FRec y = w_at(at);
-        const uint32_t by = s_blk[at];
-        if (!same_location(x, bx, y, by) || !pair_races(x, bx, y, by, WARP, T.tpb, sx, WARP ? s_side[at] : 0u)) continue;
-        const uint32_t l = s_lead[at];
-        if (l != lead) flush();
-        lead = l;
-        if (frec_action(y) == 1u) rw++;
-        else ar++;
-        if (bx != by) xb++;
+        if (j == NONE) return;
+        const uint32_t sx = WARP ? f.side[T.off + idx] : 0u;
+#pragma unroll 1
+        while (j != NONE) {
+          const uint32_t at = j;
+          j = s_next[j];
+          if (j == NONE) {  // the writes, then the atomics
+            j = k;
+            k = NONE;
+          }
+          const FRec y = w_at(at);
+          const uint32_t by = s_blk[at];
+          if (!same_location(x, bx, y, by) || !pair_races(x, bx, y, by, WARP, T.tpb, sx, WARP ? s_side[at] : 0u)) continue;
+          const uint32_t l = s_lead[at];
+          if (l != lead) flush();
+          lead = l;
+          if (frec_action(y) == 1u) rw++;
+          else ar++;
+          if (bx != by) xb++;
+        }
       }
     };
     if (n_read <= RCAP) {  // (in rounds, those of other slots meet no write here)
@@ -1059,7 +1132,7 @@ hipError_t launch_filter_count(const FilterBuffers& f, hipStream_t s) {
   hipLaunchKernelGGL((warp ? k_filter_count<BY_BUCKET, true, 860, 1408> : k_filter_count<BY_BUCKET, false, 940, 1408>), grid,
                      dim3(FNT), 0, s, f);
   if ((e = hipGetLastError()) != hipSuccess || !f.late_max) return e;
-  hipLaunchKernelGGL((warp ? k_filter_count<LATE_BUCKET, true, 860, 1408> : k_filter_count<LATE_BUCKET, false, 940, 1408>),
+  hipLaunchKernelGGL((warp ? k_filter_count<LATE_BUCKET, true, 750, 1152> : k_filter_count<LATE_BUCKET, false, 800, 1152>),
                      dim3(f.late_max), dim3(FNT), 0, s, f);
   return hipGetLastError();
 }

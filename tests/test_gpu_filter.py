@@ -167,6 +167,22 @@ def test_short_calls(ctx, sizes):
         check(ctx, recs, offsets(sizes), 256, f"{len(sizes)} short traces, writes {p_write}")
 
 
+@pytest.mark.parametrize("writers", [15, 16, 17, 70, 1100])
+@pytest.mark.parametrize("p_atomic", [0.0, 0.5])
+def test_hot_word_of_many_writers(ctx, writers, p_atomic):
+    """A word that many threads read and several write, some of them in one
+    block and epoch: the buckets a later workgroup counts."""
+    rng = np.random.default_rng(writers)
+    n = 1 << 19
+    recs = records(n, rng, blocks=40, p_write=0.02)
+    at = rng.permutation(n)[: n // 8]
+    recs["unit"][at], recs["space"][at], recs["action"][at] = 1 << 23, 0, READ
+    recs["action"][at[:writers]] = np.where(rng.random(writers) < p_atomic, ATOMIC, WRITE)
+    recs["tid"][at[: writers // 2]] = 5 * 256 + rng.integers(0, 8, writers // 2)
+    want = check(ctx, recs, offsets([n]), 256, f"{writers} writers, {p_atomic} atomic")
+    assert len(want) and want["pairs_rw"].max() > n // 16
+
+
 @pytest.mark.parametrize("writes", [300, 500, 2000, 3000, 20000])
 def test_rounds(ctx, writes):
     """More racing writes in one bucket than its table holds: rounds by slot,
