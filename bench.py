@@ -185,8 +185,9 @@ def pipeline(records_per_s, name, passes, stage_ms_per_step):
     scatter 24 per further pass, scan 8; with the grouped count 24)."""
     grouped = stage_ms_per_step.get("filter_part", 0.0) > 0.0
     built = 24 if grouped else 16 + 24 + 24 * max(0.0, passes - 1) + 8
-    return {"alg_bytes_per_record": B_ALG[name], "gbps": round(records_per_s * B_ALG[name] / 1e9, 1),
-            "frac": round(records_per_s * B_ALG[name] / 1e9 / HBM_PEAK_GBPS, 4), "radix_passes": passes,
+    alg = built if grouped else B_ALG[name]
+    return {"alg_bytes_per_record": alg, "gbps": round(records_per_s * alg / 1e9, 1),
+            "frac": round(records_per_s * alg / 1e9 / HBM_PEAK_GBPS, 4), "radix_passes": passes,
             "grouped_count": grouped, "built_bytes_per_record": built, "built_gbps": round(records_per_s * built / 1e9, 1),
             "kernel_ms_per_step": round(sum(stage_ms_per_step.values()), 4)}
 
