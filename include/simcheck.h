@@ -106,7 +106,8 @@ typedef struct sim_config {
 } sim_config;
 
 enum {
-  SIM_CFG_PROFILE = 1, /* record per-stage HIP events (see sim_stage_times); disables graphs */
+  SIM_CFG_PROFILE = 1, /* record per-stage HIP events (see sim_stage_times); disables graphs, and race
+                          checks of fewer than 2^20 records sort */
   SIM_CFG_GRAPHS = 2   /* capture each call's launch sequence as a HIP graph and replay it while
                           calls keep the same shape (records pointer, offsets, threads per block,
                           stream); needs a non-NULL stream */

@@ -554,9 +554,15 @@ void barrier_result_free(sim_barrier_result* r) {
   free(r);
 }
 
+constexpr uint64_t GROUP_ROOM = 16384;  // records a grouped call's buffers are sized for, at least
 int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_recs, const uint64_t* offsets,
                 uint32_t n_traces, const uint32_t* tpb, hipStream_t s, const Sink& sink, uint64_t total,
                 uint32_t n_tiles);
+// Its pinned block: the traces' table, the head, and the entries the kernels write there.
+size_t group_host_bytes(uint32_t n_traces, uint64_t records) {
+  const uint64_t entries = std::min<uint64_t>(std::max(records, GROUP_ROOM) / 16, GROUP_HOST_ENTRIES);
+  return ((size_t)n_traces * sizeof(FTrace) + 255) / 256 * 256 + 256 + entries * sizeof(RaceOut);
+}
 
 // A second stream of the context, and the events that tie it to a call's.
 hipError_t make_side_stream(sim_ctx* c) {
@@ -1178,10 +1184,10 @@ int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const
   auto up = [](uint64_t x) { return (x + 255) / 256 * 256; };
   const size_t tr_bytes = up(n_traces * sizeof(FTrace));
   // records the buffers are sized for: room for a few entries (a server's worker is charged for its own)
-  const uint64_t room = c->dev_limit ? total : std::max<uint64_t>(total, 16384);
+  const uint64_t room = c->dev_limit ? total : std::max(total, GROUP_ROOM);
   const uint64_t cap = room / 16;
   const uint32_t host_cap = (uint32_t)std::min<uint64_t>(cap, GROUP_HOST_ENTRIES);
-  hipError_t e = grow_host(c, tr_bytes + 256 + host_cap * sizeof(RaceOut));
+  hipError_t e = grow_host(c, group_host_bytes(n_traces, room));
   if (e != hipSuccess) return hip_fail(c, e, "pinned allocation");
   c->host_gen++;  // the tables of the previous call are overwritten
   FTrace* ht = (FTrace*)c->h_meta;
@@ -1496,7 +1502,8 @@ int sim_create(sim_ctx** out, int hip_device, const sim_config* cfg) {
     const uint32_t n_tr = cfg->reserve_traces ? cfg->reserve_traces : 1;
     const uint64_t tiles = (n_rec + TILE - 1) / TILE + n_tr;
     if (n_rec >= (1ull << 32) || tiles >= (1ull << 32) || ensure(c->records, n_rec * 16) ||
-        size_buffers(c, n_rec, n_tr, (uint32_t)tiles, tiles, 8, RADIX_MAX) != hipSuccess) {
+        size_buffers(c, std::max(n_rec, GROUP_ROOM), n_tr, (uint32_t)tiles, tiles, 8, RADIX_MAX) != hipSuccess ||
+        grow_host(c, group_host_bytes(n_tr, n_rec)) != hipSuccess) {
       sim_destroy(c);
       return SIM_ENOMEM;
     }
