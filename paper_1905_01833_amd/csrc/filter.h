@@ -123,5 +123,10 @@ SC_HD bool pair_races(const FRec& a, uint32_t blk_a, const FRec& b, uint32_t blk
   if (wa != wb || ((side_a | side_b) & SIDE_DIVERGED)) return true;
   return ca == 1u && cb == 1u && side_a == side_b;
 }
+// Whether every sum of pairs that a table of nw writes and atomics and n_read
+// reads can give stays below 2^32: a location's pairs of all kinds together
+// (the cross-block pairs hold them all) are the reads' with the table and the
+// table's among themselves.
+SC_HD bool pair_sums_fit(uint32_t n_read, uint32_t nw) { return ((uint64_t)n_read + nw) * nw < 1ull << 32; }
 
 }  // namespace sc

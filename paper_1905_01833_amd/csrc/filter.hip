@@ -689,7 +689,7 @@ __global__ __launch_bounds__(FNT, 8) void k_filter_count(FilterBuffers f) {
     if (LATE && tx < HN) s_bhead[tx] = NONE;
     __syncthreads();
     const uint32_t nw = uniform(s_nw);  // (at most WCAP)
-    if ((uint64_t)n_read * nw >= 1ull << 32) {  // sums of pairs are kept in 32 bits
+    if (!pair_sums_fit(n_read, nw)) {  // sums of pairs are kept in 32 bits
       if (tx == 0) atomicOr(&f.ctrl->error_flags, ERR_GROUP_FULL);
       return;
     }

@@ -485,3 +485,19 @@ extern "C" uint64_t hs_filter_most(const rec* recs, uint64_t n, uint32_t lgb) {
   for (uint64_t i = 0; i < n; i++) c[filter_bucket(filter_group(recs[i].unit, 0, recs[i].epoch, recs[i].space), lgb)]++;
   return *std::max_element(c.begin(), c.end());
 }
+
+// Sums of pairs that the guard lets through but that do not fit 32 bits: a
+// location that n_read reads of other blocks and all nw writes of the table
+// (of as many blocks) share, for reads on both sides of the guard's line.
+extern "C" int hs_pair_sums(uint32_t nw_max) {
+  int bad = 0;
+  for (uint32_t nw = 1; nw <= nw_max; nw++) {
+    uint64_t r = (1ull << 32) / nw + 2;  // the line lies at or below this
+    if (r > 0xFFFFFFFFull) r = 0xFFFFFFFFull;
+    for (uint32_t k = 0; k < 4 * nw + 8 && r; k++, r--) {
+      const uint64_t xb = r * nw + (uint64_t)nw * (nw - 1) / 2;
+      if (pair_sums_fit((uint32_t)r, nw) && xb >= 1ull << 32) bad++;
+    }
+  }
+  return bad + (pair_sums_fit(1000000, 940) ? 0 : 1);
+}

@@ -89,3 +89,12 @@ def test_strided_words_spread_over_buckets(step):
     for lgb in (4, 8):
         mean = n / (1 << lgb)
         assert lib.hs_filter_most(r.ctypes.data, n, lgb) < mean + 6 * mean ** 0.5, (step, lgb)
+
+
+def test_guard_covers_every_sum_of_pairs():
+    """The cross-block sum of a location holds its reads' pairs with all of the
+    table and the table's own pairs: no call just below the guard wraps it."""
+    lib = _hostsim()
+    lib.hs_pair_sums.restype = ctypes.c_int
+    lib.hs_pair_sums.argtypes = [ctypes.c_uint32]
+    assert lib.hs_pair_sums(1024) == 0
