@@ -107,7 +107,9 @@ typedef struct sim_config {
 
 enum {
   SIM_CFG_PROFILE = 1, /* record per-stage HIP events (see sim_stage_times); disables graphs, and race
-                          checks of fewer than 2^20 records sort */
+                          checks of fewer than 2^20 records sort, unless the default shape (all
+                          fields 0) is set for their size class (sim_set_tuning): they then run, and
+                          are timed, as without the flag */
   SIM_CFG_GRAPHS = 2   /* capture each call's launch sequence as a HIP graph and replay it while
                           calls keep the same shape (records pointer, offsets, threads per block,
                           stream); needs a non-NULL stream */
@@ -386,6 +388,11 @@ const char* sim_stage_name(int stage);
 /* ----------------------------------------------------------------- tuning */
 
 /* Launch shape of the tile kernels (tiles are 4096 records of one trace).
+ * The kernels are those that sort a call's records.  Barrier and fitness
+ * checks, no-allocation calls and calls with a trace of more than 2^27
+ * records always run them; other race checks count their races by group
+ * without sorting, except where their size class has a shape with a field
+ * set: that asks for the sort in this shape.
  * Shapes change speed only: every shape gives the same result.  A context
  * keeps one shape per size class; class k covers calls of 2^(k-1) ..
  * 2^k - 1 records in total (k = 0 .. 32, see sim_size_class).  A call uses
@@ -429,7 +436,10 @@ int sim_get_tuning(const sim_ctx* ctx, uint32_t size_class, sim_tuning* t);
  * `reps` calls (0: 3; at least 5 when a call takes under 10 ms) taking turns
  * with as many calls of the current shape, so that a drift of the GPU's
  * speed during tuning reaches both; it replaces the current shape only when
- * its fastest call is at least 0.5 % faster than the current shape's.  The
+ * its fastest call is at least 0.5 % faster than the current shape's.  At
+ * last the shape found is timed against a call without one, where that does
+ * not sort: if it is no slower, the default shape (all fields 0) is chosen,
+ * and ms is its time.  The
  * chosen shape is stored for the input's size class and written to *best.
  * Results of the trial calls are discarded; on error the class keeps its
  * old shape.                                                               */

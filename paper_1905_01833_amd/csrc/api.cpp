@@ -300,6 +300,12 @@ uint32_t size_class(uint64_t total) {
   return k < SIM_SIZE_CLASSES ? k : SIM_SIZE_CLASSES - 1;
 }
 
+// Whether a tuning says anything about the sort's launches.
+bool has_shape(const sim_tuning& t) {
+  return t.stream_wgs_per_cu || t.sort_wgs_per_cu || t.scan_wgs_per_cu || t.group_shift_bias || t.scatter_threads ||
+         t.digit_bits;
+}
+
 // Launch shape of a call of `total` records: the forced candidate while
 // autotuning, else the shape of its size class, else of the nearest tuned
 // class, else one workgroup per tile and no group-size bias.
@@ -465,11 +471,15 @@ struct Sink {
 constexpr uint64_t GROUP_MAX_RECORDS = 1ull << 27;
 static_assert(GROUP_MAX_RECORDS <= FILTER_MAX_RECORDS, "the longest trace the buckets are made for");
 // A profiling context sorts calls of fewer records: its users read the sorting
-// pipeline's passes from the stage times of such calls.
+// pipeline's passes from the stage times of such calls.  (With the default
+// shape set for their class such calls are counted and profiled by group.)
 constexpr uint64_t GROUP_MIN_PROFILED = 1ull << 20;
 bool group_pays(const sim_ctx* c, const uint64_t* offsets, uint32_t n_traces, uint64_t total) {
-  if (c->force || n_traces > GROUP_MAX_TRACES) return false;  // (tuning times the sort)
-  if (total == 0 || ((c->flags & SIM_CFG_PROFILE) && total < GROUP_MIN_PROFILED)) return false;
+  if (c->force || total == 0 || n_traces > GROUP_MAX_TRACES) return false;  // (a forced shape is the sort's)
+  // A shape set for the call's size class asks for the sort it shapes; the
+  // default shape, set, for what the call takes without one, profiled or not.
+  const uint32_t cls = size_class(total);
+  if (c->tuned[cls] ? has_shape(c->tuning[cls]) : (c->flags & SIM_CFG_PROFILE) && total < GROUP_MIN_PROFILED) return false;
   for (uint32_t i = 0; i < n_traces; i++)
     if (offsets[i + 1] - offsets[i] > GROUP_MAX_RECORDS) return false;
   return true;
@@ -1802,9 +1812,12 @@ int sim_autotune(sim_ctx* c, const sim_record* d_records, const uint64_t* offset
   const uint32_t saved_flags = c->flags;
   c->flags &= ~(uint32_t)(SIM_CFG_GRAPHS | SIM_CFG_PROFILE);  // plain launches, timed on the host
   hipStream_t s = (hipStream_t)stream;
-  // wall time of one complete call with shape t
-  auto one_call = [&](const sim_tuning& t, double* ms) -> int {
-    c->force = &t;
+  // wall time of one complete call with shape t (nullptr: none, whatever path the call then takes)
+  const uint32_t cls = size_class(total);
+  auto one_call = [&](const sim_tuning* t, double* ms) -> int {
+    c->force = t;
+    const bool was_tuned = c->tuned[cls];
+    if (!t) c->tuned[cls] = false;
     sim_result* res = nullptr;
     const auto t0 = std::chrono::steady_clock::now();
     Sink sink;
@@ -1812,6 +1825,7 @@ int sim_autotune(sim_ctx* c, const sim_record* d_records, const uint64_t* offset
     const int rc1 = run(c, d_records, nullptr, offsets, n_traces, threads_per_block, s, sink, false);
     const auto t1 = std::chrono::steady_clock::now();
     c->force = nullptr;
+    c->tuned[cls] = was_tuned;
     sim_result_free(res);
     *ms = std::chrono::duration<double, std::milli>(t1 - t0).count();
     return rc1;
@@ -1820,7 +1834,7 @@ int sim_autotune(sim_ctx* c, const sim_record* d_records, const uint64_t* offset
   // turns (so that a drift of the GPU's speed during tuning, from clocks or
   // caches, reaches both alike); the work is deterministic: noise only adds
   // time
-  auto measure_pair = [&](const sim_tuning& a, const sim_tuning& b2, double* ms_a, double* ms_b) -> int {
+  auto measure_pair = [&](const sim_tuning* a, const sim_tuning* b2, double* ms_a, double* ms_b) -> int {
     *ms_a = *ms_b = 1e300;
     for (uint32_t r = 0; r < reps; r++) {
       double x = 0;
@@ -1838,8 +1852,9 @@ int sim_autotune(sim_ctx* c, const sim_record* d_records, const uint64_t* offset
   sim_tuning cur{0, 0, 0, 0, 0, 0, 0.0};
   double cur_ms = 0;
   double warm = 0;
-  rc = one_call(cur, &warm);  // buffers, pass count, digit width
-  if (!rc) rc = one_call(cur, &warm);
+  const bool was_tuned = c->tuned[cls];
+  rc = one_call(&cur, &warm);  // buffers, pass count, digit width
+  if (!rc) rc = one_call(&cur, &warm);
   // short calls are noisier: at least 5 repetitions below 10 ms
   if (!rc && warm < 10.0 && reps < 5) reps = 5;
   // coordinate descent over the five knobs, one at a time
@@ -1856,7 +1871,7 @@ int sim_autotune(sim_ctx* c, const sim_record* d_records, const uint64_t* offset
       if (knob == 3) t.group_shift_bias = bias0 + kBias[q];
       if (knob == 4) t.scatter_threads = scatter_threads(cur, n_tiles) == 512 ? 256 : 512;  // the other shape
       double ms = 0, base = 0;
-      rc = measure_pair(cur, t, &base, &ms);
+      rc = measure_pair(&cur, &t, &base, &ms);
       if (!rc && ms < base * 0.995) {  // a shape must win beyond the noise to replace the current one
         cur = t;
         cur_ms = ms;
@@ -1865,10 +1880,28 @@ int sim_autotune(sim_ctx* c, const sim_record* d_records, const uint64_t* offset
       }
     }
   }
+  // the default path, where it is another one: stored as the default shape,
+  // which every other call of the class then takes; a sort in its default
+  // shape that beats it is stored with the scatter's threads spelled out
+  c->tuned[cls] = false;
+  const bool other = !rc && group_pays(c, offsets, n_traces, total);
+  c->tuned[cls] = was_tuned;
+  if (other) {
+    double ms = 0, base = 0;
+    c->group_pause[KIND_PLAIN] = 0;
+    rc = one_call(nullptr, &warm);  // (buffers)
+    if (!rc) rc = measure_pair(&cur, nullptr, &base, &ms);
+    if (!rc && ms <= base) {
+      cur = sim_tuning{0, 0, 0, 0, 0, 0, 0.0};
+      cur_ms = ms;
+    } else if (!rc) {
+      cur_ms = base;
+      if (!has_shape(cur)) cur.scatter_threads = scatter_threads(cur, n_tiles);
+    }
+  }
   c->flags = saved_flags;
   if (rc) return rc;
   cur.ms = cur_ms;
-  const uint32_t cls = size_class(total);
   c->tuning[cls] = cur;
   c->tuned[cls] = true;
   c->tuning_gen++;

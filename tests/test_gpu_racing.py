@@ -1,0 +1,99 @@
+"""Traces that race heavily: entries and summaries equal the oracle's, and a
+call costs about what sorting its records costs, or less, whatever the words
+that race look like (many writers and readers of a word, words written by
+every thread, histograms, as many racing locations as there are words)."""
+import time
+
+import numpy as np
+import pytest
+
+import oracle
+from tracegen import ATOMIC, READ, RECORD_DTYPE, WRITE
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+HOT = 1 << 40
+
+
+def private(n, rng, tpb=256):
+    """A trace that does not race: a quarter of the records write words of
+    their own, the others read a region that nobody writes."""
+    r = np.zeros(n, dtype=RECORD_DTYPE)
+    i = np.arange(n)
+    k = -(-n // (max(1, n // (tpb * 64)) * tpb))
+    r["tid"] = i // (tpb * k) * tpb + i % tpb
+    w = rng.random(n) < 0.25
+    r["action"] = np.where(w, WRITE, READ)
+    r["unit"] = np.where(w, (1 << 24) + i, rng.integers(0, 1 << 24, n))
+    return r
+
+
+def writers(n, rng, count, readers):
+    """`count` threads write one word, `readers` records read it."""
+    r = private(n, rng)
+    at = rng.permutation(n)[: count + readers]
+    r["unit"][at] = HOT
+    r["action"][at] = np.where(np.arange(len(at)) < count, WRITE, READ)
+    return r
+
+
+def call(ctx, dev, side=None):
+    torch.cuda.synchronize()
+    t = time.perf_counter()
+    if side is None:
+        got = ctx.check_traces_device(dev, None, 256)
+    else:
+        got = ctx.check_traces_warp_device(dev, side, None, 256)
+    return got, time.perf_counter() - t
+
+
+def compare(name, recs, clean, limit, warp=False):
+    """The oracle's result, on a context's first call after one that did not
+    race, and at most `limit` times what the call that sorts takes (the least
+    of a few tries each)."""
+    import paper_1905_01833_amd as pkg
+
+    print(f"[gpu] racing, {name}: {len(recs)} records", flush=True)
+    dev, cdev = (torch.from_numpy(np.ascontiguousarray(r).view(np.uint8).reshape(-1, 16)).to("cuda:0") for r in (recs, clean))
+    side = dside = None
+    if warp:
+        side = (np.arange(len(recs)) % 7).astype(np.uint32)
+        dside = torch.from_numpy(side.view(np.int32)).to("cuda:0")
+        want, wsum = oracle.closed_form_warp(recs, side, None, 256)
+    else:
+        want, wsum = oracle.closed_form_par(recs, tpb=256)
+    first, sort = [], []
+    for _ in range(4):
+        c = pkg.Context(0)
+        try:
+            call(c, cdev, dside)
+            for k in range(3):
+                (got, gsum), t = call(c, dev, dside)
+                assert got.tobytes() == want.tobytes() and gsum.tobytes() == wsum.tobytes(), (name, k)
+                if k == 0:
+                    first.append(t)
+            for k in range(3):
+                torch.cuda.synchronize()
+                t = time.perf_counter()
+                got, _, _ = c.check_sync_device(dev, None, 256)
+                sort.append(time.perf_counter() - t)
+        finally:
+            c.close()
+    print(f"[gpu] {name}: {min(first) * 1e6:.0f} us, sorted {min(sort) * 1e6:.0f}, {len(want)} locations", flush=True)
+    assert min(first) < limit * min(sort), (name, min(first), min(sort))
+    return want
+
+
+@pytest.mark.parametrize("warp", [False, True])
+@pytest.mark.parametrize("log2", [10, 12, 13, 14, 16, 18, 20])
+@pytest.mark.parametrize("count", [17, 100, 800])
+def test_many_writers(log2, count, warp):
+    """A word that many threads write and a fifth of the records read: in a
+    trace counted from its records, one bucket, several, several parts."""
+    rng = np.random.default_rng(log2)
+    n = (1 << log2) - 3
+    count = min(count, n // 8)
+    want = compare(f"{count} writers of a word, 2^{log2}", writers(n, rng, count, n // 5), private(n, rng), 4.0, warp)
+    assert len(want) >= 1 and int(want["pairs_rw"].max()) > n // 100
