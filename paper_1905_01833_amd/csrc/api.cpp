@@ -1221,7 +1221,13 @@ int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const
   // a bucket is split only where a tile's run of one of at least 8 buckets is far above the usual
   const uint32_t hot_part = (uint32_t)std::max<uint64_t>(HOT_PART, total / HOT_SHARE);
   const uint32_t extra_max = max_lgb < 3 ? 0u : (uint32_t)((std::min<uint64_t>(total / FILTER_BUCKET, HOT_MAX_ITEMS) + 8) / 8 * 8);
-  const uint32_t late_max = tiles > 16 ? std::min(tiles, 1024u) : 0u;
+  const bool direct = longest <= GROUP_DIRECT_RECORDS;
+  // The later workgroups: always launched in calls of more than 16 tiles; in
+  // smaller ones (where an idle launch is 4 of 55 us) once the host sees that
+  // there is work for them.
+  const bool late_wait = direct || tiles <= 16;
+  const uint32_t late_max = std::min(direct ? n_traces : (late_wait ? buckets + extra_max : tiles), 1024u);
+  if (direct) rows = 0;
   const uint64_t rows_at = up(4 * room), extra_at = up(rows_at + 4 * rows),
                  late_at = extra_at + 8ull * extra_max;
   if (cap < 1 || late_at + 8ull * late_max > half ||
@@ -1242,7 +1248,7 @@ int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const
   f.n_traces = n_traces;
   f.n_tiles = tiles;
   f.n_buckets = buckets;
-  f.direct = longest <= GROUP_DIRECT_RECORDS;
+  f.direct = direct ? 1u : 0u;
   f.cnt = words;
   f.tile_trace = words + FC_COUNT;
   f.bucket_trace = f.tile_trace + tiles;
@@ -1257,6 +1263,7 @@ int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const
   f.hot_part = hot_part;
   f.late = (uint2*)(k0 + late_at);
   f.late_max = late_max;
+  f.late_wait = late_wait ? 1u : 0u;
   f.max_lgb = max_lgb;
   f.side = sink.side;
   f.entries = (RaceOut*)k1;
@@ -1275,6 +1282,12 @@ int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const
   if ((e = mark(0)) || (e = launch_filter_part(f, s)) || (e = mark(1)) || (e = launch_filter_count(f, s)) ||
       (e = mark(2)) || (e = launch_filter_out(f, s)) || (e = mark(3)) || (e = hipStreamSynchronize(s)))
     return hip_fail(c, e, "grouped count");
+  if (!head->error_flags && head->late) {
+    f.late_wait = 0;
+    if ((e = launch_filter_late(f, head->late, s)) || (e = mark(2)) || (e = launch_filter_out(f, s)) || (e = mark(3)) ||
+        (e = hipStreamSynchronize(s)))
+      return hip_fail(c, e, "grouped count");
+  }
   if (prof)
     for (int k = 0; k < 3; k++) {
       float ms = 0;

@@ -8,7 +8,7 @@
 // such a group or alone in it.  Records are put into buckets by a hash of
 // their group; bitmaps over a bucket's groups then leave the few writes and
 // atomics that may have a partner, and the reads that may be one, and their
-// pairs are counted one by one.
+// pairs are counted one by one, or, for words of many writers, by group.
 //
 // Types and hash functions shared by the kernels (filter.hip), the host
 // runtime (api.cpp) and the CPU tests.
@@ -97,9 +97,35 @@ SC_HD uint32_t frec_space(const FRec& a) { return (a.meta >> 18) & 1u; }
 SC_HD bool same_location(const FRec& a, uint32_t blk_a, const FRec& b, uint32_t blk_b) {
   return a.ulo == b.ulo && a.uhi == b.uhi && ((a.meta ^ b.meta) & (1u << 18)) == 0 && (frec_space(a) == 0 || blk_a == blk_b);
 }
+// A location's records fall into groups, each level's inside the one before: the
+// location, its block's records, their epoch's, their thread's.  Two records race
+// if their actions conflict and they share a group of level 0 but none of level 1,
+// or one of level 2 but none of level 3; so counts per group give the pairs,
+// signed + - + - over the levels, without a look at any pair.  GROUP_WARP: the
+// records of one warp inside a group of level 2.
+constexpr uint32_t GROUP_LEVELS = 4, GROUP_WARP = 4;
+SC_HD uint32_t warp_of(const FRec& a, uint32_t blk, uint32_t tpb) { return (a.tid - blk * tpb) >> 5; }
+SC_HD bool same_group(uint32_t level, const FRec& a, uint32_t blk_a, const FRec& b, uint32_t blk_b, uint32_t tpb) {
+  if (!same_location(a, blk_a, b, blk_b)) return false;
+  if (level >= 1 && blk_a != blk_b) return false;
+  if (level >= 2 && ((a.meta ^ b.meta) & 0xFFFFu) != 0) return false;
+  if (level == 3) return a.tid == b.tid;
+  return level != GROUP_WARP || warp_of(a, blk_a, tpb) == warp_of(b, blk_b, tpb);
+}
+// Hash of a record's group: of level 0, and of a level from that of the level
+// it lies in (the one before; level 2 for GROUP_WARP).
 SC_HD uint32_t location_hash(const FRec& a, uint32_t blk) {
   return mix32(a.ulo * 0x9E3779B1u ^ mix32(a.uhi + (frec_space(a) ? blk * 0xC2B2AE3Du + 1u : 0u)));
 }
+SC_HD uint32_t group_hash(uint32_t level, uint32_t h, const FRec& a, uint32_t blk, uint32_t tpb) {
+  const uint32_t v = level == 1 ? blk : (level == 2 ? a.meta & 0xFFFFu : (level == 3 ? a.tid : ~warp_of(a, blk, tpb)));
+  return mix32(h + v * 0x9E3779B1u + level);
+}
+// Writes and atomics of a group in one word, and the pairs among them.
+SC_HD uint32_t group_one(const FRec& a) { return frec_action(a) == 1u ? 1u : 0x10000u; }
+SC_HD uint32_t pairs_ww(uint32_t c) { return (c & 0xFFFFu) * ((c & 0xFFFFu) - 1u) / 2u; }
+SC_HD uint32_t pairs_aw(uint32_t c) { return (c & 0xFFFFu) * (c >> 16); }
+
 // Further hashes of a record's group, level 0, 1, ...: groups that share one
 // or filter_group's need not share another.
 SC_HD uint32_t filter_group2(const FRec& a, uint32_t blk, uint32_t level) {

@@ -200,9 +200,10 @@ __global__ __launch_bounds__(FNT, LGB <= 11 ? 8 : 4) void k_filter_part(FilterBu
 // location's.  Group hashes may collide: that only adds candidates, the pairs
 // are tested on the records themselves.
 //
-// The table holds WCAP writes and atomics.  A bucket with more is counted in
-// rounds, by slot.  Where that does not help (a hot atomic word whose slot
-// holds an unrelated write or read by chance), the candidates are thinned out
+// Where the chains get long, or the table of WCAP writes and atomics does not
+// hold them, a later workgroup counts the bucket (see LATE_BUCKET), in rounds,
+// by slot, if need be.  Where that does not help (a hot atomic word whose slot
+// holds an unrelated write or read by chance), it thins out the candidates
 // first: their records are read and hashed anew into maps of the same kind,
 // up to five times, and those that meet no partner there are dropped.
 //
@@ -249,14 +250,28 @@ __device__ __forceinline__ words2 load_words2(GWords p) { return *(const __attri
 // per trace, which reads the records itself, keeps their keys in record order
 // and makes the passes over those.  A call of 1279 records took 12 us in
 // k_filter_part and 12 here, and takes 12 so (47 and 36 us in all).
-enum : int { BY_BUCKET = 0, LATE_BUCKET = 1, DIRECT_TRACE = 2 };
+//
+// LATE_BUCKET and LATE_TRACE count what the other two hand over: buckets or
+// traces with more candidates than a table holds, with a word of many writers or
+// with long chains.  The others walk the chains of their table's records by
+// location, which costs least where nearly all have no partner or one, and stop
+// at CHAIN steps (MANY_WRITERS where the bucket has many reads); the late ones count by group (filter.h,
+// GROUP_LEVELS), one look-up per level and read however many wrote the word.
+// (800 writers and 3276 readers of a word in a trace of 2^14 records took 3309 us
+// by chains, 100 so.)  They take a CU each, with twice the registers.
+enum : int { BY_BUCKET = 0, LATE_BUCKET = 1, DIRECT_TRACE = 2, LATE_TRACE = 3 };
 template <int MODE, bool WARP, uint32_t WCAP, uint32_t RCAP>
-__global__ __launch_bounds__(FNT, 8) void k_filter_count(FilterBuffers f) {
-  constexpr bool LATE = MODE == LATE_BUCKET, DIRECT = MODE == DIRECT_TRACE;
+__global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_count(FilterBuffers f) {
+  constexpr bool LATE = MODE & LATE_BUCKET, DIRECT = MODE & DIRECT_TRACE;
   constexpr uint32_t NTH = FNT;
   constexpr uint32_t SB = FILTER_SLOT_BITS, W_WORDS = (1u << SB) / 32, D_WORDS = W_WORDS / 2, T_WORDS = W_WORDS / 4;
-  constexpr uint32_t HN = 512, NONE = 0xFFFFu;  // chains of writes, and as many of atomics
-  constexpr uint32_t MAX_ROUNDS = 64, MAX_LEVEL = 5, MANY_WRITERS = 16;
+  constexpr uint32_t HN = 512, END = 0xFFFFu;  // chains of writes, and as many of atomics
+  constexpr uint32_t MANY_WRITERS = 16, CHAIN = 64;
+  constexpr uint32_t HT = 8192, NONE = 0xFFFFFFFFu;  // the table of groups: index | level << 16
+  constexpr uint32_t LEVELS = WARP ? GROUP_LEVELS + 1 : GROUP_LEVELS, WARP_WALK = 64;
+  static_assert(LEVELS * WCAP < HT, "a free place in the table");
+  static_assert(WCAP <= NTH, "a thread per entry of the table");
+  constexpr uint32_t MAX_ROUNDS = 64, MAX_LEVEL = 5;
   constexpr uint32_t L_BITS = 14, L_WORDS = (1u << L_BITS) / 32;  // the maps of the thinning
   static_assert((MAX_LEVEL - 1 + 4) * L_WORDS <= W_WORDS, "they take W's place");
   __shared__ __align__(16) uint32_t s_map[W_WORDS + D_WORDS + T_WORDS];
@@ -264,22 +279,27 @@ __global__ __launch_bounds__(FNT, 8) void k_filter_count(FilterBuffers f) {
   __shared__ uint4 s_w[WCAP];
   __shared__ uint32_t s_blk[WCAP];    // their blocks; before them their record indices
   __shared__ uint32_t s_side[WARP ? WCAP : 1];
-  __shared__ uint32_t s_acc[5][WCAP]; // pairs by kind of the location whose first write this is
-  __shared__ uint32_t s_head[2 * HN];
-  __shared__ uint16_t s_next[WCAP], s_lead[WCAP];
-  __shared__ uint32_t s_bhead[LATE ? HN : 1];   // chains of one location and block
-  __shared__ uint16_t s_bnext[LATE ? WCAP : 1];
-  __shared__ uint32_t s_tot[LATE ? WCAP : 1];   // writes | atomics << 16 of the location whose first write this is
+  __shared__ uint32_t s_acc[5][WCAP]; // pairs by kind of the location whose first one this is
+  __shared__ uint16_t s_lead[WCAP];   // the first one of its location
+  __shared__ uint16_t s_next[WCAP];   // the next of its chain (late: of its warp's group)
+  constexpr uint32_t LCAP = LATE ? WCAP : 1;
+  __shared__ uint32_t s_cnt[LEVELS][LCAP];  // writes | atomics << 16 of the group whose first one this is
+  __shared__ uint32_t s_whead[WARP ? LCAP : 1];  // undiverged members of a warp's group
+  __shared__ uint32_t s_cls[MAX_ROUNDS];
+  __shared__ __align__(16) uint32_t tab[LATE ? HT : 4];
   __shared__ uint32_t s_n, s_nw, s_any, s_base;
   const uint32_t tx = threadIdx.x;
-  uint32_t bucket, part = 0;
-  if (DIRECT) {
+  uint32_t bucket, part = 0, trace = 0;
+  if (LATE) {
+    if (blockIdx.x >= f.cnt[FC_LATE]) return;
+    const uint2 it = f.late[blockIdx.x];
+    bucket = DIRECT ? 0u : it.x;
+    trace = it.x;
+    part = it.y;
+  } else if (DIRECT) {
     if (!f.tr[blockIdx.x].n) return;
     bucket = 0;
-  } else if (LATE) {
-    if (blockIdx.x >= f.cnt[FC_LATE]) return;
-    bucket = f.late[blockIdx.x].x;
-    part = f.late[blockIdx.x].y;
+    trace = blockIdx.x;
   } else if (blockIdx.x < f.extra_max) {
     if (blockIdx.x >= f.cnt[FC_EXTRA]) return;
     const uint2 it = f.extra[blockIdx.x];
@@ -296,7 +316,7 @@ __global__ __launch_bounds__(FNT, 8) void k_filter_count(FilterBuffers f) {
   part = uniform(part);
   const uint32_t item = uniform(f.extra_max && !DIRECT ? f.hot[bucket] : 1u), parts = item & ~HOT_ITEM;
   if (MODE == BY_BUCKET && (item & HOT_ITEM) && blockIdx.x >= f.extra_max) return;
-  const uint32_t trace = DIRECT ? blockIdx.x : uniform(f.bucket_trace[bucket]);
+  trace = uniform(DIRECT ? trace : f.bucket_trace[bucket]);
   FTrace T = f.tr[trace];
   T.rec = (const void*)readfirstlane((uint64_t)T.rec);
   T.n = readfirstlane(T.n);
@@ -469,7 +489,7 @@ __global__ __launch_bounds__(FNT, 8) void k_filter_count(FilterBuffers f) {
         if (!(k[u] & FILTER_ATOMIC) && !bit(D, sd)) set(D, sd);
       }
   };
-  if constexpr (DIRECT) {  // the records: their keys (slot | action), and the writes among them
+  if constexpr (MODE == DIRECT_TRACE) {  // the records: their keys (slot | action), and the writes among them
     constexpr uint32_t Q = 8;  // records in flight per thread
     const GRecords p = global_records(T.rec);
     const uint32_t shift = block_shift(T.tpb), n = (uint32_t)T.n;
@@ -570,145 +590,118 @@ __global__ __launch_bounds__(FNT, 8) void k_filter_count(FilterBuffers f) {
     append(k, pick, base, s_blk, WCAP, &s_nw);
   });
   __syncthreads();
-  static_assert(MAX_ROUNDS == 64, "a lane per round");
-  uint32_t rounds = 1, level = 0;
+  const uint32_t n_left = uniform(s_nw);
+  auto to_late = [&]() {  // by one thread
+    const uint32_t at = atomicAdd(&f.cnt[FC_LATE], 1u);
+    if (at < f.late_max) f.late[at] = make_uint2(DIRECT ? trace : bucket, part);
+    else atomicOr(&f.ctrl->error_flags, ERR_GROUP_FULL);
+  };
+  auto full = [&]() {
+    if (tx == 0) atomicOr(&f.ctrl->error_flags, ERR_GROUP_FULL);
+  };
+  // the reads' pairs, summed per thread while the location stays the same (the
+  // lanes' LDS atomics to a hot word's sums go one by one)
+  uint32_t lead = 0, rw = 0, ar = 0, xb = 0;
+  auto flush = [&]() {
+    if (rw) atomicAdd(&s_acc[K_RW][lead], rw);
+    if (ar) atomicAdd(&s_acc[K_AR][lead], ar);
+    if (xb) atomicAdd(&s_acc[K_XB][lead], xb);
+    rw = ar = xb = 0;
+  };
+  auto flush_wave = [&]() {
+    const uint64_t has = __ballot((rw | ar) != 0);
+    if (!has) return;
+    const uint32_t l = readlane(lead, (int)__builtin_ctzll(has));
+    if (__all((rw | ar) == 0 || lead == l)) {  // one location: one lane adds for the wave
+      auto add = [](uint32_t a, uint32_t c) { return a + c; };
+      rw = wave_reduce(rw, 0u, add);
+      ar = wave_reduce(ar, 0u, add);
+      xb = wave_reduce(xb, 0u, add);
+      lead = l;
+      if (__lane_id() == 0) flush();
+      rw = ar = xb = 0;
+    } else {
+      flush();
+    }
+  };
+  // an entry per location with pairs (all threads; the sums are complete)
+  auto paired = [&](uint32_t i) { return (s_acc[K_WW][i] | s_acc[K_RW][i] | s_acc[K_AW][i] | s_acc[K_AR][i]) != 0; };
+  auto emit = [&](uint32_t nw) {
+    const uint32_t i = threadIdx.x;
+    if (i == 0) s_n = 0;
+    __syncthreads();
+    const bool racing = i < nw && s_lead[i] == i && paired(i);
+    const uint64_t mask = __ballot(racing);
+    uint32_t pos = 0;
+    if (mask) {
+      if (__lane_id() == 0) pos = atomicAdd(&s_n, (uint32_t)__popcll(mask));
+      pos = (uint32_t)__builtin_amdgcn_readfirstlane((int)pos) + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+    }
+    __syncthreads();
+    const uint32_t n_new = s_n;
+    if (!n_new) return;
+    if (i == 0) {
+      s_base = atomicAdd(&f.cnt[FC_ENTRIES], n_new);
+      if (s_base + n_new > f.entries_cap) atomicOr(&f.ctrl->error_flags, ERR_GROUP_FULL);
+      const uint32_t in_trace = atomicAdd(&f.trace_cnt[trace], n_new) + n_new;
+      if (in_trace > SORT_CHUNK) atomicMax(&f.cnt[FC_MOST], in_trace);
+    }
+    __syncthreads();
+    if (racing && s_base + n_new <= f.entries_cap) {
+      const FRec x = w_at(i);
+      RaceOut e;
+      e.trace = trace;
+      e.space = (uint8_t)frec_space(x);
+      e.kinds = (uint8_t)((s_acc[K_WW][i] ? 1 : 0) | (s_acc[K_RW][i] ? 2 : 0) | (s_acc[K_AW][i] ? 4 : 0) |
+                          (s_acc[K_AR][i] ? 8 : 0) | (s_acc[K_XB][i] ? 16 : 0));
+      e.reserved16 = 0;
+      e.block = frec_space(x) ? block_of(x.tid, T.tpb, shift) : 0xFFFFFFFFu;
+      e.reserved32 = 0;
+      e.unit = ((uint64_t)x.uhi << 32) | x.ulo;
+      e.ww = s_acc[K_WW][i];
+      e.rw = s_acc[K_RW][i];
+      e.aw = s_acc[K_AW][i];
+      e.ar = s_acc[K_AR][i];
+      e.xb = s_acc[K_XB][i];
+      f.entries[s_base + pos] = e;
+    }
+  };
   // keys of D that are a round's
+  uint32_t rounds = 1;
   auto in_round = [&](const uint32_t(&k)[4], uint32_t live, uint32_t round) {
     uint32_t pick = 0;
 #pragma unroll
     for (uint32_t u = 0; u < 4; u++)
       if ((live >> u) & 1u) {
         const uint32_t s = slot_of(k[u]);
-        pick |= ((s & (rounds - 1)) == round ? bit(D, s >> 1) : 0u) << u;
+        pick |= (!LATE || (s & (rounds - 1)) == round ? bit(D, s >> 1) : 0u) << u;
       }
     return pick;
   };
-  // a record's slot in the maps of level l, and whether the levels so far kept it
-  auto level_slot = [&](const FRec& x, uint32_t l) {
-    return filter_group2(x, block_of(x.tid, T.tpb, shift), l) >> (32 - L_BITS);
-  };
-  auto kept = [&](const FRec& x) {
-    for (uint32_t l = 0; l < level; l++)
-      if (!bit(W + l * L_WORDS, level_slot(x, l))) return false;
-    return true;
-  };
-  auto keep_of = [&](const uint32_t(&k)[4], uint32_t pick, uint32_t base) {
-    if (!LATE || level == 0) return pick;
-    uint32_t left = 0;
-    for_records(k, pick, base, [&](uint32_t u, const FRec& x, uint32_t) { left |= kept(x) ? 1u << u : 0u; });
-    return left;
-  };
-  const uint32_t n_left = uniform(s_nw);
-  if (n_left > WCAP) {
-    uint32_t* const cls = s_head;  // candidates by the low bits of their slot
-    for (;;) {
-      __syncthreads();
-      if (tx < MAX_ROUNDS) cls[tx] = 0;
-      __syncthreads();
-      for_keys(true, 0, T.ntiles, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
-        const uint32_t pick = keep_of(k, in_round(k, live, 0), base);
-#pragma unroll
-        for (uint32_t u = 0; u < 4; u++)
-          if ((pick >> u) & 1u) atomicAdd(&cls[slot_of(k[u]) & (MAX_ROUNDS - 1)], 1u);
-      });
-      __syncthreads();
-      // the fewest rounds that each fit: lane r adds up the classes of round r
-      if (tx < 64) {
-        uint32_t sum = cls[tx], fit = MAX_ROUNDS;
-        if (__any(sum > WCAP)) fit = 2 * MAX_ROUNDS;
-        while (fit <= MAX_ROUNDS && fit > 1) {
-          sum += __shfl_xor(sum, (int)(fit / 2));
-          if (__any(sum > WCAP)) break;
-          fit /= 2;
-        }
-        if (tx == 0) s_base = fit;
-      }
-      __syncthreads();
-      const uint32_t fit = uniform(s_base);
-      if (fit <= 4 || (fit <= MAX_ROUNDS && (level > 1 || DIRECT || (!LATE && !f.late_max)))) {
-        rounds = fit;
-        break;
-      }
-      if (!LATE && !DIRECT && f.late_max) {  // thinned out by a workgroup of its own
-        if (tx == 0) {
-          const uint32_t at = atomicAdd(&f.cnt[FC_LATE], 1u);
-          if (at < f.late_max) f.late[at] = make_uint2(bucket, part);
-          else atomicOr(&f.ctrl->error_flags, ERR_GROUP_FULL);
-        }
-        return;
-      }
-      if (!LATE || level == MAX_LEVEL) {  // too many of one slot that do meet
-        if (tx == 0) atomicOr(&f.ctrl->error_flags, ERR_GROUP_FULL);
-        return;
-      }
-      if (LATE) {
-      // ---- one more level: writes, atomics, reads and twice written slots
-      uint32_t* const lw = W + level * L_WORDS;
-      uint32_t* const la = W + (W_WORDS - 3 * L_WORDS);
-      uint32_t* const lr = la + L_WORDS;
-      uint32_t* const l2 = lr + L_WORDS;
-      for (uint32_t i = tx; i < L_WORDS; i += NTH) lw[i] = la[i] = lr[i] = l2[i] = 0;
-      __syncthreads();
-      for_keys_records(true, 0, T.ntiles, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
-        for_records(k, in_round(k, live, 0), base, [&](uint32_t, const FRec& x, uint32_t) {
-          if (!kept(x)) return;
-          const uint32_t s = level_slot(x, level);
-          if (frec_action(x) == 1u) {
-            if ((bit(lw, s) || ((set(lw, s) >> (s & 31u)) & 1u)) && !bit(l2, s)) set(l2, s);
-          } else if (!bit(la, s)) {
-            set(la, s);
-          }
-        });
-      });
-      for_keys_records(false, r0, r1, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
-        for_records(k, in_round(k, live, 0), base, [&](uint32_t, const FRec& x, uint32_t) {
-          if (!kept(x)) return;
-          const uint32_t s = level_slot(x, level);
-          if (!bit(lr, s)) set(lr, s);
-        });
-      });
-      __syncthreads();
-      for (uint32_t i = tx; i < L_WORDS; i += NTH) lw[i] = l2[i] | (lw[i] & (la[i] | lr[i])) | (la[i] & lr[i]);
-      level++;
-      }
-    }
-  }
-#pragma unroll 1
-  for (uint32_t round = 0; round < rounds; round++) {
-    uint32_t tx = threadIdx.x;
-    asm volatile("" : "+v"(tx));  // keeps per-thread addresses out of registers across the passes
-    if (n_left > WCAP) {          // this round's
-      __syncthreads();
-      if (tx == 0) s_nw = 0;
-      __syncthreads();
-      for_keys(true, 0, T.ntiles, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
-        append(k, keep_of(k, in_round(k, live, round), base), base, s_blk, WCAP, &s_nw);
-      });
-    }
-    for (uint32_t k = tx; k < 2 * HN; k += NTH) s_head[k] = NONE;
-    if (LATE && tx < HN) s_bhead[tx] = NONE;
-    __syncthreads();
-    const uint32_t nw = uniform(s_nw);  // (at most WCAP)
-    if (!pair_sums_fit(n_read, nw)) {  // sums of pairs are kept in 32 bits
-      if (tx == 0) atomicOr(&f.ctrl->error_flags, ERR_GROUP_FULL);
+  if constexpr (!LATE) {
+    if (n_left > WCAP) {  // more than the table holds
+      if (tx == 0) to_late();
       return;
     }
-    if (!nw) continue;
+    const uint32_t nw = n_left;
+    if (!nw) return;
+    if (!pair_sums_fit(n_read, nw)) return full();  // sums of pairs are kept in 32 bits
+    uint32_t* const head = W;  // chains of writes, and as many of atomics (W is free)
+    uint32_t* const length = head + 2 * HN;  // of the latter
+    for (uint32_t k = tx; k < 3 * HN; k += NTH) head[k] = k < 2 * HN ? END : 0u;
+    const uint32_t longest = n_read > RCAP ? MANY_WRITERS : CHAIN;
+    __syncthreads();
     auto chain_of = [&](const FRec& x, uint32_t bx) { return location_hash(x, bx) & (HN - 1); };
-    auto block_chain = [&](const FRec& x, uint32_t bx) { return mix32(location_hash(x, bx) + bx) & (HN - 1); };
-#pragma unroll 1
-    for (uint32_t i = tx; i < nw; i += NTH) {
-      const uint32_t idx = s_blk[i];
+    if (tx < nw) {
+      const uint32_t i = tx, idx = s_blk[i];
       const FRec x = load_frec(idx);
       const uint32_t bx = block_of(x.tid, T.tpb, shift);
       if (WARP) s_side[i] = f.side[T.off + idx];
       s_w[i] = make_uint4(x.ulo, x.uhi, x.tid, x.meta);
       s_blk[i] = bx;
-      if constexpr (LATE) {
-        s_tot[i] = 0;
-        s_bnext[i] = (uint16_t)atomicExch(&s_bhead[block_chain(x, bx)], i);
-      }
-      s_next[i] = (uint16_t)atomicExch(&s_head[chain_of(x, bx) + (frec_action(x) == 2u ? HN : 0u)], i);
+      const uint32_t c = chain_of(x, bx), atomic = frec_action(x) == 2u;
+      s_next[i] = (uint16_t)atomicExch(&head[c + (atomic ? HN : 0u)], i);
+      if (atomic && n_read && atomicAdd(&length[c], 1u) >= longest) s_any = 2;
 #pragma unroll
       for (int q = 0; q < 5; q++) s_acc[q][i] = 0;
     }
@@ -716,235 +709,337 @@ __global__ __launch_bounds__(FNT, 8) void k_filter_count(FilterBuffers f) {
     // ---- a location's first write in the table, and the pairs of writes.
     //      (An atomic walks the writes only: a hot word's atomics meet no other
     //      atomic.  Without a write their location has no first one yet.)
-#pragma unroll 1
-    for (uint32_t i = tx; i < nw; i += NTH) {
+    if (tx < nw) {
+      const uint32_t i = tx;
       const FRec x = w_at(i);
       const uint32_t bx = s_blk[i], sx = WARP ? s_side[i] : 0u;
       const bool atomic = frec_action(x) == 2u;
-      uint32_t lead = i, ww = 0, aw = 0, xb = 0, before = 0;
+      uint32_t first = i, ww = 0, aw = 0, xw = 0, left = longest;
 #pragma unroll 1
-      for (uint32_t j = s_head[chain_of(x, bx)]; j != NONE; j = s_next[j]) {
+      for (uint32_t j = head[chain_of(x, bx)]; j != END && left; j = s_next[j], left--) {
         if (!atomic && j >= i) continue;
         const FRec y = w_at(j);
         const uint32_t by = s_blk[j];
         if (!same_location(x, bx, y, by)) continue;
-        lead = lead == i ? j : min(lead, j);
-        before++;
+        first = first == i ? j : min(first, j);
         if (part == 0 && pair_races(x, bx, y, by, WARP, T.tpb, sx, WARP ? s_side[j] : 0u)) {
           if (atomic) aw++;
           else ww++;
-          if (bx != by) xb++;
+          if (bx != by) xw++;
         }
       }
-      s_lead[i] = (uint16_t)lead;
-      if (MODE == BY_BUCKET && before >= MANY_WRITERS) s_any = 2;
-      if (ww) atomicAdd(&s_acc[K_WW][lead], ww);
-      if (aw) atomicAdd(&s_acc[K_AW][lead], aw);
-      if (xb) atomicAdd(&s_acc[K_XB][lead], xb);
+      s_lead[i] = (uint16_t)first;
+      if (!left) s_any = 2;
+      if (ww) atomicAdd(&s_acc[K_WW][first], ww);
+      if (aw) atomicAdd(&s_acc[K_AW][first], aw);
+      if (xw) atomicAdd(&s_acc[K_XB][first], xw);
     }
     __syncthreads();
-    // ---- many reads and a word of many writers: counted by a later workgroup,
-    //      per location and block.  (With 70 writers of the hottest word the
-    //      pairs one by one made a trace of 2^24 records take 668 us, 412 so.)
-    if (MODE == BY_BUCKET && f.late_max && rounds == 1 && n_read > RCAP && s_any == 2) {
-      if (tx == 0) {
-        const uint32_t at = atomicAdd(&f.cnt[FC_LATE], 1u);
-        if (at < f.late_max) f.late[at] = make_uint2(bucket, part);
-        s_base = at;
-      }
-      __syncthreads();
-      if (s_base < f.late_max) return;
+    if (s_any == 2) {  // long chains
+      if (tx == 0) to_late();
+      return;
     }
-    if constexpr (LATE) {  // from here on the chains of writes hold their locations' first ones
-      if (tx < HN) s_head[tx] = NONE;
-      __syncthreads();
-#pragma unroll 1
-      for (uint32_t i = tx; i < nw; i += NTH) {
-        const FRec x = w_at(i);
-        const bool atomic = frec_action(x) == 2u;
-        const uint32_t lead = s_lead[i];
-        if (!atomic || lead != i) atomicAdd(&s_tot[lead], atomic ? 0x10000u : 1u);
-        if (!atomic && lead == i) s_next[i] = (uint16_t)atomicExch(&s_head[chain_of(x, s_blk[i])], i);
-      }
-      __syncthreads();
-    }
-    // ---- the reads' pairs, summed per thread while the location stays the
-    //      same (the lanes' LDS atomics to a hot word's sums go one by one)
-    uint32_t lead = 0, rw = 0, ar = 0, xb = 0;
-    auto flush = [&]() {
-      if (rw) atomicAdd(&s_acc[K_RW][lead], rw);
-      if (ar) atomicAdd(&s_acc[K_AR][lead], ar);
-      if (xb) atomicAdd(&s_acc[K_XB][lead], xb);
-      rw = ar = xb = 0;
-    };
     auto count_read = [&](const FRec& x, uint32_t idx) {
       const uint32_t bx = block_of(x.tid, T.tpb, shift);
-      if constexpr (LATE) {  // all of the location's writes race but some of the read's own block's
-        const uint32_t c = chain_of(x, bx);
-        uint32_t j = s_head[c];
-        while (j != NONE && !same_location(x, bx, w_at(j), s_blk[j])) j = s_next[j];
-        if (j != NONE) {
-          uint32_t left = s_tot[j], own = 0;
+      const uint32_t c = chain_of(x, bx);
+      uint32_t j = head[c], k = head[c + HN];
+      if (j == END) {
+        j = k;
+        k = END;
+      }
+      if (j == END) return;
+      const uint32_t sx = WARP ? f.side[T.off + idx] : 0u;
 #pragma unroll 1
-          for (uint32_t q = s_bhead[block_chain(x, bx)]; q != NONE; q = s_bnext[q]) {
-            const FRec y = w_at(q);
-            if (s_blk[q] != bx || !same_location(x, bx, y, bx)) continue;
-            own++;
-            if (!pair_races(x, bx, y, bx, WARP, T.tpb, WARP ? f.side[T.off + idx] : 0u, WARP ? s_side[q] : 0u))
-              left -= frec_action(y) == 1u ? 1u : 0x10000u;
-          }
-          if (left) {
-            if (j != lead) flush();
-            lead = j;
-            rw += left & 0xFFFFu;
-            ar += left >> 16;
-            xb += (s_tot[j] & 0xFFFFu) + (s_tot[j] >> 16) - own;
-          }
-          return;
-        }
-#pragma unroll 1
-        for (j = s_head[c + HN]; j != NONE; j = s_next[j]) {  // a location with atomics only
-          const FRec y = w_at(j);
-          const uint32_t by = s_blk[j];
-          if (!same_location(x, bx, y, by) ||
-              !pair_races(x, bx, y, by, WARP, T.tpb, WARP ? f.side[T.off + idx] : 0u, WARP ? s_side[j] : 0u))
-            continue;
-          if (j != lead) flush();
-          lead = j;
-          ar++;
-          if (bx != by) xb++;
-        }
-      } else {
-        const uint32_t c = chain_of(x, bx);
-        uint32_t j = s_head[c], k = s_head[c + HN];
-        if (j == NONE) {
+      while (j != END) {
+        const uint32_t at = j;
+        j = s_next[j];
+        if (j == END) {  // the writes, then the atomics
           j = k;
-          k = NONE;
+          k = END;
         }
-        if (j == NONE) return;
-        const uint32_t sx = WARP ? f.side[T.off + idx] : 0u;
-#pragma unroll 1
-        while (j != NONE) {
-          const uint32_t at = j;
-          j = s_next[j];
-          if (j == NONE) {  // the writes, then the atomics
-            j = k;
-            k = NONE;
-          }
-          const FRec y = w_at(at);
-          const uint32_t by = s_blk[at];
-          if (!same_location(x, bx, y, by) || !pair_races(x, bx, y, by, WARP, T.tpb, sx, WARP ? s_side[at] : 0u)) continue;
-          const uint32_t l = s_lead[at];
-          if (l != lead) flush();
-          lead = l;
-          if (frec_action(y) == 1u) rw++;
-          else ar++;
-          if (bx != by) xb++;
-        }
+        const FRec y = w_at(at);
+        const uint32_t by = s_blk[at];
+        if (!same_location(x, bx, y, by) || !pair_races(x, bx, y, by, WARP, T.tpb, sx, WARP ? s_side[at] : 0u)) continue;
+        const uint32_t l = s_lead[at];
+        if (l != lead) flush();
+        lead = l;
+        if (frec_action(y) == 1u) rw++;
+        else ar++;
+        if (bx != by) xb++;
       }
     };
-    if (n_read <= RCAP) {  // (in rounds, those of other slots meet no write here)
+    if (n_read <= RCAP) {
 #pragma unroll 1
       for (uint32_t i = tx; i < n_read; i += NTH) count_read(load_frec(s_read[i]), s_read[i]);
     } else if (n_read) {
       for_keys_records(false, r0, r1, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
-        for_records(k, in_round(k, live, round), base, [&](uint32_t, const FRec& x, uint32_t idx) { count_read(x, idx); });
+        for_records(k, in_round(k, live, 0), base, [&](uint32_t, const FRec& x, uint32_t idx) { count_read(x, idx); });
       });
     }
-    {
-      const uint64_t has = __ballot((rw | ar) != 0);
-      if (has) {
-        const uint32_t l = readlane(lead, (int)__builtin_ctzll(has));
-        if (__all((rw | ar) == 0 || lead == l)) {  // one location: one lane adds for the wave
-          auto add = [](uint32_t a, uint32_t c) { return a + c; };
-          rw = wave_reduce(rw, 0u, add);
-          ar = wave_reduce(ar, 0u, add);
-          xb = wave_reduce(xb, 0u, add);
-          lead = l;
-          if (__lane_id() == 0) flush();
-        } else {
-          flush();
-        }
-      }
-    }
-    if (tx == 0) s_n = 0;
+    flush_wave();
     __syncthreads();
-    auto paired = [&](uint32_t i) { return (s_acc[K_WW][i] | s_acc[K_RW][i] | s_acc[K_AW][i] | s_acc[K_AR][i]) != 0; };
     // ---- atomics of one location that met reads but have no write: the first
     //      of them takes the sums of all
-    bool lone = false;
-    for (uint32_t i = tx; i < nw; i += NTH) lone = lone || (s_lead[i] == i && s_acc[K_AR][i] && (s_w[i].w >> 16 & 3u) == 2u);
+    const bool lone = tx < nw && s_lead[tx] == tx && s_acc[K_AR][tx] && (s_w[tx].w >> 16 & 3u) == 2u;
     if (__syncthreads_or(lone)) {
+      uint32_t first = tx;
+      if (lone) {
+        const FRec x = w_at(tx);
+        const uint32_t bx = s_blk[tx];
 #pragma unroll 1
-      for (uint32_t i = tx; i < nw; i += NTH) {
-        const FRec x = w_at(i);
-        if (s_lead[i] != i || !s_acc[K_AR][i] || frec_action(x) != 2u) continue;
-        const uint32_t bx = block_of(x.tid, T.tpb, shift);
-        uint32_t lead = i;
-#pragma unroll 1
-        for (uint32_t j = s_head[chain_of(x, bx) + HN]; j != NONE; j = s_next[j]) {
-          if (j >= lead || !s_acc[K_AR][j]) continue;
-          const FRec y = w_at(j);
-          if (same_location(x, bx, y, block_of(y.tid, T.tpb, shift))) lead = j;
+        for (uint32_t j = head[chain_of(x, bx) + HN]; j != END; j = s_next[j]) {
+          if (j >= first || !s_acc[K_AR][j]) continue;
+          if (same_location(x, bx, w_at(j), s_blk[j])) first = j;
         }
-        s_blk[i] = lead;  // (nothing reads these atomics' blocks any more)
       }
       __syncthreads();
-#pragma unroll 1
-      for (uint32_t i = tx; i < nw; i += NTH) {
-        if (s_lead[i] != i || !s_acc[K_AR][i] || (s_w[i].w >> 16 & 3u) != 2u) continue;
-        const uint32_t lead = s_blk[i];
-        if (lead == i) continue;
-        atomicAdd(&s_acc[K_AR][lead], s_acc[K_AR][i]);
-        if (s_acc[K_XB][i]) atomicAdd(&s_acc[K_XB][lead], s_acc[K_XB][i]);
-        s_lead[i] = (uint16_t)lead;
+      if (first != tx) {
+        atomicAdd(&s_acc[K_AR][first], s_acc[K_AR][tx]);
+        if (s_acc[K_XB][tx]) atomicAdd(&s_acc[K_XB][first], s_acc[K_XB][tx]);
+        s_lead[tx] = (uint16_t)first;
       }
       __syncthreads();
     }
-    // ---- an entry per location with pairs
-#pragma unroll 1
-    for (uint32_t i0 = 0; i0 < nw; i0 += NTH) {
-      const uint32_t i = i0 + tx;
-      const bool racing =
-          i < nw && s_lead[i] == i && paired(i);
-      const uint64_t mask = __ballot(racing);
-      uint32_t pos = 0;
-      if (mask) {
-        if (__lane_id() == 0) pos = atomicAdd(&s_n, (uint32_t)__popcll(mask));
-        pos = (uint32_t)__builtin_amdgcn_readfirstlane((int)pos) + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-      }
-      __syncthreads();
-      const uint32_t n_new = s_n;
-      __syncthreads();
-      if (n_new) {
-        if (tx == 0) {
-          s_base = atomicAdd(&f.cnt[FC_ENTRIES], n_new);
-          if (s_base + n_new > f.entries_cap) atomicOr(&f.ctrl->error_flags, ERR_GROUP_FULL);
-          const uint32_t in_trace = atomicAdd(&f.trace_cnt[trace], n_new) + n_new;
-          if (in_trace > SORT_CHUNK) atomicMax(&f.cnt[FC_MOST], in_trace);
-          s_n = 0;
+    emit(nw);
+  } else {
+    uint32_t level = 0;
+    static_assert(MAX_ROUNDS == 64, "a lane per round");
+    // a record's slot in the maps of level l, and whether the levels so far kept it
+    auto level_slot = [&](const FRec& x, uint32_t l) {
+      return filter_group2(x, block_of(x.tid, T.tpb, shift), l) >> (32 - L_BITS);
+    };
+    auto kept = [&](const FRec& x) {
+      for (uint32_t l = 0; l < level; l++)
+        if (!bit(W + l * L_WORDS, level_slot(x, l))) return false;
+      return true;
+    };
+    auto keep_of = [&](const uint32_t(&k)[4], uint32_t pick, uint32_t base) {
+      if (level == 0) return pick;
+      uint32_t left = 0;
+      for_records(k, pick, base, [&](uint32_t u, const FRec& x, uint32_t) { left |= kept(x) ? 1u << u : 0u; });
+      return left;
+    };
+    if (n_left > WCAP) {
+      for (;;) {
+        __syncthreads();
+        if (tx < MAX_ROUNDS) s_cls[tx] = 0;
+        __syncthreads();
+        for_keys(true, 0, T.ntiles, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
+          const uint32_t pick = keep_of(k, in_round(k, live, 0), base);
+#pragma unroll
+          for (uint32_t u = 0; u < 4; u++)
+            if ((pick >> u) & 1u) atomicAdd(&s_cls[slot_of(k[u]) & (MAX_ROUNDS - 1)], 1u);
+        });
+        __syncthreads();
+        // the fewest rounds that each fit: lane r adds up the classes of round r
+        if (tx < 64) {
+          uint32_t sum = s_cls[tx], fit = MAX_ROUNDS;
+          if (__any(sum > WCAP)) fit = 2 * MAX_ROUNDS;
+          while (fit <= MAX_ROUNDS && fit > 1) {
+            sum += __shfl_xor(sum, (int)(fit / 2));
+            if (__any(sum > WCAP)) break;
+            fit /= 2;
+          }
+          if (tx == 0) s_base = fit;
         }
         __syncthreads();
-        if (racing && s_base + n_new <= f.entries_cap) {
-          const FRec x = w_at(i);
-          RaceOut e;
-          e.trace = trace;
-          e.space = (uint8_t)frec_space(x);
-          e.kinds = (uint8_t)((s_acc[K_WW][i] ? 1 : 0) | (s_acc[K_RW][i] ? 2 : 0) | (s_acc[K_AW][i] ? 4 : 0) |
-                              (s_acc[K_AR][i] ? 8 : 0) | (s_acc[K_XB][i] ? 16 : 0));
-          e.reserved16 = 0;
-          e.block = frec_space(x) ? block_of(x.tid, T.tpb, shift) : 0xFFFFFFFFu;
-          e.reserved32 = 0;
-          e.unit = ((uint64_t)x.uhi << 32) | x.ulo;
-          e.ww = s_acc[K_WW][i];
-          e.rw = s_acc[K_RW][i];
-          e.aw = s_acc[K_AW][i];
-          e.ar = s_acc[K_AR][i];
-          e.xb = s_acc[K_XB][i];
-          f.entries[s_base + pos] = e;
+        const uint32_t fit = uniform(s_base);
+        if (fit <= 4 || (fit <= MAX_ROUNDS && (level > 1 || DIRECT))) {
+          rounds = fit;
+          break;
+        }
+        if (level == MAX_LEVEL) return full();  // too many of one slot that do meet
+        // ---- one more level: writes, atomics, reads and twice written slots
+        uint32_t* const lw = W + level * L_WORDS;
+        uint32_t* const la = W + (W_WORDS - 3 * L_WORDS);
+        uint32_t* const lr = la + L_WORDS;
+        uint32_t* const l2 = lr + L_WORDS;
+        for (uint32_t i = tx; i < L_WORDS; i += NTH) lw[i] = la[i] = lr[i] = l2[i] = 0;
+        __syncthreads();
+        for_keys_records(true, 0, T.ntiles, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
+          for_records(k, in_round(k, live, 0), base, [&](uint32_t, const FRec& x, uint32_t) {
+            if (!kept(x)) return;
+            const uint32_t s = level_slot(x, level);
+            if (frec_action(x) == 1u) {
+              if ((bit(lw, s) || ((set(lw, s) >> (s & 31u)) & 1u)) && !bit(l2, s)) set(l2, s);
+            } else if (!bit(la, s)) {
+              set(la, s);
+            }
+          });
+        });
+        for_keys_records(false, r0, r1, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
+          for_records(k, in_round(k, live, 0), base, [&](uint32_t, const FRec& x, uint32_t) {
+            if (!kept(x)) return;
+            const uint32_t s = level_slot(x, level);
+            if (!bit(lr, s)) set(lr, s);
+          });
+        });
+        __syncthreads();
+        for (uint32_t i = tx; i < L_WORDS; i += NTH) lw[i] = l2[i] | (lw[i] & (la[i] | lr[i])) | (la[i] & lr[i]);
+        level++;
+      }
+    }
+#pragma unroll 1
+    for (uint32_t round = 0; round < rounds; round++) {
+      uint32_t tx = threadIdx.x;
+      asm volatile("" : "+v"(tx));  // keeps per-thread addresses out of registers across the passes
+      if (n_left > WCAP) {          // this round's
+        __syncthreads();
+        if (tx == 0) s_nw = 0;
+        __syncthreads();
+        for_keys(true, 0, T.ntiles, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
+          append(k, keep_of(k, in_round(k, live, round), base), base, s_blk, WCAP, &s_nw);
+        });
+      }
+      for (uint32_t k = 4 * tx; k < HT; k += 4 * NTH) *(uint4*)(tab + k) = make_uint4(NONE, NONE, NONE, NONE);
+      __syncthreads();
+      const uint32_t nw = uniform(s_nw);  // (at most WCAP)
+      if (!pair_sums_fit(n_read, nw)) return full();  // sums of pairs are kept in 32 bits
+      if (!nw) continue;
+      // The first record of x's group of a level, or NONE; h: the group's hash.
+      auto find = [&](uint32_t level, uint32_t h, const FRec& x, uint32_t bx) {
+        for (uint32_t at = h & (HT - 1);; at = (at + 1) & (HT - 1)) {
+          const uint32_t e = tab[at];
+          if (e == NONE) return NONE;
+          if (e >> 16 == level && same_group(level, w_at(e & 0xFFFFu), s_blk[e & 0xFFFFu], x, bx, T.tpb)) return e & 0xFFFFu;
+        }
+      };
+      // ... made record i's where there is none yet.  (A place is taken by one
+      // compare-and-swap, and nobody waits: the records were stored before.)
+      auto find_or_add = [&](uint32_t level, uint32_t h, const FRec& x, uint32_t bx, uint32_t i) {
+        for (uint32_t at = h & (HT - 1);; at = (at + 1) & (HT - 1)) {
+          uint32_t e = __hip_atomic_load(&tab[at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          if (e == NONE) e = atomicCAS(&tab[at], NONE, level << 16 | i);
+          if (e == NONE) return i;
+          if (e >> 16 == level && same_group(level, w_at(e & 0xFFFFu), s_blk[e & 0xFFFFu], x, bx, T.tpb)) return e & 0xFFFFu;
+        }
+      };
+      auto level_hash = [&](uint32_t level, const FRec& x, uint32_t bx) {
+        uint32_t h = location_hash(x, bx);
+        for (uint32_t l = 1; l <= level; l++)
+          if (l != 3 || level == 3) h = group_hash(l, h, x, bx, T.tpb);
+        return h;
+      };
+      auto several = [](uint32_t c) { return c != 1u && c != 0x10000u; };
+      if (tx < nw) {
+        const uint32_t idx = s_blk[tx];
+        const FRec x = load_frec(idx);
+        if (WARP) {
+          s_side[WARP ? tx : 0] = f.side[T.off + idx];
+          s_whead[WARP ? tx : 0] = NONE;
+        }
+        s_w[tx] = make_uint4(x.ulo, x.uhi, x.tid, x.meta);
+        s_blk[tx] = block_of(x.tid, T.tpb, shift);
+#pragma unroll
+        for (uint32_t l = 0; l < LEVELS; l++) s_cnt[l][tx] = 0;
+#pragma unroll
+        for (int q = 0; q < 5; q++) s_acc[q][tx] = 0;
+      }
+      __syncthreads();
+      if (tx < nw) {  // by location
+        const FRec x = w_at(tx);
+        const uint32_t bx = s_blk[tx], lead = find_or_add(0, location_hash(x, bx), x, bx, tx);
+        s_lead[tx] = (uint16_t)lead;
+        atomicAdd(&s_cnt[0][lead], group_one(x));
+      }
+      __syncthreads();
+#pragma unroll 1
+      for (uint32_t q = tx; q < (LEVELS - 1) * nw; q += NTH) {  // ... and, where it has several, by block, epoch and thread
+        uint32_t l = 1, i = q;
+        for (; i >= nw; l++) i -= nw;
+        if (!several(s_cnt[0][s_lead[i]]) || (l == GROUP_WARP && (s_side[WARP ? i : 0] & SIDE_DIVERGED))) continue;
+        const FRec x = w_at(i);
+        const uint32_t bx = s_blk[i];
+        const uint32_t g = find_or_add(l, level_hash(l, x, bx), x, bx, i), before = atomicAdd(&s_cnt[l][g], group_one(x));
+        if (WARP && l == GROUP_WARP) {
+          s_next[i] = (uint16_t)atomicExch(&s_whead[WARP ? g : 0], i);
+          if ((before & 0xFFFFu) + (before >> 16) >= WARP_WALK) s_any = 2;
         }
       }
       __syncthreads();
+      if (WARP && s_any == 2) {  // a warp's records of one word are walked one by one: many of them are for the sort
+        full();
+        return;
+      }
+      // fn(an undiverged record of x's warp, epoch and word by another thread)
+      auto for_warp = [&](const FRec& x, uint32_t bx, auto&& fn) {
+        if constexpr (WARP) {
+          const uint32_t g = find(GROUP_WARP, level_hash(GROUP_WARP, x, bx), x, bx);
+          if (g == NONE) return;
+#pragma unroll 1
+          for (uint32_t j = s_whead[g] & END; j != END; j = s_next[j])
+            if (s_w[j].z != x.tid) fn(j);
+        }
+      };
+      if (part == 0 && tx < nw) {  // the pairs of writes and atomics
+        const uint32_t lead = s_lead[tx];
+        if (several(s_cnt[0][lead])) {
+          uint32_t ww = 0, aw = 0, xb = 0;
+#pragma unroll
+          for (uint32_t l = 0; l < GROUP_LEVELS; l++) {  // (no record: the group's first one is another)
+            const uint32_t c = s_cnt[l][tx], pw = c ? pairs_ww(c) : 0u, pa = pairs_aw(c);
+            ww += (l & 1) ? 0u - pw : pw;
+            aw += (l & 1) ? 0u - pa : pa;
+            if (l < 2) xb += (l & 1) ? 0u - pw - pa : pw + pa;
+          }
+          if (WARP && !(s_side[WARP ? tx : 0] & SIDE_DIVERGED)) {
+            const FRec x = w_at(tx);
+            const uint32_t bx = s_blk[tx];
+            for_warp(x, bx, [&](uint32_t j) {  // ordered by lockstep, but two writes of one statement
+              if (j >= tx) return;
+              const FRec y = w_at(j);
+              if (pair_races(x, bx, y, bx, true, T.tpb, s_side[WARP ? tx : 0], s_side[WARP ? j : 0])) return;
+              if (frec_action(x) == 1u && frec_action(y) == 1u) ww--;
+              else if (frec_action(x) != frec_action(y)) aw--;
+            });
+          }
+          if (ww) atomicAdd(&s_acc[K_WW][lead], ww);
+          if (aw) atomicAdd(&s_acc[K_AW][lead], aw);
+          if (xb) atomicAdd(&s_acc[K_XB][lead], xb);
+        }
+      }
+      auto count_read = [&](const FRec& x, uint32_t idx) {
+        const uint32_t bx = block_of(x.tid, T.tpb, shift);
+        uint32_t h = location_hash(x, bx), l0 = NONE, left = 0, cross = 0;
+#pragma unroll 1
+        for (uint32_t l = 0; l < GROUP_LEVELS; l++) {
+          const uint32_t hl = l ? group_hash(l, h, x, bx, T.tpb) : h, g = find(l, hl, x, bx);
+          if (g == NONE) break;
+          h = hl;
+          const uint32_t c = s_cnt[l][g];
+          left += (l & 1) ? 0u - c : c;
+          if (l < 2) cross = left;
+          if (l == 0) {
+            l0 = g;
+            if (!several(c)) {  // one record: the pair itself
+              const uint32_t by = s_blk[g];
+              if (!pair_races(x, bx, w_at(g), by, WARP, T.tpb, WARP ? f.side[T.off + idx] : 0u, WARP ? s_side[g] : 0u)) return;
+              if (bx == by) cross = 0;
+              break;
+            }
+          }
+          if (WARP && l == 2 && !(f.side[T.off + idx] & SIDE_DIVERGED))
+            for_warp(x, bx, [&](uint32_t j) { left -= group_one(w_at(j)); });
+        }
+        if (!left) return;
+        if (l0 != lead) flush();
+        lead = l0;
+        rw += left & 0xFFFFu;
+        ar += left >> 16;
+        xb += (cross & 0xFFFFu) + (cross >> 16);
+      };
+      if (n_read <= RCAP) {  // (in rounds, those of other slots meet no write here)
+#pragma unroll 1
+        for (uint32_t i = tx; i < n_read; i += NTH) count_read(load_frec(s_read[i]), s_read[i]);
+      } else if (n_read) {
+        for_keys_records(false, r0, r1, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
+          for_records(k, in_round(k, live, round), base, [&](uint32_t, const FRec& x, uint32_t idx) { count_read(x, idx); });
+        });
+      }
+      flush_wave();
+      lead = 0;
+      __syncthreads();
+      emit(nw);
     }
   }
 }
@@ -975,7 +1070,7 @@ __global__ __launch_bounds__(NT) void k_entries_place(FilterBuffers f) {
   __shared__ uint32_t s_first[GROUP_MAX_TRACES];
   __shared__ uint32_t s_scan[NWAVE];
   const uint32_t n = f.cnt[FC_ENTRIES], tx = threadIdx.x;
-  if (f.ctrl->error_flags) return;
+  if (f.ctrl->error_flags || (f.late_wait && f.cnt[FC_LATE])) return;
   const uint32_t per = (f.n_traces + NT - 1) / NT, t0 = min(f.n_traces, tx * per), t1 = min(f.n_traces, t0 + per);
   uint32_t sum = 0;
 #pragma unroll 4
@@ -1006,15 +1101,16 @@ __global__ __launch_bounds__(NT) void k_entries_place(FilterBuffers f) {
 __global__ __launch_bounds__(NT) void k_entries_sort(FilterBuffers f) {
   __shared__ uint64_t s_place[SORT_CHUNK], s_unit[SORT_CHUNK];
   const uint32_t t = blockIdx.x, tx = threadIdx.x;
-  const uint32_t total = f.cnt[FC_ENTRIES], err = f.ctrl->error_flags;
+  const uint32_t total = f.cnt[FC_ENTRIES], err = f.ctrl->error_flags, late = f.late_wait ? f.cnt[FC_LATE] : 0u;
   if (blockIdx.x == 0 && blockIdx.y == 0 && tx == 0) {
     GroupHead h;
     h.entries = total;
     h.error_flags = err;
+    h.late = late;
     h.first_bad = f.ctrl->first_bad;
     *f.head = h;
   }
-  if (err) return;
+  if (err || late) return;
   const uint32_t n = f.trace_cnt[t], first = f.n_traces > 1 ? f.trace_first[t] : 0u;
   const RaceOut* src = (f.n_traces > 1 ? f.placed : f.entries) + first;
   RaceOut* dst = (n <= SORT_CHUNK ? (total <= f.host_cap ? f.host_entries : f.sorted)
@@ -1065,7 +1161,7 @@ __global__ __launch_bounds__(NT) void k_entries_sort(FilterBuffers f) {
 // search, the entries of the other chunks before it (equal ones of earlier
 // chunks come first).
 __global__ __launch_bounds__(NT) void k_entries_merge(FilterBuffers f) {
-  if (f.ctrl->error_flags || f.cnt[FC_MOST] <= SORT_CHUNK) return;
+  if (f.ctrl->error_flags || (f.late_wait && f.cnt[FC_LATE]) || f.cnt[FC_MOST] <= SORT_CHUNK) return;
   const uint32_t total = f.cnt[FC_ENTRIES];
   const RaceOut* const all = f.n_traces > 1 ? f.entries : f.placed;
   for (uint32_t i = blockIdx.x * NT + threadIdx.x; i < total; i += gridDim.x * NT) {
@@ -1124,16 +1220,23 @@ hipError_t launch_filter_count(const FilterBuffers& f, hipStream_t s) {
   }
   const dim3 grid(f.extra_max + tile_grid(f.n_buckets, 0, 0));
   const bool warp = f.side != nullptr;
-  if (f.direct) {
-    hipLaunchKernelGGL((warp ? k_filter_count<DIRECT_TRACE, true, 860, 1408> : k_filter_count<DIRECT_TRACE, false, 940, 1408>),
+  if (f.direct)
+    hipLaunchKernelGGL((warp ? k_filter_count<DIRECT_TRACE, true, 960, 1408> : k_filter_count<DIRECT_TRACE, false, 1024, 1408>),
                        dim3(f.n_traces), dim3(FNT), 0, s, f);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL((warp ? k_filter_count<BY_BUCKET, true, 860, 1408> : k_filter_count<BY_BUCKET, false, 940, 1408>), grid,
-                     dim3(FNT), 0, s, f);
-  if ((e = hipGetLastError()) != hipSuccess || !f.late_max) return e;
-  hipLaunchKernelGGL((warp ? k_filter_count<LATE_BUCKET, true, 750, 1152> : k_filter_count<LATE_BUCKET, false, 800, 1152>),
-                     dim3(f.late_max), dim3(FNT), 0, s, f);
+  else
+    hipLaunchKernelGGL((warp ? k_filter_count<BY_BUCKET, true, 960, 1408> : k_filter_count<BY_BUCKET, false, 1024, 1408>), grid,
+                       dim3(FNT), 0, s, f);
+  if ((e = hipGetLastError()) != hipSuccess || f.late_wait) return e;
+  return launch_filter_late(f, f.late_max, s);
+}
+hipError_t launch_filter_late(const FilterBuffers& f, uint32_t n, hipStream_t s) {
+  const bool warp = f.side != nullptr;
+  if (f.direct)
+    hipLaunchKernelGGL((warp ? k_filter_count<LATE_TRACE, true, 1024, 1408> : k_filter_count<LATE_TRACE, false, 1024, 1408>),
+                       dim3(std::min(n, f.late_max)), dim3(FNT), 0, s, f);
+  else
+    hipLaunchKernelGGL((warp ? k_filter_count<LATE_BUCKET, true, 1024, 1408> : k_filter_count<LATE_BUCKET, false, 1024, 1408>),
+                       dim3(std::min(n, f.late_max)), dim3(FNT), 0, s, f);
   return hipGetLastError();
 }
 hipError_t launch_filter_out(const FilterBuffers& f, hipStream_t s) {

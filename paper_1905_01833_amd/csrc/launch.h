@@ -129,7 +129,7 @@ struct Buffers {            // device pointers of one call
 
 // Counters of a grouped call (FilterBuffers::cnt): entries found, further
 // workgroups of hot buckets, entries of the trace with most (where they exceed
-// SORT_CHUNK), buckets whose candidates are thinned out.
+// SORT_CHUNK), buckets or traces for the later workgroups.
 enum : uint32_t { FC_ENTRIES = 0, FC_EXTRA = 1, FC_MOST = 2, FC_LATE = 3, FC_COUNT = 4 };
 constexpr uint32_t SORT_CHUNK = 2048;         // entries sorted in one workgroup's LDS
 constexpr uint32_t GROUP_MAX_TRACES = 8192;   // traces of a grouped call
@@ -137,6 +137,8 @@ constexpr uint32_t GROUP_MAX_TRACES = 8192;   // traces of a grouped call
 struct GroupHead {          // what the host needs of a grouped call besides its entries
   uint32_t entries, error_flags;
   uint64_t first_bad;
+  uint32_t late;            // with FilterBuffers::late_wait: what is still to be counted
+  uint32_t pad;
 };
 struct FilterBuffers {      // device pointers of a call's grouped race count (filter.h, filter.hip)
   FTrace* tr;
@@ -151,8 +153,9 @@ struct FilterBuffers {      // device pointers of a call's grouped race count (f
   uint2* extra;             // the parts of split buckets: (bucket, part)
   uint32_t extra_max;       // room for them (a multiple of 8; 0: no bucket is split)
   uint32_t hot_part;        // hot reads per part
-  uint2* late;              // buckets to be thinned out: (bucket, part)
-  uint32_t late_max;        // room for them (0: the call goes without)
+  uint2* late;              // buckets (traces, if direct) for the later workgroups, and their part
+  uint32_t late_max;        // room for them
+  uint32_t late_wait;       // 1: the host starts those workgroups, if there is work for them; until then nothing is put in order
   uint32_t max_lgb;         // the largest FTrace::lgb of the call
   const uint32_t* side;     // warp-aware check: one side word per record, else nullptr
   uint32_t* cnt;            // [FC_COUNT]
@@ -196,6 +199,7 @@ hipError_t launch_reset_errors(const Buffers& b, uint32_t mask, hipStream_t s);
 // pairs; the entries in order.
 hipError_t launch_filter_part(const FilterBuffers& f, hipStream_t s);
 hipError_t launch_filter_count(const FilterBuffers& f, hipStream_t s);
+hipError_t launch_filter_late(const FilterBuffers& f, uint32_t n, hipStream_t s);  // (launch_filter_count does it without late_wait)
 hipError_t launch_filter_out(const FilterBuffers& f, hipStream_t s);
 // Redundant-barrier check over the sorted keys of a finished call: clears
 // `table` (n_counts entries) and counts every trace's barrier instances.
