@@ -1231,7 +1231,7 @@ int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const
   const uint64_t rows_at = up(4 * room), extra_at = up(rows_at + 4 * rows),
                  late_at = extra_at + 8ull * extra_max;
   if (cap < 1 || late_at + 8ull * late_max > half ||
-      4ull * (tiles + 2ull * buckets + FC_COUNT) > sizeof(TraceStats) * (uint64_t)n_tiles)
+      4ull * (tiles + 3ull * buckets + FC_COUNT) > sizeof(TraceStats) * (uint64_t)n_tiles)
     return RUN_SORT;
   if (size_buffers(c, room, n_traces, n_tiles, 0, 8, RADIX) != hipSuccess) {  // (sorting may need less)
     (void)hipGetLastError();
@@ -1253,6 +1253,7 @@ int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const
   f.tile_trace = words + FC_COUNT;
   f.bucket_trace = f.tile_trace + tiles;
   f.hot = f.bucket_trace + buckets;
+  f.hot_writes = f.hot + buckets;
   f.trace_cnt = per_trace;
   f.trace_fill = per_trace + n_traces;
   f.trace_first = per_trace + 2ull * n_traces;
@@ -1264,6 +1265,8 @@ int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const
   f.late = (uint2*)(k0 + late_at);
   f.late_max = late_max;
   f.late_wait = late_wait ? 1u : 0u;
+  // (a round is 50 us of one workgroup; the whole sort of a small call takes 100 to 190)
+  f.max_rounds = late_wait ? 2u : 4u;
   f.max_lgb = max_lgb;
   f.side = sink.side;
   f.entries = (RaceOut*)k1;

@@ -68,6 +68,7 @@ __global__ __launch_bounds__(NT) void k_filter_begin(FilterBuffers f) {
     for (uint32_t i = threadIdx.x; i < 1u << T.lgb; i += NT) {
       f.bucket_trace[T.bucket0 + i] = t;
       f.hot[T.bucket0 + i] = 0;
+      f.hot_writes[T.bucket0 + i] = 0;
     }
 }
 
@@ -180,6 +181,17 @@ __global__ __launch_bounds__(FNT, LGB <= 11 ? 8 : 4) void k_filter_part(FilterBu
     }
   }
   __syncthreads();
+  // far more writes and atomics than a bucket's usual share of all records: the
+  // writes among them (32 of the keys tell) are a hot word's
+#pragma unroll 1
+  for (uint32_t b = tx * DPT; b < min((tx + 1) * DPT, B); b++) {
+    const uint32_t pair = s_cnt[b], w0 = pair & 0xFFFFu, nw = (pair >> 16) - w0;
+    if (nw <= usual + usual / 4 + 8) continue;
+    uint32_t plain = 0;
+#pragma unroll 8
+    for (uint32_t k = 0; k < 32; k++) plain += (s_key[w0 + nw * k / 32] & FILTER_ATOMIC) ? 0u : 1u;
+    if (plain) atomicAdd(&f.hot_writes[T.bucket0 + b], nw * plain / 32);
+  }
   uint32_t* out = f.keys + T.off + start;
 #pragma unroll
   for (int q = 0; q < FIT; q++) {
@@ -202,10 +214,11 @@ __global__ __launch_bounds__(FNT, LGB <= 11 ? 8 : 4) void k_filter_part(FilterBu
 //
 // Where the chains get long, or the table of WCAP writes and atomics does not
 // hold them, a later workgroup counts the bucket (see LATE_BUCKET), in rounds,
-// by slot, if need be.  Where that does not help (a hot atomic word whose slot
-// holds an unrelated write or read by chance), it thins out the candidates
-// first: their records are read and hashed anew into maps of the same kind,
-// up to five times, and those that meet no partner there are dropped.
+// by slot, if need be.  Where a few rounds do not hold them for the atomics among
+// them (a hot atomic word whose slot holds an unrelated write or read by chance),
+// it thins those out first: the bucket's writes and reads that are left are
+// hashed anew into a map, up to three times, and atomics that meet none there are
+// dropped.  What still does not fit is for the sort.
 //
 // Latency bounds it, not bytes (4 per record): a bucket's keys lie in one
 // short run per tile.  So each lane loads four keys at once and has four such
@@ -225,9 +238,17 @@ __global__ __launch_bounds__(FNT, LGB <= 11 ? 8 : 4) void k_filter_part(FilterBu
 // 170 so).  Where the items run out, a bucket stays whole and
 // in its place.
 constexpr uint32_t NO_BUCKET = 0xFFFFFFFFu, HOT_ITEM = 1u << 31;
+// Written words whose writes no table of the allowed rounds holds (estimated
+// from samples, hence the quarter more) are for the sort, and the sooner the
+// better: a flag that a quarter of 2^24 records write was found out by one
+// workgroup's passes over its bucket and their records (172 ms, before the sort's
+// one); the call takes 1163 us so, the sort alone 1041.
+constexpr uint32_t TABLE = 1024;  // writes and atomics a late workgroup's table holds
+__device__ __forceinline__ uint32_t hopeless(uint32_t rounds) { return rounds * TABLE + rounds * TABLE / 4; }
 __global__ __launch_bounds__(NT) void k_filter_plan(FilterBuffers f) {
   const uint32_t b = blockIdx.x * NT + threadIdx.x;
   if (b >= f.n_buckets) return;
+  if (f.hot_writes[b] > hopeless(f.max_rounds)) atomicOr(&f.ctrl->error_flags, ERR_GROUP_FULL);
   const uint32_t hot = f.hot[b], parts = min(f.tr[f.bucket_trace[b]].ntiles, 1u + hot / f.hot_part);
   uint32_t word = 1;
   if (hot > f.hot_part / 4) {
@@ -271,9 +292,10 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
   constexpr uint32_t LEVELS = WARP ? GROUP_LEVELS + 1 : GROUP_LEVELS, WARP_WALK = 64;
   static_assert(LEVELS * WCAP < HT, "a free place in the table");
   static_assert(WCAP <= NTH, "a thread per entry of the table");
-  constexpr uint32_t MAX_ROUNDS = 64, MAX_LEVEL = 5;
+  constexpr uint32_t CLASSES = 64, MAX_LEVEL = 3;
   constexpr uint32_t L_BITS = 14, L_WORDS = (1u << L_BITS) / 32;  // the maps of the thinning
-  static_assert((MAX_LEVEL - 1 + 4) * L_WORDS <= W_WORDS, "they take W's place");
+  static_assert(MAX_LEVEL * L_WORDS <= W_WORDS, "they take W's place");
+  static_assert(!LATE || WCAP == TABLE, "");
   __shared__ __align__(16) uint32_t s_map[W_WORDS + D_WORDS + T_WORDS];
   __shared__ uint32_t s_read[RCAP];
   __shared__ uint4 s_w[WCAP];
@@ -285,7 +307,7 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
   constexpr uint32_t LCAP = LATE ? WCAP : 1;
   __shared__ uint32_t s_cnt[LEVELS][LCAP];  // writes | atomics << 16 of the group whose first one this is
   __shared__ uint32_t s_whead[WARP ? LCAP : 1];  // undiverged members of a warp's group
-  __shared__ uint32_t s_cls[MAX_ROUNDS];
+  __shared__ uint32_t s_cls[2][CLASSES];  // candidates by the low bits of their slot: all, writes
   __shared__ __align__(16) uint32_t tab[LATE ? HT : 4];
   __shared__ uint32_t s_n, s_nw, s_any, s_base;
   const uint32_t tx = threadIdx.x;
@@ -340,9 +362,10 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
   if (tx == 0) {
     s_n = 0;
     s_nw = 0;
-    s_any = 0;
+    s_any = (f.ctrl->error_flags & ERR_GROUP_FULL) ? 3u : 0u;
   }
   __syncthreads();
+  if (s_any == 3) return;  // the call sorts (one thread has looked: all of the workgroup leave, or none)
   auto bit = [](const uint32_t* map, uint32_t s) { return (map[s >> 5] >> (s & 31u)) & 1u; };
   auto set = [&](uint32_t* map, uint32_t s) { return atomicOr(&map[s >> 5], 1u << (s & 31u)); };
   // ---- a pass over the bucket's writes (or reads) of tiles lo .. hi - 1:
@@ -561,17 +584,24 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
   };
   // The records of the keys in `pick`: fn(u, record, its index).
   auto for_records = [&](const uint32_t(&k)[4], uint32_t pick, uint32_t base, auto&& fn) {
+    constexpr uint32_t IN = LATE ? 4 : 2;  // in flight
 #pragma unroll 1
-    for (uint32_t h = 0; h < 2; h++) {  // two in flight
-      const uint32_t i0 = base + ((h ? k[2] : k[0]) & (FT - 1)), i1 = base + ((h ? k[3] : k[1]) & (FT - 1));
-      const uint32_t two = pick >> (2 * h) & 3u;
-      FRec x, y;
-      if (two & 1u) x = load_frec(i0);
-      if (two & 2u) y = load_frec(i1);
+    for (uint32_t h = 0; h < 4; h += IN) {
+      FRec x[IN];
+      uint32_t at[IN];
+#pragma unroll
+      for (uint32_t u = 0; u < IN; u++) {
+        at[u] = base + ((IN == 4 || h == 0 ? k[u] : k[(2 + u) & 3u]) & (FT - 1));
+        if ((pick >> (h + u)) & 1u) x[u] = load_frec(at[u]);
+      }
 #pragma unroll 1
-      for (uint32_t u = 0; u < 2; u++) {  // (one copy of fn)
-        if ((two >> u) & 1u) fn(2 * h + u, x, u ? i1 : i0);
-        x = y;
+      for (uint32_t u = 0; u < IN; u++) {  // (one copy of fn)
+        if ((pick >> (h + u)) & 1u) fn(h + u, x[0], at[0]);
+#pragma unroll
+        for (uint32_t q = 0; q + 1 < IN; q++) {
+          x[q] = x[q + 1];
+          at[q] = at[q + 1];
+        }
       }
     }
   };
@@ -680,6 +710,10 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
   };
   if constexpr (!LATE) {
     if (n_left > WCAP) {  // more than the table holds
+      if (n_left > hopeless(f.max_rounds)) {  // by a sample, too many writes for any
+        const uint32_t plain = (uint32_t)__syncthreads_count(tx < WCAP && frec_action(load_frec(s_blk[min(tx, WCAP - 1)])) == 1u);
+        if ((uint64_t)n_left * plain > (uint64_t)hopeless(f.max_rounds) * WCAP) return full();
+      }
       if (tx == 0) to_late();
       return;
     }
@@ -803,8 +837,8 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
     emit(nw);
   } else {
     uint32_t level = 0;
-    static_assert(MAX_ROUNDS == 64, "a lane per round");
-    // a record's slot in the maps of level l, and whether the levels so far kept it
+    static_assert(CLASSES == 64, "a lane per class");
+    // a record's slot in the map of level l, and whether the levels so far kept it
     auto level_slot = [&](const FRec& x, uint32_t l) {
       return filter_group2(x, block_of(x.tid, T.tpb, shift), l) >> (32 - L_BITS);
     };
@@ -813,69 +847,80 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
         if (!bit(W + l * L_WORDS, level_slot(x, l))) return false;
       return true;
     };
+    auto atomics = [](const uint32_t(&k)[4]) {
+      return k[0] >> 31 | k[1] >> 31 << 1 | k[2] >> 31 << 2 | k[3] >> 31 << 3;
+    };
     auto keep_of = [&](const uint32_t(&k)[4], uint32_t pick, uint32_t base) {
       if (level == 0) return pick;
-      uint32_t left = 0;
-      for_records(k, pick, base, [&](uint32_t u, const FRec& x, uint32_t) { left |= kept(x) ? 1u << u : 0u; });
+      uint32_t left = pick & ~atomics(k);
+      for_records(k, pick & ~left, base, [&](uint32_t u, const FRec& x, uint32_t) { left |= kept(x) ? 1u << u : 0u; });
       return left;
     };
+    const uint32_t most = f.max_rounds;
+    uint32_t before = 0;
     if (n_left > WCAP) {
       for (;;) {
         __syncthreads();
-        if (tx < MAX_ROUNDS) s_cls[tx] = 0;
+        if (tx < 2 * CLASSES) s_cls[tx / CLASSES][tx % CLASSES] = 0;
         __syncthreads();
-        for_keys(true, 0, T.ntiles, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
-          const uint32_t pick = keep_of(k, in_round(k, live, 0), base);
+        // (a first look at a sixteenth: where that is too much already, the rest need not be read)
+        uint32_t fit = 0, fit_writes = 0, seen = 0;
+        for (uint32_t lo = 0, hi = T.ntiles >= 32 ? T.ntiles / 16 : T.ntiles; lo < T.ntiles && fit <= most; lo = hi, hi = T.ntiles) {
+          for_keys(true, lo, hi, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
+            const uint32_t pick = keep_of(k, in_round(k, live, 0), base);
 #pragma unroll
-          for (uint32_t u = 0; u < 4; u++)
-            if ((pick >> u) & 1u) atomicAdd(&s_cls[slot_of(k[u]) & (MAX_ROUNDS - 1)], 1u);
-        });
-        __syncthreads();
-        // the fewest rounds that each fit: lane r adds up the classes of round r
-        if (tx < 64) {
-          uint32_t sum = s_cls[tx], fit = MAX_ROUNDS;
-          if (__any(sum > WCAP)) fit = 2 * MAX_ROUNDS;
-          while (fit <= MAX_ROUNDS && fit > 1) {
-            sum += __shfl_xor(sum, (int)(fit / 2));
-            if (__any(sum > WCAP)) break;
-            fit /= 2;
+            for (uint32_t u = 0; u < 4; u++)
+              if ((pick >> u) & 1u) {
+                const uint32_t c = slot_of(k[u]) & (CLASSES - 1);
+                atomicAdd(&s_cls[0][c], 1u);
+                if (!(k[u] & FILTER_ATOMIC)) atomicAdd(&s_cls[1][c], 1u);
+              }
+          });
+          __syncthreads();
+          // the fewest rounds that each fit: lane r adds up the classes of round r
+          if (tx < 2 * CLASSES) {
+            uint32_t sum = s_cls[tx / CLASSES][tx % CLASSES], r = CLASSES;
+            const uint32_t all = wave_reduce(sum, 0u, [](uint32_t a, uint32_t c) { return a + c; });
+            if (tx == 0) s_nw = all;
+            if (__any(sum > WCAP)) r = 2 * CLASSES;
+            while (r <= CLASSES && r > 1) {
+              sum += __shfl_xor(sum, (int)(r / 2));
+              if (__any(sum > WCAP)) break;
+              r /= 2;
+            }
+            if (tx == 0) s_base = r;
+            if (tx == CLASSES) s_n = r;
           }
-          if (tx == 0) s_base = fit;
+          __syncthreads();
+          fit = uniform(s_base);
+          fit_writes = uniform(s_n);
+          if (lo == 0) seen = uniform(s_nw);
         }
-        __syncthreads();
-        const uint32_t fit = uniform(s_base);
-        if (fit <= 4 || (fit <= MAX_ROUNDS && (level > 1 || DIRECT))) {
+        if (fit <= most) {
           rounds = fit;
           break;
         }
-        if (level == MAX_LEVEL) return full();  // too many of one slot that do meet
-        // ---- one more level: writes, atomics, reads and twice written slots
+        // too many writes, or atomics that do meet one or a read (a level that
+        // keeps half of them says so)
+        if (fit_writes > most || level == MAX_LEVEL || (level && seen > before / 2)) return full();
+        before = seen;
+        // ---- one more level: where the writes and the reads are that an atomic may meet
         uint32_t* const lw = W + level * L_WORDS;
-        uint32_t* const la = W + (W_WORDS - 3 * L_WORDS);
-        uint32_t* const lr = la + L_WORDS;
-        uint32_t* const l2 = lr + L_WORDS;
-        for (uint32_t i = tx; i < L_WORDS; i += NTH) lw[i] = la[i] = lr[i] = l2[i] = 0;
+        for (uint32_t i = tx; i < L_WORDS; i += NTH) lw[i] = 0;
         __syncthreads();
-        for_keys_records(true, 0, T.ntiles, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
-          for_records(k, in_round(k, live, 0), base, [&](uint32_t, const FRec& x, uint32_t) {
-            if (!kept(x)) return;
+        auto add = [&](const uint32_t(&k)[4], uint32_t pick, uint32_t base) {
+          for_records(k, pick, base, [&](uint32_t, const FRec& x, uint32_t) {
             const uint32_t s = level_slot(x, level);
-            if (frec_action(x) == 1u) {
-              if ((bit(lw, s) || ((set(lw, s) >> (s & 31u)) & 1u)) && !bit(l2, s)) set(l2, s);
-            } else if (!bit(la, s)) {
-              set(la, s);
-            }
+            if (!bit(lw, s)) set(lw, s);
           });
+        };
+        for_keys(true, 0, T.ntiles, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
+          add(k, in_round(k, live & ~atomics(k), 0), base);
         });
         for_keys_records(false, r0, r1, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
-          for_records(k, in_round(k, live, 0), base, [&](uint32_t, const FRec& x, uint32_t) {
-            if (!kept(x)) return;
-            const uint32_t s = level_slot(x, level);
-            if (!bit(lr, s)) set(lr, s);
-          });
+          add(k, in_round(k, live, 0), base);
         });
         __syncthreads();
-        for (uint32_t i = tx; i < L_WORDS; i += NTH) lw[i] = l2[i] | (lw[i] & (la[i] | lr[i])) | (la[i] & lr[i]);
         level++;
       }
     }

@@ -150,12 +150,14 @@ struct FilterBuffers {      // device pointers of a call's grouped race count (f
   uint32_t* keys;           // [record] a tile's keys by bucket (filter.h)
   uint32_t* rows;           // [tile][buckets + 1] first write | first read << 16 of each bucket in the tile
   uint32_t* hot;            // [bucket] reads of hot words as the tiles counted them, then the bucket's parts
+  uint32_t* hot_writes;     // [bucket] writes of hot words, estimated
   uint2* extra;             // the parts of split buckets: (bucket, part)
   uint32_t extra_max;       // room for them (a multiple of 8; 0: no bucket is split)
   uint32_t hot_part;        // hot reads per part
   uint2* late;              // buckets (traces, if direct) for the later workgroups, and their part
   uint32_t late_max;        // room for them
   uint32_t late_wait;       // 1: the host starts those workgroups, if there is work for them; until then nothing is put in order
+  uint32_t max_rounds;      // tables a later workgroup may fill one after another, a power of two
   uint32_t max_lgb;         // the largest FTrace::lgb of the call
   const uint32_t* side;     // warp-aware check: one side word per record, else nullptr
   uint32_t* cnt;            // [FC_COUNT]

@@ -97,3 +97,54 @@ def test_many_writers(log2, count, warp):
     count = min(count, n // 8)
     want = compare(f"{count} writers of a word, 2^{log2}", writers(n, rng, count, n // 5), private(n, rng), 3.0, warp)
     assert len(want) >= 1 and int(want["pairs_rw"].max()) > n // 100
+
+
+def flag(n, rng, share):
+    """One word: a share of the records write it, as many read it."""
+    m = int(n * share)
+    return writers(n, rng, m, m)
+
+
+def histogram(n, rng, bins):
+    """Half of the records read and write bins, without atomics."""
+    r = private(n, rng)
+    at = rng.permutation(n)[: n // 2]
+    r["unit"][at] = HOT + rng.integers(0, bins, len(at))
+    r["action"][at] = np.arange(len(at)) % 2
+    return r
+
+
+def again(n, rng):
+    """One thread writes a word again and again: no race."""
+    r = private(n, rng)
+    at = rng.permutation(n)[: n // 20]
+    r["unit"][at], r["tid"][at], r["action"][at] = HOT, 7, WRITE
+    return r
+
+
+def counters(n, rng, reads):
+    """A tenth of the records are atomics on four words, some reads among them."""
+    r = private(n, rng)
+    at = rng.permutation(n)[: n // 10]
+    r["unit"][at], r["action"][at] = HOT + np.arange(len(at)) % 4, ATOMIC
+    r["action"][at[:reads]] = READ
+    return r
+
+
+@pytest.mark.parametrize("log2", [12, 14, 16, 18, 20, 22])
+@pytest.mark.parametrize("form", ["flag 5%", "flag 25%", "64 bins", "4096 bins", "one thread", "counters", "counters, read once",
+                                  "counters, read often"])
+def test_words_no_table_holds(log2, form):
+    """Words with more writes than a table holds (and counters' atomics, which
+    need none unless they meet a read): the call that finds out that it has to
+    sort costs little more than the sort."""
+    rng = np.random.default_rng(log2)
+    n = (1 << log2) + 5
+    make = {
+        "flag 5%": lambda: flag(n, rng, 0.05), "flag 25%": lambda: flag(n, rng, 0.25),
+        "64 bins": lambda: histogram(n, rng, 64), "4096 bins": lambda: histogram(n, rng, 4096),
+        "one thread": lambda: again(n, rng), "counters": lambda: counters(n, rng, 0),
+        "counters, read once": lambda: counters(n, rng, 1), "counters, read often": lambda: counters(n, rng, n // 100),
+    }[form]
+    want = compare(f"{form}, 2^{log2}", make(), private(n, rng), 3.0)
+    assert (len(want) == 0) == (form in ("one thread", "counters"))
