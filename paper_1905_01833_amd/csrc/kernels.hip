@@ -1691,11 +1691,18 @@ __global__ __launch_bounds__(NT) void k_scan_out(Buffers b, uint32_t passes_done
   uint32_t tot;
   const uint32_t ex = block_excl_sum(inc + cf, sc, &tot);
   // the last workgroup publishes the call's total
-  if (blockIdx.x + 1 == gridDim.x && threadIdx.x == 0) b.ctrl->total_entries = group_base + tot;
+  if (blockIdx.x + 1 == gridDim.x && blockIdx.y == 0 && threadIdx.x == 0) b.ctrl->total_entries = group_base + tot;
   // The group's entries, copied in quarters of 16 bytes by all threads: a
   // tile may hold none or two thousand, so a thread finds its entry's tile in
   // the prefix (a thread per tile copied 20 entries of 64 bytes one by one
-  // where most locations race: 21 us on 500 tiles).
+  // where most locations race: 21 us on 500 tiles).  A group's copy is shared
+  // out among gridDim.y workgroups, and each thread has four quarters in flight:
+  // 524276 entries of 1024 tiles took 5034 us in four workgroups, one quarter at a
+  // time, and 2833 with a thread per tile; 62 so.
+  const uint32_t per = max((uint32_t)NT, (tot + gridDim.y - 1) / gridDim.y);  // entries
+  const uint64_t e0 = (uint64_t)blockIdx.y * per;
+  if (e0 >= tot) return;
+  const uint32_t e1 = (uint32_t)min<uint64_t>(min<uint64_t>(tot, e0 + per), b.out_cap > group_base ? b.out_cap - group_base : 0ull);
   __shared__ uint32_t s_first[NT + 1];
   __shared__ const RaceOut* s_stage[NT];
   s_first[threadIdx.x] = ex;
@@ -1712,16 +1719,24 @@ __global__ __launch_bounds__(NT) void k_scan_out(Buffers b, uint32_t passes_done
   __shared__ uint32_t s_inc[NT];
   s_inc[threadIdx.x] = inc;
   __syncthreads();
-  for (uint32_t q = threadIdx.x; q < 4 * tot; q += NT) {
-    const uint32_t e = q >> 2;
-    if (group_base + e >= b.out_cap) break;
-    uint32_t lo = 0;  // the last tile whose first entry is at or before e
+  for (uint32_t q0 = 4 * (uint32_t)e0 + threadIdx.x; q0 < 4 * e1; q0 += 4 * NT) {
+    ulonglong2 v[4];
 #pragma unroll
-    for (uint32_t step = NT / 2; step; step >>= 1)
-      if (s_first[lo + step] <= e) lo += step;
-    const uint32_t k = e - s_first[lo];
-    const RaceOut* src = k < s_inc[lo] ? s_stage[lo] + k : b.cross + ((uint64_t)blockIdx.x * GROUP + lo);
-    ((ulonglong2*)(b.out + group_base + e))[q & 3u] = ((const ulonglong2*)src)[q & 3u];
+    for (uint32_t u = 0; u < 4; u++) {
+      const uint32_t q = q0 + u * NT, e = min(q >> 2, e1 - 1);
+      uint32_t lo = 0;  // the last tile whose first entry is at or before e
+#pragma unroll
+      for (uint32_t step = NT / 2; step; step >>= 1)
+        if (s_first[lo + step] <= e) lo += step;
+      const uint32_t k = e - s_first[lo];
+      const RaceOut* src = k < s_inc[lo] ? s_stage[lo] + k : b.cross + ((uint64_t)blockIdx.x * GROUP + lo);
+      v[u] = ((const ulonglong2*)src)[q & 3u];
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < 4; u++) {
+      const uint32_t q = q0 + u * NT;
+      if (q < 4 * e1) ((ulonglong2*)(b.out + group_base))[q] = v[u];
+    }
   }
 }
 
@@ -2485,13 +2500,13 @@ hipError_t launch_scan_out(const Buffers& b, uint32_t passes_done, hipStream_t s
   if (!b.n_tiles) return hipSuccess;
   const uint32_t n_groups = cdiv(b.n_tiles, GROUP);
   if (n_groups <= DIRECT_GROUPS) {
-    hipLaunchKernelGGL(k_scan_out<true>, dim3(n_groups), dim3(NT), 0, s, b, passes_done);
+    hipLaunchKernelGGL(k_scan_out<true>, dim3(n_groups, std::min(128u, 512u / n_groups)), dim3(NT), 0, s, b, passes_done);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(k_group_sums, dim3(n_groups), dim3(NT), 0, s, b, passes_done);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_scan_out<false>, dim3(n_groups), dim3(NT), 0, s, b, passes_done);
+  hipLaunchKernelGGL(k_scan_out<false>, dim3(n_groups, std::max(1u, 256u / n_groups)), dim3(NT), 0, s, b, passes_done);
   return hipGetLastError();
 }
 hipError_t launch_reset_errors(const Buffers& b, uint32_t mask, hipStream_t s) {
