@@ -499,10 +499,10 @@ constexpr int RUN_SORT = 1;  // run_grouped: take the sorting path
 
 // Result delivery: entries downloaded from `dev_out` (n_races of them; or they
 // are in host memory already, at `host_out`), and
-// the summaries from the entry list.  Neighbouring entries of one location
+// the summaries from the entry list.  parts: neighbouring entries of one location
 // (the grouped count finds a location in several parts) become one.
 int deliver_result(sim_ctx* c, const uint64_t* offsets, uint32_t n_traces, hipStream_t s, const Sink& sink,
-                   uint64_t n_races, const void* dev_out, const sim_race* host_out = nullptr) {
+                   uint64_t n_races, const void* dev_out, bool parts = false, const sim_race* host_out = nullptr) {
   sim_trace_summary* sums = nullptr;
   sim_race* races = nullptr;
   sim_result* r = nullptr;
@@ -537,9 +537,9 @@ int deliver_result(sim_ctx* c, const uint64_t* offsets, uint32_t n_traces, hipSt
       return fail(c, SIM_EDEVICE, "entry %llu names trace %u", (unsigned long long)k, x.trace);
     }
     sums[x.trace].n_pairs += x.pairs_ww + x.pairs_rw + x.pairs_aw + x.pairs_ar;
-    if (n_locs) {
+    if (parts && n_locs) {
       sim_race& y = races[n_locs - 1];
-      if (y.trace == x.trace && y.space == x.space && y.block == x.block && y.unit == x.unit) {
+      if (y.unit == x.unit && y.block == x.block && y.space == x.space && y.trace == x.trace) {
         y.kinds |= x.kinds;
         y.pairs_ww += x.pairs_ww;
         y.pairs_rw += x.pairs_rw;
@@ -550,7 +550,7 @@ int deliver_result(sim_ctx* c, const uint64_t* offsets, uint32_t n_traces, hipSt
       }
     }
     sums[x.trace].n_race_locs += 1;
-    if (n_locs != k) races[n_locs] = x;
+    if (parts && n_locs != k) races[n_locs] = x;
     n_locs++;
   }
   if (r) r->n_races = n_locs;
@@ -1305,7 +1305,7 @@ int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const
     c->group_pause[sink.side ? KIND_WARP : KIND_PLAIN] = GROUP_PAUSE;
     return RUN_SORT;
   }
-  return deliver_result(c, offsets, n_traces, s, sink, head->entries, f.sorted,
+  return deliver_result(c, offsets, n_traces, s, sink, head->entries, f.sorted, true,
                         head->entries <= host_cap ? (const sim_race*)host_entries : nullptr);
 }
 

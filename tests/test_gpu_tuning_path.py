@@ -54,12 +54,12 @@ def test_autotune_times_the_calls_that_follow():
     least-of-few on both sides: within a factor of 1.7)."""
     import paper_1905_01833_amd as pkg
 
-    recs, _ = tracegen.c1(n_blocks=256, inject_rate=1e-4, seed=3)
+    recs, _ = tracegen.c1(n_blocks=1024, inject_rate=1e-4, seed=3)
     dev = to_dev(recs)
     want, wsum = oracle.closed_form_par(recs, tpb=256)
     c = pkg.Context(0)
     try:
-        print("[gpu] autotune 2^22 records", flush=True)
+        print("[gpu] autotune 2^24 records", flush=True)
         best = c.autotune(dev, None, 256, reps=5)
         took = []
         for _ in range(20):
