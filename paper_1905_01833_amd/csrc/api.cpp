@@ -1272,6 +1272,8 @@ int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const
   f.entries = (RaceOut*)k1;
   f.placed = (RaceOut*)(k1 + 64 * cap);
   f.sorted = (RaceOut*)k0;
+  f.merge_keys = k0 + 64 * cap;  // (over the bucket rows, which are done with by then)
+  static_assert(sizeof(RaceOut) == 64, "half of a key buffer holds the entries, the other half 16 bytes for each");
   f.entries_cap = (uint32_t)cap;
   f.head = head;
   f.host_entries = host_entries;

@@ -675,6 +675,7 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
       if (s_base + n_new > f.entries_cap) atomicOr(&f.ctrl->error_flags, ERR_GROUP_FULL);
       const uint32_t in_trace = atomicAdd(&f.trace_cnt[trace], n_new) + n_new;
       if (in_trace > SORT_CHUNK) atomicMax(&f.cnt[FC_MOST], in_trace);
+      if (in_trace > GROUP_MAX_ENTRIES) atomicOr(&f.ctrl->error_flags, ERR_GROUP_FULL);
     }
     __syncthreads();
     if (racing && s_base + n_new <= f.entries_cap) {
@@ -1132,20 +1133,45 @@ __global__ __launch_bounds__(NT) void k_entries_place(FilterBuffers f) {
     base += c;
   }
   __syncthreads();
-  for (uint32_t i = blockIdx.x * NT + tx; i < n; i += gridDim.x * NT) {
-    const uint32_t t = f.entries[i].trace;
-    copy_entry(f.placed + s_first[t] + atomicAdd(&f.trace_fill[t], 1u), f.entries + i);
+  // (Entries of one trace tend to lie together: a lane adds for those of its
+  // wave, for the wave's first few traces, as atomics to one address take about
+  // 11 ns each: 60000 entries of one of two traces took 700 us one by one.)
+  for (uint32_t i0 = blockIdx.x * NT; i0 < n; i0 += gridDim.x * NT) {
+    const uint32_t i = i0 + tx;
+    bool todo = i < n;
+    const uint32_t t = todo ? f.entries[i].trace : 0u;
+    uint32_t at = 0;
+#pragma unroll 1
+    for (uint32_t k = 0; k < 4; k++) {
+      const uint64_t left = __ballot(todo);
+      if (!left) break;
+      const uint32_t first = (uint32_t)__builtin_ctzll(left), lt = readlane(t, (int)first);
+      const uint64_t same = __ballot(todo && t == lt);
+      uint32_t base = 0;
+      if (__lane_id() == first) base = atomicAdd(&f.trace_fill[lt], (uint32_t)__popcll(same));
+      base = readlane(base, (int)first);
+      if (todo && t == lt) {
+        at = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+        todo = false;
+      }
+    }
+    if (todo) at = atomicAdd(&f.trace_fill[t], 1u);
+    if (i < n) copy_entry(f.placed + s_first[t] + at, f.entries + i);
   }
 }
 
 // An entry's place in its chunk is the number of entries before it there (of
-// equal ones, those with a smaller index).  A workgroup (trace, y) holds a
-// chunk's keys in LDS and places 16 of its entries, sixteen lanes to an entry
-// (256, a lane each, where one has many, or the call many traces): sorting 1677 entries in one
+// equal ones, those with a smaller index).  A workgroup holds a chunk's keys in
+// LDS and places 16 of its entries, sixteen lanes to an entry (256, a lane each,
+// where a trace has many, or the call many traces): sorting 1677 entries in one
 // workgroup's LDS took 68 us, 66 steps with a barrier each; this takes 17.
+// Traces of one chunk belong to the workgroups (trace, y); longer ones are shared
+// out among all: with one workgroup per trace, a call of 65 traces with 60000
+// entries in one of them took 52.7 ms, 0.5 so (the sort 0.6).
 __global__ __launch_bounds__(NT) void k_entries_sort(FilterBuffers f) {
   __shared__ uint64_t s_place[SORT_CHUNK], s_unit[SORT_CHUNK];
-  const uint32_t t = blockIdx.x, tx = threadIdx.x;
+  __shared__ uint32_t s_long[NT], s_n;
+  const uint32_t tx = threadIdx.x;
   const uint32_t total = f.cnt[FC_ENTRIES], err = f.ctrl->error_flags, late = f.late_wait ? f.cnt[FC_LATE] : 0u;
   if (blockIdx.x == 0 && blockIdx.y == 0 && tx == 0) {
     GroupHead h;
@@ -1156,55 +1182,78 @@ __global__ __launch_bounds__(NT) void k_entries_sort(FilterBuffers f) {
     *f.head = h;
   }
   if (err || late) return;
-  const uint32_t n = f.trace_cnt[t], first = f.n_traces > 1 ? f.trace_first[t] : 0u;
-  const RaceOut* src = (f.n_traces > 1 ? f.placed : f.entries) + first;
-  RaceOut* dst = (n <= SORT_CHUNK ? (total <= f.host_cap ? f.host_entries : f.sorted)
-                                  : (f.n_traces > 1 ? f.entries : f.placed)) + first;
-  const uint32_t lanes = gridDim.y > 1 && n <= 32 * SORT_CHUNK ? 16u : 1u, take = NT / lanes, per_chunk = SORT_CHUNK / take;
-  for (uint32_t item = blockIdx.y;; item += gridDim.y) {
-    const uint32_t c0 = item / per_chunk * SORT_CHUNK, g0 = item % per_chunk * take;
-    if (c0 >= n) break;
-    const uint32_t m = min(SORT_CHUNK, n - c0);
-    if (g0 >= m) continue;
-    __syncthreads();
-    for (uint32_t i0 = 0; i0 < m; i0 += 4 * NT) {
-      EntryKey k[4];
+  auto sort = [&](uint32_t t, uint32_t n, uint32_t from, uint32_t step) {
+    const uint32_t first = f.n_traces > 1 ? f.trace_first[t] : 0u;
+    const RaceOut* src = (f.n_traces > 1 ? f.placed : f.entries) + first;
+    RaceOut* dst = (n <= SORT_CHUNK ? (total <= f.host_cap ? f.host_entries : f.sorted)
+                                    : (f.n_traces > 1 ? f.entries : f.placed)) + first;
+    EntryKey* const mk = n > SORT_CHUNK ? (EntryKey*)f.merge_keys + first : nullptr;  // for the merge
+    const uint32_t lanes = gridDim.y > 1 && n <= 32 * SORT_CHUNK ? 16u : 1u, take = NT / lanes, per_chunk = SORT_CHUNK / take;
+    for (uint32_t item = from;; item += step) {
+      const uint32_t c0 = item / per_chunk * SORT_CHUNK, g0 = item % per_chunk * take;
+      if (c0 >= n) break;
+      const uint32_t m = min(SORT_CHUNK, n - c0);
+      if (g0 >= m) continue;
+      __syncthreads();
+      for (uint32_t i0 = 0; i0 < m; i0 += 4 * NT) {
+        EntryKey k[4];
 #pragma unroll
-      for (uint32_t u = 0; u < 4; u++)
-        if (i0 + u * NT + tx < m) k[u] = entry_key(src[c0 + i0 + u * NT + tx]);
+        for (uint32_t u = 0; u < 4; u++)
+          if (i0 + u * NT + tx < m) k[u] = entry_key(src[c0 + i0 + u * NT + tx]);
 #pragma unroll
-      for (uint32_t u = 0; u < 4; u++)
-        if (i0 + u * NT + tx < m) {
-          s_place[i0 + u * NT + tx] = k[u].place;
-          s_unit[i0 + u * NT + tx] = k[u].unit;
-        }
-    }
-    __syncthreads();
-    const uint32_t e = g0 + tx / lanes, q = tx & (lanes - 1);
-    uint32_t rank = 0;
-    if (e < m) {
-      const EntryKey k{s_place[e], s_unit[e]};
-#pragma unroll 8
-      for (uint32_t j = q; j < m; j += lanes) {
-        const EntryKey o{s_place[j], s_unit[j]};
-        rank += key_less(o, k) || (j < e && !key_less(k, o)) ? 1u : 0u;
+        for (uint32_t u = 0; u < 4; u++)
+          if (i0 + u * NT + tx < m) {
+            s_place[i0 + u * NT + tx] = k[u].place;
+            s_unit[i0 + u * NT + tx] = k[u].unit;
+          }
       }
+      __syncthreads();
+      const uint32_t e = g0 + tx / lanes, q = tx & (lanes - 1);
+      uint32_t rank = 0;
+      if (e < m) {
+        const EntryKey k{s_place[e], s_unit[e]};
+#pragma unroll 8
+        for (uint32_t j = q; j < m; j += lanes) {
+          const EntryKey o{s_place[j], s_unit[j]};
+          rank += key_less(o, k) || (j < e && !key_less(k, o)) ? 1u : 0u;
+        }
+      }
+      if (lanes == 16) {
+        rank += __shfl_xor(rank, 1);
+        rank += __shfl_xor(rank, 2);
+        rank += __shfl_xor(rank, 4);
+        rank += __shfl_xor(rank, 8);
+        if (e < m && q < 4) ((ulonglong2*)(dst + c0 + rank))[q] = ((const ulonglong2*)(src + c0 + e))[q];
+      } else if (e < m) {
+        copy_entry(dst + c0 + rank, src + c0 + e);
+      }
+      if (mk && e < m && q == 0) mk[c0 + rank] = EntryKey{s_place[e], s_unit[e]};
     }
-    if (lanes == 16) {
-      rank += __shfl_xor(rank, 1);
-      rank += __shfl_xor(rank, 2);
-      rank += __shfl_xor(rank, 4);
-      rank += __shfl_xor(rank, 8);
-      if (e < m && q < 4) ((ulonglong2*)(dst + c0 + rank))[q] = ((const ulonglong2*)(src + c0 + e))[q];
-    } else if (e < m) {
-      copy_entry(dst + c0 + rank, src + c0 + e);
+  };
+  const uint32_t own = f.trace_cnt[blockIdx.x];
+  if (own <= SORT_CHUNK) sort(blockIdx.x, own, blockIdx.y, gridDim.y);
+  if (f.cnt[FC_MOST] <= SORT_CHUNK) return;
+  const uint32_t all = gridDim.x * gridDim.y, me = blockIdx.y * gridDim.x + blockIdx.x;
+  for (uint32_t t0 = 0; t0 < f.n_traces; t0 += NT) {
+    __syncthreads();
+    if (tx == 0) s_n = 0;
+    __syncthreads();
+    if (t0 + tx < f.n_traces && f.trace_cnt[t0 + tx] > SORT_CHUNK) s_long[atomicAdd(&s_n, 1u)] = t0 + tx;
+    __syncthreads();
+    const uint32_t n_long = s_n;
+    for (uint32_t k = 0; k < n_long; k++) {
+      const uint32_t t = s_long[k];
+      sort(t, f.trace_cnt[t], (me + t * 61u) % all, all);
     }
   }
 }
 
 // An entry's place among its trace's: its index in its chunk and, by binary
 // search, the entries of the other chunks before it (equal ones of earlier
-// chunks come first).
+// chunks come first).  Bound by the chain of a search's loads, so four searches
+// run at once, over keys of 16 bytes: 209713 entries took 520 us one after
+// another over the entries themselves, 268 so.  It grows with the square of a
+// trace's entries, hence GROUP_MAX_ENTRIES.
 __global__ __launch_bounds__(NT) void k_entries_merge(FilterBuffers f) {
   if (f.ctrl->error_flags || (f.late_wait && f.cnt[FC_LATE]) || f.cnt[FC_MOST] <= SORT_CHUNK) return;
   const uint32_t total = f.cnt[FC_ENTRIES];
@@ -1221,23 +1270,33 @@ __global__ __launch_bounds__(NT) void k_entries_merge(FilterBuffers f) {
     }
     const uint32_t n = f.trace_cnt[t], first = f.n_traces > 1 ? f.trace_first[t] : 0u;
     if (n <= SORT_CHUNK) continue;
-    const RaceOut* e = all + first;
+    const EntryKey* const mk = (const EntryKey*)f.merge_keys + first;
     const uint32_t me = i - first, own = me / SORT_CHUNK;
-    const EntryKey k = entry_key(e[me]);
+    const EntryKey k = mk[me];
     uint32_t at = me % SORT_CHUNK;
-    for (uint32_t c0 = 0; c0 < n; c0 += SORT_CHUNK) {
-      const uint32_t c = c0 / SORT_CHUNK;
-      if (c == own) continue;
-      uint32_t lo = 0, hi = min(SORT_CHUNK, n - c0);
-      while (lo < hi) {
-        const uint32_t mid = (lo + hi) / 2;
-        const EntryKey m = entry_key(e[c0 + mid]);
-        if (c < own ? !key_less(k, m) : key_less(m, k)) lo = mid + 1;
-        else hi = mid;
+    constexpr uint32_t U = 4;
+#pragma unroll 1
+    for (uint32_t c = 0; c * SORT_CHUNK < n; c += U) {
+      uint32_t lo[U] = {0, 0, 0, 0};
+#pragma unroll 1
+      for (uint32_t step = SORT_CHUNK; step; step >>= 1) {
+        EntryKey m[U];
+#pragma unroll
+        for (uint32_t u = 0; u < U; u++) {
+          const uint32_t j = (c + u) * SORT_CHUNK + lo[u] + step - 1;
+          m[u] = mk[min(j, n - 1)];
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < U; u++) {
+          const uint32_t j = lo[u] + step - 1;
+          if (j < SORT_CHUNK && (c + u) * SORT_CHUNK + j < n && c + u != own &&
+              (c + u < own ? !key_less(k, m[u]) : key_less(m[u], k)))
+            lo[u] += step;
+        }
       }
-      at += lo;
+      at += lo[0] + lo[1] + lo[2] + lo[3];
     }
-    copy_entry((total <= f.host_cap ? f.host_entries : f.sorted) + first + at, e + me);
+    copy_entry((total <= f.host_cap ? f.host_entries : f.sorted) + first + at, all + i);
   }
 }
 
@@ -1291,7 +1350,7 @@ hipError_t launch_filter_out(const FilterBuffers& f, hipStream_t s) {
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   const uint32_t chunks = cdiv(f.entries_cap, SORT_CHUNK);
-  hipLaunchKernelGGL(k_entries_sort, dim3(f.n_traces, f.n_traces <= 64 ? std::min(1024u / f.n_traces, cdiv(f.entries_cap, 16)) : 1u), dim3(NT),
+  hipLaunchKernelGGL(k_entries_sort, dim3(f.n_traces, std::max(1u, std::min(1024u / f.n_traces, cdiv(f.entries_cap, 16)))), dim3(NT),
                      0, s, f);
   if ((e = hipGetLastError()) != hipSuccess || chunks <= 1) return e;
   hipLaunchKernelGGL(k_entries_merge, dim3(std::min(2048u, cdiv(f.entries_cap, NT))), dim3(NT), 0, s, f);

@@ -132,6 +132,10 @@ struct Buffers {            // device pointers of one call
 // SORT_CHUNK), buckets or traces for the later workgroups.
 enum : uint32_t { FC_ENTRIES = 0, FC_EXTRA = 1, FC_MOST = 2, FC_LATE = 3, FC_COUNT = 4 };
 constexpr uint32_t SORT_CHUNK = 2048;         // entries sorted in one workgroup's LDS
+// Entries of a trace, at most: beyond, merging its sorted chunks takes longer than
+// sorting its records does.  (Grouped / sorted, in us: 262144 entries of 2^24
+// records 1562 / 1822; of 2^22 records, 200000 1411 / 1118, 60000 512 / 624.)
+constexpr uint32_t GROUP_MAX_ENTRIES = 1u << 18;
 constexpr uint32_t GROUP_MAX_TRACES = 8192;   // traces of a grouped call
 
 struct GroupHead {          // what the host needs of a grouped call besides its entries
@@ -167,6 +171,7 @@ struct FilterBuffers {      // device pointers of a call's grouped race count (f
   RaceOut* entries;         // as the buckets found them
   RaceOut* placed;          // by trace
   RaceOut* sorted;          // in order
+  void* merge_keys;         // 16 bytes per entry, of traces with more than SORT_CHUNK
   uint32_t entries_cap;     // entries each of the three holds
   GroupHead* head;          // pinned host memory
   RaceOut* host_entries;    // pinned host memory: the entries in order, if no more than

@@ -1,10 +1,11 @@
-"""Calls with many racing locations: the sort's entries copied in order; against
-the oracle, and their cost against the kernels beside them."""
+"""Calls with many racing locations: the sort's entries copied in order, the
+grouped count's sorted and merged, and the line between the two; against the
+oracle, and their cost against the kernels or the path beside them."""
 import numpy as np
 import pytest
 
 import oracle
-from test_gpu_racing import HOT, private
+from test_gpu_racing import HOT, compare, private
 from tracegen import RECORD_DTYPE, WRITE
 
 pytestmark = pytest.mark.gpu
@@ -54,3 +55,52 @@ def test_the_sorts_entries_are_copied_quickly(log2, share):
         assert min(ratio) < 2, ratio
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("n_traces", [2, 64, 65, 300])
+@pytest.mark.parametrize("count", [2049, 60000, 200000])
+def test_one_trace_with_many_among_many_traces(n_traces, count):
+    """The entries of one long trace are sorted by all workgroups, whatever the
+    number of traces: the call takes at most twice the sort's time."""
+    import time
+
+    import paper_1905_01833_amd as pkg
+
+    rng = np.random.default_rng(n_traces + count)
+    long = locations(1 << 22, rng, count)
+    parts = [private(1000 + 37 * (k % 50), rng) for k in range(n_traces - 1)]
+    parts.insert(n_traces // 2, long)
+    recs = np.concatenate(parts)
+    off = np.concatenate([[0], np.cumsum([len(p) for p in parts])]).astype(np.uint64)
+    tpb = np.full(n_traces, 256, dtype=np.uint32)
+    want, wsum = oracle.closed_form_par(recs, off, tpb)
+    assert len(want) == count
+    dev = device(recs)
+    best = {}
+    c = pkg.Context(0)
+    try:
+        for shape in (None, {"scatter_threads": 512}):
+            c.set_tuning(pkg.sim_size_class(len(recs)), shape)
+            took = []
+            for rep in range(4):
+                print(f"[gpu] {count} locations in one of {n_traces} traces, shape {shape}, call {rep}", flush=True)
+                torch.cuda.synchronize()
+                t = time.perf_counter()
+                got, gsum = c.check_traces_device(dev, off, tpb)
+                took.append(time.perf_counter() - t)
+                assert got.tobytes() == want.tobytes() and gsum.tobytes() == wsum.tobytes()
+            best[shape is None] = min(took)
+    finally:
+        c.close()
+    print(f"[gpu] {best[True] * 1e6:.0f} us, sorted {best[False] * 1e6:.0f}", flush=True)
+    assert best[True] < 2 * best[False], best
+
+
+@pytest.mark.parametrize("count", [(1 << 18) - 1, 1 << 18, (1 << 18) + 1, 900000])
+def test_line_between_merging_and_sorting(count):
+    """As many entries of a trace as are merged, and one more: the first call
+    costs at most half as much again as the sort."""
+    rng = np.random.default_rng(count)
+    n = 1 << 24
+    want = compare(f"{count} locations of 2^24 records", locations(n, rng, count), private(n, rng), 1.5)
+    assert len(want) == count
