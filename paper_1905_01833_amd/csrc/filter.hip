@@ -181,8 +181,8 @@ __global__ __launch_bounds__(FNT, LGB <= 11 ? 8 : 4) void k_filter_part(FilterBu
     }
   }
   __syncthreads();
-  // far more writes and atomics than a bucket's usual share of all records: the
-  // writes among them (32 of the keys tell) are a hot word's
+  // far more writes than a bucket's usual share of all records (32 of the keys
+  // tell them from atomics): the rest are a hot word's
 #pragma unroll 1
   for (uint32_t b = tx * DPT; b < min((tx + 1) * DPT, B); b++) {
     const uint32_t pair = s_cnt[b], w0 = pair & 0xFFFFu, nw = (pair >> 16) - w0;
@@ -190,7 +190,8 @@ __global__ __launch_bounds__(FNT, LGB <= 11 ? 8 : 4) void k_filter_part(FilterBu
     uint32_t plain = 0;
 #pragma unroll 8
     for (uint32_t k = 0; k < 32; k++) plain += (s_key[w0 + nw * k / 32] & FILTER_ATOMIC) ? 0u : 1u;
-    if (plain) atomicAdd(&f.hot_writes[T.bucket0 + b], nw * plain / 32);
+    const uint32_t writes = nw * plain / 32;
+    if (writes > usual + usual / 4 + 8) atomicAdd(&f.hot_writes[T.bucket0 + b], writes - usual);
   }
   uint32_t* out = f.keys + T.off + start;
 #pragma unroll
@@ -217,7 +218,7 @@ __global__ __launch_bounds__(FNT, LGB <= 11 ? 8 : 4) void k_filter_part(FilterBu
 // by slot, if need be.  Where a few rounds do not hold them for the atomics among
 // them (a hot atomic word whose slot holds an unrelated write or read by chance),
 // it thins those out first: the bucket's writes and reads that are left are
-// hashed anew into a map, up to three times, and atomics that meet none there are
+// hashed anew into four maps, and atomics that do not meet one in all of them are
 // dropped.  What still does not fit is for the sort.
 //
 // Latency bounds it, not bytes (4 per record): a bucket's keys lie in one
@@ -292,9 +293,9 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
   constexpr uint32_t LEVELS = WARP ? GROUP_LEVELS + 1 : GROUP_LEVELS, WARP_WALK = 64;
   static_assert(LEVELS * WCAP < HT, "a free place in the table");
   static_assert(WCAP <= NTH, "a thread per entry of the table");
-  constexpr uint32_t CLASSES = 64, MAX_LEVEL = 3;
-  constexpr uint32_t L_BITS = 14, L_WORDS = (1u << L_BITS) / 32;  // the maps of the thinning
-  static_assert(MAX_LEVEL * L_WORDS <= W_WORDS, "they take W's place");
+  constexpr uint32_t CLASSES = 64;
+  constexpr uint32_t MAPS = 4, L_BITS = 15, L_WORDS = (1u << L_BITS) / 32;  // of the thinning
+  static_assert(MAPS * L_WORDS <= W_WORDS, "they take W's place");
   static_assert(!LATE || WCAP == TABLE, "");
   __shared__ __align__(16) uint32_t s_map[W_WORDS + D_WORDS + T_WORDS];
   __shared__ uint32_t s_read[RCAP];
@@ -722,11 +723,16 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
     if (!nw) return;
     if (!pair_sums_fit(n_read, nw)) return full();  // sums of pairs are kept in 32 bits
     uint32_t* const head = W;  // chains of writes, and as many of atomics (W is free)
-    uint32_t* const length = head + 2 * HN;  // of the latter
-    for (uint32_t k = tx; k < 3 * HN; k += NTH) head[k] = k < 2 * HN ? END : 0u;
+    // the latter's lengths, and which bits of a location's tag are set (low half)
+    // or clear (high half) in some record of theirs: most reads that meet a hot
+    // word's long chain by chance need not walk it
+    uint32_t* const length = head + 2 * HN;
+    uint32_t* const tags = head + 3 * HN;
+    for (uint32_t k = tx; k < 4 * HN; k += NTH) head[k] = k < 2 * HN ? END : 0u;
     const uint32_t longest = n_read > RCAP ? MANY_WRITERS : CHAIN;
     __syncthreads();
     auto chain_of = [&](const FRec& x, uint32_t bx) { return location_hash(x, bx) & (HN - 1); };
+    auto tag_of = [](uint32_t h) { return h >> 16 | (~h & 0xFFFF0000u); };
     if (tx < nw) {
       const uint32_t i = tx, idx = s_blk[i];
       const FRec x = load_frec(idx);
@@ -734,9 +740,12 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
       if (WARP) s_side[i] = f.side[T.off + idx];
       s_w[i] = make_uint4(x.ulo, x.uhi, x.tid, x.meta);
       s_blk[i] = bx;
-      const uint32_t c = chain_of(x, bx), atomic = frec_action(x) == 2u;
+      const uint32_t h = location_hash(x, bx), c = h & (HN - 1), atomic = frec_action(x) == 2u;
       s_next[i] = (uint16_t)atomicExch(&head[c + (atomic ? HN : 0u)], i);
-      if (atomic && n_read && atomicAdd(&length[c], 1u) >= longest) s_any = 2;
+      if (atomic && n_read) {
+        atomicAdd(&length[c], 1u);
+        atomicOr(&tags[c], tag_of(h));
+      }
 #pragma unroll
       for (int q = 0; q < 5; q++) s_acc[q][i] = 0;
     }
@@ -776,8 +785,12 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
     }
     auto count_read = [&](const FRec& x, uint32_t idx) {
       const uint32_t bx = block_of(x.tid, T.tpb, shift);
-      const uint32_t c = chain_of(x, bx);
+      const uint32_t h = location_hash(x, bx), c = h & (HN - 1);
       uint32_t j = head[c], k = head[c + HN];
+      if (k != END) {
+        if (tag_of(h) & ~tags[c]) k = END;  // none of its location
+        else if (length[c] > longest) s_any = 2;
+      }
       if (j == END) {
         j = k;
         k = END;
@@ -785,7 +798,7 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
       if (j == END) return;
       const uint32_t sx = WARP ? f.side[T.off + idx] : 0u;
 #pragma unroll 1
-      while (j != END) {
+      for (uint32_t left = 2 * CHAIN; j != END && left; left--) {  // (or another path counts the bucket, see above)
         const uint32_t at = j;
         j = s_next[j];
         if (j == END) {  // the writes, then the atomics
@@ -813,6 +826,10 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
     }
     flush_wave();
     __syncthreads();
+    if (s_any == 2) {  // reads of a word of many atomics
+      if (tx == 0) to_late();
+      return;
+    }
     // ---- atomics of one location that met reads but have no write: the first
     //      of them takes the sums of all
     const bool lone = tx < nw && s_lead[tx] == tx && s_acc[K_AR][tx] && (s_w[tx].w >> 16 & 3u) == 2u;
@@ -837,38 +854,40 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
     }
     emit(nw);
   } else {
-    uint32_t level = 0;
+    bool thinned = false;
     static_assert(CLASSES == 64, "a lane per class");
-    // a record's slot in the map of level l, and whether the levels so far kept it
-    auto level_slot = [&](const FRec& x, uint32_t l) {
-      return filter_group2(x, block_of(x.tid, T.tpb, shift), l) >> (32 - L_BITS);
-    };
+    // a record's place in map m, and whether all of them hold it
+    auto place = [&](const FRec& x, uint32_t bx, uint32_t m) { return filter_group2(x, bx, m) >> (32 - L_BITS); };
     auto kept = [&](const FRec& x) {
-      for (uint32_t l = 0; l < level; l++)
-        if (!bit(W + l * L_WORDS, level_slot(x, l))) return false;
-      return true;
+      const uint32_t bx = block_of(x.tid, T.tpb, shift);
+      uint32_t all = 1;
+      for (uint32_t m = 0; m < MAPS; m++) all &= bit(W + m * L_WORDS, place(x, bx, m));
+      return all != 0;
     };
     auto atomics = [](const uint32_t(&k)[4]) {
       return k[0] >> 31 | k[1] >> 31 << 1 | k[2] >> 31 << 2 | k[3] >> 31 << 3;
     };
     auto keep_of = [&](const uint32_t(&k)[4], uint32_t pick, uint32_t base) {
-      if (level == 0) return pick;
+      if (!thinned) return pick;
       uint32_t left = pick & ~atomics(k);
       for_records(k, pick & ~left, base, [&](uint32_t u, const FRec& x, uint32_t) { left |= kept(x) ? 1u << u : 0u; });
       return left;
     };
     const uint32_t most = f.max_rounds;
-    uint32_t before = 0;
-    if (n_left > WCAP) {
-      for (;;) {
+    bool listed = n_left <= WCAP;  // the list holds the candidates
+    while (!listed) {
+      uint32_t fit = 2 * CLASSES, fit_writes = 1;
+      if (thinned || n_left <= most * WCAP) {  // the candidates that are left, listed and by class
         __syncthreads();
         if (tx < 2 * CLASSES) s_cls[tx / CLASSES][tx % CLASSES] = 0;
+        if (tx == 0) s_nw = 0;
         __syncthreads();
-        // (a first look at a sixteenth: where that is too much already, the rest need not be read)
-        uint32_t fit = 0, fit_writes = 0, seen = 0;
-        for (uint32_t lo = 0, hi = T.ntiles >= 32 ? T.ntiles / 16 : T.ntiles; lo < T.ntiles && fit <= most; lo = hi, hi = T.ntiles) {
+        // (after a look at a sixteenth of the tiles: where that is too much
+        // already, the rest need not be read)
+        for (uint32_t lo = 0, hi = T.ntiles >= 32 ? T.ntiles / 16 : T.ntiles; lo < T.ntiles; lo = hi, hi = T.ntiles) {
           for_keys(true, lo, hi, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
             const uint32_t pick = keep_of(k, in_round(k, live, 0), base);
+            append(k, pick, base, s_blk, WCAP, &s_nw);
 #pragma unroll
             for (uint32_t u = 0; u < 4; u++)
               if ((pick >> u) & 1u) {
@@ -881,8 +900,6 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
           // the fewest rounds that each fit: lane r adds up the classes of round r
           if (tx < 2 * CLASSES) {
             uint32_t sum = s_cls[tx / CLASSES][tx % CLASSES], r = CLASSES;
-            const uint32_t all = wave_reduce(sum, 0u, [](uint32_t a, uint32_t c) { return a + c; });
-            if (tx == 0) s_nw = all;
             if (__any(sum > WCAP)) r = 2 * CLASSES;
             while (r <= CLASSES && r > 1) {
               sum += __shfl_xor(sum, (int)(r / 2));
@@ -895,41 +912,44 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
           __syncthreads();
           fit = uniform(s_base);
           fit_writes = uniform(s_n);
-          if (lo == 0) seen = uniform(s_nw);
+          if (fit > most) break;
         }
         if (fit <= most) {
           rounds = fit;
+          listed = uniform(s_nw) <= WCAP;
           break;
         }
-        // too many writes, or atomics that do meet one or a read (a level that
-        // keeps half of them says so)
-        if (fit_writes > most || level == MAX_LEVEL || (level && seen > before / 2)) return full();
-        before = seen;
-        // ---- one more level: where the writes and the reads are that an atomic may meet
-        uint32_t* const lw = W + level * L_WORDS;
-        for (uint32_t i = tx; i < L_WORDS; i += NTH) lw[i] = 0;
-        __syncthreads();
-        auto add = [&](const uint32_t(&k)[4], uint32_t pick, uint32_t base) {
-          for_records(k, pick, base, [&](uint32_t, const FRec& x, uint32_t) {
-            const uint32_t s = level_slot(x, level);
-            if (!bit(lw, s)) set(lw, s);
-          });
-        };
-        for_keys(true, 0, T.ntiles, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
-          add(k, in_round(k, live & ~atomics(k), 0), base);
-        });
-        for_keys_records(false, r0, r1, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
-          add(k, in_round(k, live, 0), base);
-        });
-        __syncthreads();
-        level++;
       }
+      if (fit_writes > most || thinned) return full();  // too many writes, or atomics that do meet one or a read
+      // ---- the maps: where the writes and the reads are that an atomic may meet
+      __syncthreads();
+      for (uint32_t i = tx; i < MAPS * L_WORDS; i += NTH) W[i] = 0;
+      __syncthreads();
+      auto add = [&](const FRec& x) {
+        const uint32_t bx = block_of(x.tid, T.tpb, shift);
+        for (uint32_t m = 0; m < MAPS; m++) {
+          const uint32_t s = place(x, bx, m);
+          if (!bit(W + m * L_WORDS, s)) set(W + m * L_WORDS, s);
+        }
+      };
+      for_keys(true, 0, T.ntiles, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
+        for_records(k, in_round(k, live & ~atomics(k), 0), base, [&](uint32_t, const FRec& x, uint32_t) { add(x); });
+      });
+      if (n_read <= RCAP) {
+        for (uint32_t i = tx; i < n_read; i += NTH) add(load_frec(s_read[i]));
+      } else {
+        for_keys_records(false, r0, r1, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
+          for_records(k, in_round(k, live, 0), base, [&](uint32_t, const FRec& x, uint32_t) { add(x); });
+        });
+      }
+      __syncthreads();
+      thinned = true;
     }
 #pragma unroll 1
     for (uint32_t round = 0; round < rounds; round++) {
       uint32_t tx = threadIdx.x;
       asm volatile("" : "+v"(tx));  // keeps per-thread addresses out of registers across the passes
-      if (n_left > WCAP) {          // this round's
+      if (!listed) {                // this round's
         __syncthreads();
         if (tx == 0) s_nw = 0;
         __syncthreads();

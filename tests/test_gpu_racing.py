@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 
 import oracle
+import tracegen
 from tracegen import ATOMIC, READ, RECORD_DTYPE, WRITE
 
 pytestmark = pytest.mark.gpu
@@ -148,3 +149,25 @@ def test_words_no_table_holds(log2, form):
     }[form]
     want = compare(f"{form}, 2^{log2}", make(), private(n, rng), 3.0)
     assert (len(want) == 0) == (form in ("one thread", "counters"))
+
+
+@pytest.mark.parametrize("n_blocks", [8, 32, 64, 256, 1024])
+def test_hot_atomics_are_thinned_out(n_blocks):
+    """Generated traces with one access in twenty atomic, most of them on a few
+    hot words that nobody reads or writes: a bucket whose hot word shares its
+    slot with a stranger's record is still counted, and the call does not sort."""
+    import paper_1905_01833_amd as pkg
+
+    c = pkg.Context(0, profile=True)
+    try:
+        for seed in range(4):
+            recs, _ = tracegen.c2(n_blocks=n_blocks, inject_rate=0.0, seed=seed)
+            want, wsum = oracle.closed_form_par(recs, tpb=512)
+            print(f"[gpu] {len(recs)} records with atomics, seed {seed}", flush=True)
+            c.set_tuning(pkg.sim_size_class(len(recs)), {})
+            got, gsum = c.check_traces_device(torch.from_numpy(recs.view(np.uint8).reshape(-1, 16)).to("cuda:0"), None, 512)
+            assert got.tobytes() == want.tobytes() and gsum.tobytes() == wsum.tobytes()
+            t = c.stage_times()
+            assert t["filter_count"][1] == 1 and t["keygen"][1] == 0, t
+    finally:
+        c.close()
