@@ -74,6 +74,7 @@ struct sim_ctx {
   // Calls of a kind that still take the sorting path, after one that the
   // grouped count had no room for.
   uint32_t group_pause[N_KIND] = {};
+  uint32_t group_misses[N_KIND] = {};  // such calls in a row
   uint64_t alloc_gen = 0;   // bumped whenever a device buffer is reallocated
   uint64_t meta_gen = 0;    // bumped whenever a call's tables are uploaded
   uint64_t host_gen = 0;    // bumped whenever the host copy's trace and group tables are rebuilt
@@ -485,9 +486,12 @@ bool group_pays(const sim_ctx* c, const uint64_t* offsets, uint32_t n_traces, ui
   return true;
 }
 // After a call that the grouped count had no room for (more racing locations
-// than one for sixteen records, or too many writes that share a group), this
-// many calls of the kind go without it.
+// than one for sixteen records, or too many writes that share a group), so many
+// calls of the kind go without it: none after the first such call in a row, then
+// 1, 3, 7 and at most 15.  A single one (of a server's many, say) costs the others
+// nothing; a context whose calls all race pays for one vain count in sixteen.
 constexpr uint32_t GROUP_PAUSE = 15;
+uint32_t group_pause_after(uint32_t misses) { return misses > 4 ? GROUP_PAUSE : (1u << (misses - 1)) - 1; }
 // Calls whose traces all hold no more records are counted without a partition,
 // a workgroup per trace.  Partitioned / direct, in us: one trace of 2^10 48 / 35,
 // 2^12 51 / 38, 2^13 53 / 44, 2^14 58 / 55; 64 traces of 2^8 to 2^11 56 / 42, of
@@ -1303,10 +1307,12 @@ int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const
   if (head->error_flags & LAYOUT_ERR_RECORD)
     return fail(c, SIM_ERECORD, "invalid record at index %llu (action > 2 or space > 1)",
                 (unsigned long long)head->first_bad);
+  const Kind kind = sink.side ? KIND_WARP : KIND_PLAIN;
   if (head->error_flags) {
-    c->group_pause[sink.side ? KIND_WARP : KIND_PLAIN] = GROUP_PAUSE;
+    c->group_pause[kind] = group_pause_after(++c->group_misses[kind]);
     return RUN_SORT;
   }
+  c->group_misses[kind] = 0;
   return deliver_result(c, offsets, n_traces, s, sink, head->entries, f.sorted, true,
                         head->entries <= host_cap ? (const sim_race*)host_entries : nullptr);
 }

@@ -171,3 +171,39 @@ def test_hot_atomics_are_thinned_out(n_blocks):
             assert t["filter_count"][1] == 1 and t["keygen"][1] == 0, t
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("warp", [False, True])
+def test_one_such_call_costs_the_others_nothing(warp):
+    """After a call that had to sort, calls that need not are counted; a row of
+    such calls is tried ever more rarely, and each kind of call by itself."""
+    import paper_1905_01833_amd as pkg
+
+    rng = np.random.default_rng(5)
+    n = 1 << 16
+    racing, clean = flag(n, rng, 0.25), private(n, rng)
+    side = np.zeros(n, dtype=np.uint32)
+    dside = torch.from_numpy(side.view(np.int32)).to("cuda:0") if warp else None
+    dev = [torch.from_numpy(r.view(np.uint8).reshape(-1, 16)).to("cuda:0") for r in (racing, clean)]
+    want = [oracle.closed_form_warp(r, side, None, 256) if warp else oracle.closed_form(r, None, 256) for r in (racing, clean)]
+    c = pkg.Context(0, profile=True)
+    c.set_tuning(pkg.sim_size_class(n), {})
+    try:
+        def counted(k):
+            print(f"[gpu] {'racing' if k == 0 else 'clean'} call, warp-aware {warp}", flush=True)
+            got, _ = call(c, dev[k], dside)
+            assert got[0].tobytes() == want[k][0].tobytes() and got[1].tobytes() == want[k][1].tobytes()
+            t = c.stage_times()
+            return t["filter_count"][1] > 0, t["keygen"][1] > 0
+
+        assert counted(1) == (True, False)
+        for _ in range(3):
+            assert counted(0) == (True, True)  # tried, then sorted
+            assert counted(1) == (True, False)
+        tried = [counted(0)[0] for _ in range(40)]
+        assert tried == [k in (0, 1, 3, 7, 15, 31) for k in range(40)]
+        if warp:
+            got, _ = c.check_traces_device(dev[1], None, 256)
+            assert c.stage_times()["keygen"][1] == 0
+    finally:
+        c.close()
