@@ -1153,9 +1153,9 @@ __global__ __launch_bounds__(NT) void k_entries_place(FilterBuffers f) {
     base += c;
   }
   __syncthreads();
-  // (Entries of one trace tend to lie together: a lane adds for those of its
-  // wave, for the wave's first few traces, as atomics to one address take about
-  // 11 ns each: 60000 entries of one of two traces took 700 us one by one.)
+  // (Entries of one trace tend to lie together: where a wave has many, a lane adds
+  // for all of them, as atomics to one address take about 11 ns each: 60000
+  // entries of one of two traces took 700 us one by one.)
   for (uint32_t i0 = blockIdx.x * NT; i0 < n; i0 += gridDim.x * NT) {
     const uint32_t i = i0 + tx;
     bool todo = i < n;
@@ -1167,6 +1167,7 @@ __global__ __launch_bounds__(NT) void k_entries_place(FilterBuffers f) {
       if (!left) break;
       const uint32_t first = (uint32_t)__builtin_ctzll(left), lt = readlane(t, (int)first);
       const uint64_t same = __ballot(todo && t == lt);
+      if (__popcll(same) < 16) break;
       uint32_t base = 0;
       if (__lane_id() == first) base = atomicAdd(&f.trace_fill[lt], (uint32_t)__popcll(same));
       base = readlane(base, (int)first);
@@ -1203,6 +1204,7 @@ __global__ __launch_bounds__(NT) void k_entries_sort(FilterBuffers f) {
   }
   if (err || late) return;
   auto sort = [&](uint32_t t, uint32_t n, uint32_t from, uint32_t step) {
+    if (!n) return;
     const uint32_t first = f.n_traces > 1 ? f.trace_first[t] : 0u;
     const RaceOut* src = (f.n_traces > 1 ? f.placed : f.entries) + first;
     RaceOut* dst = (n <= SORT_CHUNK ? (total <= f.host_cap ? f.host_entries : f.sorted)
@@ -1250,7 +1252,7 @@ __global__ __launch_bounds__(NT) void k_entries_sort(FilterBuffers f) {
       if (mk && e < m && q == 0) mk[c0 + rank] = EntryKey{s_place[e], s_unit[e]};
     }
   };
-  const uint32_t own = f.trace_cnt[blockIdx.x];
+  const uint32_t own = blockIdx.x < f.n_traces ? f.trace_cnt[blockIdx.x] : 0u;
   if (own <= SORT_CHUNK) sort(blockIdx.x, own, blockIdx.y, gridDim.y);
   if (f.cnt[FC_MOST] <= SORT_CHUNK) return;
   const uint32_t all = gridDim.x * gridDim.y, me = blockIdx.y * gridDim.x + blockIdx.x;
@@ -1370,8 +1372,11 @@ hipError_t launch_filter_out(const FilterBuffers& f, hipStream_t s) {
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   const uint32_t chunks = cdiv(f.entries_cap, SORT_CHUNK);
-  hipLaunchKernelGGL(k_entries_sort, dim3(f.n_traces, std::max(1u, std::min(1024u / f.n_traces, cdiv(f.entries_cap, 16)))), dim3(NT),
-                     0, s, f);
+  // (many traces: a workgroup each, and as many as it takes for a long one among them)
+  hipLaunchKernelGGL(k_entries_sort,
+                     f.n_traces <= 64 ? dim3(f.n_traces, std::min(1024u / f.n_traces, cdiv(f.entries_cap, 16)))
+                                      : dim3(std::max(f.n_traces, 512u)),
+                     dim3(NT), 0, s, f);
   if ((e = hipGetLastError()) != hipSuccess || chunks <= 1) return e;
   hipLaunchKernelGGL(k_entries_merge, dim3(std::min(2048u, cdiv(f.entries_cap, NT))), dim3(NT), 0, s, f);
   return hipGetLastError();
