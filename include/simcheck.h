@@ -110,9 +110,11 @@ enum {
                           checks of fewer than 2^20 records sort, unless the default shape (all
                           fields 0) is set for their size class (sim_set_tuning): they then run, and
                           are timed, as without the flag */
-  SIM_CFG_GRAPHS = 2   /* capture each call's launch sequence as a HIP graph and replay it while
-                          calls keep the same shape (records pointer, offsets, threads per block,
-                          stream); needs a non-NULL stream */
+  SIM_CFG_GRAPHS = 2   /* calls that sort (see sim_tuning): capture each call's launch sequence as a HIP
+                          graph and replay it while calls keep the same shape (records pointer,
+                          offsets, threads per block, stream); needs a non-NULL stream.  Race checks
+                          that count by group launch their few kernels directly, which takes less
+                          time than a graph's launch; so do warp-aware and fitness calls */
 };
 
 typedef struct sim_ctx sim_ctx;
@@ -384,6 +386,10 @@ typedef struct sim_stage_time {
 
 int sim_stage_times(const sim_ctx* ctx, sim_stage_time* out, int cap);
 const char* sim_stage_name(int stage);
+
+/* Calls of this context so far whose launches were a captured graph's
+ * (SIM_CFG_GRAPHS).                                                        */
+uint32_t sim_graph_launches(const sim_ctx* ctx);
 
 /* ----------------------------------------------------------------- tuning */
 

@@ -47,7 +47,7 @@ EXPORTS = [
     "sim_check_traces_device_noalloc", "sim_result_free", "sim_check_traces_warp_device", "sim_check_traces_warp",
     "sim_check_sync_device", "sim_check_sync", "sim_barrier_result_free", "sim_eval_fitness_device",
     "sim_eval_fitness", "sim_check_divergence_device", "sim_check_divergence", "sim_divergence_result_free",
-    "sim_stage_times", "sim_stage_name", "sim_size_class", "sim_set_tuning", "sim_get_tuning", "sim_autotune",
+    "sim_stage_times", "sim_stage_name", "sim_graph_launches", "sim_size_class", "sim_set_tuning", "sim_get_tuning", "sim_autotune",
     "sim_server_create", "sim_server_destroy", "sim_submit", "sim_submit_device", "sim_poll", "sim_wait",
     "sim_server_get_stats", "sim_server_last_error",
 ]
@@ -188,6 +188,8 @@ def load() -> ctypes.CDLL:
     lib.sim_stage_times.argtypes = [P, ctypes.POINTER(_StageTime), ctypes.c_int]
     lib.sim_stage_name.restype = ctypes.c_char_p
     lib.sim_stage_name.argtypes = [ctypes.c_int]
+    lib.sim_graph_launches.restype = ctypes.c_uint32
+    lib.sim_graph_launches.argtypes = [P]
     lib.sim_size_class.restype = ctypes.c_uint32
     lib.sim_size_class.argtypes = [ctypes.c_uint64]
     lib.sim_set_tuning.restype = ctypes.c_int
@@ -516,6 +518,11 @@ def sim_stage_times(ctx):
     return {lib.sim_stage_name(i).decode(): (arr[i].ms, arr[i].launches) for i in range(n)}
 
 
+def sim_graph_launches(ctx) -> int:
+    """Calls of a context whose launches were a captured graph's."""
+    return int(load().sim_graph_launches(ctx))
+
+
 def sim_size_class(total_records: int) -> int:
     return int(load().sim_size_class(int(total_records)))
 
@@ -685,6 +692,9 @@ class Context:
 
     def stage_times(self):
         return sim_stage_times(self._ctx)
+
+    def graph_launches(self) -> int:
+        return sim_graph_launches(self._ctx)
 
     def autotune(self, tensor, offsets=None, threads_per_block=1, stream=None, reps: int = 3) -> dict:
         """Autotune the launch shape for calls the size of this input (device

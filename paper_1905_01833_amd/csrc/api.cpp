@@ -5,10 +5,10 @@
 // host staging for the small per-call tables and results.  A check is one
 // ordered sequence of kernel launches on one stream and one synchronisation;
 // there is no CPU fallback.  Most checks count their races by group
-// (run_grouped, filter.hip); barrier and fitness checks, captured calls and
-// those the grouped count has no room for sort (kernels.hip).  Rare conditions
-// cost
-// a second round on the device: a trace needing more radix passes than the
+// (run_grouped, filter.hip); barrier and fitness checks, no-allocation calls,
+// calls whose size class has a launch shape, those with a trace of more than
+// 2^27 records and those the grouped count has no room for sort (kernels.hip).
+// Rare conditions cost a second round on the device: a trace needing more radix passes than the
 // previous call did, a tile with more racing locations than its staging
 // slice holds, or more racing locations than the output buffer holds.
 //
@@ -105,6 +105,8 @@ struct sim_ctx {
     bool wide = false;
     uint32_t db = 0;  // digit width of the captured passes
   } graph;
+
+  uint32_t graph_launches = 0;  // calls whose launches were a graph's
 
   // launch shapes per size class (set by hand or by sim_autotune)
   sim_tuning tuning[SIM_SIZE_CLASSES] = {};
@@ -967,6 +969,7 @@ int run(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_
   }
   if (replay) {
     e = hipGraphLaunch(G.exec, s);
+    c->graph_launches++;
   } else if (use_graph) {
     if (G.exec) (void)hipGraphExecDestroy(G.exec);
     G.exec = nullptr;
@@ -994,6 +997,7 @@ int run(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_
       G.wide = wide;
       G.db = db;
       e = hipGraphLaunch(G.exec, s);
+      c->graph_launches++;
     } else {  // capture not possible here: run the launches directly
       (void)hipGetLastError();
       if (G.exec) (void)hipGraphExecDestroy(G.exec);
@@ -1288,6 +1292,8 @@ int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const
   if (f.tr_src == f.tr && (e = hipMemcpyAsync(f.tr, ht, n_traces * sizeof(FTrace), hipMemcpyHostToDevice, s)))
     return hip_fail(c, e, "table upload");
   c->meta_gen++;
+  // (Graph contexts launch directly as well: replaying these four to seven kernels
+  // as a graph took 61 us for a call of 2^14 records, launching them 55.)
   if ((e = mark(0)) || (e = launch_filter_part(f, s)) || (e = mark(1)) || (e = launch_filter_count(f, s)) ||
       (e = mark(2)) || (e = launch_filter_out(f, s)) || (e = mark(3)) || (e = hipStreamSynchronize(s)))
     return hip_fail(c, e, "grouped count");
@@ -1793,6 +1799,8 @@ int sim_stage_times(const sim_ctx* c, sim_stage_time* out, int cap) {
   for (int i = 0; i < n; i++) out[i] = c->times[i];
   return n;
 }
+
+uint32_t sim_graph_launches(const sim_ctx* c) { return c ? c->graph_launches : 0; }
 
 const char* sim_stage_name(int stage) { return (stage >= 0 && stage < N_STAGE) ? kStageNames[stage] : ""; }
 
