@@ -75,6 +75,7 @@ struct sim_ctx {
   // grouped count had no room for.
   uint32_t group_pause[N_KIND] = {};
   uint32_t group_misses[N_KIND] = {};  // such calls in a row
+  bool group_rounds[N_KIND] = {};      // the previous grouped call's buckets had candidates for several tables
   uint64_t alloc_gen = 0;   // bumped whenever a device buffer is reallocated
   uint64_t meta_gen = 0;    // bumped whenever a call's tables are uploaded
   uint64_t host_gen = 0;    // bumped whenever the host copy's trace and group tables are rebuilt
@@ -1199,6 +1200,7 @@ int run(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_
 int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const* trace_recs, const uint64_t* offsets,
                 uint32_t n_traces, const uint32_t* tpb, hipStream_t s, const Sink& sink, uint64_t total,
                 uint32_t n_tiles) {
+  const Kind kind = sink.side ? KIND_WARP : KIND_PLAIN;
   auto up = [](uint64_t x) { return (x + 255) / 256 * 256; };
   const size_t tr_bytes = up(n_traces * sizeof(FTrace));
   // records the buffers are sized for: room for a few entries (a server's worker is charged for its own)
@@ -1275,6 +1277,7 @@ int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const
   f.late_wait = late_wait ? 1u : 0u;
   // (a round is 50 us of one workgroup; the whole sort of a small call takes 100 to 190)
   f.max_rounds = late_wait ? 2u : 4u;
+  f.rounds = c->group_rounds[kind] ? 1u : 0u;
   f.max_lgb = max_lgb;
   f.side = sink.side;
   f.entries = (RaceOut*)k1;
@@ -1313,7 +1316,7 @@ int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const
   if (head->error_flags & LAYOUT_ERR_RECORD)
     return fail(c, SIM_ERECORD, "invalid record at index %llu (action > 2 or space > 1)",
                 (unsigned long long)head->first_bad);
-  const Kind kind = sink.side ? KIND_WARP : KIND_PLAIN;
+  c->group_rounds[kind] = head->rounds > (late_wait ? 0u : buckets / 32);
   if (head->error_flags) {
     c->group_pause[kind] = group_pause_after(++c->group_misses[kind]);
     return RUN_SORT;

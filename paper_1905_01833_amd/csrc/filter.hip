@@ -56,6 +56,7 @@ __global__ __launch_bounds__(NT) void k_filter_begin(FilterBuffers f) {
     f.cnt[FC_EXTRA] = 0;
     f.cnt[FC_MOST] = 0;
     f.cnt[FC_LATE] = 0;
+    f.cnt[FC_ROUNDS] = 0;
   }
   const FTrace T = f.tr_src[t];
   if (threadIdx.x == 0) {
@@ -281,10 +282,18 @@ __device__ __forceinline__ words2 load_words2(GWords p) { return *(const __attri
 // GROUP_LEVELS), one look-up per level and read however many wrote the word.
 // (800 writers and 3276 readers of a word in a trace of 2^14 records took 3309 us
 // by chains, 100 so.)  They take a CU each, with twice the registers.
-enum : int { BY_BUCKET = 0, LATE_BUCKET = 1, DIRECT_TRACE = 2, LATE_TRACE = 3 };
+//
+// ROUNDS: as BY_BUCKET or DIRECT_TRACE, but up to four tables of candidates are
+// filled one after another before a bucket is handed over.  Random words collide
+// often enough for that where nearly all records write.  The loop costs registers
+// (batch of 4096 traces: 4405 us with it, 4137 without), so a context takes it
+// after a call where one bucket in 32 was such (in a small call, any): 2^24
+// records that all write words of their own take 691 us with later workgroups,
+// 395 so.
+enum : int { BY_BUCKET = 0, LATE_BUCKET = 1, DIRECT_TRACE = 2, LATE_TRACE = 3, ROUNDS = 4 };
 template <int MODE, bool WARP, uint32_t WCAP, uint32_t RCAP>
 __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_count(FilterBuffers f) {
-  constexpr bool LATE = MODE & LATE_BUCKET, DIRECT = MODE & DIRECT_TRACE;
+  constexpr bool LATE = MODE & LATE_BUCKET, DIRECT = MODE & DIRECT_TRACE, LOOP = MODE & ROUNDS;
   constexpr uint32_t NTH = FNT;
   constexpr uint32_t SB = FILTER_SLOT_BITS, W_WORDS = (1u << SB) / 32, D_WORDS = W_WORDS / 2, T_WORDS = W_WORDS / 4;
   constexpr uint32_t HN = 512, END = 0xFFFFu;  // chains of writes, and as many of atomics
@@ -338,7 +347,7 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
   bucket = uniform(bucket);
   part = uniform(part);
   const uint32_t item = uniform(f.extra_max && !DIRECT ? f.hot[bucket] : 1u), parts = item & ~HOT_ITEM;
-  if (MODE == BY_BUCKET && (item & HOT_ITEM) && blockIdx.x >= f.extra_max) return;
+  if (!LATE && !DIRECT && (item & HOT_ITEM) && blockIdx.x >= f.extra_max) return;
   trace = uniform(DIRECT ? trace : f.bucket_trace[bucket]);
   FTrace T = f.tr[trace];
   T.rec = (const void*)readfirstlane((uint64_t)T.rec);
@@ -363,6 +372,7 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
   if (tx == 0) {
     s_n = 0;
     s_nw = 0;
+    if (LOOP) s_cls[0][0] = s_cls[0][1] = s_cls[0][2] = s_cls[0][3] = 0;
     s_any = (f.ctrl->error_flags & ERR_GROUP_FULL) ? 3u : 0u;
   }
   __syncthreads();
@@ -513,7 +523,7 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
         if (!(k[u] & FILTER_ATOMIC) && !bit(D, sd)) set(D, sd);
       }
   };
-  if constexpr (MODE == DIRECT_TRACE) {  // the records: their keys (slot | action), and the writes among them
+  if constexpr (DIRECT && !LATE) {  // the records: their keys (slot | action), and the writes among them
     constexpr uint32_t Q = 8;  // records in flight per thread
     const GRecords p = global_records(T.rec);
     const uint32_t shift = block_shift(T.tpb), n = (uint32_t)T.n;
@@ -607,21 +617,33 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
     }
   };
 
-  // ---- the writes and atomics that are left: all of them
-  for_keys(true, 0, T.ntiles, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
-    uint32_t pick = 0;
+  // ---- the writes and atomics that are left: all of them, listed
+  uint32_t rounds = 1;
+  auto list_writes = [&](bool first, uint32_t round) {  // (the first time W and T tell them, then D alone)
+    for_keys(true, 0, T.ntiles, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
+      uint32_t pick = 0;
 #pragma unroll
-    for (uint32_t u = 0; u < 4; u++)
-      if ((live >> u) & 1u) {
-        const uint32_t s = slot_of(k[u]);
-        const uint32_t in_d = bit(D, s >> 1), other = (k[u] & FILTER_ATOMIC) ? bit(W, s) : bit(A, s >> 2);
-        pick |= (in_d | other) << u;
-        if (other && !in_d) set(D, s >> 1);  // (D alone tells the candidates from here on)
+      for (uint32_t u = 0; u < 4; u++)
+        if ((live >> u) & 1u) {
+          const uint32_t s = slot_of(k[u]);
+          uint32_t in_d = bit(D, s >> 1);
+          if (first) {
+            const uint32_t other = (k[u] & FILTER_ATOMIC) ? bit(W, s) : bit(A, s >> 2);
+            if (other && !in_d) set(D, s >> 1);
+            in_d |= other;
+          }
+          pick |= ((s & (rounds - 1)) == round ? in_d : 0u) << u;
+        }
+      append(k, pick, base, s_blk, WCAP, &s_nw);
+      if (LOOP && !first && rounds == 1) {  // (by the low bits of the slot, for tables of them)
+#pragma unroll
+        for (uint32_t u = 0; u < 4; u++)
+          if ((pick >> u) & 1u) atomicAdd(&s_cls[0][slot_of(k[u]) & 3u], 1u);
       }
-    append(k, pick, base, s_blk, WCAP, &s_nw);
-  });
-  __syncthreads();
-  const uint32_t n_left = uniform(s_nw);
+    });
+    __syncthreads();
+    return uniform(s_nw);
+  };
   auto to_late = [&]() {  // by one thread
     const uint32_t at = atomicAdd(&f.cnt[FC_LATE], 1u);
     if (at < f.late_max) f.late[at] = make_uint2(DIRECT ? trace : bucket, part);
@@ -629,6 +651,11 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
   };
   auto full = [&]() {
     if (tx == 0) atomicOr(&f.ctrl->error_flags, ERR_GROUP_FULL);
+  };
+  // a later workgroup's (but the sort's, where some of the bucket's entries are out)
+  auto give_up = [&](uint32_t round) {
+    if (round) return full();
+    if (threadIdx.x == 0) to_late();
   };
   // the reads' pairs, summed per thread while the location stays the same (the
   // lanes' LDS atomics to a hot word's sums go one by one)
@@ -699,7 +726,6 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
     }
   };
   // keys of D that are a round's
-  uint32_t rounds = 1;
   auto in_round = [&](const uint32_t(&k)[4], uint32_t live, uint32_t round) {
     uint32_t pick = 0;
 #pragma unroll
@@ -711,149 +737,172 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
     return pick;
   };
   if constexpr (!LATE) {
-    if (n_left > WCAP) {  // more than the table holds
-      if (n_left > hopeless(f.max_rounds)) {  // by a sample, too many writes for any
-        const uint32_t plain = (uint32_t)__syncthreads_count(tx < WCAP && frec_action(load_frec(s_blk[min(tx, WCAP - 1)])) == 1u);
-        if ((uint64_t)n_left * plain > (uint64_t)hopeless(f.max_rounds) * WCAP) return full();
-      }
-      if (tx == 0) to_late();
-      return;
-    }
-    const uint32_t nw = n_left;
-    if (!nw) return;
-    if (!pair_sums_fit(n_read, nw)) return full();  // sums of pairs are kept in 32 bits
-    uint32_t* const head = W;  // chains of writes, and as many of atomics (W is free)
-    // the latter's lengths, and which bits of a location's tag are set (low half)
-    // or clear (high half) in some record of theirs: most reads that meet a hot
-    // word's long chain by chance need not walk it
-    uint32_t* const length = head + 2 * HN;
-    uint32_t* const tags = head + 3 * HN;
-    for (uint32_t k = tx; k < 4 * HN; k += NTH) head[k] = k < 2 * HN ? END : 0u;
-    const uint32_t longest = n_read > RCAP ? MANY_WRITERS : CHAIN;
-    __syncthreads();
-    auto chain_of = [&](const FRec& x, uint32_t bx) { return location_hash(x, bx) & (HN - 1); };
-    auto tag_of = [](uint32_t h) { return h >> 16 | (~h & 0xFFFF0000u); };
-    if (tx < nw) {
-      const uint32_t i = tx, idx = s_blk[i];
-      const FRec x = load_frec(idx);
-      const uint32_t bx = block_of(x.tid, T.tpb, shift);
-      if (WARP) s_side[i] = f.side[T.off + idx];
-      s_w[i] = make_uint4(x.ulo, x.uhi, x.tid, x.meta);
-      s_blk[i] = bx;
-      const uint32_t h = location_hash(x, bx), c = h & (HN - 1), atomic = frec_action(x) == 2u;
-      s_next[i] = (uint16_t)atomicExch(&head[c + (atomic ? HN : 0u)], i);
-      if (atomic && n_read) {
-        atomicAdd(&length[c], 1u);
-        atomicOr(&tags[c], tag_of(h));
-      }
-#pragma unroll
-      for (int q = 0; q < 5; q++) s_acc[q][i] = 0;
-    }
-    __syncthreads();
-    // ---- a location's first write in the table, and the pairs of writes.
-    //      (An atomic walks the writes only: a hot word's atomics meet no other
-    //      atomic.  Without a write their location has no first one yet.)
-    if (tx < nw) {
-      const uint32_t i = tx;
-      const FRec x = w_at(i);
-      const uint32_t bx = s_blk[i], sx = WARP ? s_side[i] : 0u;
-      const bool atomic = frec_action(x) == 2u;
-      uint32_t first = i, ww = 0, aw = 0, xw = 0, left = longest;
+    uint32_t round = 0;
 #pragma unroll 1
-      for (uint32_t j = head[chain_of(x, bx)]; j != END && left; j = s_next[j], left--) {
-        if (!atomic && j >= i) continue;
-        const FRec y = w_at(j);
-        const uint32_t by = s_blk[j];
-        if (!same_location(x, bx, y, by)) continue;
-        first = first == i ? j : min(first, j);
-        if (part == 0 && pair_races(x, bx, y, by, WARP, T.tpb, sx, WARP ? s_side[j] : 0u)) {
-          if (atomic) aw++;
-          else ww++;
-          if (bx != by) xw++;
+    for (bool first = true;; first = false) {
+      uint32_t tx = threadIdx.x;
+      if (LOOP) asm volatile("" : "+v"(tx));  // keeps per-thread addresses out of registers across the passes
+      const uint32_t nw = list_writes(first, round);
+      if (nw > WCAP) {  // more than the table holds
+        if (LOOP && rounds > 1) return give_up(round);
+        if (nw > 4 * WCAP) {
+          // by a sample, more writes than a late workgroup may take either
+          const uint32_t plain = (uint32_t)__syncthreads_count(tx < WCAP && frec_action(load_frec(s_blk[min(tx, WCAP - 1)])) == 1u);
+          if ((uint64_t)nw * plain > (uint64_t)hopeless(f.max_rounds) * WCAP) return full();
+          return give_up(0);
         }
+        if (tx == 0 && first) atomicAdd(&f.cnt[FC_ROUNDS], 1u);
+        if (!LOOP) return give_up(0);
+        // First once more, as D grew while they were listed, and counted by the low
+        // bits of their slots; then in two or four tables that hold them.
+        if (!first) {
+          const uint32_t c0 = s_cls[0][0], c1 = s_cls[0][1], c2 = s_cls[0][2], c3 = s_cls[0][3];
+          if (max(max(c0, c1), max(c2, c3)) > WCAP) return give_up(0);
+          rounds = uniform(max(c0 + c2, c1 + c3) > WCAP ? 4u : 2u);
+        }
+        __syncthreads();
+        if (tx == 0) s_nw = 0;
+        __syncthreads();
+        continue;
       }
-      s_lead[i] = (uint16_t)first;
-      if (!left) s_any = 2;
-      if (ww) atomicAdd(&s_acc[K_WW][first], ww);
-      if (aw) atomicAdd(&s_acc[K_AW][first], aw);
-      if (xw) atomicAdd(&s_acc[K_XB][first], xw);
-    }
-    __syncthreads();
-    if (s_any == 2) {  // long chains
-      if (tx == 0) to_late();
-      return;
-    }
-    auto count_read = [&](const FRec& x, uint32_t idx) {
-      const uint32_t bx = block_of(x.tid, T.tpb, shift);
-      const uint32_t h = location_hash(x, bx), c = h & (HN - 1);
-      uint32_t j = head[c], k = head[c + HN];
-      if (k != END) {
-        if (tag_of(h) & ~tags[c]) k = END;  // none of its location
-        else if (length[c] > longest) s_any = 2;
+      if (!LOOP && !nw) return;
+      if (!pair_sums_fit(n_read, nw)) return full();  // sums of pairs are kept in 32 bits
+      uint32_t* const head = W;  // chains of writes, and as many of atomics (W is free)
+      // the latter's lengths, and which bits of a location's tag are set (low half)
+      // or clear (high half) in some record of theirs: most reads that meet a hot
+      // word's long chain by chance need not walk it
+      uint32_t* const length = head + 2 * HN;
+      uint32_t* const tags = head + 3 * HN;
+      for (uint32_t k = tx; k < 4 * HN; k += NTH) head[k] = k < 2 * HN ? END : 0u;
+      const uint32_t longest = n_read > RCAP ? MANY_WRITERS : CHAIN;
+      __syncthreads();
+      auto chain_of = [&](const FRec& x, uint32_t bx) { return location_hash(x, bx) & (HN - 1); };
+      auto tag_of = [](uint32_t h) { return h >> 16 | (~h & 0xFFFF0000u); };
+      if (tx < nw) {
+        const uint32_t i = tx, idx = s_blk[i];
+        const FRec x = load_frec(idx);
+        const uint32_t bx = block_of(x.tid, T.tpb, shift);
+        if (WARP) s_side[i] = f.side[T.off + idx];
+        s_w[i] = make_uint4(x.ulo, x.uhi, x.tid, x.meta);
+        s_blk[i] = bx;
+        const uint32_t h = location_hash(x, bx), c = h & (HN - 1), atomic = frec_action(x) == 2u;
+        s_next[i] = (uint16_t)atomicExch(&head[c + (atomic ? HN : 0u)], i);
+        if (atomic && n_read) {
+          atomicAdd(&length[c], 1u);
+          atomicOr(&tags[c], tag_of(h));
+        }
+#pragma unroll
+        for (int q = 0; q < 5; q++) s_acc[q][i] = 0;
       }
-      if (j == END) {
-        j = k;
-        k = END;
-      }
-      if (j == END) return;
-      const uint32_t sx = WARP ? f.side[T.off + idx] : 0u;
+      __syncthreads();
+      // ---- a location's first write in the table, and the pairs of writes.
+      //      (An atomic walks the writes only: a hot word's atomics meet no other
+      //      atomic.  Without a write their location has no first one yet.)
+      if (tx < nw) {
+        const uint32_t i = tx;
+        const FRec x = w_at(i);
+        const uint32_t bx = s_blk[i], sx = WARP ? s_side[i] : 0u;
+        const bool atomic = frec_action(x) == 2u;
+        uint32_t first = i, ww = 0, aw = 0, xw = 0, left = longest;
 #pragma unroll 1
-      for (uint32_t left = 2 * CHAIN; j != END && left; left--) {  // (or another path counts the bucket, see above)
-        const uint32_t at = j;
-        j = s_next[j];
-        if (j == END) {  // the writes, then the atomics
+        for (uint32_t j = head[chain_of(x, bx)]; j != END && left; j = s_next[j], left--) {
+          if (!atomic && j >= i) continue;
+          const FRec y = w_at(j);
+          const uint32_t by = s_blk[j];
+          if (!same_location(x, bx, y, by)) continue;
+          first = first == i ? j : min(first, j);
+          if (part == 0 && pair_races(x, bx, y, by, WARP, T.tpb, sx, WARP ? s_side[j] : 0u)) {
+            if (atomic) aw++;
+            else ww++;
+            if (bx != by) xw++;
+          }
+        }
+        s_lead[i] = (uint16_t)first;
+        if (!left) s_any = 2;
+        if (ww) atomicAdd(&s_acc[K_WW][first], ww);
+        if (aw) atomicAdd(&s_acc[K_AW][first], aw);
+        if (xw) atomicAdd(&s_acc[K_XB][first], xw);
+      }
+      __syncthreads();
+      if (s_any == 2) {  // long chains
+        return give_up(round);
+      }
+      auto count_read = [&](const FRec& x, uint32_t idx) {
+        const uint32_t bx = block_of(x.tid, T.tpb, shift);
+        const uint32_t h = location_hash(x, bx), c = h & (HN - 1);
+        uint32_t j = head[c], k = head[c + HN];
+        if (k != END) {
+          if (tag_of(h) & ~tags[c]) k = END;  // none of its location
+          else if (length[c] > longest) s_any = 2;
+        }
+        if (j == END) {
           j = k;
           k = END;
         }
-        const FRec y = w_at(at);
-        const uint32_t by = s_blk[at];
-        if (!same_location(x, bx, y, by) || !pair_races(x, bx, y, by, WARP, T.tpb, sx, WARP ? s_side[at] : 0u)) continue;
-        const uint32_t l = s_lead[at];
-        if (l != lead) flush();
-        lead = l;
-        if (frec_action(y) == 1u) rw++;
-        else ar++;
-        if (bx != by) xb++;
-      }
-    };
-    if (n_read <= RCAP) {
+        if (j == END) return;
+        const uint32_t sx = WARP ? f.side[T.off + idx] : 0u;
 #pragma unroll 1
-      for (uint32_t i = tx; i < n_read; i += NTH) count_read(load_frec(s_read[i]), s_read[i]);
-    } else if (n_read) {
-      for_keys_records(false, r0, r1, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
-        for_records(k, in_round(k, live, 0), base, [&](uint32_t, const FRec& x, uint32_t idx) { count_read(x, idx); });
-      });
-    }
-    flush_wave();
-    __syncthreads();
-    if (s_any == 2) {  // reads of a word of many atomics
-      if (tx == 0) to_late();
-      return;
-    }
-    // ---- atomics of one location that met reads but have no write: the first
-    //      of them takes the sums of all
-    const bool lone = tx < nw && s_lead[tx] == tx && s_acc[K_AR][tx] && (s_w[tx].w >> 16 & 3u) == 2u;
-    if (__syncthreads_or(lone)) {
-      uint32_t first = tx;
-      if (lone) {
-        const FRec x = w_at(tx);
-        const uint32_t bx = s_blk[tx];
-#pragma unroll 1
-        for (uint32_t j = head[chain_of(x, bx) + HN]; j != END; j = s_next[j]) {
-          if (j >= first || !s_acc[K_AR][j]) continue;
-          if (same_location(x, bx, w_at(j), s_blk[j])) first = j;
+        for (uint32_t left = 2 * CHAIN; j != END && left; left--) {  // (or another path counts the bucket, see above)
+          const uint32_t at = j;
+          j = s_next[j];
+          if (j == END) {  // the writes, then the atomics
+            j = k;
+            k = END;
+          }
+          const FRec y = w_at(at);
+          const uint32_t by = s_blk[at];
+          if (!same_location(x, bx, y, by) || !pair_races(x, bx, y, by, WARP, T.tpb, sx, WARP ? s_side[at] : 0u)) continue;
+          const uint32_t l = s_lead[at];
+          if (l != lead) flush();
+          lead = l;
+          if (frec_action(y) == 1u) rw++;
+          else ar++;
+          if (bx != by) xb++;
         }
+      };
+      if (n_read <= RCAP) {
+#pragma unroll 1
+        for (uint32_t i = tx; i < n_read; i += NTH) count_read(load_frec(s_read[i]), s_read[i]);
+      } else if (n_read) {
+        for_keys_records(false, r0, r1, [&](const uint32_t(&k)[4], uint32_t live, uint32_t base) {
+          for_records(k, in_round(k, live, round), base, [&](uint32_t, const FRec& x, uint32_t idx) { count_read(x, idx); });
+        });
       }
+      flush_wave();
       __syncthreads();
-      if (first != tx) {
-        atomicAdd(&s_acc[K_AR][first], s_acc[K_AR][tx]);
-        if (s_acc[K_XB][tx]) atomicAdd(&s_acc[K_XB][first], s_acc[K_XB][tx]);
-        s_lead[tx] = (uint16_t)first;
+      if (s_any == 2) {  // reads of a word of many atomics
+        return give_up(round);
       }
+      // ---- atomics of one location that met reads but have no write: the first
+      //      of them takes the sums of all
+      const bool lone = tx < nw && s_lead[tx] == tx && s_acc[K_AR][tx] && (s_w[tx].w >> 16 & 3u) == 2u;
+      if (__syncthreads_or(lone)) {
+        uint32_t first = tx;
+        if (lone) {
+          const FRec x = w_at(tx);
+          const uint32_t bx = s_blk[tx];
+#pragma unroll 1
+          for (uint32_t j = head[chain_of(x, bx) + HN]; j != END; j = s_next[j]) {
+            if (j >= first || !s_acc[K_AR][j]) continue;
+            if (same_location(x, bx, w_at(j), s_blk[j])) first = j;
+          }
+        }
+        __syncthreads();
+        if (first != tx) {
+          atomicAdd(&s_acc[K_AR][first], s_acc[K_AR][tx]);
+          if (s_acc[K_XB][tx]) atomicAdd(&s_acc[K_XB][first], s_acc[K_XB][tx]);
+          s_lead[tx] = (uint16_t)first;
+        }
+        __syncthreads();
+      }
+      emit(nw);
+      if (!LOOP || ++round == rounds) return;
+      __syncthreads();
+      if (tx == 0) s_nw = 0;
       __syncthreads();
     }
-    emit(nw);
   } else {
+    const uint32_t n_left = list_writes(true, 0);
     bool thinned = false;
     static_assert(CLASSES == 64, "a lane per class");
     // a record's place in map m, and whether all of them hold it
@@ -1199,6 +1248,7 @@ __global__ __launch_bounds__(NT) void k_entries_sort(FilterBuffers f) {
     h.entries = total;
     h.error_flags = err;
     h.late = late;
+    h.rounds = f.cnt[FC_ROUNDS];
     h.first_bad = f.ctrl->first_bad;
     *f.head = h;
   }
@@ -1346,12 +1396,15 @@ hipError_t launch_filter_count(const FilterBuffers& f, hipStream_t s) {
   }
   const dim3 grid(f.extra_max + tile_grid(f.n_buckets, 0, 0));
   const bool warp = f.side != nullptr;
-  if (f.direct)
-    hipLaunchKernelGGL((warp ? k_filter_count<DIRECT_TRACE, true, 960, 1408> : k_filter_count<DIRECT_TRACE, false, 1024, 1408>),
-                       dim3(f.n_traces), dim3(FNT), 0, s, f);
-  else
-    hipLaunchKernelGGL((warp ? k_filter_count<BY_BUCKET, true, 960, 1408> : k_filter_count<BY_BUCKET, false, 1024, 1408>), grid,
-                       dim3(FNT), 0, s, f);
+  auto count = [&](auto mode) {
+    constexpr int M = decltype(mode)::value;
+    hipLaunchKernelGGL((warp ? k_filter_count<M, true, 960, 1408> : k_filter_count<M, false, 1024, 1408>),
+                       (M & DIRECT_TRACE) ? dim3(f.n_traces) : grid, dim3(FNT), 0, s, f);
+  };
+  if (f.direct && f.rounds) count(std::integral_constant<int, DIRECT_TRACE | ROUNDS>());
+  else if (f.direct) count(std::integral_constant<int, DIRECT_TRACE>());
+  else if (f.rounds) count(std::integral_constant<int, BY_BUCKET | ROUNDS>());
+  else count(std::integral_constant<int, BY_BUCKET>());
   if ((e = hipGetLastError()) != hipSuccess || f.late_wait) return e;
   return launch_filter_late(f, f.late_max, s);
 }

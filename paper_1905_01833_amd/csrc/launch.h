@@ -129,8 +129,9 @@ struct Buffers {            // device pointers of one call
 
 // Counters of a grouped call (FilterBuffers::cnt): entries found, further
 // workgroups of hot buckets, entries of the trace with most (where they exceed
-// SORT_CHUNK), buckets or traces for the later workgroups.
-enum : uint32_t { FC_ENTRIES = 0, FC_EXTRA = 1, FC_MOST = 2, FC_LATE = 3, FC_COUNT = 4 };
+// SORT_CHUNK), buckets or traces for the later workgroups, those whose candidates
+// fill two to four tables.
+enum : uint32_t { FC_ENTRIES = 0, FC_EXTRA = 1, FC_MOST = 2, FC_LATE = 3, FC_ROUNDS = 4, FC_COUNT = 5 };
 constexpr uint32_t SORT_CHUNK = 2048;         // entries sorted in one workgroup's LDS
 // Entries of a trace, at most: beyond, merging its sorted chunks takes longer than
 // sorting its records does.  (Grouped / sorted, in us: 262144 entries of 2^24
@@ -142,7 +143,7 @@ struct GroupHead {          // what the host needs of a grouped call besides its
   uint32_t entries, error_flags;
   uint64_t first_bad;
   uint32_t late;            // with FilterBuffers::late_wait: what is still to be counted
-  uint32_t pad;
+  uint32_t rounds;          // FC_ROUNDS
 };
 struct FilterBuffers {      // device pointers of a call's grouped race count (filter.h, filter.hip)
   FTrace* tr;
@@ -161,6 +162,7 @@ struct FilterBuffers {      // device pointers of a call's grouped race count (f
   uint2* late;              // buckets (traces, if direct) for the later workgroups, and their part
   uint32_t late_max;        // room for them
   uint32_t late_wait;       // 1: the host starts those workgroups, if there is work for them; until then nothing is put in order
+  uint32_t rounds;          // 1: the first workgroups fill such tables themselves
   uint32_t max_rounds;      // tables a later workgroup may fill one after another, a power of two
   uint32_t max_lgb;         // the largest FTrace::lgb of the call
   const uint32_t* side;     // warp-aware check: one side word per record, else nullptr

@@ -207,3 +207,46 @@ def test_one_such_call_costs_the_others_nothing(warp):
             assert c.stage_times()["keygen"][1] == 0
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("warp", [False, True])
+@pytest.mark.parametrize("n", [8190, 16384, (1 << 16) + 5, 1 << 19, (1 << 22) + 77])
+@pytest.mark.parametrize("form", ["all write", "half atomic", "few words"])
+def test_several_tables_of_candidates(form, n, warp):
+    """Buckets whose candidates fill two to four tables: by later workgroups on
+    the first call, by the first ones from then on, and as before again after a
+    call that had none."""
+    import paper_1905_01833_amd as pkg
+
+    rng = np.random.default_rng(n)
+    r = private(n, rng)
+    if form == "all write":
+        r["unit"], r["action"] = (1 << 24) + np.arange(n), WRITE
+    elif form == "half atomic":
+        at = rng.random(n) < 0.5
+        r["unit"] = np.where(at, HOT + rng.integers(0, max(16, n // 128), n), r["unit"])
+        r["action"] = np.where(at, ATOMIC, r["action"])
+    else:  # words that a few threads of one block write and read, in every bucket
+        at = rng.permutation(n)[: n // 2]
+        r["unit"][at] = HOT + rng.integers(0, max(8, n // 8), len(at))
+        r["tid"][at] = rng.integers(0, 3, len(at)) * 40
+        r["action"][at] = rng.integers(0, 2, len(at))
+    at = rng.permutation(n)[: 2 * (n // 500)]  # and pairs that race
+    r["unit"][at], r["action"][at] = (1 << 41) + np.arange(len(at)) // 2, WRITE
+    r["tid"][at] = np.arange(len(at)) % 2 * 100
+    clean = private(n, rng)
+    side = (np.arange(n) % 3).astype(np.uint32) if warp else None
+    dside = torch.from_numpy(side.view(np.int32)).to("cuda:0") if warp else None
+    sets = []
+    for x in (r, clean):
+        want = oracle.closed_form_warp(x, side, None, 256) if warp else oracle.closed_form_par(x, tpb=256)
+        sets.append((torch.from_numpy(x.view(np.uint8).reshape(-1, 16)).to("cuda:0"), want))
+    c = pkg.Context(0)
+    try:
+        for k, x in enumerate((0, 0, 0, 1, 0, 1, 1, 0)):
+            print(f"[gpu] several tables, {form}, {n} records, warp-aware {warp}, call {k}", flush=True)
+            (got, gsum), _ = call(c, sets[x][0], dside)
+            assert got.tobytes() == sets[x][1][0].tobytes() and gsum.tobytes() == sets[x][1][1].tobytes(), (form, n, k)
+    finally:
+        c.close()
+    assert len(sets[0][1][0]) >= n // 500
