@@ -75,6 +75,7 @@ struct sim_ctx {
   // grouped count had no room for.
   uint32_t group_pause[N_KIND] = {};
   uint32_t group_misses[N_KIND] = {};  // such calls in a row
+  bool group_late[N_KIND] = {};        // the previous grouped call had work for the later workgroups
   bool group_rounds[N_KIND] = {};      // the previous grouped call's buckets had candidates for several tables
   uint64_t alloc_gen = 0;   // bumped whenever a device buffer is reallocated
   uint64_t meta_gen = 0;    // bumped whenever a call's tables are uploaded
@@ -1232,11 +1233,12 @@ int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const
   const uint32_t hot_part = (uint32_t)std::max<uint64_t>(HOT_PART, total / HOT_SHARE);
   const uint32_t extra_max = max_lgb < 3 ? 0u : (uint32_t)((std::min<uint64_t>(total / FILTER_BUCKET, HOT_MAX_ITEMS) + 8) / 8 * 8);
   const bool direct = longest <= GROUP_DIRECT_RECORDS;
-  // The later workgroups: always launched in calls of more than 16 tiles; in
-  // smaller ones (where an idle launch is 4 of 55 us) once the host sees that
-  // there is work for them.
-  const bool late_wait = direct || tiles <= 16;
-  const uint32_t late_max = std::min(direct ? n_traces : (late_wait ? buckets + extra_max : tiles), 1024u);
+  const bool small = direct || tiles <= 16;
+  // The later workgroups: launched with the others where the previous call had
+  // work for them, else once the host sees that there is some (an idle launch is 2
+  // of the 90 us of 700000 records, the host's look and launch about 12).
+  const bool late_wait = !c->group_late[kind];
+  const uint32_t late_max = std::min(direct ? n_traces : std::max(tiles, buckets + extra_max), 1024u);
   if (direct) rows = 0;
   const uint64_t rows_at = up(4 * room), extra_at = up(rows_at + 4 * rows),
                  late_at = extra_at + 8ull * extra_max;
@@ -1276,7 +1278,7 @@ int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const
   f.late_max = late_max;
   f.late_wait = late_wait ? 1u : 0u;
   // (a round is 50 us of one workgroup; the whole sort of a small call takes 100 to 190)
-  f.max_rounds = late_wait ? 2u : 4u;
+  f.max_rounds = small ? 2u : 4u;
   f.rounds = c->group_rounds[kind] ? 1u : 0u;
   f.max_lgb = max_lgb;
   f.side = sink.side;
@@ -1300,7 +1302,7 @@ int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const
   if ((e = mark(0)) || (e = launch_filter_part(f, s)) || (e = mark(1)) || (e = launch_filter_count(f, s)) ||
       (e = mark(2)) || (e = launch_filter_out(f, s)) || (e = mark(3)) || (e = hipStreamSynchronize(s)))
     return hip_fail(c, e, "grouped count");
-  if (!head->error_flags && head->late) {
+  if (!head->error_flags && late_wait && head->late) {
     f.late_wait = 0;
     if ((e = launch_filter_late(f, head->late, s)) || (e = mark(2)) || (e = launch_filter_out(f, s)) || (e = mark(3)) ||
         (e = hipStreamSynchronize(s)))
@@ -1316,7 +1318,8 @@ int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const
   if (head->error_flags & LAYOUT_ERR_RECORD)
     return fail(c, SIM_ERECORD, "invalid record at index %llu (action > 2 or space > 1)",
                 (unsigned long long)head->first_bad);
-  c->group_rounds[kind] = head->rounds > (late_wait ? 0u : buckets / 32);
+  c->group_rounds[kind] = head->rounds > (small ? 0u : buckets / 32);
+  c->group_late[kind] = head->late != 0;
   if (head->error_flags) {
     c->group_pause[kind] = group_pause_after(++c->group_misses[kind]);
     return RUN_SORT;

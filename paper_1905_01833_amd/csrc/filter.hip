@@ -1242,7 +1242,7 @@ __global__ __launch_bounds__(NT) void k_entries_sort(FilterBuffers f) {
   __shared__ uint64_t s_place[SORT_CHUNK], s_unit[SORT_CHUNK];
   __shared__ uint32_t s_long[NT], s_n;
   const uint32_t tx = threadIdx.x;
-  const uint32_t total = f.cnt[FC_ENTRIES], err = f.ctrl->error_flags, late = f.late_wait ? f.cnt[FC_LATE] : 0u;
+  const uint32_t total = f.cnt[FC_ENTRIES], err = f.ctrl->error_flags, late = f.cnt[FC_LATE];
   if (blockIdx.x == 0 && blockIdx.y == 0 && tx == 0) {
     GroupHead h;
     h.entries = total;
@@ -1252,7 +1252,7 @@ __global__ __launch_bounds__(NT) void k_entries_sort(FilterBuffers f) {
     h.first_bad = f.ctrl->first_bad;
     *f.head = h;
   }
-  if (err || late) return;
+  if (err || (f.late_wait && late)) return;
   auto sort = [&](uint32_t t, uint32_t n, uint32_t from, uint32_t step) {
     if (!n) return;
     const uint32_t first = f.n_traces > 1 ? f.trace_first[t] : 0u;

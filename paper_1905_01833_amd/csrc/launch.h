@@ -142,7 +142,7 @@ constexpr uint32_t GROUP_MAX_TRACES = 8192;   // traces of a grouped call
 struct GroupHead {          // what the host needs of a grouped call besides its entries
   uint32_t entries, error_flags;
   uint64_t first_bad;
-  uint32_t late;            // with FilterBuffers::late_wait: what is still to be counted
+  uint32_t late;            // FC_LATE (with FilterBuffers::late_wait: still to be counted)
   uint32_t rounds;          // FC_ROUNDS
 };
 struct FilterBuffers {      // device pointers of a call's grouped race count (filter.h, filter.hip)
