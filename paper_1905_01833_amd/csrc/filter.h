@@ -61,8 +61,8 @@ SC_HD uint32_t filter_sbits(uint64_t n, uint32_t lgb) {
   return b < 10 ? 10u : (b > FILTER_SLOT_BITS ? FILTER_SLOT_BITS : b);
 }
 
-// 32-bit mixing of a word (a published integer hash of the multiply and
-// xor-shift kind: every input bit reaches every output bit).
+// 32-bit mixing of a word: lowbias32, the multiply and xor-shift hash with the
+// constants that Chris Wellons published after a search for low bias.
 SC_HD uint32_t mix32(uint32_t x) {
   x ^= x >> 16;
   x *= 0x7feb352du;

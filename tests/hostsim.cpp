@@ -12,6 +12,7 @@
 #include <algorithm>
 #include <cstdint>
 #include <cstring>
+#include <unordered_map>
 #include <vector>
 
 #include "../paper_1905_01833_amd/csrc/barrier.h"
@@ -380,12 +381,16 @@ extern "C" int hs_digit_plan(uint64_t seed, int trials) {
 }
 
 // The grouped race count (filter.h) as its kernels take it: buckets of the
-// records' groups, bitmaps A, P and D over their slots, the pairs of the
-// writes and atomics in D among themselves and with the reads in A.  side:
-// one side word per record (the warp-aware check), or null.  The writes are
-// seen in record order, or backwards.  Entries of one location are added up.
+// records' groups, bitmaps W (a write in the slot), T (an atomic in one of four)
+// and D (in one of two, what may have a partner: a second write, a read whose slot
+// is in W or T, a write and an atomic that meet), and the pairs of the candidates.
+// side: one side word per record (the warp-aware check), or null.  Entries of one
+// location are added up.
+// how: 1: the writes are seen backwards; 2: pairs by counts per group instead of
+// one by one; 4: in four rounds, by slot; 8: atomics that meet no write or read in
+// all of four further maps are dropped.
 extern "C" int64_t hs_group(const rec* recs, const uint64_t* off, uint32_t n_traces, const uint32_t* tpb,
-                            const uint32_t* side, int backwards, race* out, uint64_t cap, uint64_t* n_tested) {
+                            const uint32_t* side, int how, race* out, uint64_t cap, uint64_t* n_tested) {
   std::vector<race> all;
   *n_tested = 0;
   for (uint32_t t = 0; t < n_traces; t++) {
@@ -395,63 +400,146 @@ extern "C" int64_t hs_group(const rec* recs, const uint64_t* off, uint32_t n_tra
     std::vector<std::vector<uint32_t>> bucket((size_t)1 << lgb);
     std::vector<uint32_t> slot(n);
     for (uint64_t k = 0; k < n; k++) {
-      const uint64_t i = backwards ? n - 1 - k : k;
+      const uint64_t i = (how & 1) ? n - 1 - k : k;
       const uint32_t h = filter_group(r[i].unit, r[i].tid / tpb[t], r[i].epoch, r[i].space);
       bucket[filter_bucket(h, lgb)].push_back((uint32_t)i);
       slot[i] = filter_slot(h) & smask;
     }
+    auto at = [&](uint32_t i) { return frec(r[i].unit, r[i].tid, r[i].epoch, r[i].action, r[i].space); };
+    auto blk = [&](uint32_t i) { return r[i].tid / tpb[t]; };
+    auto word = [&](uint32_t i) { return side ? side[off[t] + i] : 0u; };
     for (auto& b : bucket) {
-      std::vector<uint8_t> A((size_t)smask + 1), P((size_t)smask / 4 + 1), D((size_t)smask / 2 + 1);
-      std::vector<uint32_t> writes, reads;
+      std::vector<uint8_t> W((size_t)smask + 1), T((size_t)smask / 4 + 1), D((size_t)smask / 2 + 1);
+      std::vector<uint32_t> left, reads;
       for (uint32_t i : b)
-        if (r[i].action) {
-          if (r[i].action == 1) P[slot[i] >> 2] = 1;
-          if (A[slot[i]] && (r[i].action == 1 || P[slot[i] >> 2])) D[slot[i] >> 1] = 1;
-          A[slot[i]] = 1;
+        if (r[i].action == 2) T[slot[i] >> 2] = 1;
+        else if (r[i].action == 1) {
+          if (W[slot[i]]) D[slot[i] >> 1] = 1;
+          W[slot[i]] = 1;
         }
       for (uint32_t i : b)
-        if (!r[i].action && A[slot[i]]) {
+        if (!r[i].action && (W[slot[i]] || T[slot[i] >> 2])) {
           D[slot[i] >> 1] = 1;
           reads.push_back(i);
         }
       for (uint32_t i : b)
-        if (r[i].action && D[slot[i] >> 1]) writes.push_back(i);
-      *n_tested += writes.size() + reads.size();
-      std::vector<race> found(writes.size());
-      std::vector<size_t> lead(writes.size());
-      auto at = [&](uint32_t i) { return frec(r[i].unit, r[i].tid, r[i].epoch, r[i].action, r[i].space); };
-      auto pair = [&](uint32_t i, uint32_t j, race& e) {
-        const FRec x = at(i), y = at(j);
-        const uint32_t bx = x.tid / tpb[t], by = y.tid / tpb[t];
-        if (!pair_races(x, bx, y, by, side != nullptr, tpb[t], side ? side[off[t] + i] : 0, side ? side[off[t] + j] : 0)) return;
-        const uint32_t lo = std::min(frec_action(x), frec_action(y)), hi = std::max(frec_action(x), frec_action(y));
-        if (lo == 0) (hi == 1 ? e.rw : e.ar)++;
-        else (hi == 1 ? e.ww : e.aw)++;
-        if (bx != by) e.xb++;
-      };
-      auto same = [&](uint32_t i, uint32_t j) {
-        return same_location(at(i), r[i].tid / tpb[t], at(j), r[j].tid / tpb[t]);
-      };
-      for (size_t i = 0; i < writes.size(); i++) {
-        lead[i] = i;
-        std::memset(&found[i], 0, sizeof(race));
-        for (size_t j = i; j-- > 0;)
-          if (same(writes[i], writes[j])) lead[i] = j;
-        for (size_t j = 0; j < i; j++)
-          if (same(writes[i], writes[j])) pair(writes[i], writes[j], found[lead[i]]);
+        if (r[i].action && (r[i].action == 1 ? T[slot[i] >> 2] : W[slot[i]])) D[slot[i] >> 1] = 1;
+      for (uint32_t i : b)
+        if (r[i].action && D[slot[i] >> 1]) left.push_back(i);
+      if (how & 8) {
+        constexpr uint32_t MAPS = 4, BITS = 15;
+        std::vector<uint8_t> map((size_t)MAPS << BITS);
+        auto place = [&](uint32_t i, uint32_t m) { return ((size_t)m << BITS) + (filter_group2(at(i), blk(i), m) >> (32 - BITS)); };
+        for (uint32_t m = 0; m < MAPS; m++) {
+          for (uint32_t i : left)
+            if (r[i].action == 1) map[place(i, m)] = 1;
+          for (uint32_t i : reads) map[place(i, m)] = 1;
+        }
+        std::vector<uint32_t> kept;
+        for (uint32_t i : left) {
+          bool k = true;
+          for (uint32_t m = 0; m < MAPS; m++) k = k && (r[i].action == 1 || map[place(i, m)]);
+          if (k) kept.push_back(i);
+        }
+        left.swap(kept);
       }
-      for (uint32_t i : reads)
-        for (size_t j = 0; j < writes.size(); j++)
-          if (same(i, writes[j])) pair(i, writes[j], found[lead[j]]);
-      for (size_t i = 0; i < writes.size(); i++) {
-        race e = found[i];
-        if (e.ww + e.rw + e.aw + e.ar == 0) continue;
-        const rec& x = r[writes[i]];
-        e.trace = t;
-        e.space = x.space;
-        e.block = x.space ? x.tid / tpb[t] : 0xFFFFFFFFu;
-        e.unit = x.unit;
-        all.push_back(e);
+      *n_tested += left.size() + reads.size();
+      const uint32_t rounds = (how & 4) ? 4 : 1;
+      for (uint32_t round = 0; round < rounds; round++) {
+        std::vector<uint32_t> tab;
+        for (uint32_t i : left)
+          if ((slot[i] & (rounds - 1)) == round) tab.push_back(i);
+        const size_t nw = tab.size();
+        std::vector<race> found(nw);
+        std::memset(found.data(), 0, nw * sizeof(race));
+        auto in_group = [&](uint32_t level, uint32_t i, uint32_t j) {
+          return same_group(level, at(i), blk(i), at(j), blk(j), tpb[t]);
+        };
+        std::vector<size_t> lead(nw);
+        for (size_t i = 0; i < nw; i++)
+          for (lead[i] = 0; !in_group(0, tab[i], tab[lead[i]]);) lead[i]++;
+        if (how & 2) {
+          // counts per group at its first record, found by its hash
+          std::vector<uint32_t> count[GROUP_LEVELS];
+          std::unordered_map<uint64_t, std::vector<uint32_t>> by_hash;  // level << 32 | hash: first records
+          auto hash = [&](uint32_t level, uint32_t i) {
+            uint32_t h = location_hash(at(i), blk(i));
+            for (uint32_t l = 1; l <= level; l++) h = group_hash(l, h, at(i), blk(i), tpb[t]);
+            return (uint64_t)level << 32 | h;
+          };
+          auto first = [&](uint32_t level, uint32_t i) -> int64_t {
+            for (uint32_t j : by_hash[hash(level, i)])
+              if (in_group(level, tab[j], i)) return j;
+            return -1;
+          };
+          for (uint32_t l = 0; l < GROUP_LEVELS; l++) {
+            count[l].assign(nw, 0);
+            for (size_t i = 0; i < nw; i++) {
+              int64_t g = first(l, tab[i]);
+              if (g < 0) by_hash[hash(l, tab[i])].push_back((uint32_t)(g = (int64_t)i));
+              count[l][(size_t)g] += group_one(at(tab[i]));
+            }
+            for (size_t i = 0; i < nw; i++) {
+              race& e = found[lead[i]];
+              const uint32_t ww = pairs_ww(count[l][i]), aw = pairs_aw(count[l][i]);
+              e.ww += (l & 1) ? 0ull - ww : ww;
+              e.aw += (l & 1) ? 0ull - aw : aw;
+              if (l < 2) e.xb += (l & 1) ? 0ull - ww - aw : ww + aw;
+            }
+          }
+          auto ordered = [&](uint32_t i, uint32_t j) {  // by lockstep: not a race for that alone
+            return side && in_group(GROUP_WARP, i, j) && !((word(i) | word(j)) & SIDE_DIVERGED) && r[i].tid != r[j].tid &&
+                   !(r[i].action == 1 && r[j].action == 1 && word(i) == word(j));
+          };
+          for (size_t i = 0; i < nw; i++)
+            for (size_t j = 0; j < i; j++)
+              if (ordered(tab[i], tab[j])) {
+                if (r[tab[i]].action == 1 && r[tab[j]].action == 1) found[lead[i]].ww--;
+                else if (r[tab[i]].action != r[tab[j]].action) found[lead[i]].aw--;
+              }
+          for (uint32_t i : reads) {
+            const int64_t g0 = first(0, i);
+            if (g0 < 0) continue;
+            uint32_t sum = 0, cross = 0;
+            for (uint32_t l = 0; l < GROUP_LEVELS; l++) {
+              const int64_t g = first(l, i);
+              if (g < 0) break;
+              sum += (l & 1) ? 0u - count[l][(size_t)g] : count[l][(size_t)g];
+              if (l < 2) cross = sum;
+            }
+            for (size_t j = 0; j < nw; j++)
+              if (ordered(i, tab[j])) sum -= group_one(at(tab[j]));
+            race& e = found[lead[(size_t)g0]];
+            e.rw += sum & 0xFFFFu;
+            e.ar += sum >> 16;
+            e.xb += (cross & 0xFFFFu) + (cross >> 16);
+          }
+        } else {
+          auto pair = [&](uint32_t i, uint32_t j, race& e) {
+            const FRec x = at(i), y = at(j);
+            if (!pair_races(x, blk(i), y, blk(j), side != nullptr, tpb[t], word(i), word(j))) return;
+            const uint32_t lo = std::min(frec_action(x), frec_action(y)), hi = std::max(frec_action(x), frec_action(y));
+            if (lo == 0) (hi == 1 ? e.rw : e.ar)++;
+            else (hi == 1 ? e.ww : e.aw)++;
+            if (blk(i) != blk(j)) e.xb++;
+          };
+          for (size_t i = 0; i < nw; i++)
+            for (size_t j = 0; j < i; j++)
+              if (in_group(0, tab[i], tab[j])) pair(tab[i], tab[j], found[lead[i]]);
+          for (uint32_t i : reads)
+            for (size_t j = 0; j < nw; j++)
+              if (in_group(0, i, tab[j])) pair(i, tab[j], found[lead[j]]);
+        }
+        for (size_t i = 0; i < nw; i++) {
+          race e = found[i];
+          if (e.ww + e.rw + e.aw + e.ar == 0) continue;
+          const rec& x = r[tab[i]];
+          e.trace = t;
+          e.space = x.space;
+          e.block = x.space ? x.tid / tpb[t] : 0xFFFFFFFFu;
+          e.unit = x.unit;
+          all.push_back(e);
+        }
       }
     }
   }

@@ -98,3 +98,29 @@ def test_guard_covers_every_sum_of_pairs():
     lib.hs_pair_sums.restype = ctypes.c_int
     lib.hs_pair_sums.argtypes = [ctypes.c_uint32]
     assert lib.hs_pair_sums(1024) == 0
+
+
+@pytest.mark.parametrize("how", [2, 3, 4, 6, 8, 10, 12, 14])
+@pytest.mark.parametrize("warp", [False, True])
+def test_groups_rounds_and_thinning(how, warp):
+    """Pairs from counts per group, in rounds by slot, and with atomics thinned
+    out, alone and together: the same entries as pair by pair, and the oracle's."""
+    lib = _hostsim()
+    lib.hs_group.restype = ctypes.c_int64
+    lib.hs_group.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_uint32, ctypes.c_void_p, ctypes.c_void_p,
+                             ctypes.c_int, ctypes.c_void_p, ctypes.c_uint64, ctypes.POINTER(ctypes.c_uint64)]
+    rng = np.random.default_rng(how + 100 * warp)
+    for n, units, blocks, tpb in ((40, 3, 2, 40), (300, 5, 3, 64), (2000, 300, 4, 33), (20000, 4000, 40, 96), (3000, 1, 2, 256)):
+        r = np.zeros(n, dtype=RECORD_DTYPE)
+        r["tid"] = rng.integers(0, blocks * tpb, n)
+        r["epoch"] = rng.integers(0, 3, n)
+        r["action"] = rng.choice([READ, READ, WRITE, ATOMIC], n)
+        r["space"] = rng.integers(0, 2, n)
+        r["unit"] = rng.integers(0, units, n)
+        side = (rng.integers(0, 3, n) | np.where(rng.random(n) < 0.3, 1 << 31, 0)).astype(np.uint32) if warp else None
+        off, tp = np.array([0, n], dtype=np.uint64), np.array([tpb], dtype=np.uint32)
+        want, _ = oracle.closed_form(r, off, tp) if side is None else oracle.closed_form_warp(r, side, off, tp)
+        out, tested = np.zeros(n + 1, dtype=want.dtype), ctypes.c_uint64(0)
+        m = lib.hs_group(r.ctypes.data, off.ctypes.data, 1, tp.ctypes.data, None if side is None else side.ctypes.data, how,
+                         out.ctypes.data, len(out), ctypes.byref(tested))
+        assert m == len(want) and out[:m].tobytes() == want.tobytes(), (n, units)
