@@ -112,14 +112,18 @@ SC_HD bool same_group(uint32_t level, const FRec& a, uint32_t blk_a, const FRec&
   if (level == 3) return a.tid == b.tid;
   return level != GROUP_WARP || warp_of(a, blk_a, tpb) == warp_of(b, blk_b, tpb);
 }
-// Hash of a record's group: of level 0, and of a level from that of the level
-// it lies in (the one before; level 2 for GROUP_WARP).
+// Hashes: a record's location (of a global word that is filter_group's, so its high
+// bits are the bucket's), and its groups inside a location (of which the high bits
+// count) from that of the level they lie in (the one before; level 2 for GROUP_WARP),
+// starting from groups_hash of the location's first record's index.
 SC_HD uint32_t location_hash(const FRec& a, uint32_t blk) {
   return mix32(a.ulo * 0x9E3779B1u ^ mix32(a.uhi + (frec_space(a) ? blk * 0xC2B2AE3Du + 1u : 0u)));
 }
+SC_HD uint32_t groups_hash(uint32_t first) { return first * 0x85EBCA77u; }
 SC_HD uint32_t group_hash(uint32_t level, uint32_t h, const FRec& a, uint32_t blk, uint32_t tpb) {
   const uint32_t v = level == 1 ? blk : (level == 2 ? a.meta & 0xFFFFu : (level == 3 ? a.tid : ~warp_of(a, blk, tpb)));
-  return mix32(h + v * 0x9E3779B1u + level);
+  h = (h ^ v) * 0x9E3779B1u + level;
+  return h ^ (h >> 15);
 }
 // Writes and atomics of a group in one word, and the pairs among them.
 SC_HD uint32_t group_one(const FRec& a) { return frec_action(a) == 1u ? 1u : 0x10000u; }

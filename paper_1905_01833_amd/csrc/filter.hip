@@ -321,10 +321,13 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
   __shared__ __align__(16) uint32_t tab[LATE ? HT : 4];
   __shared__ uint32_t s_n, s_nw, s_any, s_base;
   const uint32_t tx = threadIdx.x;
-  uint32_t bucket, part = 0, trace = 0;
+  uint32_t bucket, part = 0, trace = 0, share = 1;
   if (LATE) {
-    if (blockIdx.x >= f.cnt[FC_LATE]) return;
-    const uint2 it = f.late[blockIdx.x];
+    // few items: two or four workgroups each, with a share of the reads
+    const uint32_t n = min(f.cnt[FC_LATE], f.late_max);  // (more of them: the call sorts)
+    if (!DIRECT) share = n <= 64 ? 4u : (n <= 128 ? 2u : 1u);
+    if (blockIdx.x >= n * share) return;
+    const uint2 it = f.late[blockIdx.x / share];
     bucket = DIRECT ? 0u : it.x;
     trace = it.x;
     part = it.y;
@@ -346,7 +349,8 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
   auto uniform = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); };
   bucket = uniform(bucket);
   part = uniform(part);
-  const uint32_t item = uniform(f.extra_max && !DIRECT ? f.hot[bucket] : 1u), parts = item & ~HOT_ITEM;
+  const uint32_t item = uniform(f.extra_max && !DIRECT ? f.hot[bucket] : 1u), parts = (item & ~HOT_ITEM) * uniform(share);
+  if (LATE) part = part * uniform(share) + blockIdx.x % uniform(share);
   if (!LATE && !DIRECT && (item & HOT_ITEM) && blockIdx.x >= f.extra_max) return;
   trace = uniform(DIRECT ? trace : f.bucket_trace[bucket]);
   FTrace T = f.tr[trace];
@@ -777,7 +781,10 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
       const uint32_t longest = n_read > RCAP ? MANY_WRITERS : CHAIN;
       __syncthreads();
       auto chain_of = [&](const FRec& x, uint32_t bx) { return location_hash(x, bx) & (HN - 1); };
-      auto tag_of = [](uint32_t h) { return h >> 16 | (~h & 0xFFFF0000u); };
+      auto tag_of = [](uint32_t h) {  // (one bucket's hashes have their high bits in common)
+        h *= 0x9E3779B1u;
+        return h >> 16 | (~h & 0xFFFF0000u);
+      };
       if (tx < nw) {
         const uint32_t i = tx, idx = s_blk[i];
         const FRec x = load_frec(idx);
@@ -1011,26 +1018,42 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
       const uint32_t nw = uniform(s_nw);  // (at most WCAP)
       if (!pair_sums_fit(n_read, nw)) return full();  // sums of pairs are kept in 32 bits
       if (!nw) continue;
-      // The first record of x's group of a level, or NONE; h: the group's hash.
-      auto find = [&](uint32_t level, uint32_t h, const FRec& x, uint32_t bx) {
-        for (uint32_t at = h & (HT - 1);; at = (at + 1) & (HT - 1)) {
+      // Table entries of x's location (l0: its first record, or NONE) and of its
+      // groups there: their first records.  Inside a location its first record
+      // stands for it, in hashes and comparisons.
+      auto is_group = [&](uint32_t level, uint32_t e, uint32_t l0, const FRec& x, uint32_t bx) {
+        if (e >> 16 != level) return false;
+        const uint32_t j = e & 0xFFFFu;
+        if (level == 0) return same_location(w_at(j), s_blk[j], x, bx);
+        if (s_lead[j] != l0 || s_blk[j] != bx) return false;
+        if (level == 1) return true;
+        const FRec y = w_at(j);
+        if (((y.meta ^ x.meta) & 0xFFFFu) != 0) return false;
+        return level == 2 || (level == 3 ? y.tid == x.tid : warp_of(y, bx, T.tpb) == warp_of(x, bx, T.tpb));
+      };
+      // (The high bits of a location's hash are those of its bucket, so the low ones
+      // place it; a group's high ones.)
+      static_assert(HT == 1u << 13, "places from a hash's high bits");
+      auto place_of = [](uint32_t level, uint32_t h) { return level ? h >> (32 - 13) : h & (HT - 1); };
+      auto find = [&](uint32_t level, uint32_t h, uint32_t l0, const FRec& x, uint32_t bx) {
+        for (uint32_t at = place_of(level, h);; at = (at + 1) & (HT - 1)) {
           const uint32_t e = tab[at];
           if (e == NONE) return NONE;
-          if (e >> 16 == level && same_group(level, w_at(e & 0xFFFFu), s_blk[e & 0xFFFFu], x, bx, T.tpb)) return e & 0xFFFFu;
+          if (is_group(level, e, l0, x, bx)) return e & 0xFFFFu;
         }
       };
       // ... made record i's where there is none yet.  (A place is taken by one
       // compare-and-swap, and nobody waits: the records were stored before.)
-      auto find_or_add = [&](uint32_t level, uint32_t h, const FRec& x, uint32_t bx, uint32_t i) {
-        for (uint32_t at = h & (HT - 1);; at = (at + 1) & (HT - 1)) {
+      auto find_or_add = [&](uint32_t level, uint32_t h, uint32_t l0, const FRec& x, uint32_t bx, uint32_t i) {
+        for (uint32_t at = place_of(level, h);; at = (at + 1) & (HT - 1)) {
           uint32_t e = __hip_atomic_load(&tab[at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
           if (e == NONE) e = atomicCAS(&tab[at], NONE, level << 16 | i);
           if (e == NONE) return i;
-          if (e >> 16 == level && same_group(level, w_at(e & 0xFFFFu), s_blk[e & 0xFFFFu], x, bx, T.tpb)) return e & 0xFFFFu;
+          if (is_group(level, e, l0, x, bx)) return e & 0xFFFFu;
         }
       };
-      auto level_hash = [&](uint32_t level, const FRec& x, uint32_t bx) {
-        uint32_t h = location_hash(x, bx);
+      auto level_hash = [&](uint32_t level, uint32_t l0, const FRec& x, uint32_t bx) {
+        uint32_t h = groups_hash(l0);
         for (uint32_t l = 1; l <= level; l++)
           if (l != 3 || level == 3) h = group_hash(l, h, x, bx, T.tpb);
         return h;
@@ -1053,7 +1076,7 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
       __syncthreads();
       if (tx < nw) {  // by location
         const FRec x = w_at(tx);
-        const uint32_t bx = s_blk[tx], lead = find_or_add(0, location_hash(x, bx), x, bx, tx);
+        const uint32_t bx = s_blk[tx], lead = find_or_add(0, location_hash(x, bx), 0u, x, bx, tx);
         s_lead[tx] = (uint16_t)lead;
         atomicAdd(&s_cnt[0][lead], group_one(x));
       }
@@ -1064,8 +1087,8 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
         for (; i >= nw; l++) i -= nw;
         if (!several(s_cnt[0][s_lead[i]]) || (l == GROUP_WARP && (s_side[WARP ? i : 0] & SIDE_DIVERGED))) continue;
         const FRec x = w_at(i);
-        const uint32_t bx = s_blk[i];
-        const uint32_t g = find_or_add(l, level_hash(l, x, bx), x, bx, i), before = atomicAdd(&s_cnt[l][g], group_one(x));
+        const uint32_t bx = s_blk[i], l0 = s_lead[i];
+        const uint32_t g = find_or_add(l, level_hash(l, l0, x, bx), l0, x, bx, i), before = atomicAdd(&s_cnt[l][g], group_one(x));
         if (WARP && l == GROUP_WARP) {
           s_next[i] = (uint16_t)atomicExch(&s_whead[WARP ? g : 0], i);
           if ((before & 0xFFFFu) + (before >> 16) >= WARP_WALK) s_any = 2;
@@ -1077,9 +1100,9 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
         return;
       }
       // fn(an undiverged record of x's warp, epoch and word by another thread)
-      auto for_warp = [&](const FRec& x, uint32_t bx, auto&& fn) {
+      auto for_warp = [&](uint32_t l0, const FRec& x, uint32_t bx, auto&& fn) {
         if constexpr (WARP) {
-          const uint32_t g = find(GROUP_WARP, level_hash(GROUP_WARP, x, bx), x, bx);
+          const uint32_t g = find(GROUP_WARP, level_hash(GROUP_WARP, l0, x, bx), l0, x, bx);
           if (g == NONE) return;
 #pragma unroll 1
           for (uint32_t j = s_whead[g] & END; j != END; j = s_next[j])
@@ -1100,7 +1123,7 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
           if (WARP && !(s_side[WARP ? tx : 0] & SIDE_DIVERGED)) {
             const FRec x = w_at(tx);
             const uint32_t bx = s_blk[tx];
-            for_warp(x, bx, [&](uint32_t j) {  // ordered by lockstep, but two writes of one statement
+            for_warp(lead, x, bx, [&](uint32_t j) {  // ordered by lockstep, but two writes of one statement
               if (j >= tx) return;
               const FRec y = w_at(j);
               if (pair_races(x, bx, y, bx, true, T.tpb, s_side[WARP ? tx : 0], s_side[WARP ? j : 0])) return;
@@ -1113,28 +1136,33 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
           if (xb) atomicAdd(&s_acc[K_XB][lead], xb);
         }
       }
+      uint32_t last = NONE;  // (a hot word's reads come one after another)
       auto count_read = [&](const FRec& x, uint32_t idx) {
         const uint32_t bx = block_of(x.tid, T.tpb, shift);
-        uint32_t h = location_hash(x, bx), l0 = NONE, left = 0, cross = 0;
+        uint32_t l0 = last;
+        if (l0 == NONE || !same_location(w_at(l0), s_blk[l0], x, bx)) {
+          l0 = find(0, location_hash(x, bx), 0u, x, bx);
+          if (l0 == NONE) return;
+          last = l0;
+        }
+        uint32_t left = s_cnt[0][l0], cross = left;
+        if (!several(left)) {  // one record: the pair itself
+          const uint32_t by = s_blk[l0];
+          if (!pair_races(x, bx, w_at(l0), by, WARP, T.tpb, WARP ? f.side[T.off + idx] : 0u, WARP ? s_side[l0] : 0u)) return;
+          if (bx == by) cross = 0;
+        } else {
+          uint32_t h = groups_hash(l0);
 #pragma unroll 1
-        for (uint32_t l = 0; l < GROUP_LEVELS; l++) {
-          const uint32_t hl = l ? group_hash(l, h, x, bx, T.tpb) : h, g = find(l, hl, x, bx);
-          if (g == NONE) break;
-          h = hl;
-          const uint32_t c = s_cnt[l][g];
-          left += (l & 1) ? 0u - c : c;
-          if (l < 2) cross = left;
-          if (l == 0) {
-            l0 = g;
-            if (!several(c)) {  // one record: the pair itself
-              const uint32_t by = s_blk[g];
-              if (!pair_races(x, bx, w_at(g), by, WARP, T.tpb, WARP ? f.side[T.off + idx] : 0u, WARP ? s_side[g] : 0u)) return;
-              if (bx == by) cross = 0;
-              break;
-            }
+          for (uint32_t l = 1; l < GROUP_LEVELS; l++) {
+            h = group_hash(l, h, x, bx, T.tpb);
+            const uint32_t g = find(l, h, l0, x, bx);
+            if (g == NONE) break;
+            const uint32_t c = s_cnt[l][g];
+            left += (l & 1) ? 0u - c : c;
+            if (l == 1) cross = left;
+            if (WARP && l == 2 && !(f.side[T.off + idx] & SIDE_DIVERGED))
+              for_warp(l0, x, bx, [&](uint32_t j) { left -= group_one(w_at(j)); });
           }
-          if (WARP && l == 2 && !(f.side[T.off + idx] & SIDE_DIVERGED))
-            for_warp(x, bx, [&](uint32_t j) { left -= group_one(w_at(j)); });
         }
         if (!left) return;
         if (l0 != lead) flush();
@@ -1410,12 +1438,13 @@ hipError_t launch_filter_count(const FilterBuffers& f, hipStream_t s) {
 }
 hipError_t launch_filter_late(const FilterBuffers& f, uint32_t n, hipStream_t s) {
   const bool warp = f.side != nullptr;
+  n = std::min(n, f.late_max);
   if (f.direct)
     hipLaunchKernelGGL((warp ? k_filter_count<LATE_TRACE, true, 1024, 1408> : k_filter_count<LATE_TRACE, false, 1024, 1408>),
-                       dim3(std::min(n, f.late_max)), dim3(FNT), 0, s, f);
-  else
+                       dim3(n), dim3(FNT), 0, s, f);
+  else  // (room for up to 256 workgroups of a few items)
     hipLaunchKernelGGL((warp ? k_filter_count<LATE_BUCKET, true, 1024, 1408> : k_filter_count<LATE_BUCKET, false, 1024, 1408>),
-                       dim3(std::min(n, f.late_max)), dim3(FNT), 0, s, f);
+                       dim3(std::max(n, std::min(4 * n, 256u))), dim3(FNT), 0, s, f);
   return hipGetLastError();
 }
 hipError_t launch_filter_out(const FilterBuffers& f, hipStream_t s) {

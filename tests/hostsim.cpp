@@ -12,6 +12,7 @@
 #include <algorithm>
 #include <cstdint>
 #include <cstring>
+#include <functional>
 #include <unordered_map>
 #include <vector>
 
@@ -462,12 +463,13 @@ extern "C" int64_t hs_group(const rec* recs, const uint64_t* off, uint32_t n_tra
           // counts per group at its first record, found by its hash
           std::vector<uint32_t> count[GROUP_LEVELS];
           std::unordered_map<uint64_t, std::vector<uint32_t>> by_hash;  // level << 32 | hash: first records
-          auto hash = [&](uint32_t level, uint32_t i) {
-            uint32_t h = location_hash(at(i), blk(i));
+          std::function<int64_t(uint32_t, uint32_t)> first;
+          auto hash = [&](uint32_t level, uint32_t i) {  // (inside a location its first record stands for it)
+            uint32_t h = level ? groups_hash((uint32_t)first(0, i)) : location_hash(at(i), blk(i));
             for (uint32_t l = 1; l <= level; l++) h = group_hash(l, h, at(i), blk(i), tpb[t]);
             return (uint64_t)level << 32 | h;
           };
-          auto first = [&](uint32_t level, uint32_t i) -> int64_t {
+          first = [&](uint32_t level, uint32_t i) -> int64_t {
             for (uint32_t j : by_hash[hash(level, i)])
               if (in_group(level, tab[j], i)) return j;
             return -1;
