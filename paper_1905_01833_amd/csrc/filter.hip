@@ -322,6 +322,7 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
   __shared__ uint32_t s_n, s_nw, s_any, s_base;
   const uint32_t tx = threadIdx.x;
   uint32_t bucket, part = 0, trace = 0, share = 1;
+  const uint32_t flags = DIRECT ? 0u : f.ctrl->error_flags;
   if (LATE) {
     // few items: two or four workgroups each, with a share of the reads
     const uint32_t n = min(f.cnt[FC_LATE], f.late_max);  // (more of them: the call sorts)
@@ -377,10 +378,10 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
     s_n = 0;
     s_nw = 0;
     if (LOOP) s_cls[0][0] = s_cls[0][1] = s_cls[0][2] = s_cls[0][3] = 0;
-    s_any = (f.ctrl->error_flags & ERR_GROUP_FULL) ? 3u : 0u;
+    s_any = (flags & ERR_GROUP_FULL) ? 3u : 0u;
   }
   __syncthreads();
-  if (s_any == 3) return;  // the call sorts (one thread has looked: all of the workgroup leave, or none)
+  if (!DIRECT && s_any == 3) return;  // the call sorts (one thread has looked: all of the workgroup leave, or none)
   auto bit = [](const uint32_t* map, uint32_t s) { return (map[s >> 5] >> (s & 31u)) & 1u; };
   auto set = [&](uint32_t* map, uint32_t s) { return atomicOr(&map[s >> 5], 1u << (s & 31u)); };
   // ---- a pass over the bucket's writes (or reads) of tiles lo .. hi - 1:
@@ -686,12 +687,10 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
       flush();
     }
   };
-  // an entry per location with pairs (all threads; the sums are complete)
+  // an entry per location with pairs (all threads; the sums are complete, s_n is 0)
   auto paired = [&](uint32_t i) { return (s_acc[K_WW][i] | s_acc[K_RW][i] | s_acc[K_AW][i] | s_acc[K_AR][i]) != 0; };
   auto emit = [&](uint32_t nw) {
     const uint32_t i = threadIdx.x;
-    if (i == 0) s_n = 0;
-    __syncthreads();
     const bool racing = i < nw && s_lead[i] == i && paired(i);
     const uint64_t mask = __ballot(racing);
     uint32_t pos = 0;
@@ -876,6 +875,7 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
         });
       }
       flush_wave();
+      if (tx == 0) s_n = 0;
       __syncthreads();
       if (s_any == 2) {  // reads of a word of many atomics
         return give_up(round);
@@ -1181,6 +1181,7 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
       }
       flush_wave();
       lead = 0;
+      if (tx == 0) s_n = 0;
       __syncthreads();
       emit(nw);
     }
@@ -1270,7 +1271,8 @@ __global__ __launch_bounds__(NT) void k_entries_sort(FilterBuffers f) {
   __shared__ uint64_t s_place[SORT_CHUNK], s_unit[SORT_CHUNK];
   __shared__ uint32_t s_long[NT], s_n;
   const uint32_t tx = threadIdx.x;
-  const uint32_t total = f.cnt[FC_ENTRIES], err = f.ctrl->error_flags, late = f.cnt[FC_LATE];
+  const uint32_t total = f.cnt[FC_ENTRIES], err = f.ctrl->error_flags, late = f.cnt[FC_LATE], most = f.cnt[FC_MOST];
+  const uint32_t own = blockIdx.x < f.n_traces ? f.trace_cnt[blockIdx.x] : 0u;
   if (blockIdx.x == 0 && blockIdx.y == 0 && tx == 0) {
     GroupHead h;
     h.entries = total;
@@ -1330,9 +1332,8 @@ __global__ __launch_bounds__(NT) void k_entries_sort(FilterBuffers f) {
       if (mk && e < m && q == 0) mk[c0 + rank] = EntryKey{s_place[e], s_unit[e]};
     }
   };
-  const uint32_t own = blockIdx.x < f.n_traces ? f.trace_cnt[blockIdx.x] : 0u;
   if (own <= SORT_CHUNK) sort(blockIdx.x, own, blockIdx.y, gridDim.y);
-  if (f.cnt[FC_MOST] <= SORT_CHUNK) return;
+  if (most <= SORT_CHUNK) return;
   const uint32_t all = gridDim.x * gridDim.y, me = blockIdx.y * gridDim.x + blockIdx.x;
   for (uint32_t t0 = 0; t0 < f.n_traces; t0 += NT) {
     __syncthreads();
