@@ -3,14 +3,16 @@
     python bench.py [--gpus 1] [--steps K] [--warmup W]
 
 One step is one complete check of one batch of synthetic traces through the
-C ABI (sim_check_traces_device): key statistics, key generation, the radix
-passes, the pair count and the download of the racing-location list.  The
+C ABI (sim_check_traces_device), every kernel of it and the download of the
+racing-location list: the count by group, or for traces above 2^27 records the
+sort (key statistics, key generation, radix passes, pair count).  The
 records are generated on the host, copied to HBM once, and stay resident
 while K steps are timed between two device synchronisations.
 
 The headline workload is the batched one (4096 traces of uneven size in one
-call, autotuned launch shape, launch sequence replayed as a HIP graph); the
-same traces checked one call per trace (the plain path) are timed beside it.
+call, on the path and with the launch shape that the autotuner found fastest;
+where that is the sort, its launches are replayed as a HIP graph); the same
+traces checked one call per trace (the plain path) are timed beside it.
 Legs for the single-trace workloads (2^24 and 2^28 records) and for serving
 (Poisson arrivals of device-resident requests, then a load sweep) follow.
 
@@ -58,7 +60,7 @@ FILTER_STAGES = ("filter_part", "filter_count")
 
 C3_DESC = ("c3: batched, 4096 traces in one call, sizes log-uniform 2^8..2^20 records, 1..256 blocks x 256 threads, "
            "75% reads, shared window 48 KiB/block, global reads Zipf(1.1) over 64 MiB, barrier every 16 accesses, "
-           "injected races 1e-4, autotuned launch shape, HIP-graph replay")
+           "injected races 1e-4, path and launch shape by the autotuner")
 
 
 def log(msg):
@@ -212,7 +214,7 @@ def check_workload(pkg, torch, name, steps, warmup, recs, offsets, tpb, desc, au
     dev = torch.from_numpy(recs.view(np.uint8).reshape(-1, 16)).to("cuda:0")
     torch.cuda.synchronize()
     # a stream of its own (default priority): the library captures and
-    # replays HIP graphs on a non-null stream only
+    # replays the HIP graphs of sorting calls on a non-null stream only
     side = torch.cuda.Stream()
     stream = side.cuda_stream
     ctx = pkg.Context(0, graphs=True)

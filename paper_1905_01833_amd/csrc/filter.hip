@@ -14,7 +14,8 @@
 //   k_filter_plan   workgroups for buckets with hot words
 //   k_filter_count  per bucket: bitmaps of its groups in LDS, then the pairs
 //                   of the writes and atomics that may race, among themselves
-//                   and with the reads; one entry per racing location
+//                   and with the reads; one entry per racing location.  A second
+//                   launch counts the buckets that the first left for later
 //   k_entries_place / k_entries_sort / k_entries_merge  the entries in order
 #include <hip/hip_runtime.h>
 
@@ -424,7 +425,7 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
       }
       return;
     }
-    const uint32_t len = writes ? run / 4 : run - run / 4;  // (a quarter of the records write)
+    const uint32_t len = writes ? run / 4 : run - run / 4;  // (a guess: it only sets how many lanes share a run)
     const uint32_t most = 31u - (uint32_t)__builtin_clz(NTH / min(NTH, hi - lo));  // with it every run has a group
     uint32_t lg = len > 16 ? 32u - (uint32_t)__builtin_clz((len - 1) / 16) : 0u;
     lg = min(lg, 10u);
