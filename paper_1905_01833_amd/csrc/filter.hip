@@ -802,9 +802,10 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
         for (int q = 0; q < 5; q++) s_acc[q][i] = 0;
       }
       __syncthreads();
-      // ---- a location's first write in the table, and the pairs of writes.
-      //      (An atomic walks the writes only: a hot word's atomics meet no other
-      //      atomic.  Without a write their location has no first one yet.)
+      // ---- a location's first write in the table (without one its first atomic),
+      //      and the pairs of writes.  (A hot word's atomics meet no other atomic:
+      //      where their chain is long, only reads of it would tell them apart, and
+      //      those are for another path.)
       if (tx < nw) {
         const uint32_t i = tx;
         const FRec x = w_at(i);
@@ -824,6 +825,11 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
             if (bx != by) xw++;
           }
         }
+        if (atomic && n_read && first == i && length[chain_of(x, bx)] <= longest) {
+#pragma unroll 1
+          for (uint32_t j = head[chain_of(x, bx) + HN]; j != END; j = s_next[j])
+            if (j < first && same_location(x, bx, w_at(j), s_blk[j])) first = j;
+        }
         s_lead[i] = (uint16_t)first;
         if (!left) s_any = 2;
         if (ww) atomicAdd(&s_acc[K_WW][first], ww);
@@ -839,8 +845,12 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
         const uint32_t h = location_hash(x, bx), c = h & (HN - 1);
         uint32_t j = head[c], k = head[c + HN];
         if (k != END) {
-          if (tag_of(h) & ~tags[c]) k = END;  // none of its location
-          else if (length[c] > longest) s_any = 2;
+          if (tag_of(h) & ~tags[c]) {  // none of its location
+            k = END;
+          } else if (length[c] > longest) {
+            s_any = 2;
+            return;
+          }
         }
         if (j == END) {
           j = k;
@@ -880,28 +890,6 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
       __syncthreads();
       if (s_any == 2) {  // reads of a word of many atomics
         return give_up(round);
-      }
-      // ---- atomics of one location that met reads but have no write: the first
-      //      of them takes the sums of all
-      const bool lone = tx < nw && s_lead[tx] == tx && s_acc[K_AR][tx] && (s_w[tx].w >> 16 & 3u) == 2u;
-      if (__syncthreads_or(lone)) {
-        uint32_t first = tx;
-        if (lone) {
-          const FRec x = w_at(tx);
-          const uint32_t bx = s_blk[tx];
-#pragma unroll 1
-          for (uint32_t j = head[chain_of(x, bx) + HN]; j != END; j = s_next[j]) {
-            if (j >= first || !s_acc[K_AR][j]) continue;
-            if (same_location(x, bx, w_at(j), s_blk[j])) first = j;
-          }
-        }
-        __syncthreads();
-        if (first != tx) {
-          atomicAdd(&s_acc[K_AR][first], s_acc[K_AR][tx]);
-          if (s_acc[K_XB][tx]) atomicAdd(&s_acc[K_XB][first], s_acc[K_XB][tx]);
-          s_lead[tx] = (uint16_t)first;
-        }
-        __syncthreads();
       }
       emit(nw);
       if (!LOOP || ++round == rounds) return;

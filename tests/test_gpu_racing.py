@@ -250,3 +250,24 @@ def test_several_tables_of_candidates(form, n, warp):
     finally:
         c.close()
     assert len(sets[0][1][0]) >= n // 500
+
+
+def read_often(n, rng, atomics, share):
+    """`atomics` atomics on each of eight words that nobody writes, and a share
+    of the records reads them."""
+    r = private(n, rng)
+    at = rng.permutation(n)[: int(n * share) + 8 * atomics]
+    r["unit"][at], r["action"][at] = HOT + np.arange(len(at)) % 8, READ
+    r["action"][at[: 8 * atomics]] = ATOMIC
+    return r
+
+
+@pytest.mark.parametrize("log2", [13, 16, 18, 20])
+@pytest.mark.parametrize("atomics", [2, 16, 17, 100])
+def test_reads_of_words_with_a_few_atomics(log2, atomics):
+    """Many reads of words that a few atomics update and nobody writes: the sums
+    of a word's pairs are kept together, not one for each of its atomics."""
+    rng = np.random.default_rng(100 * log2 + atomics)
+    n = (1 << log2) + 3
+    want = compare(f"{atomics} atomics, 2^{log2}", read_often(n, rng, atomics, 0.4), private(n, rng), 3.0)
+    assert len(want) == 8
