@@ -706,7 +706,7 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
       s_base = atomicAdd(&f.cnt[FC_ENTRIES], n_new);
       if (s_base + n_new > f.entries_cap) atomicOr(&f.ctrl->error_flags, ERR_GROUP_FULL);
       const uint32_t in_trace = atomicAdd(&f.trace_cnt[trace], n_new) + n_new;
-      if (in_trace > SORT_CHUNK) atomicMax(&f.cnt[FC_MOST], in_trace);
+      if (in_trace > SORT_ALONE) atomicMax(&f.cnt[FC_MOST], in_trace);
       if (in_trace > GROUP_MAX_ENTRIES) atomicOr(&f.ctrl->error_flags, ERR_GROUP_FULL);
     }
     __syncthreads();
@@ -1251,11 +1251,12 @@ __global__ __launch_bounds__(NT) void k_entries_place(FilterBuffers f) {
 // An entry's place in its chunk is the number of entries before it there (of
 // equal ones, those with a smaller index).  A workgroup holds a chunk's keys in
 // LDS and places 16 of its entries, sixteen lanes to an entry (256, a lane each,
-// where a trace has many, or the call many traces): sorting 1677 entries in one
+// where there are many): sorting 1677 entries in one
 // workgroup's LDS took 68 us, 66 steps with a barrier each; this takes 17.
-// Traces of one chunk belong to the workgroups (trace, y); longer ones are shared
-// out among all: with one workgroup per trace, a call of 65 traces with 60000
-// entries in one of them took 52.7 ms, 0.5 so (the sort 0.6).
+// Traces of one chunk (of SORT_ALONE entries, in a call of many traces) belong to the
+// workgroups (trace, y); longer ones are shared out among all.  With one workgroup
+// per trace, a call of 65 traces with 60000 entries in one of them took 52.7 ms, 0.5
+// so (the sort 0.6); with 2048 entries in one of them, 1750 us and 140 (the sort 270).
 __global__ __launch_bounds__(NT) void k_entries_sort(FilterBuffers f) {
   __shared__ uint64_t s_place[SORT_CHUNK], s_unit[SORT_CHUNK];
   __shared__ uint32_t s_long[NT], s_n;
@@ -1272,6 +1273,8 @@ __global__ __launch_bounds__(NT) void k_entries_sort(FilterBuffers f) {
     *f.head = h;
   }
   if (err || (f.late_wait && late)) return;
+  const uint32_t all = gridDim.x * gridDim.y, me = blockIdx.y * gridDim.x + blockIdx.x;
+  const uint32_t alone = gridDim.y > 1 ? SORT_CHUNK : SORT_ALONE;
   auto sort = [&](uint32_t t, uint32_t n, uint32_t from, uint32_t step) {
     if (!n) return;
     const uint32_t first = f.n_traces > 1 ? f.trace_first[t] : 0u;
@@ -1279,7 +1282,7 @@ __global__ __launch_bounds__(NT) void k_entries_sort(FilterBuffers f) {
     RaceOut* dst = (n <= SORT_CHUNK ? (total <= f.host_cap ? f.host_entries : f.sorted)
                                     : (f.n_traces > 1 ? f.entries : f.placed)) + first;
     EntryKey* const mk = n > SORT_CHUNK ? (EntryKey*)f.merge_keys + first : nullptr;  // for the merge
-    const uint32_t lanes = gridDim.y > 1 && n <= 32 * SORT_CHUNK ? 16u : 1u, take = NT / lanes, per_chunk = SORT_CHUNK / take;
+    const uint32_t lanes = (gridDim.y > 1 ? n <= 32 * SORT_CHUNK : n > SORT_ALONE && total <= 64 * all) ? 16u : 1u, take = NT / lanes, per_chunk = SORT_CHUNK / take;
     for (uint32_t item = from;; item += step) {
       const uint32_t c0 = item / per_chunk * SORT_CHUNK, g0 = item % per_chunk * take;
       if (c0 >= n) break;
@@ -1321,14 +1324,13 @@ __global__ __launch_bounds__(NT) void k_entries_sort(FilterBuffers f) {
       if (mk && e < m && q == 0) mk[c0 + rank] = EntryKey{s_place[e], s_unit[e]};
     }
   };
-  if (own <= SORT_CHUNK) sort(blockIdx.x, own, blockIdx.y, gridDim.y);
-  if (most <= SORT_CHUNK) return;
-  const uint32_t all = gridDim.x * gridDim.y, me = blockIdx.y * gridDim.x + blockIdx.x;
+  if (own <= alone) sort(blockIdx.x, own, blockIdx.y, gridDim.y);
+  if (most <= alone) return;
   for (uint32_t t0 = 0; t0 < f.n_traces; t0 += NT) {
     __syncthreads();
     if (tx == 0) s_n = 0;
     __syncthreads();
-    if (t0 + tx < f.n_traces && f.trace_cnt[t0 + tx] > SORT_CHUNK) s_long[atomicAdd(&s_n, 1u)] = t0 + tx;
+    if (t0 + tx < f.n_traces && f.trace_cnt[t0 + tx] > alone) s_long[atomicAdd(&s_n, 1u)] = t0 + tx;
     __syncthreads();
     const uint32_t n_long = s_n;
     for (uint32_t k = 0; k < n_long; k++) {

@@ -129,10 +129,11 @@ struct Buffers {            // device pointers of one call
 
 // Counters of a grouped call (FilterBuffers::cnt): entries found, further
 // workgroups of hot buckets, entries of the trace with most (where they exceed
-// SORT_CHUNK), buckets or traces for the later workgroups, those whose candidates
+// SORT_ALONE), buckets or traces for the later workgroups, those whose candidates
 // fill two to four tables.
 enum : uint32_t { FC_ENTRIES = 0, FC_EXTRA = 1, FC_MOST = 2, FC_LATE = 3, FC_ROUNDS = 4, FC_COUNT = 5 };
 constexpr uint32_t SORT_CHUNK = 2048;         // entries sorted in one workgroup's LDS
+constexpr uint32_t SORT_ALONE = 256;          // ... of which one workgroup places so many at once
 // Entries of a trace, at most: beyond, merging its sorted chunks takes longer than
 // sorting its records does.  (Grouped / sorted, in us: 262144 entries of 2^24
 // records 1562 / 1822; of 2^22 records, 200000 1411 / 1118, 60000 512 / 624.)

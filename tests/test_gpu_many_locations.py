@@ -104,3 +104,41 @@ def test_line_between_merging_and_sorting(count):
     n = 1 << 24
     want = compare(f"{count} locations of 2^24 records", locations(n, rng, count), private(n, rng), 2.0)
     assert len(want) == count
+
+
+@pytest.mark.parametrize("n_traces", [65, 300])
+@pytest.mark.parametrize("count", [255, 256, 257, 1000, 2047, 2048])
+def test_a_chunk_of_entries_among_many_traces(n_traces, count):
+    """Up to a chunk of entries in one trace of many: their order is not left to
+    one workgroup; the call takes at most twice the sort's time."""
+    import time
+
+    import paper_1905_01833_amd as pkg
+
+    rng = np.random.default_rng(n_traces + count)
+    parts = [private(300 + 7 * (k % 50), rng) for k in range(n_traces - 1)]
+    parts.insert(n_traces // 2, locations(1 << 17, rng, count))
+    recs = np.concatenate(parts)
+    off = np.concatenate([[0], np.cumsum([len(p) for p in parts])]).astype(np.uint64)
+    tpb = np.full(n_traces, 256, dtype=np.uint32)
+    want, wsum = oracle.closed_form_par(recs, off, tpb)
+    assert len(want) == count
+    dev = device(recs)
+    best = {}
+    c = pkg.Context(0)
+    try:
+        for shape in (None, {"scatter_threads": 512}):
+            c.set_tuning(pkg.sim_size_class(len(recs)), shape)
+            took = []
+            for rep in range(6):
+                print(f"[gpu] {count} locations in one of {n_traces} short traces, shape {shape}, call {rep}", flush=True)
+                torch.cuda.synchronize()
+                t = time.perf_counter()
+                got, gsum = c.check_traces_device(dev, off, tpb)
+                took.append(time.perf_counter() - t)
+                assert got.tobytes() == want.tobytes() and gsum.tobytes() == wsum.tobytes()
+            best[shape is None] = min(took)
+    finally:
+        c.close()
+    print(f"[gpu] {best[True] * 1e6:.0f} us, sorted {best[False] * 1e6:.0f}", flush=True)
+    assert best[True] < 2 * best[False], best
