@@ -1231,7 +1231,7 @@ int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const
   const uint64_t half = 8 * room;  // bytes of a key buffer
   // a bucket is split only where a tile's run of one of at least 8 buckets is far above the usual
   const uint32_t hot_part = (uint32_t)std::max<uint64_t>(HOT_PART, total / HOT_SHARE);
-  const uint32_t extra_max = max_lgb < 3 ? 0u : (uint32_t)((std::min<uint64_t>(total / FILTER_BUCKET, HOT_MAX_ITEMS) + 8) / 8 * 8);
+  const uint32_t full_parts = (uint32_t)(total / hot_part), extra_max = max_lgb < 3 ? 0u : hot_items(full_parts);
   const bool direct = longest <= GROUP_DIRECT_RECORDS;
   const bool small = direct || tiles <= 16;
   // The later workgroups: launched with the others where the previous call had
@@ -1273,6 +1273,7 @@ int run_grouped(sim_ctx* c, const sim_record* d_records, const sim_record* const
   f.rows = (uint32_t*)(k0 + rows_at);
   f.extra = (uint2*)(k0 + extra_at);
   f.extra_max = extra_max;
+  f.extra_big = extra_max ? hot_big_items(full_parts) : 0u;
   f.hot_part = hot_part;
   f.late = (uint2*)(k0 + late_at);
   f.late_max = late_max;

@@ -58,6 +58,7 @@ __global__ __launch_bounds__(NT) void k_filter_begin(FilterBuffers f) {
     f.cnt[FC_MOST] = 0;
     f.cnt[FC_LATE] = 0;
     f.cnt[FC_ROUNDS] = 0;
+    f.cnt[FC_EXTRA2] = 0;
   }
   const FTrace T = f.tr_src[t];
   if (threadIdx.x == 0) {
@@ -238,8 +239,8 @@ __global__ __launch_bounds__(FNT, LGB <= 11 ? 8 : 4) void k_filter_part(FilterBu
 // Workgroups of hot buckets: item i is (bucket, part).  They come first in the
 // grid, also those of one part: started among the others, a bucket that takes
 // four times as long ends long after them (215 us for a trace of 2^24 records,
-// 170 so).  Where the items run out, a bucket stays whole and
-// in its place.
+// 170 so).  Where the items run out, a bucket (of HOT_BIG parts at most) stays whole
+// and in its place.
 constexpr uint32_t NO_BUCKET = 0xFFFFFFFFu, HOT_ITEM = 1u << 31;
 // Written words whose writes no table of the allowed rounds holds (estimated
 // from samples, hence the quarter more) are for the sort, and the sooner the
@@ -255,9 +256,11 @@ __global__ __launch_bounds__(NT) void k_filter_plan(FilterBuffers f) {
   const uint32_t hot = f.hot[b], parts = min(f.tr[f.bucket_trace[b]].ntiles, 1u + hot / f.hot_part);
   uint32_t word = 1;
   if (hot > f.hot_part / 4) {
-    const uint32_t at = atomicAdd(&f.cnt[FC_EXTRA], parts);
-    const bool room = at < f.extra_max && parts <= f.extra_max - at;
-    for (uint32_t k = 0; k < parts && at + k < f.extra_max; k++) f.extra[at + k] = make_uint2(room ? b : NO_BUCKET, k);
+    const bool big = parts > HOT_BIG;
+    const uint32_t lo = big ? 0u : f.extra_big, max = big ? f.extra_big : f.extra_max - f.extra_big;
+    const uint32_t at = atomicAdd(&f.cnt[big ? FC_EXTRA : FC_EXTRA2], parts);
+    const bool room = at < max && parts <= max - at;
+    for (uint32_t k = 0; k < parts && at + k < max; k++) f.extra[lo + at + k] = make_uint2(room ? b : NO_BUCKET, k);
     if (room) word = parts | HOT_ITEM;
   }
   f.hot[b] = word;
@@ -338,7 +341,8 @@ __global__ __launch_bounds__(FNT, (MODE & LATE_BUCKET) ? 4 : 8) void k_filter_co
     bucket = 0;
     trace = blockIdx.x;
   } else if (blockIdx.x < f.extra_max) {
-    if (blockIdx.x >= f.cnt[FC_EXTRA]) return;
+    const bool big = blockIdx.x < f.extra_big;
+    if (blockIdx.x - (big ? 0u : f.extra_big) >= f.cnt[big ? FC_EXTRA : FC_EXTRA2]) return;
     const uint2 it = f.extra[blockIdx.x];
     if (it.x == NO_BUCKET) return;
     bucket = it.x;

@@ -127,11 +127,11 @@ struct Buffers {            // device pointers of one call
   uint32_t digit_bits;      // digit width of the radix passes after pass 0: RADIX_BITS or RADIX_WIDE_BITS
 };
 
-// Counters of a grouped call (FilterBuffers::cnt): entries found, further
-// workgroups of hot buckets, entries of the trace with most (where they exceed
+// Counters of a grouped call (FilterBuffers::cnt): entries found, items of the
+// hottest buckets and of other hot ones, entries of the trace with most (where they exceed
 // SORT_ALONE), buckets or traces for the later workgroups, those whose candidates
 // fill two to four tables.
-enum : uint32_t { FC_ENTRIES = 0, FC_EXTRA = 1, FC_MOST = 2, FC_LATE = 3, FC_ROUNDS = 4, FC_COUNT = 5 };
+enum : uint32_t { FC_ENTRIES = 0, FC_EXTRA = 1, FC_MOST = 2, FC_LATE = 3, FC_ROUNDS = 4, FC_EXTRA2 = 5, FC_COUNT = 6 };
 constexpr uint32_t SORT_CHUNK = 2048;         // entries sorted in one workgroup's LDS
 constexpr uint32_t SORT_ALONE = 256;          // ... of which one workgroup places so many at once
 // Entries of a trace, at most: beyond, merging its sorted chunks takes longer than
@@ -159,6 +159,7 @@ struct FilterBuffers {      // device pointers of a call's grouped race count (f
   uint32_t* hot_writes;     // [bucket] writes of hot words, estimated
   uint2* extra;             // the parts of split buckets: (bucket, part)
   uint32_t extra_max;       // room for them (a multiple of 8; 0: no bucket is split)
+  uint32_t extra_big;       // ... of which for buckets of more than HOT_BIG parts (the first)
   uint32_t hot_part;        // hot reads per part
   uint2* late;              // buckets (traces, if direct) for the later workgroups, and their part
   uint32_t late_max;        // room for them

@@ -271,3 +271,20 @@ def test_reads_of_words_with_a_few_atomics(log2, atomics):
     n = (1 << log2) + 3
     want = compare(f"{atomics} atomics, 2^{log2}", read_often(n, rng, atomics, 0.4), private(n, rng), 3.0)
     assert len(want) == 8
+
+
+@pytest.mark.parametrize("log2", [17, 19, 20, 22])
+@pytest.mark.parametrize("others", [0, 7, 63])
+def test_most_records_read_one_word(log2, others):
+    """One word is read by half of a trace's records and others by the rest: the
+    bucket of the first is split over workgroups wherever the others are, on every
+    call (some calls left it whole)."""
+    rng = np.random.default_rng(log2 + others)
+    n = (1 << log2) + 7
+    r = private(n, rng)
+    at = rng.permutation(n)
+    r["unit"], r["action"] = HOT + 1 + np.arange(n) % max(1, others), READ
+    r["unit"][at[: n // 2]] = HOT
+    r["action"][at[n // 2 - 10 : n // 2 + 40 * others]] = ATOMIC
+    want = compare(f"half of 2^{log2} read a word, the others {others}", r, private(n, rng), 3.0)
+    assert len(want) == 1 + others
